@@ -15,6 +15,7 @@
 #include <hip/hip_ext.h>
 
 #include "../../include/c2t.h"
+#include "k_direct.h"
 #include "k_logits.h"
 #include "k_tree.h"
 
@@ -279,7 +280,7 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
     const size_t lds = std::max(std::max(std::max(map_lds, list_lds), score_lds), (size_t)16 * 1024);
     sp.lds_bytes = (int)lds;
     sp.w_lds_off = -1;
-    hipExtLaunchKernelGGL((k_logits_generic<0, NT_F32>), dim3(grid), dim3(NT_F32), lds, s, ev0, ev1, 0, logits, stride,
+    hipExtLaunchKernelGGL((k_logits_direct<0, NT_F32>), dim3(grid), dim3(NT_F32), lds, s, ev0, ev1, 0, logits, stride,
                           c.vocab, cps, (const float*)x->st.cls, x->st, sp);
   }
   return hipGetLastError();

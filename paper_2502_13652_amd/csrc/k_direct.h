@@ -1,0 +1,297 @@
+// Logits pass without a histogram: every logit's exponential is evaluated in fp64 as it is read, in one
+// pass over the segment.  The path of fp32 rows (whose values are too many to be counted).
+//
+// What bounds it.  About twenty vector instructions a logit, most of them fp64 at the rate of fp32
+// ones: 20 cycles of a CU per wavefront of logits, i.e. 31 GB/s of fp32 logits per CU and 7.9 TB/s for
+// the chip, which is what HBM delivers.  The two-pass form that it replaces read the segment twice (the
+// maximum first) and spent about fifty instructions in the library's exp.
+//
+// Sums.  Each wavefront keeps Z = sum e^(x-a) and S = sum (x-a) e^(x-a) against its own largest logit so far, a
+// (uniform over the wave; re-referenced when a tile raises it, which happens a few times a segment), so
+// every term of S has one sign and nothing overflows.  No barrier is needed for any of it.
+//
+// Exponential.  e^t = 2^(k/32) e^r with k = rint(32 t / ln 2), |r| <= ln 2 / 64 (Cody and Waite's reduction, Tang's
+// table): 2^(j/32) for j = 0..31 from a 256-byte LDS table (32 doubles fill the 64 banks once: equal banks mean
+// equal addresses, so the random reads of a wave never conflict), e^r from a polynomial of degree 5
+// interpolated at Chebyshev nodes (1.4e-16 relative with rounded coefficients).  t <= 0 here, and the error of
+// the one-constant reduction, |k| 7e-19, matters only as |t| e^t.
+//
+// Top K without reading anything twice: the K-th largest of 64 maxima (of the 64 lane columns of the workgroup) is
+// a lower bound of the K-th largest logit from the first tile on; the few logits that reach it are appended
+// to a list in LDS as they stream past, and the list is ranked exactly at the end.  The bound is raised from
+// the maxima so far at tiles 2, 4, 8, ...: stale maxima only make it lower, so no barrier is needed there.
+// Rows that overflow the list (thousands of logits above the bound: massive ties, sorted rows) take
+// generic_segment.
+#pragma once
+#include "k_logits.h"
+
+namespace c2t {
+
+constexpr int EXP_TAB = 32;
+constexpr int DIRECT_CHUNKS = 4;               // chunks a lane reads per tile: 64 bytes, two tiles in flight
+
+// 2^(j/32) with j << 15 taken off its upper word: adding k << 15 for any k = 32 q + j then gives 2^(k/32)
+__device__ __forceinline__ double exp_tab_entry(int j) {
+  const uint64_t u = (uint64_t)__double_as_longlong(exp2((double)j * 0.03125));
+  return __longlong_as_double((long long)(u - ((uint64_t)j << 47)));
+}
+__device__ __forceinline__ float max3_raw(float a, float b, float c) {     // without the canonicalising copies fmaxf adds per operand
+  float d;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+// e^t for t <= 0 (clamped at -700: 1e-304, nothing beside the largest term, which is 1)
+__device__ __forceinline__ double exp_nonpositive(double t, const double* tab) {
+  constexpr double SHIFT = 6755399441055744.0;               // 1.5 * 2^52: the sum's low word is the rounded integer
+  const double kf = __builtin_fma(t, 0x1.71547652b82fep+5, SHIFT);
+  const int k = __double2loint(kf);
+  const double r = __builtin_fma(kf - SHIFT, -0x1.62e42fefa39efp-6, t);
+  const double e = tab[k & (EXP_TAB - 1)];
+  double p = __builtin_fma(0x1.11115c0928b20p-7, r, 0x1.5555d887832fap-5);
+  p = __builtin_fma(p, r, 0x1.5555555547d38p-3);
+  p = __builtin_fma(p, r, 0x1.ffffffffd0b99p-2);
+  p = __builtin_fma(p, r, 1.0);
+  p = __builtin_fma(p, r, 1.0);
+  return __hiloint2double(__double2hiint(e) + (int)((uint32_t)k << 15), __double2loint(e)) * p;
+}
+
+template <int NT>
+struct DirectShared {
+  static constexpr int NW = NT / WAVE;
+  double exp_tab[EXP_TAB];
+  double wave_z[NW], wave_s[NW];
+  float wave_a[NW];
+  float col_max[NW][WAVE];                      // running maximum of every lane
+  int32_t n_list, bad;
+};
+
+// K-th largest of the 64 column maxima, to its upper 16 bits (a lower bound of the K-th largest logit seen)
+template <int NT>
+__device__ __forceinline__ float column_bound(const DirectShared<NT>& sh, int K) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  float m = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < NT / WAVE; ++w) m = fmaxf(m, __hip_atomic_load(&sh.col_max[w][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+  const uint32_t key[1] = {sortable_key(m)};
+  const uint32_t t = wave_kth_largest<1, 16>(key, K);
+  return t < 0x007FFFFFu ? -INFINITY : key_to_float(t);      // (below -inf's key once the low bits are cleared)
+}
+
+template <int DT, int NT>
+struct DirectState {                            // of one wavefront
+  float a, lane_max, tau;                       // a: reference of the sums, the wave's largest logit so far (uniform)
+  double Z, S;
+  bool bad;
+};
+
+// Logits of a tile that the segment does not have read as -inf: chunks past its end, the padding of the row's last chunk.
+template <int DT, int NT>
+__device__ __forceinline__ void blank_tile(uint4 (&q)[DIRECT_CHUNKS], const Segment& sg, int first) {
+  constexpr uint32_t NONE = DT == 1 ? 0xff80ff80u : 0xff800000u;
+#pragma unroll
+  for (int c = 0; c < DIRECT_CHUNKS; ++c) {
+    const int g = first + c * NT + (int)threadIdx.x;
+    const int nv = g >= sg.ncell ? 0 : sg.c0 + g == sg.tail_chunk ? sg.tail_valid : LogitTraits<DT>::EPC;
+    uint32_t w[4] = {q[c].x, q[c].y, q[c].z, q[c].w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (DT == 1) {
+        if (2 * j >= nv) w[j] = NONE;
+        else if (2 * j + 1 >= nv) w[j] = (w[j] & 0xffffu) | (NONE & 0xffff0000u);
+      } else if (j >= nv) w[j] = NONE;
+    }
+    q[c] = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+
+// One tile: sums, and the logits that reach the bound.  t: the tile's number.
+template <int DT, int NT>
+__device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int t, const Segment& sg, int V, int K,
+                                            DirectState<DT, NT>& s, DirectShared<NT>& sh, const SelectLds& sel) {
+  typedef LogitTraits<DT> T;
+  const int tid = threadIdx.x;
+  float cm[DIRECT_CHUNKS];
+#pragma unroll
+  for (int c = 0; c < DIRECT_CHUNKS; ++c) {
+    float x[T::EPC];
+    T::unpack(q[c], x);
+    cm[c] = max3_raw(x[0], x[1], x[2]);
+#pragma unroll
+    for (int j = 3; j < T::EPC; j += 2) cm[c] = max3_raw(cm[c], x[j], x[j + 1 < T::EPC ? j + 1 : j]);
+  }
+  const float tm = max3_raw(max3_raw(cm[0], cm[1], cm[2]), cm[3], cm[3]);
+  s.lane_max = max3_raw(s.lane_max, tm, tm);
+  __hip_atomic_store(&sh.col_max[tid >> 6][tid & (WAVE - 1)], s.lane_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  const float wm = wave_max(tm);
+  if (wm > s.a) {                                            // uniform
+    if (s.a > -INFINITY) {
+      const double d = fmax((double)s.a - (double)wm, -700.0), f = exp_nonpositive(d, sh.exp_tab);
+      s.S = (s.S + d * s.Z) * f; s.Z *= f;
+    }
+    s.a = wm;
+  }
+  const double ad = (double)s.a;
+#pragma unroll
+  for (int c = 0; c < DIRECT_CHUNKS; ++c) {
+    uint4 qc = q[c];
+    asm volatile("" : "+v"(qc.x), "+v"(qc.y), "+v"(qc.z), "+v"(qc.w));     // (conversions of later chunks are not hoisted: they would spill)
+    float x[T::EPC];
+    T::unpack(qc, x);
+#pragma unroll
+    for (int j = 0; j < T::EPC; ++j) {
+      s.bad |= !(x[j] < INFINITY);
+      const double d = fmax((double)x[j] - ad, -700.0);
+      const double e = exp_nonpositive(d, sh.exp_tab);
+      s.Z += e; s.S = __builtin_fma(d, e, s.S);
+      if (j % 4 == 3) asm volatile("" : "+v"(s.Z), "+v"(s.S));   // four exponentials at a time cover their latency; more would spill
+    }
+  }
+  if (t == 0) __syncthreads();                               // the first tile's maxima are complete
+  if ((t & (t - 1)) == 0 && t != 1) s.tau = fmaxf(s.tau, column_bound<NT>(sh, K));
+  float* el_v = (float*)sel.list;
+  int32_t* el_i = (int32_t*)(sel.list + (size_t)sel.list_cap * 4);
+#pragma unroll
+  for (int c = 0; c < DIRECT_CHUNKS; ++c) {
+    if (__builtin_amdgcn_ballot_w64(cm[c] >= s.tau) == 0ull) continue;
+    float x[T::EPC];
+    T::unpack(q[c], x);
+    const int g = (t * DIRECT_CHUNKS + c) * NT + tid;
+#pragma unroll
+    for (int j = 0; j < T::EPC; ++j) {
+      const int id = (sg.c0 + g) * T::EPC + j;
+      if (x[j] >= s.tau && g < sg.ncell && id < V) {
+        const int slot = atomicAdd(&sh.n_list, 1);
+        if (slot < sel.list_cap) { el_v[slot] = x[j]; el_i[slot] = id; }
+      }
+    }
+  }
+}
+
+// One segment, by a whole workgroup.  map_lds: the cell map of generic_segment, which rows that overflow the list
+// fall back to; the list overlays it.
+template <int DT, int NT>
+__device__ __forceinline__ void direct_segment(const uint4* __restrict__ rowp, int V, int K, const Segment& sg,
+                                               unsigned char* map_lds, const SelectLds& sel, RowResult* rr) {
+  constexpr int NW = NT / WAVE, TILE = DIRECT_CHUNKS * NT;
+  __shared__ DirectShared<NT> sh;
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
+  if (tid < EXP_TAB) sh.exp_tab[tid] = exp_tab_entry(tid);
+  if (tid == 0) { sh.n_list = 0; sh.bad = 0; }
+  __syncthreads();
+  const int n_tiles = (sg.ncell + TILE - 1) / TILE, n_whole = sg.tail_chunk >= 0 ? sg.ncell - 1 : sg.ncell;
+  const uint64_t base = (uint64_t)(rowp + sg.c0);
+  const uint64_t base_u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
+                          ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32);
+  // the bounds check returns zeros past the segment's last chunk without reading
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, sg.ncell * 16, 0x00020000);
+  const uint32_t vo = (uint32_t)tid * 16u;
+  uint4 qa[DIRECT_CHUNKS], qb[DIRECT_CHUNKS];
+  auto load = [&](uint4 (&q)[DIRECT_CHUNKS], int t) {
+#pragma unroll
+    for (int c = 0; c < DIRECT_CHUNKS; ++c) q[c] = load_stream_buffer(rs, vo, (uint32_t)(t * DIRECT_CHUNKS + c) * (NT * 16u));
+  };
+  DirectState<DT, NT> s;
+  s.a = s.lane_max = s.tau = -INFINITY; s.Z = s.S = 0.0; s.bad = false;
+  load(qa, 0);
+  if (n_tiles > 1) load(qb, 1);
+  for (int t = 0; t < n_tiles; t += 2) {
+    if ((t + 1) * TILE > n_whole) blank_tile<DT, NT>(qa, sg, t * TILE);
+    direct_tile<DT, NT>(qa, t, sg, V, K, s, sh, sel);
+    if (t + 1 >= n_tiles) break;
+    if (t + 2 < n_tiles) load(qa, t + 2);
+    if ((t + 2) * TILE > n_whole) blank_tile<DT, NT>(qb, sg, (t + 1) * TILE);
+    direct_tile<DT, NT>(qb, t + 1, sg, V, K, s, sh, sel);
+    if (t + 3 < n_tiles) load(qb, t + 3);
+  }
+  C2T_PT(PT_STREAM_END);
+  s.Z = wave_sum(s.Z); s.S = wave_sum(s.S);
+  if (lane == 0) { sh.wave_z[wid] = s.Z; sh.wave_s[wid] = s.S; sh.wave_a[wid] = s.a; }
+  if (s.bad) sh.bad = 1;
+  __syncthreads();
+  C2T_PT(PT_HIST_COMPLETE);
+  const bool seg_bad = sh.bad != 0;
+  int n_el = sh.n_list;
+  if (n_el > sel.list_cap) {
+    generic_segment<DT, NT, 1>(rowp, V, K, 0, sg, map_lds, sel, rr, 0u);
+    return;
+  }
+  if (n_el > 2 * WAVE) {
+    // Long segments: the list still holds what reached the first, lowest bounds.  Cut it with the final one.
+    constexpr int KEEP = 8;                                  // entries a thread holds at once
+    float* el_v = (float*)sel.list;
+    int32_t* el_i = (int32_t*)(sel.list + (size_t)sel.list_cap * 4);
+    const float tau = column_bound<NT>(sh, K);
+    int kept = 0;
+    __syncthreads();                                         // everybody has read the length
+    for (int o = 0; o < n_el; o += KEEP * NT) {              // entries only move down: below everything not yet read
+      float v[KEEP]; int32_t id[KEEP];
+#pragma unroll
+      for (int k = 0; k < KEEP; ++k) {
+        const int e = o + k * NT + tid;
+        v[k] = e < n_el ? el_v[e] : -INFINITY; id[k] = e < n_el ? el_i[e] : -1;
+      }
+      if (tid == 0) sh.n_list = kept;
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < KEEP; ++k) {
+        if (id[k] >= 0 && v[k] >= tau) {
+          const int slot = atomicAdd(&sh.n_list, 1);
+          el_v[slot] = v[k]; el_i[slot] = id[k];
+        }
+      }
+      __syncthreads();
+      kept = sh.n_list;
+      __syncthreads();
+    }
+  }
+  const int n_top = rank_list<NT>(K, sel, &sh.n_list, rr->topv, rr->topi);
+  C2T_PT(PT_RANKED);
+  if (wid == 0) {                                            // lanes 0 .. NW-1 hold one wave's sums each; fixed order
+    const float a = lane < NW ? sh.wave_a[lane] : -INFINITY, m = wave_max(a);
+    double tz = 0.0, ts = 0.0;
+    if (a > -INFINITY) {
+      const double d = (double)a - (double)m, f = exp_nonpositive(fmax(d, -700.0), sh.exp_tab);
+      tz = sh.wave_z[lane] * f; ts = (sh.wave_s[lane] + d * sh.wave_z[lane]) * f;
+    }
+    static_assert(NW <= 16, "one DPP row holds the per-wave sums");
+    tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
+    tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
+    tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
+    tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts);
+    if (lane == 0) {
+      RowPartial r;
+      r.ref = (double)m; r.a = (double)m; r.Z = seg_bad ? 0.0 : tz; r.S = seg_bad ? 0.0 : ts;
+      r.n_top = seg_bad ? 0 : n_top; r.flags = seg_bad ? 1u : 0u;
+      rr->part = r;
+    }
+  }
+}
+
+// grid: rows_launched * nsplit workgroups of NT threads.
+// Dynamic LDS (sp.lds_bytes): the list of the selection, over the cell map of generic_segment (cps keys); reused by the tail.
+template <int DT, int NT>
+__global__ __launch_bounds__(NT, 4) void k_logits_direct(
+    const void* __restrict__ logits, int64_t row_stride_elems, int V, int cps, const float* __restrict__ cls,
+    TreeState st, ScoreParams sp) {
+  typedef LogitTraits<DT> T;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const int nsplit = sp.nsplit, K = sp.K;
+  const int split = blockIdx.x % nsplit;
+  const RowOfWorkgroup rw = row_of_workgroup(st, sp, blockIdx.x / nsplit);
+  const int b = rw.b, f = rw.f, rl = b * sp.rows_per_seq + f, nf = rw.nf;
+  if (f >= nf) { if (nf == 0) end_of_sequence(st, sp, b, f, split); return; }   // uniform for the workgroup
+  const int64_t row = (int64_t)b * sp.F + f;
+  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_elems * (DT == 1 ? 2 : 4));
+  const Segment sg = make_segment<T::EPC>(V, split, cps);
+  __shared__ RowResult rr;
+  C2T_PT(PT_START);
+  const float parent_P = st.fr_P[row];                     // requested ahead of the logits, stored behind them
+  if (sg.ncell == 0) { if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; } }
+  else direct_segment<DT, NT>(rowp, V, K, sg, dyn_lds, make_select_lds<NT, 1, T::EPC>(dyn_lds, sp.lds_bytes), &rr);
+  if (nsplit == 1 && sp.M > 0) { __syncthreads(); top_m_of_split_row<DT, NT>(rowp, V, sp.M, rr); }
+  if (threadIdx.x == 0) rr.parent_P = parent_P;
+  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, dyn_lds, cls, nullptr,     // split records are indexed by launched row
+                   [&](RowResult& r) { top_m_of_split_row<DT, NT>(rowp, V, sp.M, r); });
+}
+
+}  // namespace c2t

@@ -614,32 +614,6 @@ __device__ __forceinline__ RowOfWorkgroup row_of_workgroup(const TreeState& st, 
   return r;
 }
 
-// grid: rows_launched * nsplit workgroups of NT threads.
-// Dynamic LDS (sp.lds_bytes): the cell map (cps keys), reused for the element list of the selection
-// ((2K-1) * EPC entries of 8 bytes at least) and by the tail.
-template <int DT, int NT>
-__global__ __launch_bounds__(NT) void k_logits_generic(
-    const void* __restrict__ logits, int64_t row_stride_elems, int V, int cps, const float* __restrict__ cls,
-    TreeState st, ScoreParams sp) {
-  typedef LogitTraits<DT> T;
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int nsplit = sp.nsplit, K = sp.K;
-  const int split = blockIdx.x % nsplit;
-  const RowOfWorkgroup rw = row_of_workgroup(st, sp, blockIdx.x / nsplit);
-  const int b = rw.b, f = rw.f, rl = b * sp.rows_per_seq + f, nf = rw.nf;
-  if (f >= nf) { if (nf == 0) end_of_sequence(st, sp, b, f, split); return; }   // uniform for the workgroup
-  const int64_t row = (int64_t)b * sp.F + f;
-  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_elems * (DT == 1 ? 2 : 4));
-  const Segment sg = make_segment<T::EPC>(V, split, cps);
-  __shared__ RowResult rr;
-  C2T_PT(PT_START);
-  if (threadIdx.x == 0) rr.parent_P = st.fr_P[row];        // off the tail's critical path
-  if (sg.ncell == 0) { if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; } }
-  else generic_segment<DT, NT, 1>(rowp, V, K, nsplit > 1 ? 0 : sp.M, sg, dyn_lds, make_select_lds<NT, 1, T::EPC>(dyn_lds, sp.lds_bytes), &rr, 0u);   // split rows: see top_m_of_split_row
-  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, dyn_lds, cls, nullptr,     // split records are indexed by launched row
-                   [&](RowResult& r) { top_m_of_split_row<DT, NT>(rowp, V, sp.M, r); });
-}
-
 // ---------------------------------------------------------------------------------------
 // bf16 fast path: value histogram.
 // ---------------------------------------------------------------------------------------
