@@ -237,6 +237,7 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   // deal the live rows round the CUs
   sp.compact = (rows_per_seq > 1 && (int64_t)grid > (int64_t)x->n_cus && (int64_t)grid <= 4 * (int64_t)x->n_cus &&
                 c.batch <= COMPACT_MAX_B) ? 1 : 0;
+  sp.k_inverse = (uint32_t)(((1u << 20) + c.top_k - 1) / c.top_k);
   sp.h = c.hidden; sp.layer = x->layer; sp.z_beta = x->z_beta; sp.M = c.entropy_top_m; sp.D = c.max_depth;
   if (c.logits_dtype == C2T_BF16) {
     const int64_t cus = x->n_cus;
@@ -277,9 +278,16 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
 #undef C2T_LAUNCH_HIST_BUILD
 #undef C2T_LAUNCH_HIST
   } else {
-    const size_t lds = std::max(std::max(std::max(map_lds, list_lds), score_lds), (size_t)16 * 1024);
-    sp.lds_bytes = (int)lds;
-    sp.w_lds_off = -1;
+    const size_t lds_work = (std::max(std::max(std::max(map_lds, list_lds), score_lds), (size_t)16 * 1024) + 15) / 16 * 16;
+    sp.lds_bytes = (int)lds_work;
+    sp.w_lds_off = (int)lds_work;                           // the classifier's parameters, padded to 16 bytes
+    const size_t lds = lds_work + ((size_t)(5 * c.hidden + 1) * 4 + 15) / 16 * 16;
+    size_t& raised = x->lds_raised[0];
+    if (lds > raised) {                                     // beyond the 48 KB a kernel may use without asking
+      hipError_t e = hipFuncSetAttribute((const void*)k_logits_direct<0, NT_F32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+      raised = lds;
+    }
     hipExtLaunchKernelGGL((k_logits_direct<0, NT_F32>), dim3(grid), dim3(NT_F32), lds, s, ev0, ev1, 0, logits, stride,
                           c.vocab, cps, (const float*)x->st.cls, x->st, sp);
   }
@@ -439,7 +447,9 @@ int c2t_finalize_tree(c2t_ctx* x, const c2t_tree_out* o, void* stream) {
     return C2T_ERR_INVALID_ARG;
   if (x->layer < 0) return C2T_ERR_STATE;
   TreeOut t{o->tokens, o->parent, o->position, o->conf, o->joint_prob, o->entropy, o->n_nodes, o->mask, o->status};
-  hipLaunchKernelGGL(k_finalize, dim3(x->cfg.batch), dim3(256), 0, (hipStream_t)stream, x->st, t, x->cfg.budget);
+  const int per_slice = mask_rows_per_slice(x->cfg.budget);
+  hipLaunchKernelGGL(k_finalize, dim3(x->cfg.batch, (x->cfg.budget + per_slice - 1) / per_slice), dim3(FIN_NT), 0, (hipStream_t)stream, x->st, t,
+                     x->cfg.budget);
   if (hipGetLastError() != hipSuccess) return C2T_ERR_HIP;
   x->finalized = true;
   return C2T_OK;

@@ -15,9 +15,17 @@ enum PhaseMark { PT_START = 0, PT_STREAM_END, PT_HIST_COMPLETE, PT_SUMS, PT_TAU,
                  PT_PUBLISHED, PT_TICKET, PT_PRUNED, PT_PRUNE_LOADED, PT_PRUNE_FIRST, PT_PRUNE_PRESELECTED, PT_PRUNE_RANKED, PT_MERGED };
 #ifdef C2T_PHASE_TIMES
 __device__ unsigned long long c2t_phase_times[PT_WORKGROUPS * PT_SLOTS];
-#define C2T_PT(i) do { if (threadIdx.x == 0 && blockIdx.x < c2t::PT_WORKGROUPS) c2t::c2t_phase_times[blockIdx.x * c2t::PT_SLOTS + (i)] = wall_clock64(); } while (0)
+// The marks go to LDS (a store to memory would be waited for at the next hand-over) and out at the workgroup's end.
+__device__ __forceinline__ unsigned long long* phase_marks() { __shared__ unsigned long long t[PT_SLOTS]; return t; }
+__device__ __forceinline__ void phase_start() { for (int i = 0; i < PT_SLOTS; ++i) phase_marks()[i] = 0ull; phase_marks()[0] = wall_clock64(); }
+__device__ __forceinline__ void phase_flush() {
+  if (threadIdx.x == 0 && blockIdx.x < PT_WORKGROUPS) for (int i = 0; i < PT_SLOTS; ++i) c2t_phase_times[blockIdx.x * PT_SLOTS + i] = phase_marks()[i];
+}
+#define C2T_PT(i) do { if (threadIdx.x == 0) { if ((i) == 0) c2t::phase_start(); else c2t::phase_marks()[i] = wall_clock64(); } } while (0)
+#define C2T_PT_FLUSH() c2t::phase_flush()
 #else
 #define C2T_PT(i) do { } while (0)
+#define C2T_PT_FLUSH() do { } while (0)
 #endif
 
 // Per (row, split) result of the logits pass: Z = sum_j e^(x_j - a), S = sum_j (x_j - ref) e^(x_j - a),
@@ -65,6 +73,19 @@ __device__ __forceinline__ RowPartial ld_dev(const RowPartial* p) {
 }
 // every vector memory operation this wave has issued is complete
 __device__ __forceinline__ void wait_vector_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Requests every 64-byte line of the kernel's arguments at once.  The compiler loads an argument where it is used,
+// and a first touch of a line costs 320 cycles (0.14 us) each time, one after the other through the latency-bound tail
+// of a layer; a line that is in the scalar cache costs 44.
+template <int BYTES>
+__device__ __forceinline__ void touch_kernel_arguments() {
+  const __attribute__((address_space(4))) char* p = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(BYTES > 384 && BYTES <= 448, "seven lines");
+  uint32_t a, b, c, d, e, f, g;
+  asm volatile("s_load_dword %0, %7, 0\n s_load_dword %1, %7, 64\n s_load_dword %2, %7, 128\n s_load_dword %3, %7, 192\n"
+               "s_load_dword %4, %7, 256\n s_load_dword %5, %7, 320\n s_load_dword %6, %7, 384\n s_waitcnt lgkmcnt(0)"
+               : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d), "=&s"(e), "=&s"(f), "=&s"(g) : "s"(p));
+}
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }

@@ -148,8 +148,8 @@ __device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int
   }
   if (t == 0) __syncthreads();                               // the first tile's maxima are complete
   if ((t & (t - 1)) == 0 && t != 1) s.tau = fmaxf(s.tau, column_bound<NT>(sh, K));
-  float* el_v = (float*)sel.list;
-  int32_t* el_i = (int32_t*)(sel.list + (size_t)sel.list_cap * 4);
+  float* el_v = sel.values();
+  int32_t* el_i = sel.ids();
 #pragma unroll
   for (int c = 0; c < DIRECT_CHUNKS; ++c) {
     if (__builtin_amdgcn_ballot_w64(cm[c] >= s.tau) == 0ull) continue;
@@ -168,12 +168,12 @@ __device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int
 }
 
 // One segment, by a whole workgroup.  map_lds: the cell map of generic_segment, which rows that overflow the list
-// fall back to; the list overlays it.
+// fall back to; the list overlays it.  The per-wave sums stay in `sh` (see combine_waves).
 template <int DT, int NT>
-__device__ __forceinline__ void direct_segment(const uint4* __restrict__ rowp, int V, int K, const Segment& sg,
-                                               unsigned char* map_lds, const SelectLds& sel, RowResult* rr) {
-  constexpr int NW = NT / WAVE, TILE = DIRECT_CHUNKS * NT;
-  __shared__ DirectShared<NT> sh;
+__device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ rowp, int V, int K, const Segment& sg,
+                                                     unsigned char* map_lds, const SelectLds& sel, const ClassifierStage cst,
+                                                     DirectShared<NT>& sh, RowResult* rr) {
+  constexpr int TILE = DIRECT_CHUNKS * NT;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
   if (tid < EXP_TAB) sh.exp_tab[tid] = exp_tab_entry(tid);
   if (tid == 0) { sh.n_list = 0; sh.bad = 0; }
@@ -204,22 +204,22 @@ __device__ __forceinline__ void direct_segment(const uint4* __restrict__ rowp, i
     if (t + 3 < n_tiles) load(qb, t + 3);
   }
   C2T_PT(PT_STREAM_END);
+  store_classifier(cst);                                     // published by the barriers below
   s.Z = wave_sum(s.Z); s.S = wave_sum(s.S);
   if (lane == 0) { sh.wave_z[wid] = s.Z; sh.wave_s[wid] = s.S; sh.wave_a[wid] = s.a; }
   if (s.bad) sh.bad = 1;
   __syncthreads();
   C2T_PT(PT_HIST_COMPLETE);
-  const bool seg_bad = sh.bad != 0;
-  int n_el = sh.n_list;
+  const int n_el = sh.n_list;
   if (n_el > sel.list_cap) {
     generic_segment<DT, NT, 1>(rowp, V, K, 0, sg, map_lds, sel, rr, 0u);
-    return;
+    return SegmentTop{RANKED_IN_RR, false};
   }
   if (n_el > 2 * WAVE) {
     // Long segments: the list still holds what reached the first, lowest bounds.  Cut it with the final one.
     constexpr int KEEP = 8;                                  // entries a thread holds at once
-    float* el_v = (float*)sel.list;
-    int32_t* el_i = (int32_t*)(sel.list + (size_t)sel.list_cap * 4);
+    float* el_v = sel.values();
+    int32_t* el_i = sel.ids();
     const float tau = column_bound<NT>(sh, K);
     int kept = 0;
     __syncthreads();                                         // everybody has read the length
@@ -244,26 +244,30 @@ __device__ __forceinline__ void direct_segment(const uint4* __restrict__ rowp, i
       __syncthreads();
     }
   }
-  const int n_top = rank_list<NT>(K, sel, &sh.n_list, rr->topv, rr->topi);
-  C2T_PT(PT_RANKED);
-  if (wid == 0) {                                            // lanes 0 .. NW-1 hold one wave's sums each; fixed order
-    const float a = lane < NW ? sh.wave_a[lane] : -INFINITY, m = wave_max(a);
-    double tz = 0.0, ts = 0.0;
-    if (a > -INFINITY) {
-      const double d = (double)a - (double)m, f = exp_nonpositive(fmax(d, -700.0), sh.exp_tab);
-      tz = sh.wave_z[lane] * f; ts = (sh.wave_s[lane] + d * sh.wave_z[lane]) * f;
-    }
-    static_assert(NW <= 16, "one DPP row holds the per-wave sums");
-    tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts);
-    if (lane == 0) {
-      RowPartial r;
-      r.ref = (double)m; r.a = (double)m; r.Z = seg_bad ? 0.0 : tz; r.S = seg_bad ? 0.0 : ts;
-      r.n_top = seg_bad ? 0 : n_top; r.flags = seg_bad ? 1u : 0u;
-      rr->part = r;
-    }
+  return SegmentTop{min(sh.n_list, sel.list_cap), false};
+}
+// The segment's record from the wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.
+template <int NT>
+__device__ __forceinline__ void combine_waves(const DirectShared<NT>& sh, RowResult& rr) {
+  constexpr int NW = NT / WAVE;
+  static_assert(NW <= 16, "one DPP row holds the per-wave sums");
+  const int lane = threadIdx.x & (WAVE - 1);
+  const float a = lane < NW ? sh.wave_a[lane] : -INFINITY, m = wave_max(a);
+  double tz = 0.0, ts = 0.0;
+  if (a > -INFINITY) {
+    const double d = (double)a - (double)m, f = exp_nonpositive(fmax(d, -700.0), sh.exp_tab);
+    tz = sh.wave_z[lane] * f; ts = (sh.wave_s[lane] + d * sh.wave_z[lane]) * f;
+  }
+  tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
+  tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
+  tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
+  tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts);
+  if (lane == 0) {
+    const bool bad = sh.bad != 0;
+    RowPartial r;
+    r.ref = (double)m; r.a = (double)m; r.Z = bad ? 0.0 : tz; r.S = bad ? 0.0 : ts;
+    r.n_top = 0; r.flags = bad ? 1u : 0u;
+    rr.part = r;
   }
 }
 
@@ -275,6 +279,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
     TreeState st, ScoreParams sp) {
   typedef LogitTraits<DT> T;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
+  touch_kernel_arguments<32 + (int)sizeof(TreeState) + (int)sizeof(ScoreParams)>();
   const int nsplit = sp.nsplit, K = sp.K;
   const int split = blockIdx.x % nsplit;
   const RowOfWorkgroup rw = row_of_workgroup(st, sp, blockIdx.x / nsplit);
@@ -285,13 +290,28 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
   const Segment sg = make_segment<T::EPC>(V, split, cps);
   __shared__ RowResult rr;
   C2T_PT(PT_START);
-  const float parent_P = st.fr_P[row];                     // requested ahead of the logits, stored behind them
-  if (sg.ncell == 0) { if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; } }
-  else direct_segment<DT, NT>(rowp, V, K, sg, dyn_lds, make_select_lds<NT, 1, T::EPC>(dyn_lds, sp.lds_bytes), &rr);
-  if (nsplit == 1 && sp.M > 0) { __syncthreads(); top_m_of_split_row<DT, NT>(rowp, V, sp.M, rr); }
-  if (threadIdx.x == 0) rr.parent_P = parent_P;
-  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, dyn_lds, cls, nullptr,     // split records are indexed by launched row
-                   [&](RowResult& r) { top_m_of_split_row<DT, NT>(rowp, V, sp.M, r); });
+  __shared__ DirectShared<NT> sh;
+  const ClassifierStage cst = stage_classifier(cls, sp.h, sp.w_lds_off >= 0 ? (float*)(dyn_lds + sp.w_lds_off) : nullptr);
+  const SelectLds sel = make_select_lds<NT, 1, T::EPC>(dyn_lds, sp.lds_bytes);
+  SegmentTop top{RANKED_IN_RR, false};
+  bool have_record = true;                                 // (uniform) rr.part is complete
+  if (sg.ncell == 0) {
+    store_classifier(cst);
+    if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
+    __syncthreads();
+  } else {
+    top = direct_segment<DT, NT>(rowp, V, K, sg, dyn_lds, sel, cst, sh, &rr);
+    have_record = top.n_el < 0;
+  }
+  const auto top_m = [&](RowResult& r) { top_m_of_split_row<DT, NT>(rowp, V, sp.M, r); };
+  if (nsplit == 1 && sp.M > 0) {
+    if (!have_record && threadIdx.x < WAVE) combine_waves(sh, rr);
+    __syncthreads();
+    have_record = true;
+    top_m(rr);
+  }
+  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst,     // split records are indexed by launched row
+                   [&] { if (!have_record) combine_waves(sh, rr); }, top_m);
 }
 
 }  // namespace c2t

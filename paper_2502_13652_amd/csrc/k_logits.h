@@ -36,26 +36,9 @@
 
 namespace c2t {
 
-constexpr int SEL_CELL_CAP = 256;              // size of the candidate-cell list
 #ifndef C2T_TAU_LOW_BIT
 #define C2T_TAU_LOW_BIT 16
 #endif
-
-// LDS the selection may use once the cell list is built: the element list ((value, id), 8 bytes
-// an entry, overlaying histogram and cell map) and the number of cells a launch may keep:
-// min(SEL_CELL_CAP, NT / CPC, list entries / elements per cell), which the host keeps >= 2K - 1.
-struct SelectLds {
-  unsigned char* list;
-  int list_cap;       // entries
-  int cell_cap;
-};
-template <int NT, int CPC, int EPC>
-__device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int bytes) {
-  SelectLds s;
-  s.list = base; s.list_cap = bytes / 8;
-  s.cell_cap = min(min(SEL_CELL_CAP, NT / CPC), s.list_cap / (CPC * EPC));
-  return s;
-}
 
 template <int DT> struct LogitTraits;
 template <> struct LogitTraits<1> {     // bf16
@@ -159,8 +142,8 @@ __device__ __forceinline__ void collect_cells(const uint4* __restrict__ rowp, in
                                               const int32_t* cell_list, int n_cells, const SelectLds& sel, int32_t* sh_cnt) {
   typedef LogitTraits<DT> T;
   const int tid = threadIdx.x;
-  float* el_v = (float*)sel.list;
-  int32_t* el_i = (int32_t*)(sel.list + (size_t)sel.list_cap * 4);
+  float* el_v = sel.values();
+  int32_t* el_i = sel.ids();
   int my_chunk = -1;
   uint4 q = make_uint4(0, 0, 0, 0);
   if (tid < n_cells * CPC) {                                 // n_cells <= cell_cap <= NT / CPC
@@ -190,8 +173,8 @@ __device__ __forceinline__ void tie_scan(const uint4* __restrict__ rowp, const S
   typedef LogitTraits<DT> T;
   constexpr int NW = NT / WAVE;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
-  float* el_v = (float*)sel.list;
-  int32_t* el_i = (int32_t*)(sel.list + (size_t)sel.list_cap * 4);
+  float* el_v = sel.values();
+  int32_t* el_i = sel.ids();
   int found = 0;                                             // uniform
 #pragma unroll 1
   for (int base = sg.c0; base < sg.c1 && found < need; base += NT) {
@@ -219,60 +202,6 @@ __device__ __forceinline__ void tie_scan(const uint4* __restrict__ rowp, const S
     found += total;
     __syncthreads();
   }
-}
-
-// Rank the element list exactly by (logit desc, id asc) and write the best K.
-template <int NT>
-__device__ __forceinline__ int rank_list(int K, const SelectLds& sel, const int32_t* sh_cnt, float* topv, int32_t* topi) {
-  const int tid = threadIdx.x;
-  const float* el_v = (const float*)sel.list;
-  const int32_t* el_i = (const int32_t*)(sel.list + (size_t)sel.list_cap * 4);
-  const int n_el = min(*sh_cnt, sel.list_cap);
-  if (n_el <= 64) {
-    // short list (the usual case: K to 2K-1 elements): T lanes per element, each compares it with
-    // every T-th entry, one value per step; the partial ranks are summed over the T lanes
-    int tshift = 0;
-    while (tshift < 4 && (n_el << (tshift + 1)) <= NT) ++tshift;
-    const int T = 1 << tshift, e = tid >> tshift, sub = tid & (T - 1);
-    const bool mine = e < n_el;
-    const float v = mine ? el_v[e] : 0.f; const int id = mine ? el_i[e] : 0;
-    int rank = 0;
-    if (mine) {
-      for (int o = sub; o < n_el; o += T) {
-        const float q = el_v[o];
-        if (q > v) rank += 1;
-        else if (q == v && o != e) rank += el_i[o] < id;
-      }
-    }
-    if (tshift >= 1) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)rank);
-    if (tshift >= 2) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)rank);
-    if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
-    if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
-    if (mine && sub == 0 && rank < K) { topv[rank] = v; topi[rank] = id; }
-    return min(n_el, K);
-  }
-#pragma unroll 1
-  for (int e = tid; e < n_el; e += NT) {
-    const float v = el_v[e]; const int id = el_i[e];
-    int rank = 0;
-    // eight values per step (entries past n_el are masked): every dependent LDS read is slow while
-    // the neighbouring workgroups fill their histograms
-#pragma unroll 1
-    for (int o = 0; o < n_el; o += 8) {
-      const float4 qa = *(const float4*)(el_v + o), qb = *(const float4*)(el_v + o + 4);
-      const float vo[8] = {qa.x, qa.y, qa.z, qa.w, qb.x, qb.y, qb.z, qb.w};
-      uint32_t eq = 0;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const bool in = o + t < n_el;
-        rank += in && vo[t] > v; eq |= (in && vo[t] == v ? 1u : 0u) << t;
-      }
-      eq &= ~(e >= o && e < o + 8 ? 1u << (e - o) : 0u);    // not the element itself
-      while (eq) { const int t = __ffs(eq) - 1; eq &= eq - 1; rank += el_i[o + t] < id; }
-    }
-    if (rank < K) { topv[rank] = v; topi[rank] = id; }
-  }
-  return min(n_el, K);
 }
 
 // Sum of Z and S over the workgroup in a fixed order (wave butterflies, then waves ascending).
@@ -531,14 +460,15 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
   collect_cells<DT, NT, CPC>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
   if (ties) tie_scan<DT, NT>(rowp, sg, V, tau, K, sel, &sh_cnt, scan_tmp);
   C2T_PT(PT_CELLS_READ);
-  const int n_top = rank_list<NT>(K, sel, &sh_cnt, rr->topv, rr->topi);
-  C2T_PT(PT_RANKED);
+  const int n_el = min(sh_cnt, sel.list_cap), n_top = min(n_el, K);
+  rank_list<NT>(K, sel, n_el, rr->topv, rr->topi);
   if (tid == 0) {
     RowPartial r;
     r.ref = (double)m; r.a = (double)m; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = seg_bad ? 0 : n_top; r.flags = (seg_bad ? 1u : 0u) | info_flags;
     rr->part = r;
     if (top_m > 0) { rr->ZM = sum_m[0]; rr->SM = sum_m[1]; }
   }
+  __syncthreads();                                           // rr is complete
 }
 
 // Workgroups of a sequence whose frontier is empty have nothing to read; the first of them
@@ -968,19 +898,20 @@ __device__ __forceinline__ bool share_row(const ScoreParams& sp, int split, int6
 // hist: HP_WORDS words; map_lds: one 2-byte key per cell, padded to 16 bytes; sel: see SelectLds.
 // TOPM: built with the entropy over the M largest logits (a separate instantiation, so that the
 // default kernel carries none of its registers).
-// COOP: built with the hand-over of a shared row (see share_row); returns false in the workgroups
-// that have handed their segment over and are done, true in the one that holds the row's result.
+// COOP: built with the hand-over of a shared row (see share_row); returns HANDED_OVER in the workgroups
+// that have handed their segment over and are done.
+constexpr int HANDED_OVER = -2, RANKED_IN_RR = -1;     // SegmentTop::n_el
 template <int NT, bool TOPM, int WPS, int REPL, bool COOP>
-__device__ __forceinline__ bool hist_segment(const uint4* __restrict__ rowp, int V, int K, int M, const Segment& sg_own,
+__device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ rowp, int V, int K, int M, const Segment& sg_own,
                                              const double* __restrict__ tab_e, uint32_t* __restrict__ hist,
                                              unsigned char* map_lds, const SelectLds& sel, RowResult* rr,
-                                             const ClassifierStage cst, const ScoreParams& sp, int split, int64_t row_launched,
-                                             int32_t* row_ticket) {
+                                             const ClassifierStage cst, const TreeState& st, const ScoreParams& sp, int split,
+                                             int64_t row_launched, int64_t slot) {
   constexpr int NW = NT / WAVE;
   constexpr int WPL = HP_WORDS / NT;                   // words per lane in the epilogue (8 at 512 threads)
   static_assert(NW <= 16 && WPL % 4 == 0, "one DPP row holds the per-wave partials; a lane reads whole 16-byte runs");
   uint16_t* map = (uint16_t*)map_lds;
-  __shared__ double red_d[2][NW], sum_d[2], sum_m[2];
+  __shared__ double red_d[2][NW], sum_d[2];
   __shared__ float red_v[NW];
   __shared__ uint32_t red_m[NW];
   __shared__ OutsideAcc sh_out;
@@ -1119,7 +1050,7 @@ __device__ __forceinline__ bool hist_segment(const uint4* __restrict__ rowp, int
     }
   }
   if (shared_row) {
-    if (!share_row<NT>(sp, split, row_launched, row_ticket, sg, hist, w0, map, &sh_out, red_m)) return false;
+    if (!share_row<NT>(sp, split, row_launched, st.row_tickets + slot, sg, hist, w0, map, &sh_out, red_m)) return SegmentTop{HANDED_OVER, false};
     sg = make_segment<8>(V, 0, (V + 7) / 8);             // the epilogue below is the whole row's
     ef = load_exp_factors(tab_e, tid);
   }
@@ -1250,7 +1181,7 @@ __device__ __forceinline__ bool hist_segment(const uint4* __restrict__ rowp, int
       (TOPM && n_tiny > 0 && tot_p < M && M < tot_p + n_tiny)) {
     __syncthreads();
     generic_segment<1, NT, HP_CPC>(rowp, V, K, M, sg, map_lds, sel, rr, 2u);
-    return true;
+    return SegmentTop{RANKED_IN_RR, false};
   }
   if (TOPM) {
     // Eq. 2, second line: Z and S restricted to the M largest logits.  A lane's values, from the
@@ -1289,7 +1220,7 @@ __device__ __forceinline__ bool hist_segment(const uint4* __restrict__ rowp, int
           const double zt = (double)n_tiny + sh_out.s_tiny;
           tz += zt; ts += sh_out.s_tiny - (double)m * zt;
         }
-        sum_m[0] = tz; sum_m[1] = ts;
+        rr->ZM = tz; rr->SM = ts;
       }
     }
   }
@@ -1324,18 +1255,20 @@ __device__ __forceinline__ bool hist_segment(const uint4* __restrict__ rowp, int
     if (tid == 0) sh_cnt = 0;
     __syncthreads();
   }
-  collect_cells<1, NT, HP_CPC>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
-  if (ties) tie_scan<1, NT>(rowp, sg, V, tau, eq_limit, sel, &sh_cnt, scan_tmp);
-  C2T_PT(PT_CELLS_READ);
-  const int n_top = rank_list<NT>(K, sel, &sh_cnt, rr->topv, rr->topi);
-  C2T_PT(PT_RANKED);
-  if (tid == 0) {
-    RowPartial r;
-    r.ref = (double)m; r.a = 0.0; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = n_top; r.flags = 0u;
-    rr->part = r;
-    if (TOPM) { rr->ZM = sum_m[0]; rr->SM = sum_m[1]; }
+  // While the first wavefronts wait for the cells they read again (n_cells is K to 2K, four chunks each), the last one
+  // forms the row's entropy from the sums: fp64 log, exp and divide, half a microsecond and more off the tail.
+  const bool entropy = sp.nsplit == 1;
+  if (wid == NW - 1) {
+    if (lane == 0) { RowPartial r; r.ref = (double)m; r.a = 0.0; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = 0; r.flags = 0u; rr->part = r; }
+    if (entropy) row_entropy(st, sp, slot, (double)m, 0.0, sum_d[0], sum_d[1], 0u, *rr);
   }
-  return true;
+  collect_cells<1, NT, HP_CPC>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
+  if (ties) {
+    tie_scan<1, NT>(rowp, sg, V, tau, eq_limit, sel, &sh_cnt, scan_tmp);
+    __syncthreads();
+  }
+  C2T_PT(PT_CELLS_READ);
+  return SegmentTop{min(sh_cnt, sel.list_cap), entropy};
 }
 
 // grid: rows_launched * nsplit workgroups of NT threads.
@@ -1348,6 +1281,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     const void* __restrict__ logits, int64_t row_stride_elems, int V, int cps, const double* __restrict__ tab_e,
     const float* __restrict__ cls, TreeState st, ScoreParams sp) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
+  touch_kernel_arguments<40 + (int)sizeof(TreeState) + (int)sizeof(ScoreParams)>();
   const int nsplit = (COOP && sp.coop > 1) ? sp.coop : sp.nsplit, K = sp.K;     // workgroups per row, either way
   const int split = blockIdx.x % nsplit;
   const RowOfWorkgroup rw = row_of_workgroup(st, sp, blockIdx.x / nsplit);
@@ -1358,19 +1292,21 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
   const Segment sg = make_segment<8>(V, split, cps);
   __shared__ RowResult rr;
   C2T_PT(PT_START);
-  if (threadIdx.x == 0) rr.parent_P = st.fr_P[row];        // off the tail's critical path
   // The classifier's parameters (5h+1 <= 1281 floats) are copied to LDS for the scoring step: the
   // loads are issued now, four floats a thread, and stored behind the streaming loop.
   const ClassifierStage cst = stage_classifier(cls, sp.h, (!TOPM && sp.w_lds_off >= 0) ? (float*)(dyn_lds + sp.w_lds_off) : nullptr);
+  const SelectLds sel = make_select_lds<NT, HP_CPC, 8>(dyn_lds, sp.lds_bytes);
+  SegmentTop top{RANKED_IN_RR, false};
   if (sg.ncell == 0) {                                     // (loaded again here: the copy above must not stay in registers for this)
     store_classifier(stage_classifier(cls, sp.h, cst.dst));
     if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
+    __syncthreads();
+  } else {
+    top = hist_segment<NT, TOPM, WPS, REPL, COOP>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, dyn_lds + HP_WORDS * 4 * REPL,
+                                                  sel, &rr, cst, st, sp, split, rl, row);
+    if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
-  else if (!hist_segment<NT, TOPM, WPS, REPL, COOP>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, dyn_lds + HP_WORDS * 4 * REPL,
-                        make_select_lds<NT, HP_CPC, 8>(dyn_lds, sp.lds_bytes), &rr, cst, sp, split, rl,
-                        st.row_tickets + (int64_t)b * sp.F + f))
-    return;                                                // a shared row's segment, handed over
-  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, dyn_lds, cls, cst.dst,
+  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst, [] {},
                    [&](RowResult& r) { if (TOPM) top_m_of_split_row<1, NT>(rowp, V, sp.M, r); });
 }
 

@@ -110,6 +110,41 @@ __device__ __forceinline__ float mlp_logit_lds(LdsFloats w, int h, float P, floa
   return z;
 }
 
+// The same for wide classifiers, by a whole workgroup of NT threads: a lane per candidate would wait for five wide LDS
+// reads per four units, 256 units one after the other (6.5 us); here every thread forms hidden activations of
+// one candidate, NT / K units at a time, and only the chain z = fma(w2_j, a_j, z) is left to the candidate's lane.
+// Same operations in the same order.  P: LDS, the candidates' joint probabilities; act: scratch of act_bytes;
+// entry behind a barrier that publishes P.  Returns z in lanes tid < K.
+template <int NT>
+__device__ __forceinline__ float mlp_logit_spread(LdsFloats w, int h, const float* P, float H, float d, int K, uint32_t k_inverse,
+                                                  float* act, int act_bytes) {
+  const int tid = threadIdx.x;
+  LdsFloats W1 = w; LdsFloats b1 = w + 3 * h; LdsFloats w2 = w + 4 * h;
+  const int step = NT / K, first = (int)(((uint32_t)tid * k_inverse) >> 20), cand = tid - first * K;      // first = tid / K
+  const int block = min(h, act_bytes / (4 * K));             // units whose activations fit the scratch
+  const float Pc = P[cand];
+  float z = w[5 * h];
+  for (int j0 = 0; j0 < h; j0 += block) {
+    const int n = min(block, h - j0);
+    if (first < step) {
+      for (int u = first; u < n; u += step) {
+        const int j = j0 + u;
+        float a = __fmaf_rn(W1[3 * j + 0], Pc, b1[j]);
+        a = __fmaf_rn(W1[3 * j + 1], H, a);
+        a = __fmaf_rn(W1[3 * j + 2], d, a);
+        act[u * K + cand] = a > 0.0f ? a : 0.0f;
+      }
+    }
+    __syncthreads();
+    if (tid < K) {
+#pragma unroll 8
+      for (int u = 0; u < n; ++u) z = __fmaf_rn(w2[j0 + u], act[u * K + tid], z);
+    }
+    __syncthreads();
+  }
+  return z;
+}
+
 constexpr int SP_MAX_F = 64;
 constexpr int C2T_MAX_BUDGET_DEV = 1024;                  // n_out limit of the reranking
 constexpr int C2T_MAX_CANDIDATES_DEV = 2048;              // F*K limit of the per-sequence step
@@ -126,6 +161,7 @@ struct ScoreParams {
   int lds_bytes;                                             // dynamic LDS of the launch
   int w_lds_off;                                             // byte offset of the classifier's copy in dynamic LDS, -1: none
   int compact;                                               // 1: workgroup w takes the w-th live row (see row_of_workgroup)
+  uint32_t k_inverse;                                        // ceil(2^20 / K): (i * k_inverse) >> 20 is i / K for i < 2048, K <= 64
   float z_beta;
   // Shared rows of the histogram path (coop > 1, then nsplit == 1): `coop` workgroups count one row's
   // segments and hand their counts over through memory; the last to arrive runs the row's epilogue.
@@ -136,171 +172,240 @@ struct ScoreParams {
   CoopAcc* coop_acc;                                         // [launched row][coop]
 };
 
-// What one workgroup of the logits pass leaves in LDS for its (row, split): the record and the
-// segment's top-K list (value desc, id asc).
+// What one workgroup of the logits pass leaves in LDS for its (row, split): the record, the segment's
+// top-K list (value desc, id asc) where it has been ranked, and what scoring the row needs besides.
 struct RowResult {
   RowPartial part;
   double ZM, SM;      // the sums of Z and S restricted to the M largest logits (Eq. 2, second line); M > 0 only
-  float parent_P;     // joint probability of the row's frontier node, fetched when the workgroup starts
+  double Zr;          // sum of e^(x - R) over the row, R = part.ref
+  float H;            // entropy of the row
+  uint32_t bad;       // no candidate comes from this row
+  float parent_P, parent_s; int32_t parent_hidx;     // of the row's frontier node
   float topv[64];
   int32_t topi[64];
 };
 
-// ---- row level, splits > 1: combine the row's split records (fp64) and top lists into `rr`.
-// Run by the workgroup that delivered the row's last split; `lds`/`lds_bytes` is free scratch.
-__device__ __forceinline__ void merge_row(const ScoreParams& sp, int64_t row_launched, RowResult& rr,
-                                          unsigned char* lds, size_t lds_bytes) {
-  const int tid = threadIdx.x, nt = blockDim.x, nsplit = sp.nsplit, K = sp.K;
-  const RowPartial* rp = sp.part + row_launched * nsplit;
-  const float* tv = sp.part_topv + row_launched * nsplit * K;
-  const int32_t* ti = sp.part_topi + row_launched * nsplit * K;
-  const int per_row = nsplit * K;
-  const bool staged = (size_t)per_row * 8 <= lds_bytes;      // the lists fit the staging area in LDS
-  // Everything the merge reads is requested before anything is waited for: one memory round trip instead of
-  // four dependent ones (maximum, records, list lengths, entries).  A thread's first list entry (all of them
-  // when the row's lists hold at most one entry a thread): requested whether valid or not, masked below.
-  const bool in0 = staged && tid < per_row;
-  int n_top0 = 0, i0 = -1; float v0 = 0.f;
-  if (in0) { n_top0 = ld_dev(&rp[tid / K].n_top); v0 = ld_dev(tv + tid); i0 = ld_dev(ti + tid); }
-  if (tid < WAVE) {                                          // wave 0: the sums, one split per lane and step
-    const int lane = tid;
-    float Rf = -INFINITY; uint32_t fl = 0;                   // ref holds a logit: exact as a float
-    double Z = 0.0, S = 0.0;
-    if (nsplit <= WAVE) {
-      RowPartial pq = empty_partial();
-      if (lane < nsplit) pq = ld_dev(rp + lane);
-      Rf = wave_max(lane < nsplit ? (float)pq.ref : -INFINITY);
-      fl = wave_reduce_u32(pq.flags, 0u, [](uint32_t x, uint32_t y) { return x | y; });
-      const double R = (double)Rf;
-      if (pq.Z > 0.0 && pq.ref > -INFINITY) {
-        const double da = pq.a - R, dl = pq.ref - R;         // re-reference to the row maximum R; dl <= 0
-        const double sc = da == 0.0 ? 1.0 : exp(da);
-        Z = pq.Z * sc; S = (pq.S + dl * pq.Z) * sc;
-      }
-    } else {
-      for (int q = lane; q < nsplit; q += WAVE) { Rf = fmaxf(Rf, (float)ld_dev(&rp[q].ref)); fl |= ld_dev(&rp[q].flags); }
-      Rf = wave_max(Rf);
-      fl = wave_reduce_u32(fl, 0u, [](uint32_t x, uint32_t y) { return x | y; });
-      const double R = (double)Rf;
-      for (int q = lane; q < nsplit; q += WAVE) {
-        const RowPartial pq = ld_dev(rp + q);
-        if (pq.Z > 0.0 && pq.ref > -INFINITY) {
-          const double da = pq.a - R, dl = pq.ref - R;
-          const double sc = da == 0.0 ? 1.0 : exp(da);
-          Z += pq.Z * sc; S += (pq.S + dl * pq.Z) * sc;
-        }
-      }
-    }
-    const double R = (double)Rf;
-    Z = wave_sum(Z); S = wave_sum(S);
-    if (lane == 0) { rr.part.ref = R; rr.part.a = R; rr.part.Z = Z; rr.part.S = S; rr.part.flags = fl; rr.part.n_top = 0; }
-  }
-  // An entry's merged rank = number of entries of the row's lists ahead of it.
-  float* sv = (float*)lds; int32_t* si = (int32_t*)(lds + (size_t)per_row * 4);
-  __shared__ int32_t n_valid;
-  if (tid == 0) n_valid = 0;
-  __syncthreads();
-  if (staged) {
-    // an unused slot of a list: below every entry in the order (value desc, id asc), -inf entries included
-    constexpr int32_t NO_ID = 0x7fffffff;
-    if (in0) {
-      const bool ok = tid % K < n_top0;
-      sv[tid] = ok ? v0 : -INFINITY;
-      si[tid] = ok ? i0 : NO_ID;
-      if (ok) atomicAdd(&n_valid, 1);
-    }
-    for (int ent = tid + nt; ent < per_row; ent += nt) {
-      const int q = ent / K, e = ent % K;
-      const bool ok = e < ld_dev(&rp[q].n_top);
-      sv[ent] = ok ? ld_dev(tv + ent) : -INFINITY;
-      si[ent] = ok ? ld_dev(ti + ent) : NO_ID;
-      if (ok) atomicAdd(&n_valid, 1);
-    }
-    __syncthreads();
-    for (int ent = tid; ent < per_row; ent += nt) {
-      const int vi = si[ent];
-      if (vi == NO_ID) continue;
-      const float v = sv[ent];
-      const int ahead = count_ahead4(sv, per_row, 0, 4, v, ent, [&](int o) { return si[o] < vi; });
-      if (ahead < K) { rr.topv[ahead] = v; rr.topi[ahead] = vi; }
-    }
-  } else {
-    // the lists exceed the staging area (very many splits): rank from global memory
-    for (int ent = tid; ent < per_row; ent += nt) {
-      const int q = ent / K, e = ent % K;
-      if (e >= ld_dev(&rp[q].n_top)) continue;
-      atomicAdd(&n_valid, 1);
-      const float v = ld_dev(tv + ent); const int vi = ld_dev(ti + ent);
-      int ahead = 0;
-      for (int q2 = 0; q2 < nsplit; ++q2) {
-        const int n2 = ld_dev(&rp[q2].n_top);
-        for (int e2 = 0; e2 < n2; ++e2) {
-          const float v2 = ld_dev(tv + q2 * K + e2);
-          ahead += (v2 > v) || (v2 == v && ld_dev(ti + q2 * K + e2) < vi);
-        }
-      }
-      if (ahead < K) { rr.topv[ahead] = v; rr.topi[ahead] = vi; }
-    }
-  }
-  __syncthreads();
-  if (tid == 0) rr.part.n_top = min(n_valid, K);
-  __syncthreads();
+// LDS of the selection of a segment's (or a row's) K largest logits: the element list ((value, id), 8 bytes an
+// entry, overlaying histogram and cell map) and the number of cells a launch may keep:
+// min(SEL_CELL_CAP, NT / CPC, list entries / elements per cell), which the host keeps >= 2K - 1.
+constexpr int SEL_CELL_CAP = 256;              // size of the candidate-cell list
+struct SelectLds {
+  unsigned char* list;
+  int list_cap;       // entries
+  int cell_cap;
+  __device__ __forceinline__ float* values() const { return (float*)list; }
+  __device__ __forceinline__ int32_t* ids() const { return (int32_t*)(list + (size_t)list_cap * 4); }
+};
+template <int NT, int CPC, int EPC>
+__device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int bytes) {
+  SelectLds s;
+  s.list = base; s.list_cap = bytes / 8;
+  s.cell_cap = min(min(SEL_CELL_CAP, NT / CPC), s.list_cap / (CPC * EPC));
+  return s;
 }
 
-// ---- row level: entropy (Eq. 2), generation and joint probabilities (Eq. 1), classifier logit
-// (Eq. 3) of the row's K candidates, from the complete row result in `rr`.  One lane per candidate.
-// `w`: the classifier parameters in global memory, read-only for the whole kernel: every lane
-// reads the same addresses, so the loads are scalar and touch neither LDS nor the vector memory path.
-__device__ __forceinline__ void score_row(const TreeState& s, const ScoreParams& sp, int b, int f, const RowResult& rr,
-                                          const float* __restrict__ w, const float* w_lds) {
-  const int tid = threadIdx.x, K = sp.K;
-  if (tid >= K) return;
-  const float parP = rr.parent_P;
-  const double R = rr.part.ref, Z = rr.part.Z;
-  const uint32_t fl = rr.part.flags;
-  const bool bad = (fl & 1u) != 0 || !(Z > 0.0) || !(R > -INFINITY) || !(R < INFINITY);
-  // re-reference the sums from the offset a to the row maximum R (= ref): p_j = e^(x_j - R) / Zr,
-  // H = -sum p ln p = ln Zr - Sr / Zr
-  const double sc = rr.part.a == R ? 1.0 : exp(rr.part.a - R);
-  const double Zr = Z * sc, Sr = rr.part.S * sc;
+// ---- ranking of the element list by (logit desc, id asc), exactly; the best K go to topv, topi.
+// Short lists (the usual case: K to 2K-1 elements): T lanes per element, each compares it with every T-th entry, one
+// value per step; the partial ranks are summed over the T lanes.  Only the first RANK_NT threads take part, so that
+// another wavefront can form the row's entropy meanwhile.
+constexpr int RANK_SHORT = 64, RANK_NT = 256;
+__device__ __forceinline__ void rank_short(int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
+  const int tid = threadIdx.x;
+  const float* el_v = sel.values(); const int32_t* el_i = sel.ids();
+  if (tid >= RANK_NT) return;                                // whole wavefronts
+  int tshift = 0;
+  while (tshift < 4 && (n_el << (tshift + 1)) <= RANK_NT) ++tshift;
+  const int T = 1 << tshift, e = tid >> tshift, sub = tid & (T - 1);
+  const bool mine = e < n_el;
+  int rank = 0, id = 0; float v = 0.f;
+  if (mine) {
+    v = el_v[e]; id = el_i[e];
+    for (int o = sub; o < n_el; o += T) {
+      const float q = el_v[o];
+      if (q > v) rank += 1;
+      else if (q == v && o != e) rank += el_i[o] < id;
+    }
+  }
+  if (tshift >= 1) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)rank);
+  if (tshift >= 2) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)rank);
+  if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
+  if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
+  if (mine && sub == 0 && rank < K) { topv[rank] = v; topi[rank] = id; }
+}
+// Any length, all threads: the best K to topv, topi.
+template <int NT>
+__device__ __forceinline__ void rank_long(int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
+  const float* el_v = sel.values(); const int32_t* el_i = sel.ids();
+#pragma unroll 1
+  for (int e = threadIdx.x; e < n_el; e += NT) {
+    const float v = el_v[e]; const int id = el_i[e];
+    // every dependent LDS read is slow while the neighbouring workgroups fill their histograms
+    const int rank = count_ahead4(el_v, n_el, 0, 4, v, e, [&](int o) { return el_i[o] < id; });
+    if (rank < K) { topv[rank] = v; topi[rank] = id; }
+  }
+}
+template <int NT>
+__device__ __forceinline__ void rank_list(int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
+  if (n_el <= RANK_SHORT) rank_short(K, sel, n_el, topv, topi);
+  else rank_long<NT>(K, sel, n_el, topv, topi);
+}
+
+// ---- row level: entropy (Eq. 2) from the row's sums, and what the row's frontier node hands down; by one wavefront.
+// Re-references the sums from the offset a to the row maximum R: p_j = e^(x_j - R) / Zr, H = -sum p ln p = ln Zr - Sr / Zr.
+__device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParams& sp, int64_t slot, double R, double a, double Z, double S,
+                                            uint32_t flags, RowResult& rr) {
+  const float pp = s.fr_P[slot];
+  int hidx = -1; float ps = INFINITY;
+  if (s.h_tok) { hidx = s.fr_hidx[slot]; ps = s.fr_s[slot]; }
+  const bool bad = (flags & 1u) != 0 || !(Z > 0.0) || !(R > -INFINITY) || !(R < INFINITY);
+  const double sc = a == R ? 1.0 : exp(a - R);
+  const double Zr = Z * sc, Sr = S * sc;
   // Eq. 2, second line: -sum over the M most probable tokens of p ln p, p from the full softmax:
   // (ln Zr * ZMr - SMr) / Zr with the sums restricted to those tokens
   const float H = bad ? 0.f : sp.M > 0 ? (float)((log(Zr) * (rr.ZM * sc) - rr.SM * sc) / Zr) : (float)(log(Zr) - Sr / Zr);
+  if (lane_id() == 0) {
+    rr.Zr = Zr; rr.H = H; rr.bad = bad ? 1u : 0u;
+    rr.parent_P = pp; rr.parent_s = ps; rr.parent_hidx = hidx;
+  }
+}
+
+// ---- row level: generation and joint probability (Eq. 1) and classifier logit (Eq. 3) of the row's n candidates, from
+// the complete row result in `rr`; one lane of the first wavefront per candidate (a wavefront issues the classifier's
+// chain once for all of them).
+// `w`: the classifier parameters in global memory, read-only for the whole kernel: every lane
+// reads the same addresses, so the loads are scalar and touch neither LDS nor the vector memory path.
+#ifndef C2T_MLP_SPREAD_MIN
+#define C2T_MLP_SPREAD_MIN 48
+#endif
+constexpr int MLP_SPREAD_MIN = C2T_MLP_SPREAD_MIN;   // hidden units from which on the whole workgroup evaluates the classifier
+template <int NT>
+__device__ __forceinline__ void score_row(const TreeState& s, const ScoreParams& sp, int b, int f, RowResult& rr, int n,
+                                          const float* __restrict__ w, const float* w_lds, unsigned char* lds) {
+  const int tid = threadIdx.x, K = sp.K, FK = sp.F * K;
+  const float H = rr.H;
+  const bool spread = w_lds && sp.h >= MLP_SPREAD_MIN;       // (uniform)
   float z = -INFINITY, p32 = 0.f, P32 = 0.f; int tok = -1;
-  if (!bad && tid < rr.part.n_top) {
+  const bool mine = !rr.bad && tid < n;                      // n <= K
+  if (mine) {
     tok = rr.topi[tid];
-    p32 = (float)(exp((double)rr.topv[tid] - R) / Zr);
-    P32 = parP * p32;
+    p32 = (float)(exp((double)rr.topv[tid] - rr.part.ref) / rr.Zr);
+    P32 = rr.parent_P * p32;
+  }
+  if (spread) {
+    if (tid < K) rr.topv[tid] = P32;                         // each lane overwrites the logit it has just read
+    __syncthreads();
+    z = mlp_logit_spread<NT>((LdsFloats)w_lds, sp.h, rr.topv, H, (float)sp.layer, K, sp.k_inverse, (float*)lds, sp.lds_bytes);
+    if (!mine) z = -INFINITY;
+  }
+  if (tid >= K) return;
+  if (mine && !spread) {
     z = w_lds ? mlp_logit_lds((LdsFloats)w_lds, sp.h, P32, H, (float)sp.layer) : mlp_logit(w, sp.h, P32, H, (float)sp.layer);
   }
-  const int64_t o = (int64_t)b * sp.F * K + (int64_t)f * K + tid;
-  st_dev(s.c_tok + o, tok); st_dev(s.c_p + o, p32); st_dev(s.c_P + o, P32); st_dev(s.c_H + o, H); st_dev(s.c_z + o, z);
-  if (tid == 0) st_dev(s.row_info + (int64_t)b * sp.F + f, (uint32_t)(bad ? 1u : 0u) | (fl & 2u));
+  const int64_t row = (int64_t)b * FK + (int64_t)f * K;     // uniform; the lane's offset stays 32 bits wide
+  st_dev(s.c_tok + row + tid, tok); st_dev(s.c_p + row + tid, p32); st_dev(s.c_P + row + tid, P32);
+  st_dev(s.c_H + row + tid, H); st_dev(s.c_z + row + tid, z);
+  if (tid == 0) st_dev(s.row_info + (int64_t)b * sp.F + f, (uint32_t)(rr.bad ? 1u : 0u) | (rr.part.flags & 2u));
   if (s.h_tok) {                                             // keep the candidate for the reranking
-    const int FK = sp.F * K;
-    const int64_t hi = ((int64_t)b * sp.D + sp.layer) * FK + (int64_t)f * K + tid;
-    s.h_tok[hi] = tok; s.h_par[hi] = s.fr_hidx[(int64_t)b * sp.F + f];
-    s.h_P[hi] = P32; s.h_H[hi] = H; s.h_z[hi] = z;
-    s.h_s[hi] = fminf(s.fr_s[(int64_t)b * sp.F + f], z);
+    const int64_t h = ((int64_t)b * sp.D + sp.layer) * FK + (int64_t)f * K;
+    s.h_tok[h + tid] = tok; s.h_par[h + tid] = rr.parent_hidx;
+    s.h_P[h + tid] = P32; s.h_H[h + tid] = H; s.h_z[h + tid] = z;
+    s.h_s[h + tid] = fminf(rr.parent_s, z);
+  }
+}
+
+// ---- row level, splits > 1, by the workgroup that delivered the row's last split.
+// Everything the merge reads is requested before anything is waited for: one memory round trip.  One wavefront
+// combines the split records in fp64; the others stage the lists in the element list, where an unused
+// slot of a split's list lies below every entry in the order (value desc, id asc), -inf entries included.
+constexpr int32_t NO_ID = 0x7fffffff;
+struct RowSums { double R, Z, S; uint32_t flags; int n_valid; };       // uniform over the wavefront
+__device__ __forceinline__ RowSums merge_records(const RowPartial* rp, int nsplit) {
+  const int lane = lane_id();
+  RowSums m; m.n_valid = 0;
+  float Rf = -INFINITY; uint32_t fl = 0; double Z = 0.0, S = 0.0;       // ref holds a logit: exact as a float
+  if (nsplit <= WAVE) {
+    RowPartial pq = empty_partial();
+    if (lane < nsplit) pq = ld_dev(rp + lane);
+    Rf = wave_max(lane < nsplit ? (float)pq.ref : -INFINITY);
+    fl = wave_reduce_u32(pq.flags, 0u, [](uint32_t x, uint32_t y) { return x | y; });
+    m.n_valid = wave_sum_i(pq.n_top);
+    const double R = (double)Rf;
+    if (pq.Z > 0.0 && pq.ref > -INFINITY) {
+      const double da = pq.a - R, dl = pq.ref - R;           // re-reference to the row maximum R; dl <= 0
+      const double sc = da == 0.0 ? 1.0 : exp(da);
+      Z = pq.Z * sc; S = (pq.S + dl * pq.Z) * sc;
+    }
+  } else {
+    int nv = 0;
+    for (int q = lane; q < nsplit; q += WAVE) { Rf = fmaxf(Rf, (float)ld_dev(&rp[q].ref)); fl |= ld_dev(&rp[q].flags); nv += ld_dev(&rp[q].n_top); }
+    Rf = wave_max(Rf);
+    fl = wave_reduce_u32(fl, 0u, [](uint32_t x, uint32_t y) { return x | y; });
+    m.n_valid = wave_sum_i(nv);
+    const double R = (double)Rf;
+    for (int q = lane; q < nsplit; q += WAVE) {
+      const RowPartial pq = ld_dev(rp + q);
+      if (pq.Z > 0.0 && pq.ref > -INFINITY) {
+        const double da = pq.a - R, dl = pq.ref - R;
+        const double sc = da == 0.0 ? 1.0 : exp(da);
+        Z += pq.Z * sc; S += (pq.S + dl * pq.Z) * sc;
+      }
+    }
+  }
+  m.R = (double)Rf; m.flags = fl; m.Z = wave_sum(Z); m.S = wave_sum(S);
+  return m;
+}
+__device__ __forceinline__ void stage_lists(const ScoreParams& sp, int64_t row_launched, const SelectLds& sel) {
+  const int nsplit = sp.nsplit, K = sp.K, per_row = nsplit * K, nt = blockDim.x;
+  const RowPartial* rp = sp.part + row_launched * nsplit;
+  const float* tv = sp.part_topv + row_launched * per_row;
+  const int32_t* ti = sp.part_topi + row_launched * per_row;
+  for (int ent = threadIdx.x; ent < per_row; ent += nt) {
+    const int n_top = ld_dev(&rp[ent / K].n_top);
+    const float v = ld_dev(tv + ent); const int32_t id = ld_dev(ti + ent);
+    const bool ok = ent % K < n_top;
+    sel.values()[ent] = ok ? v : -INFINITY;
+    sel.ids()[ent] = ok ? id : NO_ID;
+  }
+}
+// Lists that exceed the element list (very many splits): ranked from global memory, the best K to rr.topv, rr.topi.
+__device__ __forceinline__ void rank_lists_from_memory(const ScoreParams& sp, int64_t row_launched, RowResult& rr) {
+  const int nsplit = sp.nsplit, K = sp.K, per_row = nsplit * K, nt = blockDim.x;
+  const RowPartial* rp = sp.part + row_launched * nsplit;
+  const float* tv = sp.part_topv + row_launched * per_row;
+  const int32_t* ti = sp.part_topi + row_launched * per_row;
+  for (int ent = threadIdx.x; ent < per_row; ent += nt) {
+    const int q = ent / K, e = ent % K;
+    if (e >= ld_dev(&rp[q].n_top)) continue;
+    const float v = ld_dev(tv + ent); const int vi = ld_dev(ti + ent);
+    int ahead = 0;
+    for (int q2 = 0; q2 < nsplit; ++q2) {
+      const int n2 = ld_dev(&rp[q2].n_top);
+      for (int e2 = 0; e2 < n2; ++e2) {
+        const float v2 = ld_dev(tv + q2 * K + e2);
+        ahead += (v2 > v) || (v2 == v && ld_dev(ti + q2 * K + e2) < vi);
+      }
+    }
+    if (ahead < K) { rr.topv[ahead] = v; rr.topi[ahead] = vi; }
   }
 }
 
 // ---- sequence level: both prunings of Sec. 4.2 with the node budget, tree append, next frontier.
 // Run by one whole workgroup once every row of the sequence has been scored.
 //
-// Survivors of the first pruning are compacted into LDS lists (a 64-bit key of z and token, and the
-// candidate index).  Only the n_keep best of them matter: when the list is long, a 4096-bin histogram
-// over the top 12 bits of the order-preserving key of z finds the bin that holds the n_keep-th largest z,
-// and the list is cut down to the survivors from that bin upwards before the exact ranking.  The ranking
-// gives each survivor to T = 2^tshift lanes, which split the list between them, two keys per LDS read.
-#ifndef C2T_PRUNE_PRESELECT_MIN
-#define C2T_PRUNE_PRESELECT_MIN 64
+// What bounds it: latency; a handful of dependent steps on at most 2048 candidates.  Everything the step reads is requested
+// at once.  Only the n_keep best survivors of the first pruning matter: of 64 (or 128) groups of candidates, one
+// per lane, the n_keep-th largest group maximum is a lower bound of the n_keep-th largest z, found by a wavefront from
+// ballots; what reaches it (two dozen candidates where 16 are kept) is listed in LDS and ranked exactly.  The
+// ranking gives each listed candidate to T = 2^tshift lanes, which split the list between them, two keys per LDS read.
+// Lists that stay long, layers of equal z above all, are first cut by a radix select on the whole keys.
+#ifndef C2T_PRUNE_RANK_MAX
+#define C2T_PRUNE_RANK_MAX 128
 #endif
 #ifndef C2T_PRUNE_UNDECIDED_MAX
 #define C2T_PRUNE_UNDECIDED_MAX 64
 #endif
 constexpr int PRUNE_HIST_WORDS = 2048;        // 4096 bins, two 16-bit counters per word
-constexpr int PRUNE_PRESELECT_MIN = C2T_PRUNE_PRESELECT_MIN;   // shorter lists are ranked directly
+constexpr int PRUNE_RANK_MAX = C2T_PRUNE_RANK_MAX;             // longer lists are cut before the ranking
 constexpr int PRUNE_UNDECIDED_MAX = C2T_PRUNE_UNDECIDED_MAX; // the select stops once at most so many survivors share the selected digits
 
 __host__ __device__ inline size_t score_lds_bytes(int h, int FK) {
@@ -308,8 +413,36 @@ __host__ __device__ inline size_t score_lds_bytes(int h, int FK) {
   return ((size_t)3 * ((FK + 31) & ~31) + PRUNE_HIST_WORDS) * 4;
 }
 
+// A threshold that at least n of the NV * 64 maxima reach (0 if fewer than n are not 0), as high as it takes for at most
+// `enough` of them to reach it, or their n-th largest.  Two bits a step from the top, ballots, uniform result.
+template <int NV>
+__device__ __forceinline__ uint32_t bound_from_maxima(const uint32_t (&m)[NV], int n, int enough) {
+  uint32_t prefix = 0;
+  for (int shift = 30; shift >= 0; shift -= 2) {
+    int cnt[3] = {0, 0, 0};                                  // how many reach prefix + 1, 2, 3 steps
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) cnt[q] += __popcll(__ballot(m[v] >= (prefix | ((uint32_t)(q + 1) << shift))));
+    const int q = (cnt[0] >= n) + (cnt[1] >= n) + (cnt[2] >= n);
+    prefix |= (uint32_t)q << shift;
+    if (q && (q == 3 ? cnt[2] : q == 2 ? cnt[1] : cnt[0]) <= enough) break;
+  }
+  return prefix;
+}
+
 template <int NT>
-__device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds) {
+struct PruneShared {
+  int32_t n_list, n_red, flags_or, sel_bin, sel_above, sel_count;
+  int32_t scan_w[NT / WAVE], surv_w[NT / WAVE];
+  float list_P[PRUNE_RANK_MAX], list_H[PRUNE_RANK_MAX];     // of the first entries, as listed
+  int32_t old_node[SP_MAX_F];
+  float old_s[SP_MAX_F];
+};
+
+// PER: candidates per thread; F * K <= PER * NT.
+template <int NT, int PER>
+__device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps) {
   constexpr int NW = NT / WAVE;
   const int F = sp.F, K = sp.K, N = sp.N, layer = sp.layer;
   const float z_beta = sp.z_beta;
@@ -321,65 +454,102 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   uint64_t* skey = (uint64_t*)lds;
   int32_t* sidx = (int32_t*)(skey + FKp);
   uint32_t* hist = (uint32_t*)(sidx + FKp);
-  __shared__ int32_t n_surv, n_red, flags_or, sel_bin, sel_above, sel_count;
-  __shared__ int32_t scan_w[NW];
-  __shared__ int32_t new_tok[SP_MAX_F], new_pslot[SP_MAX_F], new_node[SP_MAX_F];
-  __shared__ float new_P[SP_MAX_F], new_s[SP_MAX_F];
-  __shared__ int32_t new_hidx[SP_MAX_F];
+  uint32_t* lane_max = hist;                                 // [NW][WAVE]; the histogram comes later, if at all
+  static_assert(NW * WAVE <= PRUNE_HIST_WORDS, "the lanes' maxima fit there");
 
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
-  // the candidates' z and tokens are requested up front for all F*K slots: one memory round trip
-  constexpr int PER = C2T_MAX_CANDIDATES_DEV / NT;           // candidates per thread
-  const int per = (FK + NT - 1) / NT;
-  float my_z[PER]; int32_t my_tok[PER];
+  const int64_t cb = (int64_t)b * FK, fb = (int64_t)b * F;   // uniform bases: the lanes' offsets stay 32 bits wide
+  // the candidates of all F*K slots are requested up front: one memory round trip
+  float my_z[PER], my_P[PER], my_H[PER]; int32_t my_tok[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = tid + k * NT;
-    if (k < per && i < FK) {
-      const int64_t o = (int64_t)b * FK + i;
-      my_z[k] = ld_dev(s.c_z + o); my_tok[k] = ld_dev(s.c_tok + o);
+    my_z[k] = my_P[k] = my_H[k] = 0.f; my_tok[k] = -1;
+    if (i < FK) {
+      my_z[k] = ld_dev(s.c_z + cb + i); my_tok[k] = ld_dev(s.c_tok + cb + i);
+      my_P[k] = ld_dev(s.c_P + cb + i); my_H[k] = ld_dev(s.c_H + cb + i);
     }
   }
-  const uint32_t info = tid < F ? ld_dev(s.row_info + (int64_t)b * F + tid) : 0u;
+  const uint32_t info = tid < F ? ld_dev(s.row_info + fb + tid) : 0u;
   const int nn = s.n_nodes[b];
+  if (tid < nf) {                                            // the old frontier is read here, for good: the new one is stored over it below
+    ps.old_node[tid] = s.fr_node[fb + tid];
+    ps.old_s[tid] = s.h_tok ? s.fr_s[fb + tid] : INFINITY;
+  }
   // the kept flags start at zero (all F*K slots: slots of unused rows are unspecified anyway); stored
   // now, so that they are long complete when the ranking stores the ones
-  for (int i = tid; i < FK; i += NT) s.c_kept[(int64_t)b * FK + i] = 0;
-  if (tid == 0) { n_surv = 0; n_red = 0; flags_or = 0; sel_bin = 0; }
-  for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u;
-  __syncthreads();
-  if (tid < nf && info) atomicOr(&flags_or, (int)info);
-  C2T_PT(PT_PRUNE_LOADED);                                   // (thread 0's own loads have arrived: info is used above)
+#pragma unroll
+  for (int k = 0; k < PER; ++k) if (tid + k * NT < FK) s.c_kept[cb + tid + k * NT] = 0;
+  if (tid == 0) { ps.n_list = 0; ps.n_red = 0; ps.flags_or = 0; ps.sel_bin = 0; }
 
   // ---- first pruning: z > logit(beta) ----
   const int ncand = nf * K;
+  uint32_t zk[PER], mx = 0u; int cnt = 0;                    // key of z, 0: not a survivor
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = tid + k * NT;
-    if (k < per && i < ncand) {
-      if (my_tok[k] >= 0 && my_z[k] > z_beta) {
-        const int u = atomicAdd(&n_surv, 1);
-        const uint32_t zk = sortable_key(my_z[k]);
-        skey[u] = ((uint64_t)zk << 32) | (uint32_t)~my_tok[k]; sidx[u] = i;
-        const uint32_t bin = zk >> 20;
-        atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u);
+    zk[k] = (i < ncand && my_tok[k] >= 0 && my_z[k] > z_beta) ? sortable_key(my_z[k]) : 0u;
+    mx = max(mx, zk[k]);
+    cnt += __popcll(__ballot(zk[k] != 0u));
+  }
+  C2T_PT(PT_PRUNE_LOADED);
+  lane_max[tid] = mx;
+  if (lane == 0) ps.surv_w[wid] = cnt;
+  __syncthreads();
+  if (tid < nf && info) atomicOr(&ps.flags_or, (int)info);
+  C2T_PT(PT_PRUNE_FIRST);
+
+  // ---- second pruning + budget: rank survivors by (z desc, token asc, slot asc) ----
+  int n_surv = 0;
+#pragma unroll
+  for (int v = 0; v < NW; ++v) n_surv += ps.surv_w[v];
+  const int n_keep = max(0, min(min(F, N - nn), n_surv));
+  uint32_t bound = 1u;                                       // every survivor
+  if (n_keep > 0 && n_surv > PRUNE_RANK_MAX) {
+    uint32_t m[2] = {0u, 0u};
+#pragma unroll
+    for (int v = 0; v < NW; ++v) m[v & 1] = max(m[v & 1], lane_max[v * WAVE + lane]);
+    if (n_keep <= 32) { const uint32_t m1[1] = {max(m[0], m[1])}; bound = bound_from_maxima<1>(m1, n_keep, n_keep + 24); }
+    else bound = bound_from_maxima<2>(m, n_keep, n_keep + 24);
+    bound = max(bound, 1u);
+  }
+  if (n_keep > 0) {
+    uint64_t hit[PER]; int tot = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) { hit[k] = __ballot(zk[k] >= bound); tot += __popcll(hit[k]); }
+    if (tot) {                                               // (uniform over the wave) one addition a wave gives the places
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&ps.n_list, tot);
+      at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        if (zk[k] >= bound) {
+          const int u = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hit[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit[k], 0u));
+          skey[u] = ((uint64_t)zk[k] << 32) | (uint32_t)~my_tok[k]; sidx[u] = tid + k * NT;
+          if (u < PRUNE_RANK_MAX) { ps.list_P[u] = my_P[k]; ps.list_H[u] = my_H[k]; }
+        }
+        at += __popcll(hit[k]);
       }
     }
   }
   wait_vector_memory();                                      // the zeros are written before any thread stores a one
   __syncthreads();
-  C2T_PT(PT_PRUNE_FIRST);
-
-  // ---- second pruning + budget: rank survivors by (z desc, token asc, slot asc) ----
-  int ns = n_surv;
-  const int n_keep = max(0, min(min(F, N - nn), ns));
-  if (n_keep > 0 && ns > PRUNE_PRESELECT_MIN) {
+  int ns = ps.n_list;
+  const bool listed_order = ns <= PRUNE_RANK_MAX;            // ps.list_P, ps.list_H hold the entries' P and H
+  if (n_keep > 0 && !listed_order) {
     // Radix select on the 64-bit keys, twelve bits a level, from the top: the histogram of the level's digit over
     // the survivors that are still undecided (those whose higher digits equal the digits selected so far; at the
-    // first level all of them, counted during the first pruning) gives the digit at which the running count from
-    // the top reaches what is still needed; survivors below it are dropped.  Typical layers are done after one
-    // level (a dozen survivors left); layers of equal z go on into the token bits instead of ranking hundreds of
-    // tied survivors against each other.
+    // first level all of them) gives the digit at which the running count from
+    // the top reaches what is still needed; survivors below it are dropped.  Layers of equal z go on into the
+    // token bits instead of ranking hundreds of tied survivors against each other.
+    for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int u = tid + k * NT;
+      if (u < ns) { const uint32_t bin = (uint32_t)(skey[u] >> 52); atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u); }
+    }
+    __syncthreads();
     int need = n_keep, shift = 52;                           // (uniform) still to be taken from the undecided; the level's digit is key >> shift
     uint64_t prefix = 0ull;                                  // the digits selected so far: the undecided have key >> (shift + 12) == prefix
     for (;;) {
@@ -389,29 +559,29 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
 #pragma unroll
       for (int j = 0; j < WPT; ++j) { w[j] = hist[PRUNE_HIST_WORDS - 1 - (tid * WPT + j)]; c += (int)(w[j] & 0xffffu) + (int)(w[j] >> 16); }
       const int incl = wave_scan_incl(c);
-      if (lane == WAVE - 1) scan_w[wid] = incl;
+      if (lane == WAVE - 1) ps.scan_w[wid] = incl;
       __syncthreads();
       int above = incl - c;
 #pragma unroll
-      for (int v = 0; v < NW; ++v) if (v < wid) above += scan_w[v];
+      for (int v = 0; v < NW; ++v) if (v < wid) above += ps.scan_w[v];
       if (above < need && above + c >= need) {               // exactly one thread
         int run = above;
 #pragma unroll
         for (int j = 0; j < WPT; ++j) {
           const int word = PRUNE_HIST_WORDS - 1 - (tid * WPT + j);
           const int hi = (int)(w[j] >> 16), lo = (int)(w[j] & 0xffffu);
-          if (run < need && run + hi >= need) { sel_bin = 2 * word + 1; sel_above = run; sel_count = hi; }
+          if (run < need && run + hi >= need) { ps.sel_bin = 2 * word + 1; ps.sel_above = run; ps.sel_count = hi; }
           run += hi;
-          if (run < need && run + lo >= need) { sel_bin = 2 * word; sel_above = run; sel_count = lo; }
+          if (run < need && run + lo >= need) { ps.sel_bin = 2 * word; ps.sel_above = run; ps.sel_count = lo; }
           run += lo;
         }
       }
-      if (tid == 0) n_red = 0;
+      if (tid == 0) ps.n_red = 0;
       __syncthreads();
       // cut the list down, in place: read, barrier, write
-      const uint64_t cut = (prefix << 12) | (uint64_t)(uint32_t)sel_bin;
-      const int undecided = sel_count;
-      need -= sel_above;
+      const uint64_t cut = (prefix << 12) | (uint64_t)(uint32_t)ps.sel_bin;
+      const int undecided = ps.sel_count;
+      need -= ps.sel_above;
       uint64_t rk[PER]; int32_t ri[PER];
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
@@ -423,13 +593,13 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         if (ri[k] >= 0 && (rk[k] >> shift) >= cut) {
-          const int u = atomicAdd(&n_red, 1);
+          const int u = atomicAdd(&ps.n_red, 1);
           skey[u] = rk[k]; sidx[u] = ri[k];
         }
       }
       for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u;   // for the next level, if there is one
       __syncthreads();
-      ns = n_red;
+      ns = ps.n_red;
       if (undecided <= PRUNE_UNDECIDED_MAX || shift < 12) break;      // (uniform) few enough to rank; or the last whole digit done
       prefix = cut; shift -= 12;
 #pragma unroll
@@ -459,12 +629,10 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
       const int i = mine ? sidx[u] : 0;
       const float z = key_to_float((uint32_t)(key >> 32));
       const int tok = (int)~(uint32_t)key;
-      // what an appended node needs, requested before the ranking so that the latency overlaps it
-      float P = 0.f, H = 0.f, par_s = INFINITY; int par = -1;
+      float P = 0.f, H = 0.f;
       if (mine && sub == 0) {
-        const int64_t o = (int64_t)b * FK + i;
-        P = ld_dev(s.c_P + o); H = ld_dev(s.c_H + o); par = s.fr_node[(int64_t)b * F + i / K];
-        if (s.h_tok) par_s = s.fr_s[(int64_t)b * F + i / K];
+        if (listed_order) { P = ps.list_P[u]; H = ps.list_H[u]; }
+        else { P = ld_dev(s.c_P + cb + i); H = ld_dev(s.c_H + cb + i); }
       }
       // rank = survivors with a greater key, and those with the same key (the same token under two parents, with
       // the same z) and a lower candidate index; the survivor's T lanes take two keys a step each
@@ -484,30 +652,23 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
       if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
       if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
       if (mine && sub == 0 && rank < n_keep) {
-        const int node = nn + rank, f = i / K;
-        const int64_t o = (int64_t)b * FK + i, t = (int64_t)b * N + node;
-        s.c_kept[o] = 1;
-        s.t_tok[t] = tok; s.t_parent[t] = par; s.t_depth[t] = layer;
-        s.t_P[t] = P; s.t_H[t] = H; s.t_z[t] = z;
-        new_tok[rank] = tok; new_pslot[rank] = f; new_node[rank] = node; new_P[rank] = P;
-        new_hidx[rank] = layer * FK + i; new_s[rank] = fminf(par_s, z);
+        const int f = (int)(((uint32_t)i * sp.k_inverse) >> 20);         // i / K
+        const int64_t tb = (int64_t)b * N + nn;
+        s.c_kept[cb + i] = 1;
+        s.t_tok[tb + rank] = tok; s.t_parent[tb + rank] = ps.old_node[f]; s.t_depth[tb + rank] = layer;
+        s.t_P[tb + rank] = P; s.t_H[tb + rank] = H; s.t_z[tb + rank] = z;
+        s.fr_tok[fb + rank] = tok; s.fr_pslot[fb + rank] = f; s.fr_node[fb + rank] = nn + rank; s.fr_P[fb + rank] = P;
+        if (s.h_tok) { s.fr_hidx[fb + rank] = layer * FK + i; s.fr_s[fb + rank] = fminf(ps.old_s[f], z); }
       }
     }
   }
-  __syncthreads();
   C2T_PT(PT_PRUNE_RANKED);
-  if (tid < n_keep) {
-    const int64_t o = (int64_t)b * F + tid;
-    s.fr_tok[o] = new_tok[tid]; s.fr_pslot[o] = new_pslot[tid];
-    s.fr_node[o] = new_node[tid]; s.fr_P[o] = new_P[tid];
-    if (s.h_tok) { s.fr_hidx[o] = new_hidx[tid]; s.fr_s[o] = new_s[tid]; }
-  }
   if (tid == 0) {
     if (s.h_tok) s.h_ncand[(int64_t)b * sp.D + layer] = ncand;
     s.n_nodes[b] = nn + n_keep;
     s.nf[(layer + 1) & 1][b] = n_keep;
     s.n_cand[b] = ncand;
-    if (flags_or) s.status[b] |= (uint32_t)flags_or;
+    if (ps.flags_or) s.status[b] |= (uint32_t)ps.flags_or;
     if (n_keep) atomicAdd(&s.layer_rows[layer + 1], n_keep);
   }
 }
@@ -532,33 +693,73 @@ __device__ __forceinline__ bool last_arrival(int32_t* ticket, int expected) {
   return sh_last != 0;
 }
 
-// Tail of the logits pass for the workgroup that owned (sequence b, frontier slot f, split): `rr`
-// holds its segment's result.  The workgroup that completes a row scores the row's candidates; the
-// workgroup that completes a sequence's last row prunes and appends.  Both overlap with the other
-// workgroups' streaming, so the whole layer is one launch.
+// How a workgroup leaves its segment's largest logits: n_el elements in the element list, not ranked yet, or (n_el < 0)
+// ranked in rr.topv, rr.topi with rr.part.n_top of them.  entropy: row_entropy has been run on an unsplit row.
+struct SegmentTop { int n_el; bool entropy; };
+
+// Tail of the logits pass for the workgroup that owned (sequence b, frontier slot f, split).  The workgroup
+// that completes a row scores the row's candidates; the workgroup that completes a sequence's last row prunes
+// and appends.  Both overlap with the other workgroups' streaming, so the whole layer is one launch.
+// On entry a barrier lies behind the last write to the list and to rr, except that `record()`, called by the last
+// wavefront while the others rank the list, completes rr.part (sums, flags; its lane 0 writes).
 // after_merge(rr): called by the whole workgroup that has merged a split row, before the row is scored
 // (the entropy over the M largest logits of a split row is computed there, over the whole row).
-template <int NT, typename AfterMerge>
+template <int NT, typename Record, typename AfterMerge>
 __device__ __forceinline__ void finish_layer(const TreeState& s, const ScoreParams& sp, int b, int f, int nf, int split,
-                                             int64_t row_launched, RowResult& rr, unsigned char* lds,
-                                             const float* __restrict__ cls, const float* cls_lds, AfterMerge after_merge) {
+                                             int64_t row_launched, RowResult& rr, SegmentTop top, const SelectLds& sel, unsigned char* lds,
+                                             const float* __restrict__ cls, const float* cls_lds, Record record, AfterMerge after_merge) {
+  constexpr int NW = NT / WAVE;
   const int tid = threadIdx.x, K = sp.K;
+  const bool last_wave = (tid >> 6) == NW - 1;
+  const int64_t slot = (int64_t)b * sp.F + f;
+  if (last_wave) {
+    record();
+    if (sp.nsplit == 1 && !top.entropy) row_entropy(s, sp, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
+  }
+  if (top.n_el >= 0) rank_list<NT>(K, sel, top.n_el, rr.topv, rr.topi);
   __syncthreads();                                           // rr is complete
+  int n = top.n_el >= 0 ? min(top.n_el, K) : rr.part.n_top;
+  C2T_PT(PT_RANKED);
   if (sp.nsplit > 1) {
-    const int64_t po = row_launched * sp.nsplit + split;
-    if (tid < rr.part.n_top) { st_dev(sp.part_topv + po * K + tid, rr.topv[tid]); st_dev(sp.part_topi + po * K + tid, rr.topi[tid]); }
-    if (tid == 0) st_dev(sp.part + po, rr.part);
-    if (!last_arrival(s.row_tickets + (int64_t)b * sp.F + f, sp.nsplit)) return;
-    merge_row(sp, row_launched, rr, lds, (size_t)sp.lds_bytes);
-    after_merge(rr);
+    const int nsplit = sp.nsplit, per_row = nsplit * K;
+    const int64_t po = row_launched * nsplit + split;
+    if (rr.part.flags & 1u) n = 0;
+    if (tid < n) { st_dev(sp.part_topv + po * K + tid, rr.topv[tid]); st_dev(sp.part_topi + po * K + tid, rr.topi[tid]); }
+    if (tid == 0) { RowPartial r = rr.part; r.n_top = n; st_dev(sp.part + po, r); }
+    if (!last_arrival(s.row_tickets + slot, nsplit)) { C2T_PT_FLUSH(); return; }
+    const bool staged = per_row <= sel.list_cap;             // the lists fit the element list
+    const RowPartial* rp = sp.part + row_launched * nsplit;
+    RowSums m;
+    if (last_wave) m = merge_records(rp, nsplit);
+    if (staged) stage_lists(sp, row_launched, sel); else rank_lists_from_memory(sp, row_launched, rr);
+    __syncthreads();
+    if (last_wave) {
+      if (lane_id() == 0) {
+        RowPartial r; r.ref = m.R; r.a = m.R; r.Z = m.Z; r.S = m.S; r.flags = m.flags; r.n_top = min(m.n_valid, K);
+        rr.part = r;
+      }
+      if (sp.M <= 0) row_entropy(s, sp, slot, m.R, m.R, m.Z, m.S, m.flags, rr);
+    }
+    if (staged) rank_list<NT>(K, sel, per_row, rr.topv, rr.topi);
+    __syncthreads();
+    if (sp.M > 0) {
+      after_merge(rr);
+      if (last_wave) row_entropy(s, sp, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
+      __syncthreads();
+    }
+    n = rr.part.n_top;
     C2T_PT(PT_MERGED);
   }
-  score_row(s, sp, b, f, rr, cls, cls_lds);
+  score_row<NT>(s, sp, b, f, rr, n, cls, cls_lds, lds);
   C2T_PT(PT_PUBLISHED);
-  if (!last_arrival(s.tickets + b, nf)) return;              // nf: the sequence's frontier size, known since the workgroup started
+  if (!last_arrival(s.tickets + b, nf)) { C2T_PT_FLUSH(); return; }   // nf: the sequence's frontier size, known since the workgroup started
   C2T_PT(PT_TICKET);
-  prune_sequence<NT>(s, sp, b, nf, lds);
+  // one candidate a thread wherever that is enough: an eighth of the instructions of the general form
+  __shared__ PruneShared<NT> ps;
+  if (sp.F * K <= NT) prune_sequence<NT, 1>(s, sp, b, nf, lds, ps);
+  else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(s, sp, b, nf, lds, ps);
   C2T_PT(PT_PRUNED);
+  C2T_PT_FLUSH();
 }
 
 struct TreeOut {
@@ -566,41 +767,60 @@ struct TreeOut {
   int32_t* n_nodes; uint8_t* mask; uint32_t* status;
 };
 
-// One workgroup per sequence: copy the node arrays, confidence = sigmoid(z), ancestor mask.
-__global__ __launch_bounds__(256) void k_finalize(TreeState s, TreeOut o, int N) {
-  const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
-  const int n = s.n_nodes[b];
-  uint8_t* mk = o.mask + (int64_t)b * N * N;
-  // N*N bytes zeroed with 4-byte stores where alignment allows
-  const int64_t nb = (int64_t)N * N;
-  if ((((uintptr_t)mk) & 3) == 0) {
-    uint32_t* m4 = (uint32_t*)mk;
-    for (int64_t i = tid; i < nb / 4; i += nt) m4[i] = 0;
-    for (int64_t i = (nb / 4) * 4 + tid; i < nb; i += nt) mk[i] = 0;
-  } else {
-    for (int64_t i = tid; i < nb; i += nt) mk[i] = 0;
-  }
-  for (int i = tid; i < N; i += nt) {
-    const int64_t t = (int64_t)b * N + i;
-    if (i < n) {
-      const float z = s.t_z[t];
-      o.tokens[t] = s.t_tok[t]; o.parent[t] = s.t_parent[t]; o.position[t] = s.t_depth[t] + 1;
-      o.conf[t] = 1.0f / (1.0f + expf(-z));
-      o.joint_prob[t] = s.t_P[t]; o.entropy[t] = s.t_H[t];
-    } else {
-      o.tokens[t] = -1; o.parent[t] = -1; o.position[t] = 0;
-      o.conf[t] = 0.f; o.joint_prob[t] = 0.f; o.entropy[t] = 0.f;
-    }
-  }
-  if (tid == 0) { o.n_nodes[b] = n; o.status[b] = s.status[b]; }
+// ---- emission: rows [r0, r1) of a sequence's N x N ancestor mask (byte j of row i: j is i or an ancestor of i), by a
+// workgroup of NT threads.  What bounds it: the walks (a few dependent steps a node) and N*N bytes written; so the
+// parents are read once into LDS, a thread walks one row there and sets its bits in an LDS bit array laid out like the
+// bytes, and the bytes are written once, sixteen a store, from the bits (before: the mask was cleared first, every
+// step of a walk was a load from memory, and one workgroup did a whole sequence: 34 us for 1024 nodes, 3 us now).
+constexpr int MASK_SLICE = 16384;              // bytes of the mask a workgroup writes at most (one row at least)
+constexpr int MASK_BIT_WORDS = MASK_SLICE / 32 + 1;
+__host__ __device__ inline int mask_rows_per_slice(int N) { return N >= MASK_SLICE ? 1 : MASK_SLICE / N; }
+__device__ __forceinline__ uint32_t spread_bits(uint32_t b) { return (b * 0x00204081u) & 0x01010101u; }    // bit t of b (0..3) to byte t
+// parent: LDS, [N]; bits: LDS, MASK_BIT_WORDS; n: nodes of the tree.  A barrier lies behind the writes to parent.
+template <int NT>
+__device__ __forceinline__ void write_mask_rows(uint8_t* __restrict__ mask, int N, int n, int r0, int r1, const int32_t* parent, uint32_t* bits) {
+  const int tid = threadIdx.x, total = (r1 - r0) * N;        // <= MASK_SLICE
+  for (int i = tid; i < (total >> 5) + 1; i += NT) bits[i] = 0u;
   __syncthreads();
-  for (int i = tid; i < n; i += nt) {
-    int j = i, guard = 0;
-    while (j >= 0 && guard++ <= N) {       // parents have smaller indices: the walk ends at -1
-      mk[(int64_t)i * N + j] = 1;
-      j = s.t_parent[(int64_t)b * N + j];
-    }
+  for (int i = r0 + tid; i < min(r1, n); i += NT) {
+    const int base = (i - r0) * N;
+    for (int j = i; j >= 0; j = parent[j]) atomicOr(&bits[(base + j) >> 5], 1u << ((base + j) & 31));     // parents have smaller indices: the walk ends at -1
   }
+  __syncthreads();
+  uint8_t* out = mask + (int64_t)r0 * N;
+  const int head = min(total, (int)((0u - (uint32_t)(uintptr_t)out) & 15u)), chunks = (total - head) >> 4, tail = head + chunks * 16;
+  auto bit = [&](int e) { return (uint8_t)((bits[e >> 5] >> (e & 31)) & 1u); };
+  if (tid < head) out[tid] = bit(tid);
+  for (int c = tid; c < chunks; c += NT) {
+    const int e = head + c * 16, sh = e & 31;
+    uint32_t w = bits[e >> 5] >> sh;
+    if (sh > 16) w |= bits[(e >> 5) + 1] << (32 - sh);
+    *(uint4*)(out + e) = make_uint4(spread_bits(w & 15u), spread_bits((w >> 4) & 15u), spread_bits((w >> 8) & 15u), spread_bits((w >> 12) & 15u));
+  }
+  if (tail + tid < total) out[tail + tid] = bit(tail + tid);   // fewer than sixteen
+}
+
+// Copy the node arrays, confidence = sigmoid(z), ancestor mask.  grid: (sequences, slices of the mask's rows).
+constexpr int FIN_NT = 256;
+__global__ __launch_bounds__(FIN_NT) void k_finalize(TreeState s, TreeOut o, int N) {
+  __shared__ int32_t parent[C2T_MAX_BUDGET_DEV];
+  __shared__ uint32_t bits[MASK_BIT_WORDS];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const int per_slice = mask_rows_per_slice(N), r0 = blockIdx.y * per_slice, r1 = min(r0 + per_slice, N);
+  const int64_t tb = (int64_t)b * N;
+  const int n = s.n_nodes[b];
+  for (int i = tid; i < r1; i += FIN_NT) parent[i] = s.t_parent[tb + i];      // (of nodes past the n-th: not used)
+  for (int i = r0 + tid; i < r1; i += FIN_NT) {
+    const bool node = i < n;
+    const float z = s.t_z[tb + i], P = s.t_P[tb + i], H = s.t_H[tb + i];
+    const int tok = s.t_tok[tb + i], par = s.t_parent[tb + i], depth = s.t_depth[tb + i];
+    o.tokens[tb + i] = node ? tok : -1; o.parent[tb + i] = node ? par : -1; o.position[tb + i] = node ? depth + 1 : 0;
+    o.conf[tb + i] = node ? 1.0f / (1.0f + expf(-z)) : 0.f;
+    o.joint_prob[tb + i] = node ? P : 0.f; o.entropy[tb + i] = node ? H : 0.f;
+  }
+  if (blockIdx.y == 0 && tid == 0) { o.n_nodes[b] = n; o.status[b] = s.status[b]; }
+  __syncthreads();
+  write_mask_rows<FIN_NT>(o.mask + tb * N, N, n, r0, r1, parent, bits);
 }
 
 
