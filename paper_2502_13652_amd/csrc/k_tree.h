@@ -269,6 +269,8 @@ __device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParam
   }
 }
 
+struct Candidate { float z, P, H; int32_t tok; uint32_t info; };   // as lane t of the first wavefront scored it; info: the row's flags
+
 // ---- row level: generation and joint probability (Eq. 1) and classifier logit (Eq. 3) of the row's n candidates, from
 // the complete row result in `rr`; one lane of the first wavefront per candidate (a wavefront issues the classifier's
 // chain once for all of them).
@@ -279,7 +281,7 @@ __device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParam
 #endif
 constexpr int MLP_SPREAD_MIN = C2T_MLP_SPREAD_MIN;   // hidden units from which on the whole workgroup evaluates the classifier
 template <int NT>
-__device__ __forceinline__ void score_row(const TreeState& s, const ScoreParams& sp, int b, int f, RowResult& rr, int n,
+__device__ __forceinline__ Candidate score_row(const TreeState& s, const ScoreParams& sp, int b, int f, RowResult& rr, int n,
                                           const float* __restrict__ w, const float* w_lds, unsigned char* lds) {
   const int tid = threadIdx.x, K = sp.K, FK = sp.F * K;
   const float H = rr.H;
@@ -297,20 +299,22 @@ __device__ __forceinline__ void score_row(const TreeState& s, const ScoreParams&
     z = mlp_logit_spread<NT>((LdsFloats)w_lds, sp.h, rr.topv, H, (float)sp.layer, K, sp.k_inverse, (float*)lds, sp.lds_bytes);
     if (!mine) z = -INFINITY;
   }
-  if (tid >= K) return;
+  const uint32_t info = (rr.bad ? 1u : 0u) | (rr.part.flags & 2u);
+  if (tid >= K) return Candidate{-INFINITY, 0.f, 0.f, -1, 0u};
   if (mine && !spread) {
     z = w_lds ? mlp_logit_lds((LdsFloats)w_lds, sp.h, P32, H, (float)sp.layer) : mlp_logit(w, sp.h, P32, H, (float)sp.layer);
   }
   const int64_t row = (int64_t)b * FK + (int64_t)f * K;     // uniform; the lane's offset stays 32 bits wide
   st_dev(s.c_tok + row + tid, tok); st_dev(s.c_p + row + tid, p32); st_dev(s.c_P + row + tid, P32);
   st_dev(s.c_H + row + tid, H); st_dev(s.c_z + row + tid, z);
-  if (tid == 0) st_dev(s.row_info + (int64_t)b * sp.F + f, (uint32_t)(rr.bad ? 1u : 0u) | (rr.part.flags & 2u));
+  if (tid == 0) st_dev(s.row_info + (int64_t)b * sp.F + f, info);
   if (s.h_tok) {                                             // keep the candidate for the reranking
     const int64_t h = ((int64_t)b * sp.D + sp.layer) * FK + (int64_t)f * K;
     s.h_tok[h + tid] = tok; s.h_par[h + tid] = rr.parent_hidx;
     s.h_P[h + tid] = P32; s.h_H[h + tid] = H; s.h_z[h + tid] = z;
     s.h_s[h + tid] = fminf(rr.parent_s, z);
   }
+  return Candidate{z, P32, H, tok, info};
 }
 
 // ---- row level, splits > 1, by the workgroup that delivered the row's last split.
@@ -401,11 +405,15 @@ __device__ __forceinline__ void rank_lists_from_memory(const ScoreParams& sp, in
 #ifndef C2T_PRUNE_RANK_MAX
 #define C2T_PRUNE_RANK_MAX 128
 #endif
+#ifndef C2T_PRUNE_DIRECT_MAX
+#define C2T_PRUNE_DIRECT_MAX 64
+#endif
 #ifndef C2T_PRUNE_UNDECIDED_MAX
 #define C2T_PRUNE_UNDECIDED_MAX 64
 #endif
 constexpr int PRUNE_HIST_WORDS = 2048;        // 4096 bins, two 16-bit counters per word
-constexpr int PRUNE_RANK_MAX = C2T_PRUNE_RANK_MAX;             // longer lists are cut before the ranking
+constexpr int PRUNE_DIRECT_MAX = C2T_PRUNE_DIRECT_MAX;         // up to so many survivors are ranked without looking for a bound (100 of them: 1.6 us, with it 1.1)
+constexpr int PRUNE_RANK_MAX = C2T_PRUNE_RANK_MAX;             // lists that are longer with it are cut by the radix select
 constexpr int PRUNE_UNDECIDED_MAX = C2T_PRUNE_UNDECIDED_MAX; // the select stops once at most so many survivors share the selected digits
 
 __host__ __device__ inline size_t score_lds_bytes(int h, int FK) {
@@ -438,11 +446,15 @@ struct PruneShared {
   float list_P[PRUNE_RANK_MAX], list_H[PRUNE_RANK_MAX];     // of the first entries, as listed
   int32_t old_node[SP_MAX_F];
   float old_s[SP_MAX_F];
+  uint32_t kept[C2T_MAX_CANDIDATES_DEV / 32];              // bit i: candidate i is appended to the tree
 };
 
 // PER: candidates per thread; F * K <= PER * NT.
+// own: the sequence has one frontier node, whose candidates this workgroup has just scored: lane t of the first
+// wavefront holds candidate t, and nothing of them has to come back from memory.
 template <int NT, int PER>
-__device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps) {
+__device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps,
+                                               bool own, const Candidate& c) {
   constexpr int NW = NT / WAVE;
   const int F = sp.F, K = sp.K, N = sp.N, layer = sp.layer;
   const float z_beta = sp.z_beta;
@@ -465,21 +477,20 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   for (int k = 0; k < PER; ++k) {
     const int i = tid + k * NT;
     my_z[k] = my_P[k] = my_H[k] = 0.f; my_tok[k] = -1;
-    if (i < FK) {
+    if (own) { if (k == 0 && tid < K) { my_z[0] = c.z; my_tok[0] = c.tok; my_P[0] = c.P; my_H[0] = c.H; } }
+    else if (i < FK) {
       my_z[k] = ld_dev(s.c_z + cb + i); my_tok[k] = ld_dev(s.c_tok + cb + i);
       my_P[k] = ld_dev(s.c_P + cb + i); my_H[k] = ld_dev(s.c_H + cb + i);
     }
   }
-  const uint32_t info = tid < F ? ld_dev(s.row_info + fb + tid) : 0u;
+  uint32_t info = own && tid == 0 ? c.info : 0u;
+  if (!own && tid < F) info = ld_dev(s.row_info + fb + tid);
   const int nn = s.n_nodes[b];
   if (tid < nf) {                                            // the old frontier is read here, for good: the new one is stored over it below
     ps.old_node[tid] = s.fr_node[fb + tid];
     ps.old_s[tid] = s.h_tok ? s.fr_s[fb + tid] : INFINITY;
   }
-  // the kept flags start at zero (all F*K slots: slots of unused rows are unspecified anyway); stored
-  // now, so that they are long complete when the ranking stores the ones
-#pragma unroll
-  for (int k = 0; k < PER; ++k) if (tid + k * NT < FK) s.c_kept[cb + tid + k * NT] = 0;
+  if (tid < (FK + 31) / 32) ps.kept[tid] = 0u;
   if (tid == 0) { ps.n_list = 0; ps.n_red = 0; ps.flags_or = 0; ps.sel_bin = 0; }
 
   // ---- first pruning: z > logit(beta) ----
@@ -505,7 +516,7 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   for (int v = 0; v < NW; ++v) n_surv += ps.surv_w[v];
   const int n_keep = max(0, min(min(F, N - nn), n_surv));
   uint32_t bound = 1u;                                       // every survivor
-  if (n_keep > 0 && n_surv > PRUNE_RANK_MAX) {
+  if (n_keep > 0 && n_surv > PRUNE_DIRECT_MAX) {
     uint32_t m[2] = {0u, 0u};
 #pragma unroll
     for (int v = 0; v < NW; ++v) m[v & 1] = max(m[v & 1], lane_max[v * WAVE + lane]);
@@ -517,10 +528,16 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
     uint64_t hit[PER]; int tot = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) { hit[k] = __ballot(zk[k] >= bound); tot += __popcll(hit[k]); }
-    if (tot) {                                               // (uniform over the wave) one addition a wave gives the places
-      int at = 0;
+    int at = 0;
+    if (bound == 1u) {                                       // every survivor: the places follow from the wavefronts' counts
+#pragma unroll
+      for (int v = 0; v < NW; ++v) at += v < wid ? ps.surv_w[v] : 0;
+      if (tid == 0) ps.n_list = n_surv;
+    } else if (tot) {                                        // one addition a wave gives the places
       if (lane == 0) at = atomicAdd(&ps.n_list, tot);
       at = __builtin_amdgcn_readfirstlane(at);
+    }
+    if (tot) {
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         if (zk[k] >= bound) {
@@ -532,7 +549,6 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
       }
     }
   }
-  wait_vector_memory();                                      // the zeros are written before any thread stores a one
   __syncthreads();
   int ns = ps.n_list;
   const bool listed_order = ns <= PRUNE_RANK_MAX;            // ps.list_P, ps.list_H hold the entries' P and H
@@ -635,26 +651,28 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
         else { P = ld_dev(s.c_P + cb + i); H = ld_dev(s.c_H + cb + i); }
       }
       // rank = survivors with a greater key, and those with the same key (the same token under two parents, with
-      // the same z) and a lower candidate index; the survivor's T lanes take two keys a step each
-      int rank = 0;
+      // the same z: rare, looked for only where a count shows them) and a lower candidate index; the survivor's T
+      // lanes take two keys a step each
+      int rank = 0;                                          // lower half: greater keys, upper half: equal ones (itself among them)
       if (mine) {
+#pragma unroll 2
         for (int v = sub * 2; v < ns; v += T * 2) {
           const uint4 q = *(const uint4*)(skey + v);
-          const uint64_t k0 = ((uint64_t)q.y << 32) | q.x, k1 = ((uint64_t)q.w << 32) | q.z;
-          const bool in1 = v + 1 < ns;
-          rank += (int)(k0 > key) + (int)(in1 && k1 > key);
-          if (k0 == key && v != u) rank += (int)(sidx[v] < i);
-          if (in1 && k1 == key && v + 1 != u) rank += (int)(sidx[v + 1] < i);
+          const uint64_t k0 = ((uint64_t)q.y << 32) | q.x, k1 = v + 1 < ns ? ((uint64_t)q.w << 32) | q.z : 0ull;
+          rank += (k0 > key ? 1 : 0) + (k1 > key ? 1 : 0) + (k0 == key ? 0x10000 : 0) + (k1 == key ? 0x10000 : 0);
         }
       }
       if (tshift >= 1) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)rank);
       if (tshift >= 2) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)rank);
       if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
       if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
+      const bool tied = mine && (rank >> 16) > 1;
+      rank &= 0xffff;
+      if (tied && sub == 0) for (int v = 0; v < ns; ++v) rank += (int)(skey[v] == key && sidx[v] < i);
       if (mine && sub == 0 && rank < n_keep) {
         const int f = (int)(((uint32_t)i * sp.k_inverse) >> 20);         // i / K
         const int64_t tb = (int64_t)b * N + nn;
-        s.c_kept[cb + i] = 1;
+        atomicOr(&ps.kept[i >> 5], 1u << (i & 31));
         s.t_tok[tb + rank] = tok; s.t_parent[tb + rank] = ps.old_node[f]; s.t_depth[tb + rank] = layer;
         s.t_P[tb + rank] = P; s.t_H[tb + rank] = H; s.t_z[tb + rank] = z;
         s.fr_tok[fb + rank] = tok; s.fr_pslot[fb + rank] = f; s.fr_node[fb + rank] = nn + rank; s.fr_P[fb + rank] = P;
@@ -662,7 +680,13 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
       }
     }
   }
+  __syncthreads();                                           // ps.kept is complete
   C2T_PT(PT_PRUNE_RANKED);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {                            // (slots of unused rows are unspecified)
+    const int i = tid + k * NT;
+    if (i < FK) s.c_kept[cb + i] = (int32_t)((ps.kept[i >> 5] >> (i & 31)) & 1u);
+  }
   if (tid == 0) {
     if (s.h_tok) s.h_ncand[(int64_t)b * sp.D + layer] = ncand;
     s.n_nodes[b] = nn + n_keep;
@@ -679,14 +703,12 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
 // 0..63), whose own wait covers them; the other waves only meet at the barrier.
 __device__ __forceinline__ bool last_arrival(int32_t* ticket, int expected) {
   __shared__ int32_t sh_last;
+  if (expected == 1) { __syncthreads(); return true; }     // the only arrival (root layers, chains): nothing is handed over
   if (threadIdx.x < WAVE) {
     wait_vector_memory();
     if (threadIdx.x == 0) {
-      if (expected == 1) sh_last = 1;                      // the only arrival (root layers, chains): no round trip to the counter
-      else {
-        sh_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expected - 1;
-        if (sh_last) st_dev(ticket, 0);
-      }
+      sh_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expected - 1;
+      if (sh_last) st_dev(ticket, 0);
     }
   }
   __syncthreads();
@@ -750,14 +772,14 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
     n = rr.part.n_top;
     C2T_PT(PT_MERGED);
   }
-  score_row<NT>(s, sp, b, f, rr, n, cls, cls_lds, lds);
+  const Candidate c = score_row<NT>(s, sp, b, f, rr, n, cls, cls_lds, lds);
   C2T_PT(PT_PUBLISHED);
   if (!last_arrival(s.tickets + b, nf)) { C2T_PT_FLUSH(); return; }   // nf: the sequence's frontier size, known since the workgroup started
   C2T_PT(PT_TICKET);
   // one candidate a thread wherever that is enough: an eighth of the instructions of the general form
   __shared__ PruneShared<NT> ps;
-  if (sp.F * K <= NT) prune_sequence<NT, 1>(s, sp, b, nf, lds, ps);
-  else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(s, sp, b, nf, lds, ps);
+  if (sp.F * K <= NT) prune_sequence<NT, 1>(s, sp, b, nf, lds, ps, nf == 1, c);
+  else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(s, sp, b, nf, lds, ps, nf == 1, c);
   C2T_PT(PT_PRUNED);
   C2T_PT_FLUSH();
 }
