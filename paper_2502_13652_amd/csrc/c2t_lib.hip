@@ -294,6 +294,18 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   return hipGetLastError();
 }
 
+// st: the context's state, with the scratch of the reranking where the caller has it
+hipError_t launch_rerank(const c2t_ctx* x, const TreeState& st, const TreeOut& t, int n_out, hipStream_t s) {
+  const int FK = x->cfg.max_frontier * x->cfg.top_k;
+  const uint32_t fk_inverse = (uint32_t)(((1ull << 32) + FK - 1) / FK);     // __umulhi(i, fk_inverse) = i / FK for i < 2^15 and FK > 1
+  hipLaunchKernelGGL(k_finalize_rerank, dim3(x->cfg.batch), dim3(RR_NT), 0, s, st, t, n_out, x->cfg.max_depth, FK, fk_inverse);
+  if (n_out > RR_MASK_ROWS_MAX) {
+    const int per_slice = mask_rows_per_slice(n_out);
+    hipLaunchKernelGGL(k_mask_of_parents, dim3(x->cfg.batch, (n_out + per_slice - 1) / per_slice), dim3(FIN_NT), 0, s, t, n_out);
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 extern "C" {
@@ -464,9 +476,7 @@ int c2t_finalize_tree_reranked(c2t_ctx* x, const c2t_tree_out* o, int32_t n_out,
   if (n_out > C2T_MAX_BUDGET) return C2T_ERR_UNSUPPORTED;
   if (!x->cfg.rerank || x->layer < 0) return C2T_ERR_STATE;
   TreeOut t{o->tokens, o->parent, o->position, o->conf, o->joint_prob, o->entropy, o->n_nodes, o->mask, o->status};
-  hipLaunchKernelGGL(k_finalize_rerank, dim3(x->cfg.batch), dim3(RR_NT), 0, (hipStream_t)stream, x->st, t, n_out,
-                     x->cfg.max_depth, x->cfg.max_frontier * x->cfg.top_k);
-  if (hipGetLastError() != hipSuccess) return C2T_ERR_HIP;
+  if (launch_rerank(x, x->st, t, n_out, (hipStream_t)stream) != hipSuccess) return C2T_ERR_HIP;
   x->finalized = true;
   return C2T_OK;
 }
@@ -487,9 +497,7 @@ int c2t_finalize_tree_reranked_static(c2t_ctx* x, const c2t_tree_out* o, int32_t
   TreeState st = x->st;
   st.h_pos = pos;                                             // every entry the kernel reads it has written in the same launch: nothing to clear
   TreeOut t{o->tokens, o->parent, o->position, o->conf, o->joint_prob, o->entropy, o->n_nodes, o->mask, o->status};
-  hipLaunchKernelGGL(k_finalize_rerank, dim3(x->cfg.batch), dim3(RR_NT), 0, (hipStream_t)stream, st, t, n_out,
-                     x->cfg.max_depth, x->cfg.max_frontier * x->cfg.top_k);
-  if (hipGetLastError() != hipSuccess) return C2T_ERR_HIP;
+  if (launch_rerank(x, st, t, n_out, (hipStream_t)stream) != hipSuccess) return C2T_ERR_HIP;
   x->finalized = true;
   return C2T_OK;
 }

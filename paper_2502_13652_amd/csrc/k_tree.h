@@ -849,57 +849,99 @@ __global__ __launch_bounds__(FIN_NT) void k_finalize(TreeState s, TreeOut o, int
 // EAGLE-2-style reranking (Sec. 2.2), one workgroup of RR_NT threads per sequence: the n_out best of
 // every candidate scored in this draft phase under the order (s desc, history index asc), s = the
 // smallest classifier logit on the candidate's path (history index = layer * F*K + slot * K + rank
-// in the row, so index order is depth, then scoring order).  The n_out-th best key is found exactly by
-// a radix select over the order-preserving 32-bit keys of s (12 + 12 + 8 bits, an LDS histogram per
-// pass over the sequence's history); candidates above it are taken, those equal to it in index
-// order; the selection (<= 1024) is then ranked by counting.  Parents precede children because s
-// never increases along a path.
-constexpr int RR_NT = 1024;
-__global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut o, int n_out, int D, int FK) {
+// in the row, so index order is depth, then scoring order).  Parents precede children because s never increases
+// along a path.
+//
+// What bounds it: latency, one workgroup per sequence; so the history is read once (its order-preserving keys go to LDS
+// where they fit, 8192 of them; longer histories are read again at each pass).  Up to RR_BOUND_MAX nodes out, a lower
+// bound of the n-th best key comes from 256 group maxima (bound_from_maxima), what reaches it is listed, ranked exactly
+// on unique 64-bit keys (key, ~index) and cut to n.  More nodes, or more than 1024 candidates above the bound (massive ties):
+// an exact radix select of the n-th best key (12 + 12 + 8 bits, an LDS histogram per pass), ties in index order.
+// One phase of 32 sequences with 600 candidates each, 60 out: 16.0 us for this kernel before, when every pass
+// read the history from memory again and divided for it.
+constexpr int RR_NT = 1024, RR_LDS_KEYS = 8192, RR_BOUND_MAX = 160;
+constexpr int RR_MASK_ROWS_MAX = 256;          // up to so many nodes out the reranking writes the mask itself; k_mask_of_parents for more
+__global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut o, int n_out, int D, int FK, uint32_t fk_inverse) {
   constexpr int NW = RR_NT / WAVE;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
   const int total = D * FK;
-  const int32_t* tok = s.h_tok + (int64_t)b * total; const int32_t* par = s.h_par + (int64_t)b * total;
-  const float* hs = s.h_s + (int64_t)b * total;
+  const int64_t hb = (int64_t)b * total, ob = (int64_t)b * n_out;
   const int32_t* ncand = s.h_ncand + (int64_t)b * D;
-  int32_t* pos = s.h_pos + (int64_t)b * total;
-  __shared__ uint32_t dig[4096];
-  __shared__ int32_t scan_w[NW];
-  __shared__ int32_t sh_digit, sh_above, sh_n;
-  __shared__ float sel_s[C2T_MAX_BUDGET_DEV];
-  __shared__ int32_t sel_i[C2T_MAX_BUDGET_DEV], sel_par[C2T_MAX_BUDGET_DEV], sel_depth[C2T_MAX_BUDGET_DEV];
-  // a thread owns a contiguous range of history indices, so that index order = thread order
-  const int per = (total + RR_NT - 1) / RR_NT, i0 = min(tid * per, total), i1 = min(i0 + per, total);
-  auto valid = [&](int i) { return (i % FK) < ncand[i / FK] && tok[i] >= 0; };
-  int my_valid = 0;
-  for (int i = i0; i < i1; ++i) my_valid += valid(i);
-  {
-    const int incl = wave_scan_incl(my_valid);
-    if (lane == WAVE - 1) scan_w[wid] = incl;
-    __syncthreads();
-    if (tid == 0) { int t = 0; for (int w = 0; w < NW; ++w) t += scan_w[w]; sh_n = t; }
-    __syncthreads();
+  __shared__ uint32_t keys[RR_LDS_KEYS];                    // then: rank of every selected history index
+  __shared__ union { uint32_t dig[4096]; uint32_t lane_max[RR_NT]; uint32_t bits[MASK_BIT_WORDS]; } u;
+  __shared__ __align__(16) uint64_t sel[C2T_MAX_BUDGET_DEV];
+  __shared__ int32_t sel_par[C2T_MAX_BUDGET_DEV];
+  __shared__ int32_t scan_w[NW], scan_e[NW];
+  __shared__ int32_t sh_digit, sh_above, n_list;
+  const bool in_lds = total <= RR_LDS_KEYS;
+  auto layer_of = [&](int i) { return FK > 1 ? (int)__umulhi((uint32_t)i, fk_inverse) : i; };       // i / FK
+  auto load_key = [&](int i) -> uint32_t {                   // 0: not a candidate
+    const int l = layer_of(i);
+    const int tok = s.h_tok[hb + i]; const float v = s.h_s[hb + i];
+    return i - l * FK < ncand[l] && tok >= 0 ? sortable_key(v) : 0u;
+  };
+  auto key_at = [&](int i) { return in_lds ? keys[i] : load_key(i); };
+
+  if (tid == 0) n_list = 0;
+  uint32_t mx = 0u; int cnt = 0;
+  for (int i = tid; i < total; i += RR_NT) {
+    const uint32_t k = load_key(i);
+    if (in_lds) keys[i] = k;
+    mx = max(mx, k); cnt += k != 0u;
   }
-  const int n_all = sh_n, n = min(n_out, n_all);
-  uint32_t prefix = 0, care = 0;
-  int remaining = n;
-  if (n > 0 && n < n_all) {
+  u.lane_max[tid] = mx;
+  cnt = wave_sum_i(cnt);
+  if (lane == 0) scan_w[wid] = cnt;
+  __syncthreads();
+  int n_all = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) n_all += scan_w[w];
+  const int n = min(n_out, n_all);
+  bool listed = false;
+  int m = 0;                                                 // entries of sel, a superset of the selection
+  if (n > 0 && (n == n_all || n <= RR_BOUND_MAX)) {
+    uint32_t bound = 1u;
+    if (n < n_all) {
+      uint32_t g[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) g[w & 3] = max(g[w & 3], u.lane_max[w * WAVE + lane]);
+      bound = max(bound_from_maxima<4>(g, n, n + 32), 1u);
+    }
+    for (int i0 = 0; i0 < total; i0 += RR_NT) {
+      const int i = i0 + tid;
+      const uint32_t k = i < total ? key_at(i) : 0u;
+      const uint64_t hit = __ballot(k >= bound);
+      if (!hit) continue;
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&n_list, __popcll(hit));
+      at = __builtin_amdgcn_readfirstlane(at) + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u));
+      if (k >= bound && at < C2T_MAX_BUDGET_DEV) sel[at] = ((uint64_t)k << 32) | (uint32_t)~i;
+    }
+    __syncthreads();
+    m = n_list;
+    listed = m <= C2T_MAX_BUDGET_DEV;
+  }
+  if (n > 0 && !listed) {
+    // a thread owns a contiguous range of history indices, so that index order = thread order
+    const int per = (total + RR_NT - 1) / RR_NT, i0 = min(tid * per, total), i1 = min(i0 + per, total);
+    uint32_t prefix = 0, care = 0;
+    int remaining = n;
     const int shifts[3] = {20, 8, 0}, widths[3] = {12, 12, 8};
 #pragma unroll 1
     for (int ps = 0; ps < 3; ++ps) {
       const int shift = shifts[ps]; const uint32_t dmask = (1u << widths[ps]) - 1u;
-      for (int i = tid; i < 4096; i += RR_NT) dig[i] = 0u;
+      __syncthreads();
+      for (int i = tid; i < 4096; i += RR_NT) u.dig[i] = 0u;
       __syncthreads();
       for (int i = i0; i < i1; ++i) {
-        if (!valid(i)) continue;
-        const uint32_t key = sortable_key(hs[i]);
-        if ((key & care) == prefix) atomicAdd(&dig[(key >> shift) & dmask], 1u);
+        const uint32_t key = key_at(i);
+        if (key && (key & care) == prefix) atomicAdd(&u.dig[(key >> shift) & dmask], 1u);
       }
       __syncthreads();
       {                                                      // thread t owns digits 4095-4t .. 4092-4t
         uint32_t c[4]; int tot = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { c[j] = dig[4095 - (4 * tid + j)]; tot += (int)c[j]; }
+        for (int j = 0; j < 4; ++j) { c[j] = u.dig[4095 - (4 * tid + j)]; tot += (int)c[j]; }
         const int incl = wave_scan_incl(tot);
         if (lane == WAVE - 1) scan_w[wid] = incl;
         __syncthreads();
@@ -917,76 +959,95 @@ __global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut 
       }
       remaining -= sh_above;
       prefix |= (uint32_t)sh_digit << shift; care |= dmask << shift;
-      __syncthreads();
     }
-  }
-  // take: keys above the n-th best key, and the first `remaining` equal to it in index order
-  const bool take_all = n >= n_all;
-  int my_gt = 0, my_eq = 0;
-  for (int i = i0; i < i1; ++i) {
-    if (!valid(i)) continue;
-    const uint32_t key = sortable_key(hs[i]);
-    my_gt += take_all || key > prefix; my_eq += !take_all && key == prefix;
-  }
-  int before_gt, before_eq;
-  {
+    // take: keys above the n-th best key, and the first `remaining` equal to it in index order
+    int my_gt = 0, my_eq = 0;
+    for (int i = i0; i < i1; ++i) {
+      const uint32_t key = key_at(i);
+      my_gt += key > prefix; my_eq += key == prefix;         // (prefix > 0: the key of a candidate)
+    }
     const int ig = wave_scan_incl(my_gt), ie = wave_scan_incl(my_eq);
-    __shared__ int32_t scan_e[NW];
+    __syncthreads();
     if (lane == WAVE - 1) { scan_w[wid] = ig; scan_e[wid] = ie; }
     __syncthreads();
-    before_gt = ig - my_gt; before_eq = ie - my_eq;
-    int tot_gt = 0;
+    int sg = ig - my_gt, se = ie - my_eq, tot_gt = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) { if (w < wid) { before_gt += scan_w[w]; before_eq += scan_e[w]; } tot_gt += scan_w[w]; }
+    for (int w = 0; w < NW; ++w) { if (w < wid) { sg += scan_w[w]; se += scan_e[w]; } tot_gt += scan_w[w]; }
     // slots: the keys above first (any order), then the ties in index order
-    int sg = before_gt, se = before_eq;
     for (int i = i0; i < i1; ++i) {
-      if (!valid(i)) continue;
-      const uint32_t key = sortable_key(hs[i]);
+      const uint32_t key = key_at(i);
       int slot = -1;
-      if (take_all || key > prefix) slot = sg++;
+      if (key > prefix) slot = sg++;
       else if (key == prefix) { if (se < remaining) slot = tot_gt + se; ++se; }
-      if (slot >= 0 && slot < n) { sel_s[slot] = hs[i]; sel_i[slot] = i; }
+      if (slot >= 0 && slot < n) sel[slot] = ((uint64_t)key << 32) | (uint32_t)~i;
     }
+    m = n;
+    __syncthreads();
   }
-  __syncthreads();
-  // rank the selection by (s desc, index asc) and emit
-  for (int e = tid; e < n; e += RR_NT) {
-    const float v = sel_s[e]; const int id = sel_i[e];
+  int32_t* const rank_lds = (int32_t*)keys;                  // the keys are not read any more: a barrier lies behind their last use
+  int32_t* const rank_mem = s.h_pos + hb;                    // histories that do not fit: the scratch of the caller
+  // rank the list by (s desc, index asc), T lanes per entry, and emit its best n
+  {
+    int tshift = 0;
+    while (tshift < 4 && (m << (tshift + 1)) <= RR_NT) ++tshift;
+    const int T = 1 << tshift, e = tid >> tshift, sub = tid & (T - 1);
+    const bool mine = e < m;
+    const uint64_t key = mine ? sel[e] : 0ull;
+    const int id = (int)~(uint32_t)key;
+    // what the entry emits is requested ahead of the ranking
+    const bool lead = mine && sub == 0;
+    int tok = -1, pid = -1; float hz = 0.f, hP = 0.f, hH = 0.f;
+    if (lead) { tok = s.h_tok[hb + id]; pid = s.h_par[hb + id]; hz = s.h_z[hb + id]; hP = s.h_P[hb + id]; hH = s.h_H[hb + id]; }
     int rank = 0;
-    for (int q = 0; q < n; ++q) { const float vq = sel_s[q]; rank += (vq > v) || (vq == v && sel_i[q] < id); }
-    pos[id] = rank;
-    sel_depth[rank] = id / FK;
-    const int64_t t = (int64_t)b * n_out + rank, h = (int64_t)b * total + id;
-    o.tokens[t] = tok[id]; o.position[t] = id / FK + 1;
-    o.conf[t] = 1.0f / (1.0f + expf(-s.h_z[h])); o.joint_prob[t] = s.h_P[h]; o.entropy[t] = s.h_H[h];
+    if (mine) {
+#pragma unroll 2
+      for (int v = sub * 2; v < m; v += T * 2) {
+        const uint4 q = *(const uint4*)(sel + v);
+        const uint64_t k0 = ((uint64_t)q.y << 32) | q.x, k1 = v + 1 < m ? ((uint64_t)q.w << 32) | q.z : 0ull;
+        rank += (k0 > key ? 1 : 0) + (k1 > key ? 1 : 0);
+      }
+    }
+    if (tshift >= 1) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)rank);
+    if (tshift >= 2) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)rank);
+    if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
+    if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
+    if (lead && rank < n) {
+      if (in_lds) rank_lds[id] = rank; else rank_mem[id] = rank;
+      sel_par[rank] = pid;
+      o.tokens[ob + rank] = tok; o.position[ob + rank] = layer_of(id) + 1;
+      o.conf[ob + rank] = 1.0f / (1.0f + expf(-hz)); o.joint_prob[ob + rank] = hP; o.entropy[ob + rank] = hH;
+    }
   }
   for (int e = n + tid; e < n_out; e += RR_NT) {
-    const int64_t t = (int64_t)b * n_out + e;
-    o.tokens[t] = -1; o.parent[t] = -1; o.position[t] = 0; o.conf[t] = 0.f; o.joint_prob[t] = 0.f; o.entropy[t] = 0.f;
+    o.tokens[ob + e] = -1; o.parent[ob + e] = -1; o.position[ob + e] = 0; o.conf[ob + e] = 0.f; o.joint_prob[ob + e] = 0.f; o.entropy[ob + e] = 0.f;
   }
-  uint8_t* mk = o.mask + (int64_t)b * n_out * n_out;
-  {
-    const int64_t nb = (int64_t)n_out * n_out;               // zeroed with 4-byte stores where alignment allows
-    if ((((uintptr_t)mk) & 3) == 0) {
-      for (int64_t i = tid; i < nb / 4; i += RR_NT) ((uint32_t*)mk)[i] = 0u;
-      for (int64_t i = (nb / 4) * 4 + tid; i < nb; i += RR_NT) mk[i] = 0;
-    } else {
-      for (int64_t i = tid; i < nb; i += RR_NT) mk[i] = 0;
-    }
-  }
-  __threadfence_block();
-  __syncthreads();                                           // pos[] of every selected candidate is written
-  for (int e = tid; e < n; e += RR_NT) {
-    const int id = sel_i[e], rank = pos[id], pid = par[id];
-    const int prank = pid < 0 ? -1 : pos[pid];
-    sel_par[rank] = prank;
-    o.parent[(int64_t)b * n_out + rank] = prank;
-  }
-  __syncthreads();
-  for (int r = tid; r < n; r += RR_NT)
-    for (int j = r; j >= 0; j = sel_par[j]) mk[(int64_t)r * n_out + j] = 1;
   if (tid == 0) { o.n_nodes[b] = n; o.status[b] = s.status[b]; }
+  if (!in_lds) __threadfence_block();
+  __syncthreads();                                           // the rank of every selected candidate is written
+  if (tid < n) {                                             // n <= 1024 = RR_NT
+    const int pid = sel_par[tid], prank = pid < 0 ? -1 : in_lds ? rank_lds[pid] : rank_mem[pid];
+    sel_par[tid] = prank;
+    o.parent[ob + tid] = prank;
+  }
+  if (n_out > RR_MASK_ROWS_MAX) return;
+  __syncthreads();
+  const int per_slice = mask_rows_per_slice(n_out);
+  for (int r0 = 0; r0 < n_out; r0 += per_slice) {
+    write_mask_rows<RR_NT>(o.mask + ob * n_out, n_out, n, r0, min(r0 + per_slice, n_out), sel_par, u.bits);
+    __syncthreads();
+  }
+}
+
+// The mask of trees whose parents have been emitted, for more nodes than one workgroup should write.  grid: (sequences, slices).
+__global__ __launch_bounds__(FIN_NT) void k_mask_of_parents(TreeOut o, int N) {
+  __shared__ int32_t parent[C2T_MAX_BUDGET_DEV];
+  __shared__ uint32_t bits[MASK_BIT_WORDS];
+  const int b = blockIdx.x, per_slice = mask_rows_per_slice(N), r0 = blockIdx.y * per_slice, r1 = min(r0 + per_slice, N);
+  const int64_t ob = (int64_t)b * N;
+  const int n = o.n_nodes[b];
+  for (int i = threadIdx.x; i < r1; i += FIN_NT) parent[i] = o.parent[ob + i];
+  __syncthreads();
+  write_mask_rows<FIN_NT>(o.mask + ob * N, N, n, r0, r1, parent, bits);
 }
 
 }  // namespace c2t
