@@ -639,6 +639,13 @@ __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(c2t_ushort2, a), __builtin_bit_cast(c2t_ushort2, b)));
 }
 
+__device__ __forceinline__ uint32_t pk_sub_sat_u16(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(c2t_ushort2, a), __builtin_bit_cast(c2t_ushort2, b)));
+}
+__device__ __forceinline__ uint32_t pk_sub_u16(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(c2t_ushort2, a) - __builtin_bit_cast(c2t_ushort2, b));
+}
+
 // What the rows' rare logits add up to, per workgroup, in LDS: the streaming loop carries none of
 // it in registers (four registers through the loop, and a copy of them per chunk, before).
 struct OutsideAcc {
@@ -669,17 +676,17 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
   const OutsideAccLds acc = (OutsideAccLds)acc_generic;
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
   if (n_valid == 8) {
-    uint32_t w2[4], inf_lo[4], inf_hi[4], dm = 0u;
+    // codes from 0xC300 on are clamped to the window's lowest value; what must not be, codes in (-2^10, -2^7] and negative
+    // NaN, shows in the packed extremes
+    uint32_t w2[4], dm = 0u, hi = 0u, lo = 0xffffffffu;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      inf_lo[j] = hp_masked(w[j] & 0xffffu) ? ~0u : 0u;
-      inf_hi[j] = hp_masked(w[j] >> 16) ? ~0u : 0u;
-      w2[j] = w[j];
-      if (inf_lo[j]) w2[j] = (w2[j] & 0xffff0000u) | LOWEST;
-      if (inf_hi[j]) w2[j] = (w2[j] & 0x0000ffffu) | (LOWEST << 16);
+      hi = pk_max_u16(hi, w[j]);
+      lo = pk_min_u16(lo, pk_sub_u16(w[j], 0xC300C300u));
+      w2[j] = pk_min_u16(w[j], LOWEST * 0x00010001u);
       dm = pk_max_u16(dm, pk_mad_u16(w2[j], TWO2, BIAS2));
     }
-    if (!(dm & 0xE000E000u)) {
+    if (((dm & 0xE000E000u) | pk_sub_sat_u16(hi, 0xFF80FF80u) | pk_sub_sat_u16(0x01800180u, lo)) == 0u) {
       // Every lane issues all eight atomics, as for a chunk inside the window; a masked logit's goes to the
       // lane's own word of masked_by_lane instead of the histogram (one address select per logit: no
       // branches, no ballots, and the 64 words lie in 64 different places, so masked logits pile up nowhere).
@@ -688,8 +695,8 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
       const LdsWords own = &acc->masked_by_lane[lane_id()], hl = (LdsWords)hist;   // LDS addresses: the selects stay 32-bit, the atomics ds_add
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const LdsWords a_hi = inf_hi[j] ? own : hl + bits_16_27(w2[j]);
-        const LdsWords a_lo = inf_lo[j] ? own : hl + (w2[j] & (HP_WORDS - 1));
+        const LdsWords a_hi = w[j] >= 0xC4800000u ? own : hl + bits_16_27(w2[j]);
+        const LdsWords a_lo = (uint16_t)w[j] >= (uint16_t)0xC480u ? own : hl + (w2[j] & (HP_WORDS - 1));
         __hip_atomic_fetch_add(a_hi, hist_increment((int32_t)w2[j] >> 31, 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __hip_atomic_fetch_add(a_lo, hist_increment(__builtin_amdgcn_sbfe((int32_t)w2[j], 15, 1), 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
@@ -751,6 +758,86 @@ __device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uin
   }
   M2 = pk_max_f16_raw(M2, pat);
   return pat;
+}
+
+// The same for a row that masks part of its vocabulary, where nearly every chunk holds masked logits: those are clamped to
+// the window's lowest value (which the maximum then never takes) and counted in the lane's own word of masked_by_lane
+// instead of the histogram, with an address select per logit but no call and nothing kept per chunk.  What the clamp must
+// not swallow, codes in (-2^10, -2^7] and negative NaN, shows in `seen` (packed maximum of the codes, packed minimum of
+// codes - 0xC300), which the caller looks at once per row.
+struct CodesSeen { uint32_t hi, lo; };
+typedef __attribute__((address_space(3))) uint32_t* LdsWords;
+__device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& M2, LdsWords hist, LdsWords own, OutsideAcc* acc, CodesSeen& seen) {
+  constexpr uint32_t TWO2 = 0x00020002u, BIAS2 = ((0x10000u - 2u * HP_MAG_LO) & 0xffffu) * 0x00010001u;
+  constexpr uint32_t LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1), FIRST_MASKED = 0xC480u;       // see hp_masked
+  const uint32_t raw[4] = {q.x, q.y, q.z, q.w};
+  uint32_t w[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    seen.hi = pk_max_u16(seen.hi, raw[j]);
+    seen.lo = pk_min_u16(seen.lo, pk_sub_u16(raw[j], 0xC300C300u));
+    w[j] = pk_min_u16(raw[j], LOWEST * 0x00010001u);
+  }
+  const uint32_t dm = pk_max_u16(pk_max_u16(pk_mad_u16(w[0], TWO2, BIAS2), pk_mad_u16(w[1], TWO2, BIAS2)),
+                                 pk_max_u16(pk_mad_u16(w[2], TWO2, BIAS2), pk_mad_u16(w[3], TWO2, BIAS2)));
+  uint32_t pat;
+  if (__builtin_amdgcn_ballot_w64((dm & 0xE000E000u) != 0u) != 0ull) {
+    pat = hist_chunk_outside(q, 8, (uint32_t*)hist, acc);
+  } else {
+    pat = pk_max_f16_raw(pk_max_f16_raw(w[0], w[1]), pk_max_f16_raw(w[2], w[3]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const LdsWords a_hi = raw[j] >= (FIRST_MASKED << 16) ? own : hist + bits_16_27(w[j]);
+      const LdsWords a_lo = (uint16_t)raw[j] >= (uint16_t)FIRST_MASKED ? own : hist + (w[j] & (HP_WORDS - 1));
+      __hip_atomic_fetch_add(a_hi, hist_increment((int32_t)w[j] >> 31, 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(a_lo, hist_increment(__builtin_amdgcn_sbfe((int32_t)w[j], 15, 1), 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+  M2 = pk_max_f16_raw(M2, pat);
+  return pat;
+}
+
+// The streaming loop of such a row: `whole` chunks from `base` and, with tail_valid > 0, a partial one behind them.  Out of
+// line, so that rows that mask nothing keep their registers.  Returns the packed maximum.
+// A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 43 us when every chunk took hist_chunk_outside, 37.
+template <int NT>
+__device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, LdsWords hist,
+                                                    __attribute__((address_space(3))) uint16_t* keys, OutsideAcc* acc) {
+  const uint64_t base_u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
+                          ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32);
+  const int whole = __builtin_amdgcn_readfirstlane(whole_chunks), tail = tail_valid > 0 ? whole : -1;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, (whole + (tail >= 0 ? 1 : 0)) * 16, 0x00020000);
+  const LdsWords own = (LdsWords)&((OutsideAccLds)acc)->masked_by_lane[lane_id()];
+  const int n = whole / (4 * NT);
+  uint32_t M2 = HP_F16_NEG_INF2, so = 0u;
+  uint4 q[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) q[k] = load_stream_buffer(rs, vo, (uint32_t)k * (NT * 16u));
+  CodesSeen seen{0u, 0xffffffffu};
+  for (int it = 0; it < n; ++it, so += 4u * NT * 16u) {
+    uint32_t key = HP_F16_NEG_INF2;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      key = pk_max_f16_raw(key, hist_chunk_masked(q[k], M2, hist, own, acc, seen));
+      q[k] = load_stream_buffer(rs, vo, so + (uint32_t)(4 + k) * (NT * 16u));
+    }
+    keys[it * NT] = (uint16_t)pk_max_f16_raw(key, key >> 16);
+  }
+  // the last, partial group: up to four chunks of this lane, the row's partial last chunk among them
+  const int g = (int)(vo >> 4) + n * 4 * NT;
+  if (g < whole || g == tail) {
+    uint32_t key = HP_F16_NEG_INF2;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (g + k * NT < whole) key = pk_max_f16_raw(key, hist_chunk_masked(q[k], M2, hist, own, acc, seen));
+      else if (g + k * NT == tail) key = pk_max_f16(key, hist_chunk_outside(q[k], tail_valid, (uint32_t*)hist, acc));
+    }
+    keys[n * NT] = (uint16_t)pk_max_f16(key, key >> 16);
+    M2 = pk_max_f16(M2, key);
+  }
+  if (pk_sub_sat_u16(seen.hi, 0xFF80FF80u) | pk_sub_sat_u16(0x01800180u, seen.lo))             // neither in the window nor masked: two-pass path
+    __hip_atomic_fetch_max(&((OutsideAccLds)acc)->mag_max, 0x7fffu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return M2;
 }
 
 // The lane that holds the M-th largest logit: the sums over the logits it contributes to the top M
@@ -905,7 +992,7 @@ template <int NT, bool TOPM, int WPS, int REPL, bool COOP>
 __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ rowp, int V, int K, int M, const Segment& sg_own,
                                              const double* __restrict__ tab_e, uint32_t* __restrict__ hist,
                                              unsigned char* map_lds, const SelectLds& sel, RowResult* rr,
-                                             const ClassifierStage cst, const TreeState& st, const ScoreParams& sp, int split,
+                                             const ClassifierStage cst, const float* __restrict__ cls, const TreeState& st, const ScoreParams& sp, int split,
                                              int64_t row_launched, int64_t slot) {
   constexpr int NW = NT / WAVE;
   constexpr int WPL = HP_WORDS / NT;                   // words per lane in the epilogue (8 at 512 threads)
@@ -967,6 +1054,26 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     __builtin_amdgcn_s_setprio(3);
     // groups of DEPTH sweeps in which every lane has a chunk; a cell is four sweeps
     const int n_groups = whole / (DEPTH * NT);
+    // A row that masks part of its vocabulary shows it in the wavefront's first two chunks (1024 logits; masks that only come
+    // later are counted chunk by chunk, out of line).  Decided once, ahead of the loop: a test inside it costs the rows that
+    // mask nothing 4 to 6 %.
+    int masks = 0;
+    // Not with four workgroups per CU, where the decision alone costs rows that mask nothing 1 % and the call gains nothing; nor
+    // for shared rows, whose segments are a group or two: root layer of 64 rows 26.7 us without it, 29.0 with it.
+    if (WPS != 8 && !COOP) {
+      uint32_t hi = pk_max_u16(pk_max_u16(q[0].x, q[0].y), pk_max_u16(q[0].z, q[0].w));
+      hi = pk_max_u16(hi, pk_max_u16(pk_max_u16(q[1].x, q[1].y), pk_max_u16(q[1].z, q[1].w)));
+      const uint64_t masked_lanes = __builtin_amdgcn_ballot_w64(pk_sub_sat_u16(hi, 0xC47FC47Fu) != 0u);
+      masks = __builtin_amdgcn_readfirstlane(n_groups > 0 && masked_lanes != 0ull ? 1 : 0);      // (a scalar branch: as a lane mask both sides' registers would be live at once)
+    }
+    vo_after = vo;
+    if (masks != 0) {                                    // (nothing of this path is live across the call: what is would be spilled for every row)
+      M2 = hist_stream_masked<NT>(base_u, whole, sg.tail_chunk >= 0 ? sg.tail_valid : 0, vo, (LdsWords)histl,
+                                  (__attribute__((address_space(3))) uint16_t*)mp, &sh_out);
+      C2T_PT(PT_STREAM_END);
+      __builtin_amdgcn_s_setprio(0);
+      store_classifier(stage_classifier(cls, sp.h, cst.dst));
+    } else {
     for (int it = n_groups; it > 0; --it, so += (uint32_t)DEPTH * NT * 16u, mp += (DEPTH / 4) * NT) {
 #pragma unroll
       for (int c = 0; c < DEPTH / 4; ++c) {
@@ -980,7 +1087,6 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
         mp[c * NT] = (uint16_t)pk_max_f16_raw(key, key >> 16);
       }
     }
-    vo_after = vo;
     C2T_PT(PT_STREAM_END);
     store_classifier(cst);                               // published by the barriers below
     const int g0 = sg.c0 + (int)(vo >> 4) + n_groups * (DEPTH * NT);
@@ -1000,6 +1106,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
         mp[c * NT] = (uint16_t)pk_max_f16(key, key >> 16);
         M2 = pk_max_f16(M2, key);                         // the partial chunk's maximum is in no other running value
       }
+    }
     }
 #undef C2T_COUNT
 #undef C2T_LOAD
@@ -1303,7 +1410,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     __syncthreads();
   } else {
     top = hist_segment<NT, TOPM, WPS, REPL, COOP>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, dyn_lds + HP_WORDS * 4 * REPL,
-                                                  sel, &rr, cst, st, sp, split, rl, row);
+                                                  sel, &rr, cst, cls, st, sp, split, rl, row);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
   finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst, [] {},

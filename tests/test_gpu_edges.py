@@ -1,0 +1,121 @@
+"""GPU parity at the edges of the kernels' tiles, lists and dispatch rules, against the oracle: the same comparisons as in
+test_gpu_rows.py and test_gpu_configs.py (token ids, trees and masks bit for bit, reals within their 1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from _harness import make_gpu, make_oracle, run_both, to_np, ORACLE_THREADS
+from test_gpu_configs import _compare_reranked
+from test_gpu_rows import test_rows_against_oracle as rows_against_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+# fp32 rows are read in tiles of 8192 logits by a workgroup; the bound on the top K is raised at tiles 2, 4, 8
+@pytest.mark.parametrize("V,K", [(8191, 1), (8192, 64), (8193, 16), (16385, 33), (40963, 64)])
+def test_fp32_rows_at_tile_edges(V, K):
+    rows_against_oracle("f32", V, K, 1)
+
+
+# bf16 rows that mask part of their vocabulary, one workgroup each: whole groups of eight sweeps (32768 logits), a rest, a partial chunk
+@pytest.mark.parametrize("V", [32768, 36865, 65549])
+def test_masked_bf16_rows_alone_on_a_cu(V):
+    rows_against_oracle("bf16", V, 16, 1)
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 40000), ("f32", 20000)])
+def test_bad_logits_among_masked_ones(dtype, V):
+    from paper_2502_13652_amd import C2TContext
+    rng = np.random.default_rng(V)
+    rows = (2 * rng.standard_normal((8, V))).astype(np.float32)
+    rows[rng.random((8, V)) < 0.3] = -np.inf
+    at = V - 5000                                            # (a NaN with its sign set is a code of its own in the histogram pass)
+    neg_nan = np.float32(np.uint32(0xFFC00000).view(np.float32))
+    for r, v in ((1, np.nan), (2, neg_nan), (3, np.inf), (5, -np.inf), (6, neg_nan)):
+        rows[r, at] = v
+    rows[6, 3] = neg_nan
+    x = torch.from_numpy(rows).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    if dtype == "bf16":
+        x.view(torch.int16)[2, at] = np.int16(np.uint16(0xFFC0).view(np.int16))
+        x.view(torch.int16)[6, [3, at]] = torch.tensor([-1, -64], dtype=torch.int16)      # 0xFFFF and 0xFFC0
+    ctx = C2TContext(8, V, 1, 4, 1, 4, 2, 1 if dtype == "bf16" else 0, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    ctx.set_row_splits(1, 1)
+    ctx.reset()
+    ctx.expand_layer(x.view(8, 1, V).cuda())
+    out = to_np(ctx.finalize_tree())
+    np.testing.assert_array_equal(out["status"] & 1, [0, 1, 1, 1, 0, 0, 1, 0])
+    np.testing.assert_array_equal(out["n_nodes"], np.where(out["status"] & 1, 0, 1))          # one frontier slot: the best child
+
+
+def _layers(cfg):
+    cache = {}
+
+    def get(l):
+        if l not in cache:
+            x = W.logits_layer(cfg, l, device="cuda")
+            per = 8 if cfg["dtype"] == "bf16" else 4
+            xp = torch.full((cfg["B"], cfg["F"], (cfg["V"] + per - 1) // per * per), float("inf"), dtype=x.dtype, device=x.device)
+            xp[:, :, :cfg["V"]] = x
+            cache[l] = xp[:, :, :cfg["V"]]
+        return cache[l]
+    return get
+
+
+def _cfg(**k):
+    return dict(dict(idx=89, B=3, V=3001, dtype="bf16", D=4, F=8, K=8, h=8, beta=0.3, N=30, zipf_s=1.0, sigma=(1.0, 4.0), spike_frac=0.1,
+                     desc="edges"), **k)
+
+
+# candidates of a sequence: one a thread up to 512, several beyond; survivors ranked directly up to 64, lists of up to 128
+# behind a bound, radix select beyond; classifiers from 48 hidden units on evaluated by the workgroup, in one or several blocks
+@pytest.mark.parametrize("F,K,h,N,dtype", [(16, 32, 47, 60, "bf16"), (27, 19, 48, 100, "bf16"), (9, 57, 50, 64, "f32"), (64, 8, 12, 200, "f32"),
+                                           (33, 62, 256, 300, "bf16"), (8, 8, 63, 20, "bf16"), (3, 64, 49, 12, "f32"), (1, 1, 64, 3, "bf16")])
+def test_sequence_step_at_its_edges(F, K, h, N, dtype):
+    total = 0
+    for seed, beta in ((0, 0.0), (1, 0.2), (2, 0.4)):
+        cfg = _cfg(F=F, K=K, h=h, N=N, dtype=dtype, beta=beta)
+        go, oo, _ = run_both(cfg, W.classifier(cfg, seed), _layers(cfg), tag="F=%d K=%d h=%d seed %d" % (F, K, h, seed))
+        total += int(go["n_nodes"].sum())
+    assert total > 0
+
+
+# the mask is written sixteen bytes a store in slices of 16384 bytes: budgets around multiples of sixteen and slice edges
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 127, 128, 129, 181, 500, 1023])
+def test_mask_at_store_and_slice_edges(N):
+    cfg = _cfg(B=2, V=700, D=18, F=64, K=8, h=4, beta=0.0, N=N)
+    go, oo, _ = run_both(cfg, W.classifier(cfg, 0), _layers(cfg), per_layer=False, tag="N=%d" % N)
+    assert (go["n_nodes"] == N).all()
+    # caller's buffers at any alignment
+    ctx = make_gpu(cfg, W.classifier(cfg, 0))
+    ctx.reset()
+    for l in range(cfg["D"]):
+        ctx.expand_layer(_layers(cfg)(l))
+    out = ctx.new_tree_out()
+    room = torch.full((2 * N * N + 8,), 7, dtype=torch.uint8, device="cuda")
+    out["mask"] = room[3:3 + 2 * N * N].view(2, N, N)
+    ctx.finalize_tree(out)
+    np.testing.assert_array_equal(out["mask"].cpu().numpy(), go["mask"])
+    assert (room[:3] == 7).all() and (room[3 + 2 * N * N:] == 7).all()
+
+
+# up to 160 nodes out behind a bound, radix select beyond; the mask in the same kernel up to 256; histories beyond 8192
+# candidates are not kept in LDS; F * K = 1
+@pytest.mark.parametrize("D,F,K,n_outs", [(6, 16, 16, (1, 64, 159, 160, 161, 256, 257, 700)), (9, 32, 32, (60, 160, 161, 900)), (12, 1, 1, (1, 5, 12, 20))])
+def test_reranking_at_its_edges(D, F, K, n_outs):
+    for seed in range(2):
+        cfg = _cfg(B=3, V=1500, D=D, F=F, K=K, h=4, beta=0.0, N=min(1024, D * F), rerank=1)
+        cls = W.classifier(cfg, seed)
+        layers = _layers(cfg)
+        g, o = make_gpu(cfg, cls), make_oracle(cfg, cls)
+        g.reset(); o.reset()
+        for l in range(D):
+            x = layers(l)
+            g.expand_layer(x)
+            if o.frontier()["n_frontier"].sum() > 0:
+                o.expand_layer(W.as_numpy_bits(x), threads=ORACLE_THREADS)
+        torch.cuda.synchronize()
+        for n_out in n_outs:
+            _compare_reranked(g, o, [0, 1, 2], n_out, "rerank D=%d F=%d K=%d seed %d" % (D, F, K, seed))
