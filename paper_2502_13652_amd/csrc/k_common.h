@@ -172,6 +172,17 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
   return (int)u;
 }
 
+// Places for a wavefront's entries in a list that several wavefronts append to: `n` entries of this lane go to the returned
+// place and the ones behind it.  One LDS addition a wavefront; an addition per entry has every one of them wait out its
+// round trip (200 cycles).  Every lane of the wave calls it; a wave without entries returns at once.
+__device__ __forceinline__ int append_places(int n, int32_t* counter) {
+  if (__builtin_amdgcn_ballot_w64(n != 0) == 0ull) return 0;  // (uniform) most wavefronts have none
+  const int incl = wave_scan_incl(n);
+  int base = 0;
+  if (lane_id() == WAVE - 1) base = atomicAdd(counter, incl);
+  return __builtin_amdgcn_readlane(base, WAVE - 1) + incl - n;
+}
+
 // Partial rank of an entry with value v (its own index: self) in a list of n values in LDS: how many of the
 // entries first4, first4 + 1, .. first4 + 3, first4 + step4, ... come before it in the order (value desc, then
 // `ahead_at_tie(index)` among equal values).  Four values per LDS read, the reads independent of each other, where a
