@@ -37,13 +37,14 @@ constexpr int HP_NT = 512;                     // workgroup size of the histogra
 constexpr int HP_REPL_ALONE = C2T_HP_REPL_ALONE;   // histogram copies of a workgroup that has its CU to itself (launches of at most one workgroup per CU)
 constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
+constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
 constexpr int NT_F32 = 512;                    // workgroup size of the generic kernel for fp32 logits (cfg1: 28.3 / 26.7 / 31.0 us per layer with 256 / 512 / 1024)
 constexpr int PARTIAL_SLOTS_MIN = 16384;       // (row, split) records the workspace always has room for
 // Row splits.  A split adds an epilogue, a device-scope ticket and a merge (a few microseconds of
 // dependent round trips), which costs more than it saves on the histogram path even for a single
 // sequence; the two-pass fp32 path is compute-heavy (an fp64 exp per element) and gains from a few.
 constexpr int TARGET_WORKGROUPS_F32 = 256;
-constexpr int MAX_DEFAULT_SPLITS_F32 = 4;
+constexpr int SPLITS_F32 = 4, MAX_SPLITS_F32 = 8, SPLIT_CHUNKS_F32 = 2700;
 // Shared rows on the histogram path (share_row): a launch of few rows, each a workgroup alone on its
 // CU, spreads every row over several CUs instead; the workgroups hand their counts over before
 // the epilogue, so the row still has one epilogue and no merge of lists.
@@ -78,11 +79,17 @@ int epc_of(const c2t_config& c) { return c.logits_dtype == C2T_BF16 ? 8 : 4; }
 int keybytes_of(const c2t_config& c) { return c.logits_dtype == C2T_BF16 ? 2 : 4; }
 int chunks_of(const c2t_config& c) { return (c.vocab + epc_of(c) - 1) / epc_of(c); }
 // fewest splits for which one workgroup's cell map fits its LDS budget
-int cpc_of(const c2t_config& c) { return c.logits_dtype == C2T_BF16 ? HP_CPC : 1; }   // chunks per map cell
-int min_splits(const c2t_config& c) {
-  const int max_chunks = (c.logits_dtype == C2T_BF16 ? MAX_MAP_BYTES_BF16 : MAX_MAP_BYTES_F32) / keybytes_of(c) * cpc_of(c);
+int cpc_of(const c2t_config& c) { return c.logits_dtype == C2T_BF16 ? HP_CPC : DIRECT_CPC; }   // chunks per map cell
+int cells_of(const c2t_config& c, int chunks) {
+  return c.logits_dtype == C2T_BF16 ? cells_in_segment<HP_NT, HP_CPC>(chunks) : cells_in_segment<NT_F32, DIRECT_CPC>(chunks);
+}
+int splits_of_cells(const c2t_config& c, int chunks_per_cell) {
+  const int max_chunks = (c.logits_dtype == C2T_BF16 ? MAX_MAP_BYTES_BF16 : MAX_MAP_BYTES_F32) / keybytes_of(c) * chunks_per_cell;
   return (chunks_of(c) + max_chunks - 1) / max_chunks;
 }
+int fewest_splits(const c2t_config& c) { return splits_of_cells(c, cpc_of(c)); }
+// fewest a caller may set (and what the workspace is sized for): fp32 segments of at most 49152 logits
+int min_splits(const c2t_config& c) { return splits_of_cells(c, c.logits_dtype == C2T_BF16 ? HP_CPC : 1); }
 
 int check_config(const c2t_config* c) {
   if (!c) return C2T_ERR_INVALID_ARG;
@@ -186,13 +193,13 @@ namespace {
 
 // default number of workgroups a row is split over when `rows` rows are launched
 int default_split(const c2t_config& c, const Layout& L, int64_t rows) {
-  const int nmin = min_splits(c);
-  if (c.logits_dtype == C2T_BF16 || c.entropy_top_m > 0) return nmin;
+  if (c.logits_dtype == C2T_BF16 || c.entropy_top_m > 0) return min_splits(c);
   const int by_size = std::max(1, chunks_of(c) / NT_F32);   // at least one full sweep of the workgroup
-  const int64_t want = std::min<int64_t>((TARGET_WORKGROUPS_F32 + rows - 1) / rows, MAX_DEFAULT_SPLITS_F32);
+  const int most = std::max(SPLITS_F32, std::min(MAX_SPLITS_F32, chunks_of(c) / SPLIT_CHUNKS_F32));
+  const int64_t want = std::min<int64_t>((TARGET_WORKGROUPS_F32 + rows - 1) / rows, most);
   const int64_t cap = L.partial_slots / rows;
   const int64_t ns = std::min<int64_t>(std::min<int64_t>(want, by_size), cap);
-  return (int)std::max<int64_t>(ns, nmin);
+  return (int)std::max<int64_t>(ns, fewest_splits(c));
 }
 
 // Workgroups that share a row when `rows` rows are launched unsplit; 1: rows are not shared.
@@ -221,7 +228,7 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   const int per_row = share.n > 1 ? share.n : nsplit;       // workgroups per row
   const int cps = share.n > 1 ? share.groups_each * COOP_GROUP_CHUNKS : (chunks_of(c) + nsplit - 1) / nsplit;
   // the cell map in LDS: the workgroup's segment; the whole row where rows are shared (the workgroup that finishes the row loads it)
-  const int cells = c.logits_dtype == C2T_BF16 ? cells_in_segment<HP_NT, HP_CPC>(share.n > 1 ? chunks_of(c) : cps) : cps;
+  const int cells = cells_of(c, share.n > 1 ? chunks_of(c) : cps);
   const size_t map_lds = ((size_t)cells * keybytes_of(c) + 15) / 16 * 16;
   // element list of the selection: (2K-1) cells of cpc chunks, 8 bytes per element
   const size_t list_lds = (size_t)(2 * c.top_k - 1) * cpc * epc_of(c) * 8;
@@ -278,7 +285,7 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
 #undef C2T_LAUNCH_HIST_BUILD
 #undef C2T_LAUNCH_HIST
   } else {
-    const size_t lds_work = (std::max(std::max(std::max(map_lds, list_lds), score_lds), (size_t)16 * 1024) + 15) / 16 * 16;
+    const size_t lds_work = (std::max(std::max(std::max(map_lds, list_lds), score_lds), LIST_BYTES_F32) + 15) / 16 * 16;
     sp.lds_bytes = (int)lds_work;
     sp.w_lds_off = (int)lds_work;                           // the classifier's parameters, padded to 16 bytes
     const size_t lds = lds_work + ((size_t)(5 * c.hidden + 1) * 4 + 15) / 16 * 16;
@@ -515,7 +522,7 @@ int c2t_set_row_splits(c2t_ctx* x, int32_t first_layer, int32_t other_layers) {
   const int nmax_size = std::max(1, chunks_of(c));
   int nf = first_layer ? first_layer : default_split(c, x->lay, c.batch);
   int no = other_layers ? other_layers : default_split(c, x->lay, (int64_t)c.batch * c.max_frontier);
-  if (nf < nmin || no < nmin || nf > nmax_size || no > nmax_size) return C2T_ERR_UNSUPPORTED;
+  if ((first_layer && nf < nmin) || (other_layers && no < nmin) || nf > nmax_size || no > nmax_size) return C2T_ERR_UNSUPPORTED;
   if ((int64_t)c.batch * nf > x->lay.partial_slots || (int64_t)c.batch * c.max_frontier * no > x->lay.partial_slots)
     return C2T_ERR_WORKSPACE;
   x->ns_first = nf; x->ns_other = no;

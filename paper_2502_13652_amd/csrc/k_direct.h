@@ -28,6 +28,7 @@
 namespace c2t {
 
 constexpr int EXP_TAB = 32;
+constexpr int DIRECT_CPC = 4;                  // chunks per cell of the fallback's map: a row of 196608 fp32 logits needs 48 KB
 constexpr int DIRECT_CHUNKS = 4;               // chunks a lane reads per tile: 64 bytes, two tiles in flight
 
 // 2^(j/32) with j << 15 taken off its upper word: adding k << 15 for any k = 32 q + j then gives 2^(k/32)
@@ -212,7 +213,7 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   C2T_PT(PT_HIST_COMPLETE);
   const int n_el = sh.n_list;
   if (n_el > sel.list_cap) {
-    generic_segment<DT, NT, 1>(rowp, V, K, 0, sg, map_lds, sel, rr, 0u);
+    generic_segment<DT, NT, DIRECT_CPC>(rowp, V, K, 0, sg, map_lds, sel, rr, 0u);
     return SegmentTop{RANKED_IN_RR, false};
   }
   if (n_el > 2 * WAVE) {
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
   C2T_PT(PT_START);
   __shared__ DirectShared<NT> sh;
   const ClassifierStage cst = stage_classifier(cls, sp.h, sp.w_lds_off >= 0 ? (float*)(dyn_lds + sp.w_lds_off) : nullptr);
-  const SelectLds sel = make_select_lds<NT, 1, T::EPC>(dyn_lds, sp.lds_bytes);
+  const SelectLds sel = make_select_lds<NT, DIRECT_CPC, T::EPC>(dyn_lds, sp.lds_bytes);
   SegmentTop top{RANKED_IN_RR, false};
   bool have_record = true;                                 // (uniform) rr.part is complete
   if (sg.ncell == 0) {
