@@ -187,7 +187,7 @@ int c2t_get_layer_rows(c2t_ctx* ctx, const int32_t** layer_rows);
 
 /* Launch-shape override for experiments: number of workgroups a logits row is split over
  * in the first layer (one row per sequence) and in later layers; 0 = library default.
- * C2T_ERR_UNSUPPORTED below the minimum the vocabulary needs.
+ * C2T_ERR_UNSUPPORTED below one workgroup per 49152 fp32 or 262144 bf16 logits (the default may be lower for fp32).
  * By default a launch of few long bf16 rows (at most 128 rows of at least 65,536 logits, e.g. a
  * single sequence's layer or a batch's first layer) lets several workgroups on otherwise idle CUs
  * count one row together: they add their histograms up through the workspace before the row's one

@@ -38,11 +38,15 @@ constexpr int HP_REPL_ALONE = C2T_HP_REPL_ALONE;   // histogram copies of a work
 constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
 constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
-constexpr int NT_F32 = 512;                    // workgroup size of the generic kernel for fp32 logits (cfg1: 28.3 / 26.7 / 31.0 us per layer with 256 / 512 / 1024)
+constexpr int NT_F32 = 512;                    // workgroup size of the fp32 kernel: two of them fill a CU at its 128 registers a lane
 constexpr int PARTIAL_SLOTS_MIN = 16384;       // (row, split) records the workspace always has room for
 // Row splits.  A split adds an epilogue, a device-scope ticket and a merge (a few microseconds of
 // dependent round trips), which costs more than it saves on the histogram path even for a single
-// sequence; the two-pass fp32 path is compute-heavy (an fp64 exp per element) and gains from a few.
+// sequence; the fp32 path issues twenty instructions a logit and gains from a few while CUs are idle: at most one
+// workgroup a CU, four a row, eight for rows that leave each a tile and a third (2700 chunks).  Layers in us, by splits:
+// 10 rows of 32000: 17.6 with 4, 24 with 16; 40 rows of 65541: 22.3 / 18.8 / 17.8 / 20.3 with 2 / 4 / 6 / 10; 16 rows of
+// 128256: 28.6 / 24.7 / 29.6 with 3 / 8 / 16.  More rows than CUs stay whole: 256 rows of 128256 49.6 with 1, 61.6
+// with 3, 86.8 with 8; 512 rows of 65536 47.3 with 1, 61.6 with 2; 2048 rows of 65536 136 with 1, 160 with 2.
 constexpr int TARGET_WORKGROUPS_F32 = 256;
 constexpr int SPLITS_F32 = 4, MAX_SPLITS_F32 = 8, SPLIT_CHUNKS_F32 = 2700;
 // Shared rows on the histogram path (share_row): a launch of few rows, each a workgroup alone on its

@@ -20,13 +20,14 @@
 //    e^x = 1 + x to fp64 accuracy for |x| < 2^-25.  So are masked logits, -inf or a finite
 //    x <= -2^10 (the masked tokens of constrained decoding): they add exactly nothing to either
 //    sum and rank after every window value.
-//  * any other row (fp32 logits; bf16 rows holding a logit >= 2^7 or in (-2^10, -2^7], +inf or
-//    a NaN, a value held by more than 65535 logits, or below-window or masked logits that could
-//    rank among the K largest): two passes over the segment with fp64 exponentials per element.
+//  * bf16 rows holding a logit >= 2^7 or in (-2^10, -2^7], +inf or a NaN, a value held by more than
+//    65535 logits, or below-window or masked logits that could rank among the K largest; fp32 rows with thousands of
+//    logits above a lower bound of the K-th largest: two passes over the segment with fp64 exponentials per element
+//    (generic_segment).  Other fp32 rows: one pass with an fp64 exponential per element (k_direct.h).
 //
 // Top-K without data-dependent work in the streaming loop: the loop records the maximum of each
-// cell as a "cell key" in an LDS map.  A cell is one chunk (fp32) or the four chunks a lane reads
-// in four consecutive sweeps of the workgroup (bf16: chunks i, i+NT, i+2NT, i+3NT of the segment).
+// cell as a "cell key" in an LDS map.  A cell is the four chunks a lane reads
+// in four consecutive sweeps of the workgroup (chunks i, i+NT, i+2NT, i+3NT of the segment).
 // Afterwards a bound tau <= K-th largest logit is known (exactly, from the histogram; or as the
 // K-th largest per-lane maximum), only cells whose key reaches tau can hold a top-K element, and
 // those few cells are re-read and their elements ranked exactly by (logit desc, id asc).

@@ -5,9 +5,9 @@ import pytest
 import torch
 
 import workloads as W
-from _harness import make_gpu, make_oracle, run_both, to_np, ORACLE_THREADS
+from _harness import close, make_gpu, make_oracle, run_both, to_np, ORACLE_THREADS
 from test_gpu_configs import _compare_reranked
-from test_gpu_rows import test_rows_against_oracle as rows_against_oracle
+from test_gpu_rows import adversarial_rows, test_rows_against_oracle as rows_against_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -16,6 +16,37 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("V,K", [(8191, 1), (8192, 64), (8193, 16), (16385, 33), (40963, 64)])
 def test_fp32_rows_at_tile_edges(V, K):
     rows_against_oracle("f32", V, K, 1)
+
+
+# Long fp32 rows of a launch with more rows than CUs: one workgroup each, whose fallback (ties, sorted rows) maps 4 chunks a
+# cell; up to 196608 logits, and split above.  The rows are dealt out ten times and more: equal rows give equal results.
+@pytest.mark.parametrize("V,K,per_row", [(49163, 64, 1), (131075, 16, 1), (196608, 8, 1), (196612, 8, 2)])
+def test_long_fp32_rows_unsplit(V, K, per_row):
+    from oracle import ref_row
+    from paper_2502_13652_amd import C2TContext, C2TError
+    names, rows = adversarial_rows(V, np.random.default_rng(V), False)
+    n, B = len(names), 260
+    stride = (V + 3) // 4 * 4 + 4
+    x = torch.full((n, 1, stride), float("inf"))
+    x[:, 0, :V] = torch.from_numpy(rows)
+    xd = x.cuda()[torch.arange(B, device="cuda") % n].contiguous()
+    ctx = C2TContext(B, V, 1, K, 1, 1, 2, 0, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    assert ctx.row_workgroups() == (per_row, per_row)
+    with pytest.raises(C2TError):
+        ctx.set_row_splits(1, 1)                             # a split count that is set keeps its limit of 49152 logits
+    ctx.set_row_splits(0, 0)
+    ctx.reset()
+    ctx.expand_layer(xd)
+    c = to_np(ctx.candidates())
+    for b, name in enumerate(names):
+        r = ref_row(x[b, 0, :V].numpy(), K)
+        k = len(r["ids"])
+        for e in range(b, B, n):
+            np.testing.assert_array_equal(c["token"][e, :k], r["ids"], err_msg=name)
+            assert close(c["p"][e, :k], r["p"].astype(np.float32), atol=1e-37).all(), name
+            assert close(c["H"][e, 0], np.float32(r["H"]), atol=V * 2.0 ** -53).all(), name       # (as in test_gpu_rows.py)
 
 
 # bf16 rows that mask part of their vocabulary, one workgroup each: whole groups of eight sweeps (32768 logits), a rest, a partial chunk
