@@ -1012,7 +1012,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
                                              const double* __restrict__ tab_e, uint32_t* __restrict__ hist,
                                              unsigned char* map_lds, const SelectLds& sel, RowResult* rr,
                                              const ClassifierStage cst, const float* __restrict__ cls, const TreeState& st, const ScoreParams& sp, int split,
-                                             int64_t row_launched, int64_t slot) {
+                                             int64_t row_launched, int b, int64_t slot) {
   constexpr int NW = NT / WAVE;
   constexpr int WPL = HP_WORDS / NT;                   // words per lane in the epilogue (8 at 512 threads)
   static_assert(NW <= 16 && WPL % 4 == 0, "one DPP row holds the per-wave partials; a lane reads whole 16-byte runs");
@@ -1413,7 +1413,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   if (wid == NW - 1) {
     if (COMBINE_LATE) combine();
     if (lane == 0) { RowPartial r; r.ref = (double)m; r.a = 0.0; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = 0; r.flags = 0u; rr->part = r; }
-    if (entropy) row_entropy(st, sp, slot, (double)m, 0.0, sum_d[0], sum_d[1], 0u, *rr);
+    if (entropy) row_entropy(st, sp, b, slot, (double)m, 0.0, sum_d[0], sum_d[1], 0u, *rr);
   }
   collect_cells<1, NT, HP_CPC, WPS != 8>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
   if (ties) {
@@ -1456,7 +1456,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     __syncthreads();
   } else {
     top = hist_segment<NT, TOPM, WPS, REPL, COOP>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, dyn_lds + HP_WORDS * 4 * REPL,
-                                                  sel, &rr, cst, cls, st, sp, split, rl, row);
+                                                  sel, &rr, cst, cls, st, sp, split, rl, b, row);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
   finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst, [] {},

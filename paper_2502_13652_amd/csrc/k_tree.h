@@ -180,7 +180,8 @@ struct RowResult {
   double Zr;          // sum of e^(x - R) over the row, R = part.ref
   float H;            // entropy of the row
   uint32_t bad;       // no candidate comes from this row
-  float parent_P, parent_s; int32_t parent_hidx;     // of the row's frontier node
+  float parent_P, parent_s; int32_t parent_hidx, parent_node;   // of the row's frontier node
+  int32_t n_nodes;    // of the sequence's tree before this layer
   float topv[64];
   int32_t topi[64];
 };
@@ -252,9 +253,10 @@ __device__ __forceinline__ void rank_list(int K, const SelectLds& sel, int n_el,
 
 // ---- row level: entropy (Eq. 2) from the row's sums, and what the row's frontier node hands down; by one wavefront.
 // Re-references the sums from the offset a to the row maximum R: p_j = e^(x_j - R) / Zr, H = -sum p ln p = ln Zr - Sr / Zr.
-__device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParams& sp, int64_t slot, double R, double a, double Z, double S,
+__device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParams& sp, int b, int64_t slot, double R, double a, double Z, double S,
                                             uint32_t flags, RowResult& rr) {
   const float pp = s.fr_P[slot];
+  const int node = s.fr_node[slot], nn = s.n_nodes[b];
   int hidx = -1; float ps = INFINITY;
   if (s.h_tok) { hidx = s.fr_hidx[slot]; ps = s.fr_s[slot]; }
   const bool bad = (flags & 1u) != 0 || !(Z > 0.0) || !(R > -INFINITY) || !(R < INFINITY);
@@ -265,7 +267,7 @@ __device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParam
   const float H = bad ? 0.f : sp.M > 0 ? (float)((log(Zr) * (rr.ZM * sc) - rr.SM * sc) / Zr) : (float)(log(Zr) - Sr / Zr);
   if (lane_id() == 0) {
     rr.Zr = Zr; rr.H = H; rr.bad = bad ? 1u : 0u;
-    rr.parent_P = pp; rr.parent_s = ps; rr.parent_hidx = hidx;
+    rr.parent_P = pp; rr.parent_s = ps; rr.parent_hidx = hidx; rr.parent_node = node; rr.n_nodes = nn;
   }
 }
 
@@ -450,11 +452,8 @@ struct PruneShared {
 };
 
 // PER: candidates per thread; F * K <= PER * NT.
-// own: the sequence has one frontier node, whose candidates this workgroup has just scored: lane t of the first
-// wavefront holds candidate t, and nothing of them has to come back from memory.
 template <int NT, int PER>
-__device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps,
-                                               bool own, const Candidate& c) {
+__device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps) {
   constexpr int NW = NT / WAVE;
   const int F = sp.F, K = sp.K, N = sp.N, layer = sp.layer;
   const float z_beta = sp.z_beta;
@@ -477,14 +476,13 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   for (int k = 0; k < PER; ++k) {
     const int i = tid + k * NT;
     my_z[k] = my_P[k] = my_H[k] = 0.f; my_tok[k] = -1;
-    if (own) { if (k == 0 && tid < K) { my_z[0] = c.z; my_tok[0] = c.tok; my_P[0] = c.P; my_H[0] = c.H; } }
-    else if (i < FK) {
+    if (i < FK) {
       my_z[k] = ld_dev(s.c_z + cb + i); my_tok[k] = ld_dev(s.c_tok + cb + i);
       my_P[k] = ld_dev(s.c_P + cb + i); my_H[k] = ld_dev(s.c_H + cb + i);
     }
   }
-  uint32_t info = own && tid == 0 ? c.info : 0u;
-  if (!own && tid < F) info = ld_dev(s.row_info + fb + tid);
+  uint32_t info = 0u;
+  if (tid < F) info = ld_dev(s.row_info + fb + tid);
   const int nn = s.n_nodes[b];
   if (tid < nf) {                                            // the old frontier is read here, for good: the new one is stored over it below
     ps.old_node[tid] = s.fr_node[fb + tid];
@@ -697,13 +695,52 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   }
 }
 
+// The same for a sequence with one frontier node (root layers, chains), whose at most 64 candidates the first wavefront of
+// this workgroup has just scored, one a lane: ranked in that wavefront's registers, no barrier, nothing of them read back
+// from memory.  LONE_ROW_FIGURES
+template <int NT>
+__device__ __forceinline__ void prune_lone_row(const TreeState& s, const ScoreParams& sp, int b, const RowResult& rr, const Candidate& c) {
+  const int tid = threadIdx.x, F = sp.F, K = sp.K, FK = F * K, layer = sp.layer;
+  const int64_t cb = (int64_t)b * FK, fb = (int64_t)b * F;
+  for (int i = tid < WAVE ? tid + NT : tid; i < FK; i += NT) s.c_kept[cb + i] = 0;
+  if (tid >= WAVE) return;
+  const bool surv = tid < K && c.tok >= 0 && c.z > sp.z_beta;
+  const uint32_t zk = sortable_key(c.z), tk = (uint32_t)~c.tok;
+  const uint64_t survivors = __ballot(surv);
+  const int nn = rr.n_nodes, n_keep = max(0, min(min(F, sp.N - nn), __popcll(survivors)));
+  int rank = 0;                                              // survivors ahead in (z desc, token asc, candidate asc)
+  if (n_keep > 0) {
+    for (uint64_t m = survivors; m; m &= m - 1) {
+      const int j = __builtin_ctzll(m);
+      const uint32_t zj = (uint32_t)__builtin_amdgcn_readlane((int)zk, j), tj = (uint32_t)__builtin_amdgcn_readlane((int)tk, j);
+      rank += (zj > zk || (zj == zk && (tj > tk || (tj == tk && j < tid)))) ? 1 : 0;
+    }
+  }
+  const bool kept = surv && rank < n_keep;
+  if (kept) {
+    const int64_t tb = (int64_t)b * sp.N + nn;
+    s.t_tok[tb + rank] = c.tok; s.t_parent[tb + rank] = rr.parent_node; s.t_depth[tb + rank] = layer;
+    s.t_P[tb + rank] = c.P; s.t_H[tb + rank] = c.H; s.t_z[tb + rank] = c.z;
+    s.fr_tok[fb + rank] = c.tok; s.fr_pslot[fb + rank] = 0; s.fr_node[fb + rank] = nn + rank; s.fr_P[fb + rank] = c.P;
+    if (s.h_tok) { s.fr_hidx[fb + rank] = layer * FK + tid; s.fr_s[fb + rank] = fminf(rr.parent_s, c.z); }
+  }
+  if (tid < FK) s.c_kept[cb + tid] = kept ? 1 : 0;
+  if (tid == 0) {
+    if (s.h_tok) s.h_ncand[(int64_t)b * sp.D + layer] = K;
+    s.n_nodes[b] = nn + n_keep;
+    s.nf[(layer + 1) & 1][b] = n_keep;
+    s.n_cand[b] = K;
+    if (c.info) s.status[b] |= c.info;
+    if (n_keep) atomicAdd(&s.layer_rows[layer + 1], n_keep);
+  }
+}
+
 // Thread 0 takes a ticket once its wave's device-coherent stores are complete: true for the
 // workgroup that took the last of `expected` (it resets the counter for the next layer).  Every
 // store the ticket publishes is issued by wave 0 (at most 64 candidates or list entries, lanes
 // 0..63), whose own wait covers them; the other waves only meet at the barrier.
 __device__ __forceinline__ bool last_arrival(int32_t* ticket, int expected) {
   __shared__ int32_t sh_last;
-  if (expected == 1) { __syncthreads(); return true; }     // the only arrival (root layers, chains): nothing is handed over
   if (threadIdx.x < WAVE) {
     wait_vector_memory();
     if (threadIdx.x == 0) {
@@ -736,7 +773,7 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
   const int64_t slot = (int64_t)b * sp.F + f;
   if (last_wave) {
     record();
-    if (sp.nsplit == 1 && !top.entropy) row_entropy(s, sp, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
+    if (sp.nsplit == 1 && !top.entropy) row_entropy(s, sp, b, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
   }
   if (top.n_el >= 0) rank_list<NT>(K, sel, top.n_el, rr.topv, rr.topi);
   __syncthreads();                                           // rr is complete
@@ -760,13 +797,13 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
         RowPartial r; r.ref = m.R; r.a = m.R; r.Z = m.Z; r.S = m.S; r.flags = m.flags; r.n_top = min(m.n_valid, K);
         rr.part = r;
       }
-      if (sp.M <= 0) row_entropy(s, sp, slot, m.R, m.R, m.Z, m.S, m.flags, rr);
+      if (sp.M <= 0) row_entropy(s, sp, b, slot, m.R, m.R, m.Z, m.S, m.flags, rr);
     }
     if (staged) rank_list<NT>(K, sel, per_row, rr.topv, rr.topi);
     __syncthreads();
     if (sp.M > 0) {
       after_merge(rr);
-      if (last_wave) row_entropy(s, sp, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
+      if (last_wave) row_entropy(s, sp, b, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
       __syncthreads();
     }
     n = rr.part.n_top;
@@ -774,12 +811,19 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
   }
   const Candidate c = score_row<NT>(s, sp, b, f, rr, n, cls, cls_lds, lds);
   C2T_PT(PT_PUBLISHED);
+  if (nf == 1) {                                             // (uniform) the only row: nothing is handed over
+    C2T_PT(PT_TICKET);
+    prune_lone_row<NT>(s, sp, b, rr, c);
+    C2T_PT(PT_PRUNED);
+    C2T_PT_FLUSH();
+    return;
+  }
   if (!last_arrival(s.tickets + b, nf)) { C2T_PT_FLUSH(); return; }   // nf: the sequence's frontier size, known since the workgroup started
   C2T_PT(PT_TICKET);
   // one candidate a thread wherever that is enough: an eighth of the instructions of the general form
   __shared__ PruneShared<NT> ps;
-  if (sp.F * K <= NT) prune_sequence<NT, 1>(s, sp, b, nf, lds, ps, nf == 1, c);
-  else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(s, sp, b, nf, lds, ps, nf == 1, c);
+  if (sp.F * K <= NT) prune_sequence<NT, 1>(s, sp, b, nf, lds, ps);
+  else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(s, sp, b, nf, lds, ps);
   C2T_PT(PT_PRUNED);
   C2T_PT_FLUSH();
 }
