@@ -39,6 +39,7 @@ constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
 constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
 constexpr int NT_F32 = 512;                    // workgroup size of the fp32 kernel: two of them fill a CU at its 128 registers a lane
+constexpr int MLP_SPREAD_MIN = 48;             // hidden units from which on a workgroup alone on its CU evaluates the classifier with all its wavefronts
 constexpr int PARTIAL_SLOTS_MIN = 16384;       // (row, split) records the workspace always has room for
 // Row splits.  A split adds an epilogue, a device-scope ticket and a merge (a few microseconds of
 // dependent round trips), which costs more than it saves on the histogram path even for a single
@@ -249,6 +250,10 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   sp.compact = (rows_per_seq > 1 && (int64_t)grid > (int64_t)x->n_cus && (int64_t)grid <= 4 * (int64_t)x->n_cus &&
                 c.batch <= COMPACT_MAX_B) ? 1 : 0;
   sp.k_inverse = (uint32_t)(((1u << 20) + c.top_k - 1) / c.top_k);
+  // The classifier by the whole workgroup where it has its CU to itself: shorter for the row (64 units: 20.1 us a root layer
+  // against 20.6, 256 units 26.0 against 27.0), but more instructions in all, which neighbours on the CU pay for: 8192 rows
+  // of 32000 with 256 units 200 us against 195, of 152064 with 64 units 524 against 521.
+  sp.spread_min = (int64_t)grid > (int64_t)x->n_cus ? C2T_MAX_HIDDEN + 1 : MLP_SPREAD_MIN;
   sp.h = c.hidden; sp.layer = x->layer; sp.z_beta = x->z_beta; sp.M = c.entropy_top_m; sp.D = c.max_depth;
   if (c.logits_dtype == C2T_BF16) {
     const int64_t cus = x->n_cus;

@@ -162,6 +162,7 @@ struct ScoreParams {
   int w_lds_off;                                             // byte offset of the classifier's copy in dynamic LDS, -1: none
   int compact;                                               // 1: workgroup w takes the w-th live row (see row_of_workgroup)
   uint32_t k_inverse;                                        // ceil(2^20 / K): (i * k_inverse) >> 20 is i / K for i < 2048, K <= 64
+  int spread_min;                                            // hidden units from which on the whole workgroup evaluates the classifier
   float z_beta;
   // Shared rows of the histogram path (coop > 1, then nsplit == 1): `coop` workgroups count one row's
   // segments and hand their counts over through memory; the last to arrive runs the row's epilogue.
@@ -278,16 +279,12 @@ struct Candidate { float z, P, H; int32_t tok; uint32_t info; };   // as lane t 
 // chain once for all of them).
 // `w`: the classifier parameters in global memory, read-only for the whole kernel: every lane
 // reads the same addresses, so the loads are scalar and touch neither LDS nor the vector memory path.
-#ifndef C2T_MLP_SPREAD_MIN
-#define C2T_MLP_SPREAD_MIN 48
-#endif
-constexpr int MLP_SPREAD_MIN = C2T_MLP_SPREAD_MIN;   // hidden units from which on the whole workgroup evaluates the classifier
 template <int NT>
 __device__ __forceinline__ Candidate score_row(const TreeState& s, const ScoreParams& sp, int b, int f, RowResult& rr, int n,
                                           const float* __restrict__ w, const float* w_lds, unsigned char* lds) {
   const int tid = threadIdx.x, K = sp.K, FK = sp.F * K;
   const float H = rr.H;
-  const bool spread = w_lds && sp.h >= MLP_SPREAD_MIN;       // (uniform)
+  const bool spread = w_lds && sp.h >= sp.spread_min;        // (uniform)
   float z = -INFINITY, p32 = 0.f, P32 = 0.f; int tok = -1;
   const bool mine = !rr.bad && tid < n;                      // n <= K
   if (mine) {
