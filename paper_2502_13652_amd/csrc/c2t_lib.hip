@@ -39,6 +39,7 @@ constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
 constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
 constexpr int NT_F32 = 512;                    // workgroup size of the fp32 kernel: two of them fill a CU at its 128 registers a lane
+static_assert(HP_NT == NT_F32, "one size of the sequence step's LDS");
 constexpr int MLP_SPREAD_MIN = 48;             // hidden units from which on a workgroup alone on its CU evaluates the classifier with all its wavefronts
 constexpr int PARTIAL_SLOTS_MIN = 16384;       // (row, split) records the workspace always has room for
 // Row splits.  A split adds an epilogue, a device-scope ticket and a merge (a few microseconds of
@@ -237,7 +238,7 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   const size_t map_lds = ((size_t)cells * keybytes_of(c) + 15) / 16 * 16;
   // element list of the selection: (2K-1) cells of cpc chunks, 8 bytes per element
   const size_t list_lds = (size_t)(2 * c.top_k - 1) * cpc * epc_of(c) * 8;
-  const size_t score_lds = score_lds_bytes(c.hidden, c.max_frontier * c.top_k);
+  const size_t score_lds = score_lds_bytes<HP_NT>(c.max_frontier * c.top_k);
   const unsigned grid = (unsigned)((int64_t)c.batch * rows_per_seq * per_row);
   ScoreParams sp;
   sp.part = x->part; sp.part_topv = x->part_topv; sp.part_topi = x->part_topi;

@@ -415,10 +415,7 @@ constexpr int PRUNE_DIRECT_MAX = C2T_PRUNE_DIRECT_MAX;         // up to so many 
 constexpr int PRUNE_RANK_MAX = C2T_PRUNE_RANK_MAX;             // lists that are longer with it are cut by the radix select
 constexpr int PRUNE_UNDECIDED_MAX = C2T_PRUNE_UNDECIDED_MAX; // the select stops once at most so many survivors share the selected digits
 
-__host__ __device__ inline size_t score_lds_bytes(int h, int FK) {
-  (void)h;
-  return ((size_t)3 * ((FK + 31) & ~31) + PRUNE_HIST_WORDS) * 4;
-}
+__host__ __device__ inline size_t prune_list_bytes(int FK) { return ((size_t)3 * ((FK + 31) & ~31) + PRUNE_HIST_WORDS) * 4; }
 
 // A threshold that at least n of the NV * 64 maxima reach (0 if fewer than n are not 0), as high as it takes for at most
 // `enough` of them to reach it, or their n-th largest.  Two bits a step from the top, ballots, uniform result.
@@ -447,6 +444,11 @@ struct PruneShared {
   float old_s[SP_MAX_F];
   uint32_t kept[C2T_MAX_CANDIDATES_DEV / 32];              // bit i: candidate i is appended to the tree
 };
+
+// Dynamic LDS of prune_sequence: its lists, then PruneShared (2 KB of static LDS would cost launches with K = 64, whose element
+// list takes 32 KB, the fourth workgroup of a CU: 1024 rows of 32000 44 us instead of 33).
+template <int NT>
+__host__ __device__ inline size_t score_lds_bytes(int FK) { return prune_list_bytes(FK) + sizeof(PruneShared<NT>); }
 
 // PER: candidates per thread; F * K <= PER * NT.
 template <int NT, int PER>
@@ -825,7 +827,7 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
   if (!last_arrival(s.tickets + b, nf)) { C2T_PT_FLUSH(); return; }   // nf: the sequence's frontier size, known since the workgroup started
   C2T_PT(PT_TICKET);
   // one candidate a thread wherever that is enough: an eighth of the instructions of the general form
-  __shared__ PruneShared<NT> ps;
+  PruneShared<NT>& ps = *(PruneShared<NT>*)(lds + prune_list_bytes(sp.F * K));
   if (sp.F * K <= NT) prune_sequence<NT, 1>(s, sp, b, nf, lds, ps);
   else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(s, sp, b, nf, lds, ps);
   C2T_PT(PT_PRUNED);
