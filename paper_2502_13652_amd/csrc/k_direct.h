@@ -16,7 +16,7 @@
 // interpolated at Chebyshev nodes (1.4e-16 relative with rounded coefficients).  t <= 0 here, and the error of
 // the one-constant reduction, |k| 7e-19, matters only as |t| e^t.
 //
-// Top K without reading anything twice: the K-th largest of 64 maxima (of the 64 lane columns of the workgroup) is
+// Top K without reading anything twice: the K-th largest of the maxima of 64 lane columns (128 for large K) is
 // a lower bound of the K-th largest logit from the first tile on; the few logits that reach it are appended
 // to a list in LDS as they stream past, and the list is ranked exactly at the end.  The bound is raised from
 // the maxima so far at tiles 2, 4, 8, ...: stale maxima only make it lower, so no barrier is needed there.
@@ -66,16 +66,29 @@ struct DirectShared {
   int32_t n_list, bad;
 };
 
-// K-th largest of the 64 column maxima, to its upper 16 bits (a lower bound of the K-th largest logit seen)
+// K-th largest of the maxima of NV * 64 columns (a column: every 64 NV-th lane of the workgroup), to the bits above LOW_BIT: a lower
+// bound of the K-th largest logit seen
+template <int NT, int NV, int LOW_BIT>
+__device__ __forceinline__ float bound_of_columns(const DirectShared<NT>& sh, int K) {
+  float m[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) m[v] = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < NT / WAVE; ++w)
+    m[w % NV] = fmaxf(m[w % NV], __hip_atomic_load(&sh.col_max[w][threadIdx.x & (WAVE - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+  uint32_t key[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) key[v] = sortable_key(m[v]);
+  const uint32_t t = wave_kth_largest<NV, LOW_BIT>(key, K);
+  return t < 0x007FFFFFu ? -INFINITY : key_to_float(t);      // (below -inf's key once the low bits are cleared)
+}
+// Of randomly placed logits 64 (H(64) - H(64 - K)) reach the bound from 64 columns: 45 for K = 32, but 89 for K = 48 and 304 for
+// K = 64, which have to be listed, cut and ranked; from 128 columns 60 and 89, for twice the ballots.  Layers of 256 rows
+// of 32000, with 64 / 128 columns: K = 48 28.4 / 26.7 us, K = 64 88 / 30 us.
+constexpr int COLUMNS64_MAX_K = 32;
 template <int NT>
 __device__ __forceinline__ float column_bound(const DirectShared<NT>& sh, int K) {
-  const int lane = threadIdx.x & (WAVE - 1);
-  float m = -INFINITY;
-#pragma unroll
-  for (int w = 0; w < NT / WAVE; ++w) m = fmaxf(m, __hip_atomic_load(&sh.col_max[w][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-  const uint32_t key[1] = {sortable_key(m)};
-  const uint32_t t = wave_kth_largest<1, 16>(key, K);
-  return t < 0x007FFFFFu ? -INFINITY : key_to_float(t);      // (below -inf's key once the low bits are cleared)
+  return K <= COLUMNS64_MAX_K ? bound_of_columns<NT, 1, 16>(sh, K) : bound_of_columns<NT, 2, 16>(sh, K);
 }
 
 template <int DT, int NT>

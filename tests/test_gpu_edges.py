@@ -150,3 +150,31 @@ def test_reranking_at_its_edges(D, F, K, n_outs):
         torch.cuda.synchronize()
         for n_out in n_outs:
             _compare_reranked(g, o, [0, 1, 2], n_out, "rerank D=%d F=%d K=%d seed %d" % (D, F, K, seed))
+
+
+def _row_layer_us(x, K, splits=0, n=9):
+    """Median duration (the kernel's own begin and end) of a layer whose rows are the sequences' root rows: x [rows][V] fp32."""
+    from paper_2502_13652_amd import C2TContext
+    rows, V = x.shape
+    ctx = C2TContext(rows, V, 1, K, 1, 1, 2, 0, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    ctx.set_row_splits(splits, splits)
+    for timed in (0, n):
+        if timed:
+            ctx.profile_enable(timed)
+        for _ in range(max(timed, 3)):
+            ctx.reset()
+            ctx.expand_layer(x.view(rows, 1, V))
+        torch.cuda.synchronize()
+    return float(np.median(ctx.profile_read(n))) * 1e3
+
+
+# What a layer of fp32 rows takes depends little on K (320 rows of 32000: 24 us with K = 10, 35 us with K = 64): the logits that
+# reach the bound on the top K, which are ranked, stay few.  With a bound from 64 columns 300 of them did at K = 64: 88 us.
+def test_fp32_layer_time_at_large_k():
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = 3 * torch.randn((320, 32000), generator=g, device="cuda")
+    small, large = _row_layer_us(x, 10), _row_layer_us(x, 64)
+    print("K=10 %.1f us, K=64 %.1f us" % (small, large), flush=True)
+    assert large < 2 * small
