@@ -17,11 +17,11 @@
 // the one-constant reduction, |k| 7e-19, matters only as |t| e^t.
 //
 // Top K without reading anything twice: the K-th largest of the maxima of 64 lane columns (128 for large K) is
-// a lower bound of the K-th largest logit from the first tile on; the few logits that reach it are appended
+// a lower bound of the K-th largest logit from the first tile on; the few finite logits that reach it are appended
 // to a list in LDS as they stream past, and the list is ranked exactly at the end.  The bound is raised from
 // the maxima so far at tiles 2, 4, 8, ...: stale maxima only make it lower, so no barrier is needed there.
-// Rows that overflow the list (thousands of logits above the bound: massive ties, sorted rows) take
-// generic_segment.
+// Lists that end up long (massive ties, large K), that overflowed (sorted rows, logits that only follow behind a masked
+// stretch) or that are short of K (nearly everything masked) are put right by settle_list.
 #pragma once
 #include "k_logits.h"
 
@@ -63,7 +63,8 @@ struct DirectShared {
   double wave_z[NW], wave_s[NW];
   float wave_a[NW];
   float col_max[NW][WAVE];                      // running maximum of every lane
-  int32_t n_list, bad;
+  int32_t scan_tmp[1][NW];
+  int32_t n_list, bad, n_reach;
 };
 
 // K-th largest of the maxima of NV * 64 columns (a column: every 64 NV-th lane of the workgroup), to the bits above LOW_BIT: a lower
@@ -97,6 +98,14 @@ struct DirectState {                            // of one wavefront
   double Z, S;
   bool bad;
 };
+
+// A segment's chunks (uniform): the bounds check returns zeros past the last one without reading
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t segment_buffer(const uint4* rowp, const Segment& sg) {
+  const uint64_t base = (uint64_t)(rowp + sg.c0);
+  const uint64_t base_u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
+                          ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, sg.ncell * 16, 0x00020000);
+}
 
 // Logits of a tile that the segment does not have read as -inf: chunks past its end, the padding of the row's last chunk.
 template <int DT, int NT>
@@ -181,23 +190,120 @@ __device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int
   }
 }
 
-// One segment, by a whole workgroup.  map_lds: the cell map of generic_segment, which rows that overflow the list
-// fall back to; the list overlays it.  The per-wave sums stay in `sh` (see combine_waves).
+// The rarer lists (the usual one holds K to 128 logits and needs none of this), by the whole workgroup.
+//  * A long list still holds what reached the first, lowest bounds: it is cut with the final one.
+//  * Where it stays long (massive ties), and where it has overflowed: T, the exact K-th largest of the 512 lanes' maxima, is at
+//    most the K-th largest logit, so if fewer than K logits exceed T, the others of the K largest equal it.  The list is cut
+//    to what exceeds T (made again from a second read of the segment if it has overflowed), and
+//  * what is missing to K entries are ties at T, or masked logits (-inf) where the list holds all finite ones: tie_scan finds those of
+//    the lowest ids.
+// Ranking all that reached the bound, with one LDS read after the other for every tied pair, took a row of 4000 equal logits
+// 3.4 ms (18 us now) and 320 rows of 32000 whose 3000 largest are equal 2.3 ms (41 us); going over an overflowed segment twice
+// more with generic_segment took 260 ascending rows of 128256 203 us (now 101).
+// More than LIST_RANK_MAX logits above T lie in fewer than K lanes (of 512), which only rows with a period of 2048 logits have:
+// they are generic_segment's (UNSETTLED).
+// Returns the list's length.  Out of line: inlined, its code stood between the loop and the tail of every row (0.7 us a layer).
+constexpr int LIST_RANK_MAX = 512, UNSETTLED = RANKED_IN_RR;
+template <int NT> using DirectSharedLds = __attribute__((address_space(3))) DirectShared<NT>*;
+typedef __attribute__((address_space(3))) unsigned char* LdsBytes;
+template <int DT, int NT>
+__device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsBytes lds, int list_cap, int cell_cap,
+                                        DirectSharedLds<NT> shl) {
+  typedef LogitTraits<DT> T;
+  const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
+  const int K = uniform(top_k);
+  const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  DirectShared<NT>& sh = *(DirectShared<NT>*)shl;
+  SelectLds sel;
+  sel.list = (unsigned char*)lds; sel.list_cap = uniform(list_cap); sel.cell_cap = uniform(cell_cap);
+  float* el_v = sel.values();
+  int32_t* el_i = sel.ids();
+  int n = uniform(sh.n_list);
+  float tie = -INFINITY;                                     // value of what may be missing
+  if (n > 2 * WAVE) {
+    constexpr int KEEP = 8;                                  // entries (chunks) a thread holds at once
+    if (n <= sel.list_cap) {
+      float bound = column_bound<NT>(sh, K);
+      int reach = 0;
+      for (int e = tid; e < n; e += NT) reach += el_v[e] >= bound;
+      reach = wave_sum_i(reach);
+      if (lane == 0 && reach) atomicAdd(&sh.n_reach, reach);
+      __syncthreads();
+      const bool strict = sh.n_reach > 2 * WAVE;
+      if (strict) tie = bound = bound_of_columns<NT, NT / WAVE, 0>(sh, K);
+      int kept = 0;
+      for (int o = 0; o < n; o += KEEP * NT) {               // entries only move down: below everything not yet read
+        float v[KEEP]; int32_t id[KEEP];
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) {
+          const int e = o + k * NT + tid;
+          v[k] = e < n ? el_v[e] : -INFINITY; id[k] = e < n ? el_i[e] : -1;
+        }
+        if (tid == 0) sh.n_list = kept;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) {
+          if (id[k] >= 0 && (strict ? v[k] > bound : v[k] >= bound)) {
+            const int slot = atomicAdd(&sh.n_list, 1);
+            el_v[slot] = v[k]; el_i[slot] = id[k];
+          }
+        }
+        __syncthreads();
+        kept = sh.n_list;
+        __syncthreads();
+      }
+      n = kept;
+    } else {
+      const float bound = bound_of_columns<NT, NT / WAVE, 0>(sh, K);
+      tie = bound;
+      const __amdgpu_buffer_rsrc_t rs = segment_buffer(rowp, sg);
+      __syncthreads();                                       // everybody has read the length
+      if (tid == 0) sh.n_list = 0;
+      __syncthreads();
+      for (int g0 = 0; g0 < sg.ncell; g0 += KEEP * NT) {
+        uint4 q[KEEP];
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) q[k] = load_stream_buffer(rs, (uint32_t)tid * 16u, (uint32_t)(g0 + k * NT) * 16u);
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k) {
+          const int g = g0 + k * NT + tid;
+          float x[T::EPC];
+          T::unpack(q[k], x);
+#pragma unroll
+          for (int j = 0; j < T::EPC; ++j) {
+            const int id = (sg.c0 + g) * T::EPC + j;
+            if (x[j] > bound && g < sg.ncell && id < V) {
+              const int slot = atomicAdd(&sh.n_list, 1);
+              if (slot < sel.list_cap) { el_v[slot] = x[j]; el_i[slot] = id; }
+            }
+          }
+        }
+      }
+      __syncthreads();
+      n = sh.n_list;
+    }
+    if (n > LIST_RANK_MAX) return UNSETTLED;
+  }
+  const int n_elems = sg.tail_chunk >= 0 ? (sg.ncell - 1) * T::EPC + sg.tail_valid : sg.ncell * T::EPC, need = min(K, n_elems) - n;
+  if (need > 0 && !sh.bad) {
+    tie_scan<DT, NT>(rowp, sg, V, tie, need, sel, &sh.n_list, sh.scan_tmp);
+    n += need;
+  }
+  return n;
+}
+
+// One segment, by a whole workgroup.  The per-wave sums stay in `sh` (see combine_waves).
 template <int DT, int NT>
 __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ rowp, int V, int K, const Segment& sg,
-                                                     unsigned char* map_lds, const SelectLds& sel, const ClassifierStage cst,
-                                                     DirectShared<NT>& sh, RowResult* rr) {
+                                                     const SelectLds& sel, const ClassifierStage cst, DirectShared<NT>& sh, RowResult* rr) {
   constexpr int TILE = DIRECT_CHUNKS * NT;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
   if (tid < EXP_TAB) sh.exp_tab[tid] = exp_tab_entry(tid);
-  if (tid == 0) { sh.n_list = 0; sh.bad = 0; }
+  if (tid == 0) { sh.n_list = 0; sh.bad = 0; sh.n_reach = 0; }
   __syncthreads();
   const int n_tiles = (sg.ncell + TILE - 1) / TILE, n_whole = sg.tail_chunk >= 0 ? sg.ncell - 1 : sg.ncell;
-  const uint64_t base = (uint64_t)(rowp + sg.c0);
-  const uint64_t base_u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
-                          ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32);
-  // the bounds check returns zeros past the segment's last chunk without reading
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, sg.ncell * 16, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs = segment_buffer(rowp, sg);
   const uint32_t vo = (uint32_t)tid * 16u;
   uint4 qa[DIRECT_CHUNKS], qb[DIRECT_CHUNKS];
   auto load = [&](uint4 (&q)[DIRECT_CHUNKS], int t) {
@@ -205,7 +311,8 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
     for (int c = 0; c < DIRECT_CHUNKS; ++c) q[c] = load_stream_buffer(rs, vo, (uint32_t)(t * DIRECT_CHUNKS + c) * (NT * 16u));
   };
   DirectState<DT, NT> s;
-  s.a = s.lane_max = s.tau = -INFINITY; s.Z = s.S = 0.0; s.bad = false;
+  s.a = s.lane_max = -INFINITY; s.Z = s.S = 0.0; s.bad = false;
+  s.tau = -3.402823466e38f;                                  // the lowest finite value: masked logits (-inf) are not listed
   load(qa, 0);
   if (n_tiles > 1) load(qb, 1);
   for (int t = 0; t < n_tiles; t += 2) {
@@ -224,41 +331,10 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   if (s.bad) sh.bad = 1;
   __syncthreads();
   C2T_PT(PT_HIST_COMPLETE);
-  const int n_el = sh.n_list;
-  if (n_el > sel.list_cap) {
-    generic_segment<DT, NT, DIRECT_CPC>(rowp, V, K, 0, sg, map_lds, sel, rr, 0u);
-    return SegmentTop{RANKED_IN_RR, false};
-  }
-  if (n_el > 2 * WAVE) {
-    // Long segments: the list still holds what reached the first, lowest bounds.  Cut it with the final one.
-    constexpr int KEEP = 8;                                  // entries a thread holds at once
-    float* el_v = sel.values();
-    int32_t* el_i = sel.ids();
-    const float tau = column_bound<NT>(sh, K);
-    int kept = 0;
-    __syncthreads();                                         // everybody has read the length
-    for (int o = 0; o < n_el; o += KEEP * NT) {              // entries only move down: below everything not yet read
-      float v[KEEP]; int32_t id[KEEP];
-#pragma unroll
-      for (int k = 0; k < KEEP; ++k) {
-        const int e = o + k * NT + tid;
-        v[k] = e < n_el ? el_v[e] : -INFINITY; id[k] = e < n_el ? el_i[e] : -1;
-      }
-      if (tid == 0) sh.n_list = kept;
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < KEEP; ++k) {
-        if (id[k] >= 0 && v[k] >= tau) {
-          const int slot = atomicAdd(&sh.n_list, 1);
-          el_v[slot] = v[k]; el_i[slot] = id[k];
-        }
-      }
-      __syncthreads();
-      kept = sh.n_list;
-      __syncthreads();
-    }
-  }
-  return SegmentTop{min(sh.n_list, sel.list_cap), false};
+  int n_el = sh.n_list;
+  if (n_el > 2 * WAVE || n_el < K) n_el = settle_list<DT, NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, sel.cell_cap, (DirectSharedLds<NT>)&sh);
+  if (n_el == UNSETTLED) generic_segment<DT, NT, DIRECT_CPC>(rowp, V, K, 0, sg, sel.list, sel, rr, 0u);   // (its cell map overlays the list)
+  return SegmentTop{n_el, false};
 }
 // The segment's record from the wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.
 template <int NT>
@@ -314,7 +390,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
     if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
     __syncthreads();
   } else {
-    top = direct_segment<DT, NT>(rowp, V, K, sg, dyn_lds, sel, cst, sh, &rr);
+    top = direct_segment<DT, NT>(rowp, V, K, sg, sel, cst, sh, &rr);
     have_record = top.n_el < 0;
   }
   const auto top_m = [&](RowResult& r) { top_m_of_split_row<DT, NT>(rowp, V, sp.M, r); };

@@ -9,7 +9,7 @@
 // Why the sums are exact.  Which children survive the two prunings is decided by comparing
 // classifier logits that are often only an ulp apart (siblings with tiny joint probability
 // share H and d), so the features must round to the same fp32 values as an fp64 evaluation
-// of the definition: fp32 exponentials are not enough.  Two paths deliver fp64-grade sums:
+// of the definition: fp32 exponentials are not enough.  These paths deliver fp64-grade sums:
 //  * bf16 rows (the fast path): a bf16 logit has at most 65536 values, and all logits of
 //    practical rows lie in 32 binades, |x| in [2^-25, 2^7).  The streaming loop only COUNTS
 //    values: one LDS atomic per element into an 8192-bin histogram (sign, 5 exponent bits,
@@ -21,9 +21,9 @@
 //    x <= -2^10 (the masked tokens of constrained decoding): they add exactly nothing to either
 //    sum and rank after every window value.
 //  * bf16 rows holding a logit >= 2^7 or in (-2^10, -2^7], +inf or a NaN, a value held by more than
-//    65535 logits, or below-window or masked logits that could rank among the K largest; fp32 rows with thousands of
-//    logits above a lower bound of the K-th largest: two passes over the segment with fp64 exponentials per element
-//    (generic_segment).  Other fp32 rows: one pass with an fp64 exponential per element (k_direct.h).
+//    65535 logits, or below-window or masked logits that could rank among the K largest: two passes over the segment with
+//    fp64 exponentials per element (generic_segment).
+//  * fp32 rows: one pass with an fp64 exponential per element (k_direct.h).
 //
 // Top-K without data-dependent work in the streaming loop: the loop records the maximum of each
 // cell as a "cell key" in an LDS map.  A cell is the four chunks a lane reads

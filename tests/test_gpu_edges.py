@@ -18,8 +18,7 @@ def test_fp32_rows_at_tile_edges(V, K):
     rows_against_oracle("f32", V, K, 1)
 
 
-# Long fp32 rows of a launch with more rows than CUs: one workgroup each, whose fallback (ties, sorted rows) maps 4 chunks a
-# cell; up to 196608 logits, and split above.  The rows are dealt out ten times and more: equal rows give equal results.
+# Long fp32 rows of a launch with more rows than CUs: one workgroup each up to 196608 logits, and split above.  The rows are dealt out ten times and more: equal rows give equal results.
 @pytest.mark.parametrize("V,K,per_row", [(49163, 64, 1), (131075, 16, 1), (196608, 8, 1), (196612, 8, 2)])
 def test_long_fp32_rows_unsplit(V, K, per_row):
     from oracle import ref_row
@@ -168,6 +167,83 @@ def _row_layer_us(x, K, splits=0, n=9):
             ctx.expand_layer(x.view(rows, 1, V))
         torch.cuda.synchronize()
     return float(np.median(ctx.profile_read(n))) * 1e3
+
+
+def _rows_equal_oracle(names, rows, K, splits):
+    from oracle import ref_row
+    from paper_2502_13652_amd import C2TContext
+    B, V = rows.shape
+    ctx = C2TContext(B, V, 1, K, 1, 1, 2, 0, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    ctx.set_row_splits(splits, splits)
+    x = torch.full((B, 1, (V + 3) // 4 * 4 + 4), float("inf"))
+    x[:, 0, :V] = torch.from_numpy(rows)
+    ctx.reset()
+    ctx.expand_layer(x.cuda())
+    c = to_np(ctx.candidates())
+    for b, name in enumerate(names):
+        r = ref_row(rows[b], K)
+        k = len(r["ids"])
+        np.testing.assert_array_equal(c["token"][b, :k], r["ids"], err_msg=name)
+        assert close(c["p"][b, :k], r["p"].astype(np.float32), atol=1e-37).all(), name
+        assert close(c["H"][b, 0], np.float32(r["H"]), atol=V * 2.0 ** -53).all(), name       # (as in test_gpu_rows.py)
+
+
+# fp32 lists that do not come out with K to 128 entries: ties at and above the K-th value, from one more than the list is ranked with
+# to one more than it holds; fewer finite logits than K; logits that follow a masked tile, which overflow it; maxima in fewer
+# lanes than K (a period of 2048 logits), up to the general path.  V: one tile, several, rows split by the caller
+@pytest.mark.parametrize("V,splits", [(4000, 1), (16387, 1), (49152, 1), (131075, 3)])
+@pytest.mark.parametrize("K", [1, 10, 64])
+def test_fp32_lists_that_are_long_or_short(V, splits, K):
+    rng = np.random.default_rng(V + K)
+    names, rows = [], []
+
+    def add(name, r):
+        names.append(name); rows.append(r.astype(np.float32))
+
+    def noise():
+        return 2 * rng.standard_normal(V)
+
+    for n in (127, 128, 129, 511, 513, 1000, 4095, 4096, 4097):
+        for value in (17.3, 16.0):                           # (a value whose low bits the bound keeps or drops)
+            if n < V:
+                r = noise(); r[rng.choice(V, n, replace=False)] = value; add("%d tied at %g" % (n, value), r)
+                r = r.copy(); r[rng.choice(V, 5, replace=False)] = 17.5; add("the same below five", r)
+    for mask in (-np.inf, -1e9, -3.4028234663852886e38):
+        for n in (1, 3, 9, 10, 63, 64, 200):
+            r = np.full(V, mask); r[rng.choice(V, n, replace=False)] = rng.standard_normal(n); add("%d not masked by %g" % (n, mask), r)
+        for head in (1, 2047, 8192, 16384, 24576):
+            if head < V:
+                r = noise(); r[:head] = mask; add("%d masked by %g ahead" % (head, mask), r)
+    add("ascending", np.sort(noise()))
+    add("ascending integers", np.floor(np.sort(8 * rng.standard_normal(V))))
+    for lanes in (1, 9, 30, 63):
+        r = noise(); r[(np.arange(V) // 4) % 512 < lanes] += 30.0; add("maxima in %d lanes" % lanes, r)
+    print("V=%d splits=%d K=%d: %d rows" % (V, splits, K, len(rows)), flush=True)
+    _rows_equal_oracle(names, np.stack(rows), K, splits)
+
+
+# Such rows take little longer than others: 320 rows of 32000 take 24 us, 23 to 51 us if they are tied, masked or sorted.  The bound is
+# what the second read of an overflowed segment and the search for ties can cost: before there were rows of 2300 us (3000 tied) and
+# of 70 (three finite logits); ten rows of 4000 took 3400 us where 11 are usual (18 now).
+@pytest.mark.parametrize("rows,V", [(10, 4000), (320, 32000)])
+def test_fp32_layer_time_of_tied_and_masked_rows(rows, V):
+    g = torch.Generator(device="cuda").manual_seed(1)
+    base = 3 * torch.randn((rows, V), generator=g, device="cuda")
+    usual = _row_layer_us(base, 10)
+    few = torch.full((rows, V), -float("inf"), device="cuda")
+    few[:, [0, V // 2, V - 1]] = torch.tensor([1.0, 2.0, 2.0], device="cuda")
+    tied = base.clone()
+    tied[:, torch.randperm(V, generator=g, device="cuda")[:3000]] = 17.3
+    ahead = base.clone()
+    ahead[:, :V // 2] = -float("inf")
+    took = {}
+    for name, x, most in (("three finite", few, 1.6), ("three above -1e9", few.clamp_min(-1e9), 2.5), ("3000 tied", tied, 2.5),
+                          ("all equal", torch.ones_like(base), 2.5), ("half masked ahead", ahead, 2.0), ("ascending", base.sort(1).values, 2.2)):
+        took[name] = (_row_layer_us(x, 10) / usual, most)
+    print("usual %.1f us," % usual, ", ".join("%s %.2f" % (k, v[0]) for k, v in took.items()), flush=True)
+    assert all(t < most for t, most in took.values())
 
 
 # What a layer of fp32 rows takes depends little on K (320 rows of 32000: 24 us with K = 10, 35 us with K = 64): the logits that
