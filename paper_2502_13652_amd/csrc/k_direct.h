@@ -400,7 +400,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
     have_record = true;
     top_m(rr);
   }
-  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst,     // split records are indexed by launched row
+  finish_layer<NT, true>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst,     // split records are indexed by launched row
                    [&] { if (!have_record) combine_waves(sh, rr); }, top_m);
 }
 

@@ -480,7 +480,7 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
   if (ties) tie_scan<DT, NT>(rowp, sg, V, tau, K, sel, &sh_cnt, scan_tmp);
   C2T_PT(PT_CELLS_READ);
   const int n_el = min(sh_cnt, sel.list_cap), n_top = min(n_el, K);
-  rank_list<NT>(K, sel, n_el, rr->topv, rr->topi);
+  rank_list<NT, false>(K, sel, n_el, rr->topv, rr->topi);
   if (tid == 0) {
     RowPartial r;
     r.ref = (double)m; r.a = (double)m; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = seg_bad ? 0 : n_top; r.flags = (seg_bad ? 1u : 0u) | info_flags;
@@ -1459,7 +1459,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
                                                   sel, &rr, cst, cls, st, sp, split, rl, b, row);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
-  finish_layer<NT>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst, [] {},
+  finish_layer<NT, false>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst, [] {},
                    [&](RowResult& r) { if (TOPM) top_m_of_split_row<1, NT>(rowp, V, sp.M, r); });
 }
 

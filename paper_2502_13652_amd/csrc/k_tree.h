@@ -187,6 +187,15 @@ struct RowResult {
   int32_t topi[64];
 };
 
+// sum over groups of 2^tshift neighbouring lanes (tshift <= 4, uniform), in each of them
+__device__ __forceinline__ int sum_of_lanes(int tshift, int v) {
+  if (tshift >= 1) v += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)v);
+  if (tshift >= 2) v += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)v);
+  if (tshift >= 3) v += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)v);
+  if (tshift >= 4) v += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)v);
+  return v;
+}
+
 // LDS of the selection of a segment's (or a row's) K largest logits: the element list ((value, id), 8 bytes an
 // entry, overlaying histogram and cell map) and the number of cells a launch may keep:
 // min(SEL_CELL_CAP, NT / CPC, list entries / elements per cell), which the host keeps >= 2K - 1.
@@ -208,15 +217,15 @@ __device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int by
 
 // ---- ranking of the element list by (logit desc, id asc), exactly; the best K go to topv, topi.
 // Short lists (the usual case: K to 2K-1 elements): T lanes per element, each compares it with every T-th entry, one
-// value per step; the partial ranks are summed over the T lanes.  Only the first RANK_NT threads take part, so that
-// another wavefront can form the row's entropy meanwhile.
-constexpr int RANK_SHORT = 64, RANK_NT = 256;
-__device__ __forceinline__ void rank_short(int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
+// value per step; the partial ranks are summed over the T lanes.  nt threads take part: all of them, or the first RANK_NT where
+// another wavefront forms the row's entropy meanwhile.
+constexpr int RANK_NT = 256;
+__device__ __forceinline__ void rank_short(int K, const SelectLds& sel, int n_el, int nt, float* topv, int32_t* topi) {
   const int tid = threadIdx.x;
   const float* el_v = sel.values(); const int32_t* el_i = sel.ids();
-  if (tid >= RANK_NT) return;                                // whole wavefronts
+  if (tid >= nt) return;                                     // whole wavefronts
   int tshift = 0;
-  while (tshift < 4 && (n_el << (tshift + 1)) <= RANK_NT) ++tshift;
+  while (tshift < 4 && (n_el << (tshift + 1)) <= nt) ++tshift;
   const int T = 1 << tshift, e = tid >> tshift, sub = tid & (T - 1);
   const bool mine = e < n_el;
   int rank = 0, id = 0; float v = 0.f;
@@ -228,10 +237,7 @@ __device__ __forceinline__ void rank_short(int K, const SelectLds& sel, int n_el
       else if (q == v && o != e) rank += el_i[o] < id;
     }
   }
-  if (tshift >= 1) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)rank);
-  if (tshift >= 2) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)rank);
-  if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
-  if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
+  rank = sum_of_lanes(tshift, rank);
   if (mine && sub == 0 && rank < K) { topv[rank] = v; topi[rank] = id; }
 }
 // Any length, all threads: the best K to topv, topi.
@@ -246,9 +252,12 @@ __device__ __forceinline__ void rank_long(int K, const SelectLds& sel, int n_el,
     if (rank < K) { topv[rank] = v; topi[rank] = id; }
   }
 }
-template <int NT>
+// Short: four lanes or more to an element.  K to 2K-1 elements with four workgroups on a CU, by all threads: K = 32 0.77 us, K = 64
+// 1.74 (by 256 of them 1.06 and, one lane to an element, 2.9).
+template <int NT, bool LAST_WAVE_BUSY>
 __device__ __forceinline__ void rank_list(int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
-  if (n_el <= RANK_SHORT) rank_short(K, sel, n_el, topv, topi);
+  constexpr int nt = LAST_WAVE_BUSY ? RANK_NT : NT;
+  if (n_el <= nt / 4) rank_short(K, sel, n_el, nt, topv, topi);
   else rank_long<NT>(K, sel, n_el, topv, topi);
 }
 
@@ -659,10 +668,7 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
           rank += (k0 > key ? 1 : 0) + (k1 > key ? 1 : 0) + (k0 == key ? 0x10000 : 0) + (k1 == key ? 0x10000 : 0);
         }
       }
-      if (tshift >= 1) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)rank);
-      if (tshift >= 2) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)rank);
-      if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
-      if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
+      rank = sum_of_lanes(tshift, rank);
       const bool tied = mine && (rank >> 16) > 1;
       rank &= 0xffff;
       if (tied && sub == 0) for (int v = 0; v < ns; ++v) rank += (int)(skey[v] == key && sidx[v] < i);
@@ -767,9 +773,10 @@ struct SegmentTop { int n_el; bool entropy; };
 // and appends.  Both overlap with the other workgroups' streaming, so the whole layer is one launch.
 // On entry a barrier lies behind the last write to the list and to rr, except that `record()`, called by the last
 // wavefront while the others rank the list, completes rr.part (sums, flags; its lane 0 writes).
+// LATE_ENTROPY: lists come with the entropy still to be formed (by the last wavefront, while the others rank).
 // after_merge(rr): called by the whole workgroup that has merged a split row, before the row is scored
 // (the entropy over the M largest logits of a split row is computed there, over the whole row).
-template <int NT, typename Record, typename AfterMerge>
+template <int NT, bool LATE_ENTROPY, typename Record, typename AfterMerge>
 __device__ __forceinline__ void finish_layer(const TreeState& s, const ScoreParams& sp, int b, int f, int nf, int split,
                                              int64_t row_launched, RowResult& rr, SegmentTop top, const SelectLds& sel, unsigned char* lds,
                                              const float* __restrict__ cls, const float* cls_lds, Record record, AfterMerge after_merge) {
@@ -781,7 +788,7 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
     record();
     if (sp.nsplit == 1 && !top.entropy) row_entropy(s, sp, b, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
   }
-  if (top.n_el >= 0) rank_list<NT>(K, sel, top.n_el, rr.topv, rr.topi);
+  if (top.n_el >= 0) rank_list<NT, LATE_ENTROPY>(K, sel, top.n_el, rr.topv, rr.topi);
   __syncthreads();                                           // rr is complete
   int n = top.n_el >= 0 ? min(top.n_el, K) : rr.part.n_top;
   C2T_PT(PT_RANKED);
@@ -805,7 +812,7 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
       }
       if (sp.M <= 0) row_entropy(s, sp, b, slot, m.R, m.R, m.Z, m.S, m.flags, rr);
     }
-    if (staged) rank_list<NT>(K, sel, per_row, rr.topv, rr.topi);
+    if (staged) rank_list<NT, true>(K, sel, per_row, rr.topv, rr.topi);
     __syncthreads();
     if (sp.M > 0) {
       after_merge(rr);
@@ -1057,10 +1064,7 @@ __global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut 
         rank += (k0 > key ? 1 : 0) + (k1 > key ? 1 : 0);
       }
     }
-    if (tshift >= 1) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, (uint32_t)rank);
-    if (tshift >= 2) rank += (int)dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, (uint32_t)rank);
-    if (tshift >= 3) rank += (int)dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, (uint32_t)rank);
-    if (tshift >= 4) rank += (int)dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rank);
+    rank = sum_of_lanes(tshift, rank);
     if (lead && rank < n) {
       if (in_lds) rank_lds[id] = rank; else rank_mem[id] = rank;
       sel_par[rank] = pid;

@@ -18,6 +18,12 @@ def test_fp32_rows_at_tile_edges(V, K):
     rows_against_oracle("f32", V, K, 1)
 
 
+# bf16 lists of K to 2K-1 elements, ranked by four lanes or more to an element up to 128 of them
+@pytest.mark.parametrize("K", [16, 17, 32, 33, 63, 64])
+def test_bf16_lists_at_the_ranking_s_edges(K):
+    rows_against_oracle("bf16", 8191, K, 1)
+
+
 # Long fp32 rows of a launch with more rows than CUs: one workgroup each up to 196608 logits, and split above.  The rows are dealt out ten times and more: equal rows give equal results.
 @pytest.mark.parametrize("V,K,per_row", [(49163, 64, 1), (131075, 16, 1), (196608, 8, 1), (196612, 8, 2)])
 def test_long_fp32_rows_unsplit(V, K, per_row):
