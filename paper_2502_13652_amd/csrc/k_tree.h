@@ -430,8 +430,16 @@ __host__ __device__ inline size_t prune_list_bytes(int FK) { return ((size_t)3 *
 // `enough` of them to reach it, or their n-th largest.  Two bits a step from the top, ballots, uniform result.
 template <int NV>
 __device__ __forceinline__ uint32_t bound_from_maxima(const uint32_t (&m)[NV], int n, int enough) {
-  uint32_t prefix = 0;
-  for (int shift = 30; shift >= 0; shift -= 2) {
+  // the upper bits that all maxima share need no round, nor does anything where they are all equal
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)m[0]);
+  uint32_t differ = 0;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) differ |= m[v] ^ first;
+  differ = wave_reduce_u32(differ, 0u, [](uint32_t x, uint32_t y) { return x | y; });
+  if (differ == 0u) return first;
+  const int top = (31 - __builtin_clz(differ)) & ~1;
+  uint32_t prefix = top == 30 ? 0u : first & ~((4u << top) - 1u);
+  for (int shift = top; shift >= 0; shift -= 2) {
     int cnt[3] = {0, 0, 0};                                  // how many reach prefix + 1, 2, 3 steps
 #pragma unroll
     for (int q = 0; q < 3; ++q)
@@ -657,8 +665,8 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
         else { P = ld_dev(s.c_P + cb + i); H = ld_dev(s.c_H + cb + i); }
       }
       // rank = survivors with a greater key, and those with the same key (the same token under two parents, with
-      // the same z: rare, looked for only where a count shows them) and a lower candidate index; the survivor's T
-      // lanes take two keys a step each
+      // the same z: looked for only where a count shows them) and a lower candidate index; the survivor's T
+      // lanes take two keys a step each.  (Ties by one lane alone: 7.5 us for 100 survivors of equal z whose rows share tokens.)
       int rank = 0;                                          // lower half: greater keys, upper half: equal ones (itself among them)
       if (mine) {
 #pragma unroll 2
@@ -669,9 +677,16 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
         }
       }
       rank = sum_of_lanes(tshift, rank);
-      const bool tied = mine && (rank >> 16) > 1;
+      const bool tied = mine && (rank >> 16) > 1;            // (the same in the entry's T lanes)
       rank &= 0xffff;
-      if (tied && sub == 0) for (int v = 0; v < ns; ++v) rank += (int)(skey[v] == key && sidx[v] < i);
+      if (__builtin_amdgcn_ballot_w64(tied) != 0ull) {       // (uniform)
+        int ahead = 0;
+        if (tied) {
+#pragma unroll 4
+          for (int v = sub; v < ns; v += T) ahead += (int)(skey[v] == key && sidx[v] < i);
+        }
+        rank += sum_of_lanes(tshift, ahead);
+      }
       if (mine && sub == 0 && rank < n_keep) {
         const int f = (int)(((uint32_t)i * sp.k_inverse) >> 20);         // i / K
         const int64_t tb = (int64_t)b * N + nn;

@@ -260,3 +260,29 @@ def test_fp32_layer_time_at_large_k():
     small, large = _row_layer_us(x, 10), _row_layer_us(x, 64)
     print("K=10 %.1f us, K=64 %.1f us" % (small, large), flush=True)
     assert large < 2 * small
+
+
+# Equal confidences are usual deep in a tree, and rows share tokens: ten rows of ten such candidates take little longer than others
+# (15.1 and 16.7 us; 23.5 where each tied candidate's rank was counted by one lane).
+def test_layer_time_of_equal_confidences():
+    V, F, K = 8000, 10, 10
+    g = torch.Generator(device="cuda").manual_seed(1)
+    bias = -1.05 * torch.log(torch.rand((1, 1, V), generator=g, device="cuda") * V + 1)
+    x = [(3 * torch.randn((1, F, V), generator=g, device="cuda") + bias).to(torch.bfloat16) for _ in range(2)]
+    took = []
+    for w2 in (1.0, 0.0):
+        from paper_2502_13652_amd import C2TContext
+        ctx = C2TContext(1, V, F, K, 2, 100, 4, 1, 0.0)
+        W1 = np.zeros((4, 3), np.float32); W1[0, 0] = 1
+        ctx.set_classifier(W1, np.zeros(4, np.float32), np.array([w2, 0, 0, 0], np.float32), 0.0)
+        for n in (0, 15):
+            if n:
+                ctx.profile_enable(2 * n)
+            for _ in range(max(n, 3)):
+                ctx.reset()
+                for l in x:
+                    ctx.expand_layer(l)
+            torch.cuda.synchronize()
+        took.append(float(np.median(ctx.profile_read(30)[1::2])) * 1e3)
+    print("varied %.1f us, equal %.1f us" % tuple(took), flush=True)
+    assert took[1] < 1.3 * took[0]
