@@ -409,7 +409,11 @@ __device__ __forceinline__ void rank_lists_from_memory(const ScoreParams& sp, in
 // per lane, the n_keep-th largest group maximum is a lower bound of the n_keep-th largest z, found by a wavefront from
 // ballots; what reaches it (two dozen candidates where 16 are kept) is listed in LDS and ranked exactly.  The
 // ranking gives each listed candidate to T = 2^tshift lanes, which split the list between them, two keys per LDS read.
-// Lists that stay long, layers of equal z above all, are first cut by a radix select on the whole keys.
+// Lists that stay long, layers of equal z above all, are first cut by a radix select on the whole keys; so are, without a
+// bound, more than 64 survivors of more than 512 candidates (several a thread), whose bound is slower to find and lets more
+// pass.  Layers with bound / radix select: 32 sequences of 32 x 32 candidates 32.1 / 30.6 us, of 32 x 64 44.5 / 42.8, 4 sequences of
+// 64 x 32 21.0 / 19.1.  Up to 512, one a thread, the bound is the faster: for one sequence of 16 x 16 1.4 us against 1.9 (first pruning
+// and preselection).
 #ifndef C2T_PRUNE_RANK_MAX
 #define C2T_PRUNE_RANK_MAX 128
 #endif
@@ -471,6 +475,7 @@ __host__ __device__ inline size_t score_lds_bytes(int FK) { return prune_list_by
 template <int NT, int PER>
 __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps) {
   constexpr int NW = NT / WAVE;
+  constexpr bool BY_DIGITS = PER > 1;                        // long lists are cut by the radix select at once
   const int F = sp.F, K = sp.K, N = sp.N, layer = sp.layer;
   const float z_beta = sp.z_beta;
   const int FK = F * K, FKp = (FK + 31) & ~31;
@@ -494,7 +499,7 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
     my_z[k] = my_P[k] = my_H[k] = 0.f; my_tok[k] = -1;
     if (i < FK) {
       my_z[k] = ld_dev(s.c_z + cb + i); my_tok[k] = ld_dev(s.c_tok + cb + i);
-      my_P[k] = ld_dev(s.c_P + cb + i); my_H[k] = ld_dev(s.c_H + cb + i);
+      if (!BY_DIGITS) { my_P[k] = ld_dev(s.c_P + cb + i); my_H[k] = ld_dev(s.c_H + cb + i); }
     }
   }
   uint32_t info = 0u;
@@ -509,16 +514,20 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
 
   // ---- first pruning: z > logit(beta) ----
   const int ncand = nf * K;
-  uint32_t zk[PER], mx = 0u; int cnt = 0;                    // key of z, 0: not a survivor
+  uint32_t zk[PER]; int cnt = 0;                             // key of z, 0: not a survivor
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int i = tid + k * NT;
     zk[k] = (i < ncand && my_tok[k] >= 0 && my_z[k] > z_beta) ? sortable_key(my_z[k]) : 0u;
-    mx = max(mx, zk[k]);
     cnt += __popcll(__ballot(zk[k] != 0u));
   }
   C2T_PT(PT_PRUNE_LOADED);
-  lane_max[tid] = mx;
+  // Groups for the bound below: a lane's candidate with those of other lanes in the other wavefronts.  Rows list their
+  // children from the most probable down, and where K divides 64 a lane holds the same rank of every row: maxima by lane alone
+  // would be maxima by rank, and half of them, all low ranks, a bound that most candidates reach.
+  static_assert(NW <= 16, "lanes 0-3, 16-19, 32-35, 48-51 of the wavefronts");
+  if (BY_DIGITS) { for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u; }
+  else lane_max[wid * WAVE + (lane ^ ((wid & 3) | ((wid >> 2) << 4)))] = zk[0];
   if (lane == 0) ps.surv_w[wid] = cnt;
   __syncthreads();
   if (tid < nf && info) atomicOr(&ps.flags_or, (int)info);
@@ -530,7 +539,8 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   for (int v = 0; v < NW; ++v) n_surv += ps.surv_w[v];
   const int n_keep = max(0, min(min(F, N - nn), n_surv));
   uint32_t bound = 1u;                                       // every survivor
-  if (n_keep > 0 && n_surv > PRUNE_DIRECT_MAX) {
+  const bool to_digits = BY_DIGITS && n_surv > PRUNE_DIRECT_MAX;
+  if (!BY_DIGITS && n_keep > 0 && n_surv > PRUNE_DIRECT_MAX) {
     uint32_t m[2] = {0u, 0u};
 #pragma unroll
     for (int v = 0; v < NW; ++v) m[v & 1] = max(m[v & 1], lane_max[v * WAVE + lane]);
@@ -557,7 +567,8 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
         if (zk[k] >= bound) {
           const int u = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hit[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit[k], 0u));
           skey[u] = ((uint64_t)zk[k] << 32) | (uint32_t)~my_tok[k]; sidx[u] = tid + k * NT;
-          if (u < PRUNE_RANK_MAX) { ps.list_P[u] = my_P[k]; ps.list_H[u] = my_H[k]; }
+          if (!BY_DIGITS && u < PRUNE_RANK_MAX) { ps.list_P[u] = my_P[k]; ps.list_H[u] = my_H[k]; }
+          if (to_digits) { const uint32_t bin = zk[k] >> 20; atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u); }
         }
         at += __popcll(hit[k]);
       }
@@ -565,21 +576,23 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   }
   __syncthreads();
   int ns = ps.n_list;
-  const bool listed_order = ns <= PRUNE_RANK_MAX;            // ps.list_P, ps.list_H hold the entries' P and H
-  if (n_keep > 0 && !listed_order) {
+  const bool listed_order = !BY_DIGITS && ns <= PRUNE_RANK_MAX;       // ps.list_P, ps.list_H hold the entries' P and H
+  if (n_keep > 0 && (BY_DIGITS ? to_digits : !listed_order)) {
     // Radix select on the 64-bit keys, twelve bits a level, from the top: the histogram of the level's digit over
     // the survivors that are still undecided (those whose higher digits equal the digits selected so far; at the
     // first level all of them) gives the digit at which the running count from
     // the top reaches what is still needed; survivors below it are dropped.  Layers of equal z go on into the
     // token bits instead of ranking hundreds of tied survivors against each other.
-    for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u;
-    __syncthreads();
+    if (!BY_DIGITS) {
+      for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u;
+      __syncthreads();
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int u = tid + k * NT;
-      if (u < ns) { const uint32_t bin = (uint32_t)(skey[u] >> 52); atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u); }
+      for (int k = 0; k < PER; ++k) {
+        const int u = tid + k * NT;
+        if (u < ns) { const uint32_t bin = (uint32_t)(skey[u] >> 52); atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u); }
+      }
+      __syncthreads();
     }
-    __syncthreads();
     int need = n_keep, shift = 52;                           // (uniform) still to be taken from the undecided; the level's digit is key >> shift
     uint64_t prefix = 0ull;                                  // the digits selected so far: the undecided have key >> (shift + 12) == prefix
     for (;;) {
