@@ -460,16 +460,19 @@ template <int NT>
 struct PruneShared {
   int32_t n_list, n_red, flags_or, sel_bin, sel_above, sel_count;
   int32_t scan_w[NT / WAVE], surv_w[NT / WAVE];
-  float list_P[PRUNE_RANK_MAX], list_H[PRUNE_RANK_MAX];     // of the first entries, as listed
   int32_t old_node[SP_MAX_F];
   float old_s[SP_MAX_F];
   uint32_t kept[C2T_MAX_CANDIDATES_DEV / 32];              // bit i: candidate i is appended to the tree
 };
 
 // Dynamic LDS of prune_sequence: its lists, then PruneShared (2 KB of static LDS would cost launches with K = 64, whose element
-// list takes 32 KB, the fourth workgroup of a CU: 1024 rows of 32000 44 us instead of 33).
+// list takes 32 KB, the fourth workgroup of a CU: 1024 rows of 32000 44 us instead of 33; another 1 KB of it launches with more than
+// 1900 candidates: 2048 rows of 32000 with 64 x 31 candidates 42 us instead of 37).
 template <int NT>
-__host__ __device__ inline size_t score_lds_bytes(int FK) { return prune_list_bytes(FK) + sizeof(PruneShared<NT>); }
+__host__ __device__ inline size_t score_lds_bytes(int FK) {
+  static_assert(sizeof(PruneShared<NT>) <= 1024, "with 64 x 32 candidates it decides over the fourth workgroup of a CU");
+  return prune_list_bytes(FK) + sizeof(PruneShared<NT>);
+}
 
 // PER: candidates per thread; F * K <= PER * NT.
 template <int NT, int PER>
@@ -486,8 +489,10 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   uint64_t* skey = (uint64_t*)lds;
   int32_t* sidx = (int32_t*)(skey + FKp);
   uint32_t* hist = (uint32_t*)(sidx + FKp);
-  uint32_t* lane_max = hist;                                 // [NW][WAVE]; the histogram comes later, if at all
-  static_assert(NW * WAVE <= PRUNE_HIST_WORDS, "the lanes' maxima fit there");
+  // in the histogram's place, which comes later, if at all: the lanes' maxima, and P and H of the first entries, as listed
+  uint32_t* lane_max = hist;                                 // [NW][WAVE]
+  float* list_P = (float*)(hist + NW * WAVE); float* list_H = list_P + PRUNE_RANK_MAX;
+  static_assert(NW * WAVE + 2 * PRUNE_RANK_MAX <= PRUNE_HIST_WORDS, "they fit there");
 
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
   const int64_t cb = (int64_t)b * FK, fb = (int64_t)b * F;   // uniform bases: the lanes' offsets stay 32 bits wide
@@ -567,7 +572,7 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
         if (zk[k] >= bound) {
           const int u = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hit[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit[k], 0u));
           skey[u] = ((uint64_t)zk[k] << 32) | (uint32_t)~my_tok[k]; sidx[u] = tid + k * NT;
-          if (!BY_DIGITS && u < PRUNE_RANK_MAX) { ps.list_P[u] = my_P[k]; ps.list_H[u] = my_H[k]; }
+          if (!BY_DIGITS && u < PRUNE_RANK_MAX) { list_P[u] = my_P[k]; list_H[u] = my_H[k]; }
           if (to_digits) { const uint32_t bin = zk[k] >> 20; atomicAdd(&hist[bin >> 1], (bin & 1u) ? 0x10000u : 1u); }
         }
         at += __popcll(hit[k]);
@@ -576,7 +581,7 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   }
   __syncthreads();
   int ns = ps.n_list;
-  const bool listed_order = !BY_DIGITS && ns <= PRUNE_RANK_MAX;       // ps.list_P, ps.list_H hold the entries' P and H
+  const bool listed_order = !BY_DIGITS && ns <= PRUNE_RANK_MAX;       // list_P, list_H hold the entries' P and H
   if (n_keep > 0 && (BY_DIGITS ? to_digits : !listed_order)) {
     // Radix select on the 64-bit keys, twelve bits a level, from the top: the histogram of the level's digit over
     // the survivors that are still undecided (those whose higher digits equal the digits selected so far; at the
@@ -674,7 +679,7 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
       const int tok = (int)~(uint32_t)key;
       float P = 0.f, H = 0.f;
       if (mine && sub == 0) {
-        if (listed_order) { P = ps.list_P[u]; H = ps.list_H[u]; }
+        if (listed_order) { P = list_P[u]; H = list_H[u]; }
         else { P = ld_dev(s.c_P + cb + i); H = ld_dev(s.c_H + cb + i); }
       }
       // rank = survivors with a greater key, and those with the same key (the same token under two parents, with
