@@ -945,11 +945,14 @@ __global__ __launch_bounds__(FIN_NT) void k_finalize(TreeState s, TreeOut o, int
 // What bounds it: latency, one workgroup per sequence; so the history is read once (its order-preserving keys go to LDS
 // where they fit, 8192 of them; longer histories are read again at each pass).  Up to RR_BOUND_MAX nodes out, a lower
 // bound of the n-th best key comes from 256 group maxima (bound_from_maxima), what reaches it is listed, ranked exactly
-// on unique 64-bit keys (key, ~index) and cut to n.  More nodes, or more than 1024 candidates above the bound (massive ties):
-// an exact radix select of the n-th best key (12 + 12 + 8 bits, an LDS histogram per pass), ties in index order.
+// on unique 64-bit keys (key, ~index) and cut to n.  More nodes, or more than RR_LIST_MAX candidates above the bound (ties, which
+// are usual: a child's smallest logit is often its parent's): an exact radix select of the n-th best key (12 + 12 + 8 bits, an
+// LDS histogram per pass), ties in index order.  32 sequences of 1536 candidates with many ties, 60 out: 46.5 us when up to
+// 1024 candidates above the bound were ranked, 17.0 now; 16384 candidates, 60 out: 95 us when each thread went through its own
+// stretch of the history for the histograms as well, 75 now.
 // One phase of 32 sequences with 600 candidates each, 60 out: 16.0 us for this kernel before, when every pass
 // read the history from memory again and divided for it.
-constexpr int RR_NT = 1024, RR_LDS_KEYS = 8192, RR_BOUND_MAX = 160;
+constexpr int RR_NT = 1024, RR_LDS_KEYS = 8192, RR_BOUND_MAX = 160, RR_LIST_MAX = 256;
 constexpr int RR_MASK_ROWS_MAX = 256;          // up to so many nodes out the reranking writes the mask itself; k_mask_of_parents for more
 __global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut o, int n_out, int D, int FK, uint32_t fk_inverse) {
   constexpr int NW = RR_NT / WAVE;
@@ -979,7 +982,7 @@ __global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut 
     if (in_lds) keys[i] = k;
     mx = max(mx, k); cnt += k != 0u;
   }
-  u.lane_max[tid] = mx;
+  u.lane_max[wid * WAVE + (lane ^ (wid >> 2))] = mx;         // (groups of different ranks: see prune_sequence)
   cnt = wave_sum_i(cnt);
   if (lane == 0) scan_w[wid] = cnt;
   __syncthreads();
@@ -1009,7 +1012,7 @@ __global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut 
     }
     __syncthreads();
     m = n_list;
-    listed = m <= C2T_MAX_BUDGET_DEV;
+    listed = m <= (n < n_all ? RR_LIST_MAX : C2T_MAX_BUDGET_DEV);
   }
   if (n > 0 && !listed) {
     // a thread owns a contiguous range of history indices, so that index order = thread order
@@ -1023,7 +1026,7 @@ __global__ __launch_bounds__(RR_NT) void k_finalize_rerank(TreeState s, TreeOut 
       __syncthreads();
       for (int i = tid; i < 4096; i += RR_NT) u.dig[i] = 0u;
       __syncthreads();
-      for (int i = i0; i < i1; ++i) {
+      for (int i = tid; i < total; i += RR_NT) {
         const uint32_t key = key_at(i);
         if (key && (key & care) == prefix) atomicAdd(&u.dig[(key >> shift) & dmask], 1u);
       }

@@ -286,3 +286,31 @@ def test_layer_time_of_equal_confidences():
         took.append(float(np.median(ctx.profile_read(30)[1::2])) * 1e3)
     print("varied %.1f us, equal %.1f us" % tuple(took), flush=True)
     assert took[1] < 1.3 * took[0]
+
+
+# Few nodes out of many candidates with equal scores cost no more than many: 60 of 1536 17 us, 161 of them 15 us (46 and 15 when
+# everything that reached the bound was ranked).
+def test_reranking_time_with_ties():
+    from paper_2502_13652_amd import C2TContext
+    B, D, F, K = 32, 6, 16, 16
+    g = torch.Generator(device="cuda").manual_seed(3)
+    ctx = C2TContext(B, 2000, F, K, D, 96, 4, 1, 0.0, rerank=1)
+    W1 = np.zeros((4, 3), np.float32); W1[0, 0] = 1; W1[1, 1] = -0.1
+    ctx.set_classifier(W1, np.full(4, 0.5, np.float32), np.array([1, 1, 0, 0], np.float32), 0.0)
+    ctx.reset()
+    for _ in range(D):
+        ctx.expand_layer((3 * torch.randn((B, F, 2000), generator=g, device="cuda")).to(torch.bfloat16))
+    took = []
+    for n_out in (60, 161):
+        out, us = ctx.new_tree_out(n_out), []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                ctx.finalize_tree_reranked(n_out, out)
+            b.record()
+            torch.cuda.synchronize()
+            us.append(a.elapsed_time(b) * 50)
+        took.append(float(np.median(us)))
+    print("60 out %.1f us, 161 out %.1f us" % tuple(took), flush=True)
+    assert took[0] < 2 * took[1]
