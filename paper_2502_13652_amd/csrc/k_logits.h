@@ -1073,17 +1073,22 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     __builtin_amdgcn_s_setprio(3);
     // groups of DEPTH sweeps in which every lane has a chunk; a cell is four sweeps
     const int n_groups = whole / (DEPTH * NT);
-    // A row that masks part of its vocabulary shows it in the wavefront's first two chunks (1024 logits; masks that only come
-    // later are counted chunk by chunk, out of line).  Decided once, ahead of the loop: a test inside it costs the rows that
-    // mask nothing 4 to 6 %.
+    // A row that masks part of its vocabulary shows it in the wavefront's first chunks (of 512 logits each): where half of them hold
+    // a masked logit, most chunks do.  Fewer, a few masked tokens or a masked stretch, are counted chunk by chunk, out of line.  256
+    // rows of 128256 by the usual loop / by the masked one: no logit masked 21.4 us / -, one 21.4 / 26.8, the first 4096 22.1 / 30.2,
+    // 1 % 40.0 / 30.3, 30 % - / 30.2.  (With fewer chunks looked at, some wavefront of some row decides wrongly, and the launch waits
+    // for it.)  Decided once, ahead of the loop: a test inside it costs the rows that mask nothing 4 to 6 %.
     int masks = 0;
     // Not with four workgroups per CU, where the decision alone costs rows that mask nothing 1 % and the call gains nothing; nor
     // for shared rows, whose segments are a group or two: root layer of 64 rows 26.7 us without it, 29.0 with it.
     if (WPS != 8 && !COOP) {
-      uint32_t hi = pk_max_u16(pk_max_u16(q[0].x, q[0].y), pk_max_u16(q[0].z, q[0].w));
-      hi = pk_max_u16(hi, pk_max_u16(pk_max_u16(q[1].x, q[1].y), pk_max_u16(q[1].z, q[1].w)));
-      const uint64_t masked_lanes = __builtin_amdgcn_ballot_w64(pk_sub_sat_u16(hi, 0xC47FC47Fu) != 0u);
-      masks = __builtin_amdgcn_readfirstlane(n_groups > 0 && masked_lanes != 0ull ? 1 : 0);      // (a scalar branch: as a lane mask both sides' registers would be live at once)
+      int n = 0;
+#pragma unroll
+      for (int k = 0; k < DEPTH; ++k) {
+        const uint32_t hi = pk_max_u16(pk_max_u16(q[k].x, q[k].y), pk_max_u16(q[k].z, q[k].w));
+        n += __builtin_amdgcn_ballot_w64(pk_sub_sat_u16(hi, 0xC47FC47Fu) != 0u) != 0ull ? 1 : 0;
+      }
+      masks = __builtin_amdgcn_readfirstlane(n_groups > 0 && 2 * n >= DEPTH ? 1 : 0);      // (a scalar branch: as a lane mask both sides' registers would be live at once)
     }
     vo_after = vo;
     if (masks != 0) {                                    // (nothing of this path is live across the call: what is would be spilled for every row)

@@ -60,6 +60,37 @@ def test_masked_bf16_rows_alone_on_a_cu(V):
     rows_against_oracle("bf16", V, 16, 1)
 
 
+# The masked loop is taken by the wavefronts of whose first eight chunks (512 logits, 4096 apart) half hold a masked logit: masked
+# stretches of whole and partial sweeps of the workgroup, single tokens in them, shares around one logit a chunk
+@pytest.mark.parametrize("V", [32768, 40007, 65549])
+@pytest.mark.parametrize("mask", [-float("inf"), -1e9])
+def test_bf16_masks_at_the_loop_s_choice(V, mask):
+    rng = np.random.default_rng(V)
+    names, rows = [], []
+    for head in (1, 4095, 4096, 12288, 12289, 16383, 16384, 16385, 28672, 32767):
+        names.append("first %d" % head); r = 2 * rng.standard_normal(V); r[:head] = mask; rows.append(r)
+        names.append("but the first %d" % head); r = 2 * rng.standard_normal(V); r[head + 1:] = mask; r[:16] = rng.standard_normal(16); rows.append(r)
+    for n in (1, 2, 3, 4, 5, 8):
+        for at in (0, 511, 3584, 4095):
+            names.append("%d chunks, token %d" % (n, at)); r = 2 * rng.standard_normal(V); r[at + 4096 * rng.choice(8, n, replace=False)] = mask; rows.append(r)
+    for share in (0.0005, 0.002, 0.005, 0.01):
+        names.append("share %g" % share); r = 2 * rng.standard_normal(V); r[rng.random(V) < share] = mask; rows.append(r)
+    _rows_equal_oracle(names, np.stack(rows).astype(np.float32), 16, 1, torch.bfloat16)
+
+
+# Rows that mask one token are counted by the usual loop (256 rows of 128256: 22 us both; 27 by the masked one), rows that mask one
+# in two hundred by the masked one (30 us; 39 where some wavefronts take the usual one)
+def test_bf16_layer_time_of_few_masked_tokens():
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = (3 * torch.randn((256, 128256), generator=g, device="cuda")).to(torch.bfloat16)
+    one, few = x.clone(), x.clone()
+    one[:, 0] = -float("inf")
+    few[torch.rand(x.shape, generator=g, device="cuda") < 0.005] = -float("inf")
+    took = [_row_layer_us(y, 16, 1) for y in (x, one, few)]
+    print("none %.1f us, one %.1f us, one in 200 %.1f us" % tuple(took), flush=True)
+    assert took[1] < 1.15 * took[0] and took[2] < 1.55 * took[0]
+
+
 @pytest.mark.parametrize("dtype,V", [("bf16", 40000), ("f32", 20000)])
 def test_bad_logits_among_masked_ones(dtype, V):
     from paper_2502_13652_amd import C2TContext
@@ -158,38 +189,40 @@ def test_reranking_at_its_edges(D, F, K, n_outs):
 
 
 def _row_layer_us(x, K, splits=0, n=9):
-    """Median duration (the kernel's own begin and end) of a layer whose rows are the sequences' root rows: x [rows][V] fp32."""
+    """Duration (the kernel's own begin and end; the least of three medians) of a layer whose rows are the sequences' root rows: x [rows][V]."""
     from paper_2502_13652_amd import C2TContext
     rows, V = x.shape
-    ctx = C2TContext(rows, V, 1, K, 1, 1, 2, 0, 0.0)
+    ctx = C2TContext(rows, V, 1, K, 1, 1, 2, x.dtype, 0.0)
     W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
     ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
     ctx.set_row_splits(splits, splits)
-    for timed in (0, n):
-        if timed:
-            ctx.profile_enable(timed)
-        for _ in range(max(timed, 3)):
+    ctx.profile_enable(n)
+    us = []
+    for _ in range(4):                                       # (the first to warm up)
+        for _ in range(n):
             ctx.reset()
             ctx.expand_layer(x.view(rows, 1, V))
         torch.cuda.synchronize()
-    return float(np.median(ctx.profile_read(n))) * 1e3
+        us.append(float(np.median(ctx.profile_read(n))) * 1e3)
+    return min(us[1:])
 
 
-def _rows_equal_oracle(names, rows, K, splits):
+def _rows_equal_oracle(names, rows, K, splits, dtype=torch.float32):
     from oracle import ref_row
     from paper_2502_13652_amd import C2TContext
     B, V = rows.shape
-    ctx = C2TContext(B, V, 1, K, 1, 1, 2, 0, 0.0)
+    ctx = C2TContext(B, V, 1, K, 1, 1, 2, dtype, 0.0)
     W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
     ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
     ctx.set_row_splits(splits, splits)
-    x = torch.full((B, 1, (V + 3) // 4 * 4 + 4), float("inf"))
-    x[:, 0, :V] = torch.from_numpy(rows)
+    x = torch.full((B, 1, (V + 7) // 8 * 8 + 8), float("inf"), dtype=dtype)
+    x[:, 0, :V] = torch.from_numpy(rows).to(dtype)
     ctx.reset()
     ctx.expand_layer(x.cuda())
     c = to_np(ctx.candidates())
+    bits = W.as_numpy_bits(x[:, 0, :V])
     for b, name in enumerate(names):
-        r = ref_row(rows[b], K)
+        r = ref_row(bits[b], K)
         k = len(r["ids"])
         np.testing.assert_array_equal(c["token"][b, :k], r["ids"], err_msg=name)
         assert close(c["p"][b, :k], r["p"].astype(np.float32), atol=1e-37).all(), name
@@ -263,7 +296,7 @@ def test_fp32_layer_time_at_large_k():
 
 
 # Equal confidences are usual deep in a tree, and rows share tokens: ten rows of ten such candidates take little longer than others
-# (15.1 and 16.7 us; 23.5 where each tied candidate's rank was counted by one lane).
+# (14 and 16 us; 23 where each tied candidate's rank was counted by one lane).
 def test_layer_time_of_equal_confidences():
     V, F, K = 8000, 10, 10
     g = torch.Generator(device="cuda").manual_seed(1)
@@ -275,17 +308,18 @@ def test_layer_time_of_equal_confidences():
         ctx = C2TContext(1, V, F, K, 2, 100, 4, 1, 0.0)
         W1 = np.zeros((4, 3), np.float32); W1[0, 0] = 1
         ctx.set_classifier(W1, np.zeros(4, np.float32), np.array([w2, 0, 0, 0], np.float32), 0.0)
-        for n in (0, 15):
-            if n:
-                ctx.profile_enable(2 * n)
-            for _ in range(max(n, 3)):
+        ctx.profile_enable(30)
+        us = []
+        for _ in range(4):                                   # (the first to warm up)
+            for _ in range(15):
                 ctx.reset()
                 for l in x:
                     ctx.expand_layer(l)
             torch.cuda.synchronize()
-        took.append(float(np.median(ctx.profile_read(30)[1::2])) * 1e3)
+            us.append(float(np.median(ctx.profile_read(30)[1::2])) * 1e3)
+        took.append(min(us[1:]))
     print("varied %.1f us, equal %.1f us" % tuple(took), flush=True)
-    assert took[1] < 1.3 * took[0]
+    assert took[1] < 1.4 * took[0]
 
 
 # Few nodes out of many candidates with equal scores cost no more than many: 60 of 1536 17 us, 161 of them 15 us (46 and 15 when
