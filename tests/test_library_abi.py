@@ -119,6 +119,9 @@ def test_rows_shared_by_workgroups_launch_shape(lib):
     assert per_row(cfg(**dict(one_seq, vocab=49160))) == (4, 4)   # 6145 chunks, four groups: the last workgroup gets the last chunk alone
     assert per_row(cfg(**dict(one_seq, vocab=65544))) == (5, 5)   # 8193 chunks: five groups, one each
     assert per_row(cfg(**dict(one_seq, vocab=32000, logits_dtype=0))) == (4, 4)   # fp32 rows are split, not shared
+    f32 = dict(one_seq, logits_dtype=0, vocab=128256, max_frontier=8)
+    # up to eight while a row's lists have no more than 256 entries to merge, four in any case
+    assert [per_row(cfg(**dict(f32, top_k=k)))[1] for k in (10, 32, 33, 48, 64)] == [8, 8, 7, 5, 4]
 
 
 def test_no_cpu_fallback_and_no_oracle_in_the_product():
