@@ -48,7 +48,8 @@ constexpr int PARTIAL_SLOTS_MIN = 16384;       // (row, split) records the works
 // workgroup a CU, four a row, eight for rows that leave each a tile and a third (2700 chunks).  Layers in us, by splits:
 // 10 rows of 32000: 17.6 with 4, 24 with 16; 40 rows of 65541: 22.3 / 18.8 / 17.8 / 20.3 with 2 / 4 / 6 / 10; 16 rows of
 // 128256: 28.6 / 24.7 / 29.6 with 3 / 8 / 16.  More than four only while the merged lists stay within 256 entries: 40 rows of 128256
-// with K = 48 53.4 / 38.7 with 7 / 5, 32 rows of K = 64 53.7 / 41.5 with 8 / 4.  More rows than CUs stay whole: 256 rows of 128256 49.6 with 1, 61.6
+// with K = 48 53.4 / 38.7 with 7 / 5, 32 rows of K = 64 53.7 / 41.5 with 8 / 4.  One workgroup a CU exceeded / kept to: 100 rows of 32000 17.5 with 3 / 15.3 with
+// 2, 160 18.8 / 16.8, 130 of 8000 13.3 / 10.1, 40 of 128256 25.1 with 7 / 19.6 with 6, 90 32.0 / 26.8, 130 (two or whole) 37.8 / 38.6.  More rows than CUs stay whole: 256 rows of 128256 49.6 with 1, 61.6
 // with 3, 86.8 with 8; 512 rows of 65536 47.3 with 1, 61.6 with 2; 2048 rows of 65536 136 with 1, 160 with 2.
 constexpr int TARGET_WORKGROUPS_F32 = 256;
 constexpr int SPLITS_F32 = 4, MAX_SPLITS_F32 = 8, SPLIT_CHUNKS_F32 = 2700, MERGED_MAX_F32 = 256;
@@ -203,7 +204,7 @@ int default_split(const c2t_config& c, const Layout& L, int64_t rows) {
   if (c.logits_dtype == C2T_BF16 || c.entropy_top_m > 0) return min_splits(c);
   const int by_size = std::max(1, chunks_of(c) / NT_F32);   // at least one full sweep of the workgroup
   const int most = std::max(SPLITS_F32, std::min(std::min(MAX_SPLITS_F32, MERGED_MAX_F32 / c.top_k), chunks_of(c) / SPLIT_CHUNKS_F32));
-  const int64_t want = std::min<int64_t>((TARGET_WORKGROUPS_F32 + rows - 1) / rows, most);
+  const int64_t want = std::max<int64_t>(std::min<int64_t>(TARGET_WORKGROUPS_F32 / rows, most), 1);
   const int64_t cap = L.partial_slots / rows;
   const int64_t ns = std::min<int64_t>(std::min<int64_t>(want, by_size), cap);
   return (int)std::max<int64_t>(ns, fewest_splits(c));

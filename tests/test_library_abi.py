@@ -120,6 +120,11 @@ def test_rows_shared_by_workgroups_launch_shape(lib):
     assert per_row(cfg(**dict(one_seq, vocab=65544))) == (5, 5)   # 8193 chunks: five groups, one each
     assert per_row(cfg(**dict(one_seq, vocab=32000, logits_dtype=0))) == (4, 4)   # fp32 rows are split, not shared
     f32 = dict(one_seq, logits_dtype=0, vocab=128256, max_frontier=8)
+    # at most one workgroup a CU
+    for rows in (30, 36, 40, 52, 70, 86, 100, 129, 160, 200, 255, 256, 257):
+        for V in (8000, 32000, 65536, 128256):
+            n = per_row(cfg(**dict(f32, batch=rows, vocab=V)))[0]
+            assert n == 1 or n * rows <= 256, (rows, V, n)
     # up to eight while a row's lists have no more than 256 entries to merge, four in any case
     assert [per_row(cfg(**dict(f32, top_k=k)))[1] for k in (10, 32, 33, 48, 64)] == [8, 8, 7, 5, 4]
 
