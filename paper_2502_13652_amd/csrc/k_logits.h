@@ -1081,14 +1081,14 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     int masks = 0;
     // Not with four workgroups per CU, where the decision alone costs rows that mask nothing 1 % and the call gains nothing; nor
     // for shared rows, whose segments are a group or two: root layer of 64 rows 26.7 us without it, 29.0 with it.
-    if (WPS != 8 && !COOP) {
+    if (WPS != 8 && !COOP && n_groups > 0) {               // (shorter rows do not wait for all their loads here)
       int n = 0;
 #pragma unroll
       for (int k = 0; k < DEPTH; ++k) {
         const uint32_t hi = pk_max_u16(pk_max_u16(q[k].x, q[k].y), pk_max_u16(q[k].z, q[k].w));
         n += __builtin_amdgcn_ballot_w64(pk_sub_sat_u16(hi, 0xC47FC47Fu) != 0u) != 0ull ? 1 : 0;
       }
-      masks = __builtin_amdgcn_readfirstlane(n_groups > 0 && 2 * n >= DEPTH ? 1 : 0);      // (a scalar branch: as a lane mask both sides' registers would be live at once)
+      masks = __builtin_amdgcn_readfirstlane(2 * n >= DEPTH ? 1 : 0);      // (a scalar branch: as a lane mask both sides' registers would be live at once)
     }
     vo_after = vo;
     if (masks != 0) {                                    // (nothing of this path is live across the call: what is would be spilled for every row)
