@@ -39,7 +39,7 @@ constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
 constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
 constexpr int NT_F32 = 512;                    // workgroup size of the fp32 kernel: two of them fill a CU at its 128 registers a lane
-static_assert(HP_NT == NT_F32, "one size of the sequence step's LDS");
+static_assert(HP_NT == NT_F32, "one size of the cell maps and of the sequence step's LDS");
 constexpr int MLP_SPREAD_MIN = 48;             // hidden units from which on a workgroup alone on its CU evaluates the classifier with all its wavefronts
 constexpr int PARTIAL_SLOTS_MIN = 16384;       // (row, split) records the workspace always has room for
 // Row splits.  A split adds an epilogue, a device-scope ticket and a merge (a few microseconds of
@@ -65,8 +65,8 @@ constexpr int SPLITS_F32 = 4, MAX_SPLITS_F32 = 8, SPLIT_CHUNKS_F32 = 2700, MERGE
 constexpr int COOP_MAX_WORKGROUPS = 256;       // workgroups of such a launch: one per CU at most
 constexpr int COOP_MAX_ROWS = COOP_MAX_WORKGROUPS / 2;
 constexpr int COOP_MAX_SHARE = C2T_COOP_MAX_SHARE;     // workgroups per row at most
-constexpr int COOP_MIN_GROUPS = C2T_COOP_MIN_GROUPS;   // shortest row that is shared, in groups of HP_CPC sweeps (32 KB)
-constexpr int COOP_GROUP_CHUNKS = HP_CPC * HP_NT;      // segments are whole groups: the row's cell map is then the segments' maps end to end
+constexpr int COOP_MIN_GROUPS = C2T_COOP_MIN_GROUPS;   // shortest row that is shared, in groups of CPC sweeps (32 KB)
+constexpr int COOP_GROUP_CHUNKS = CPC * HP_NT;         // segments are whole groups: the row's cell map is then the segments' maps end to end
 
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -86,18 +86,14 @@ struct Layout {
 int epc_of(const c2t_config& c) { return c.logits_dtype == C2T_BF16 ? 8 : 4; }
 int keybytes_of(const c2t_config& c) { return c.logits_dtype == C2T_BF16 ? 2 : 4; }
 int chunks_of(const c2t_config& c) { return (c.vocab + epc_of(c) - 1) / epc_of(c); }
-// fewest splits for which one workgroup's cell map fits its LDS budget
-int cpc_of(const c2t_config& c) { return c.logits_dtype == C2T_BF16 ? HP_CPC : DIRECT_CPC; }   // chunks per map cell
-int cells_of(const c2t_config& c, int chunks) {
-  return c.logits_dtype == C2T_BF16 ? cells_in_segment<HP_NT, HP_CPC>(chunks) : cells_in_segment<NT_F32, DIRECT_CPC>(chunks);
-}
 int splits_of_cells(const c2t_config& c, int chunks_per_cell) {
   const int max_chunks = (c.logits_dtype == C2T_BF16 ? MAX_MAP_BYTES_BF16 : MAX_MAP_BYTES_F32) / keybytes_of(c) * chunks_per_cell;
   return (chunks_of(c) + max_chunks - 1) / max_chunks;
 }
-int fewest_splits(const c2t_config& c) { return splits_of_cells(c, cpc_of(c)); }
+// fewest splits for which one workgroup's cell map fits its LDS budget (fp32: 196608 logits, 48 KB)
+int fewest_splits(const c2t_config& c) { return splits_of_cells(c, CPC); }
 // fewest a caller may set (and what the workspace is sized for): fp32 segments of at most 49152 logits
-int min_splits(const c2t_config& c) { return splits_of_cells(c, c.logits_dtype == C2T_BF16 ? HP_CPC : 1); }
+int min_splits(const c2t_config& c) { return splits_of_cells(c, c.logits_dtype == C2T_BF16 ? CPC : 1); }
 
 int check_config(const c2t_config* c) {
   if (!c) return C2T_ERR_INVALID_ARG;
@@ -136,7 +132,7 @@ Layout make_layout(const c2t_config& c) {
   L.tab_e = take((size_t)HP_TAB_DOUBLES * 8);
   L.coop_hist = L.coop_map = L.coop_acc = 0; L.coop_map_stride = 0;
   if (c.logits_dtype == C2T_BF16 && min_splits(c) == 1 && (chunks_of(c) + COOP_GROUP_CHUNKS - 1) / COOP_GROUP_CHUNKS >= COOP_MIN_GROUPS) {
-    L.coop_map_stride = (cells_in_segment<HP_NT, HP_CPC>(chunks_of(c)) + 7) / 8 * 8;
+    L.coop_map_stride = (cells_in_segment<HP_NT>(chunks_of(c)) + 7) / 8 * 8;
     L.coop_hist = take((size_t)COOP_MAX_WORKGROUPS * HP_WORDS * 4);
     L.coop_map = take((size_t)COOP_MAX_ROWS * L.coop_map_stride * 2);
     L.coop_acc = take((size_t)COOP_MAX_WORKGROUPS * sizeof(CoopAcc));
@@ -231,15 +227,14 @@ Share share_of(const c2t_config& c, const Layout& L, int n_cus, int64_t rows) {
 hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int rows_per_seq, int nsplit, bool may_share,
                          hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const c2t_config& c = x->cfg;
-  const int cpc = cpc_of(c);
   const Share share = (may_share && nsplit == 1) ? share_of(c, x->lay, x->n_cus, (int64_t)c.batch * rows_per_seq) : Share{1, 0};
   const int per_row = share.n > 1 ? share.n : nsplit;       // workgroups per row
   const int cps = share.n > 1 ? share.groups_each * COOP_GROUP_CHUNKS : (chunks_of(c) + nsplit - 1) / nsplit;
   // the cell map in LDS: the workgroup's segment; the whole row where rows are shared (the workgroup that finishes the row loads it)
-  const int cells = cells_of(c, share.n > 1 ? chunks_of(c) : cps);
+  const int cells = cells_in_segment<HP_NT>(share.n > 1 ? chunks_of(c) : cps);
   const size_t map_lds = ((size_t)cells * keybytes_of(c) + 15) / 16 * 16;
-  // element list of the selection: (2K-1) cells of cpc chunks, 8 bytes per element
-  const size_t list_lds = (size_t)(2 * c.top_k - 1) * cpc * epc_of(c) * 8;
+  // element list of the selection: (2K-1) cells of CPC chunks, 8 bytes per element
+  const size_t list_lds = (size_t)(2 * c.top_k - 1) * CPC * epc_of(c) * 8;
   const size_t score_lds = score_lds_bytes<HP_NT>(c.max_frontier * c.top_k);
   const unsigned grid = (unsigned)((int64_t)c.batch * rows_per_seq * per_row);
   ScoreParams sp;
@@ -303,11 +298,11 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
     const size_t lds = lds_work + ((size_t)(5 * c.hidden + 1) * 4 + 15) / 16 * 16;
     size_t& raised = x->lds_raised[0];
     if (lds > raised) {                                     // beyond the 48 KB a kernel may use without asking
-      hipError_t e = hipFuncSetAttribute((const void*)k_logits_direct<0, NT_F32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      hipError_t e = hipFuncSetAttribute((const void*)k_logits_direct<NT_F32>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
       raised = lds;
     }
-    hipExtLaunchKernelGGL((k_logits_direct<0, NT_F32>), dim3(grid), dim3(NT_F32), lds, s, ev0, ev1, 0, logits, stride,
+    hipExtLaunchKernelGGL(k_logits_direct<NT_F32>, dim3(grid), dim3(NT_F32), lds, s, ev0, ev1, 0, logits, stride,
                           c.vocab, cps, (const float*)x->st.cls, x->st, sp);
   }
   return hipGetLastError();

@@ -28,7 +28,6 @@
 namespace c2t {
 
 constexpr int EXP_TAB = 32;
-constexpr int DIRECT_CPC = 4;                  // chunks per cell of the fallback's map: a row of 196608 fp32 logits needs 48 KB
 constexpr int DIRECT_CHUNKS = 4;               // chunks a lane reads per tile: 64 bytes, two tiles in flight
 
 // 2^(j/32) with j << 15 taken off its upper word: adding k << 15 for any k = 32 q + j then gives 2^(k/32)
@@ -89,10 +88,11 @@ __device__ __forceinline__ float bound_of_columns(const DirectShared<NT>& sh, in
 constexpr int COLUMNS64_MAX_K = 32;
 template <int NT>
 __device__ __forceinline__ float column_bound(const DirectShared<NT>& sh, int K) {
-  return K <= COLUMNS64_MAX_K ? bound_of_columns<NT, 1, 16>(sh, K) : bound_of_columns<NT, 2, 16>(sh, K);
+  if (__builtin_expect(K > COLUMNS64_MAX_K, 0)) return bound_of_columns<NT, 2, 16>(sh, K);
+  return bound_of_columns<NT, 1, 16>(sh, K);
 }
 
-template <int DT, int NT>
+template <int NT>
 struct DirectState {                            // of one wavefront
   float a, lane_max, tau;                       // a: reference of the sums, the wave's largest logit so far (uniform)
   double Z, S;
@@ -108,30 +108,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t segment_buffer(const uint4* ro
 }
 
 // Logits of a tile that the segment does not have read as -inf: chunks past its end, the padding of the row's last chunk.
-template <int DT, int NT>
+template <int NT>
 __device__ __forceinline__ void blank_tile(uint4 (&q)[DIRECT_CHUNKS], const Segment& sg, int first) {
-  constexpr uint32_t NONE = DT == 1 ? 0xff80ff80u : 0xff800000u;
 #pragma unroll
   for (int c = 0; c < DIRECT_CHUNKS; ++c) {
     const int g = first + c * NT + (int)threadIdx.x;
-    const int nv = g >= sg.ncell ? 0 : sg.c0 + g == sg.tail_chunk ? sg.tail_valid : LogitTraits<DT>::EPC;
+    const int nv = g >= sg.ncell ? 0 : sg.c0 + g == sg.tail_chunk ? sg.tail_valid : LogitTraits<0>::EPC;
     uint32_t w[4] = {q[c].x, q[c].y, q[c].z, q[c].w};
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (DT == 1) {
-        if (2 * j >= nv) w[j] = NONE;
-        else if (2 * j + 1 >= nv) w[j] = (w[j] & 0xffffu) | (NONE & 0xffff0000u);
-      } else if (j >= nv) w[j] = NONE;
-    }
+    for (int j = 0; j < 4; ++j) if (j >= nv) w[j] = 0xff800000u;       // -inf
     q[c] = make_uint4(w[0], w[1], w[2], w[3]);
   }
 }
 
 // One tile: sums, and the logits that reach the bound.  t: the tile's number.
-template <int DT, int NT>
+template <int NT>
 __device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int t, const Segment& sg, int V, int K,
-                                            DirectState<DT, NT>& s, DirectShared<NT>& sh, const SelectLds& sel) {
-  typedef LogitTraits<DT> T;
+                                            DirectState<NT>& s, DirectShared<NT>& sh, const SelectLds& sel) {
+  typedef LogitTraits<0> T;
   const int tid = threadIdx.x;
   float cm[DIRECT_CHUNKS];
 #pragma unroll
@@ -206,10 +200,10 @@ __device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int
 constexpr int LIST_RANK_MAX = 512, UNSETTLED = RANKED_IN_RR;
 template <int NT> using DirectSharedLds = __attribute__((address_space(3))) DirectShared<NT>*;
 typedef __attribute__((address_space(3))) unsigned char* LdsBytes;
-template <int DT, int NT>
+template <int NT>
 __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsBytes lds, int list_cap, int cell_cap,
                                         DirectSharedLds<NT> shl) {
-  typedef LogitTraits<DT> T;
+  typedef LogitTraits<0> T;
   const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
   const int K = uniform(top_k);
   const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
@@ -287,14 +281,14 @@ __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, i
   }
   const int n_elems = sg.tail_chunk >= 0 ? (sg.ncell - 1) * T::EPC + sg.tail_valid : sg.ncell * T::EPC, need = min(K, n_elems) - n;
   if (need > 0 && !sh.bad) {
-    tie_scan<DT, NT>(rowp, sg, V, tie, need, sel, &sh.n_list, sh.scan_tmp);
+    tie_scan<0, NT>(rowp, sg, V, tie, need, sel, &sh.n_list, sh.scan_tmp);
     n += need;
   }
   return n;
 }
 
 // One segment, by a whole workgroup.  The per-wave sums stay in `sh` (see combine_waves).
-template <int DT, int NT>
+template <int NT>
 __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ rowp, int V, int K, const Segment& sg,
                                                      const SelectLds& sel, const ClassifierStage cst, DirectShared<NT>& sh, RowResult* rr) {
   constexpr int TILE = DIRECT_CHUNKS * NT;
@@ -310,18 +304,18 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
 #pragma unroll
     for (int c = 0; c < DIRECT_CHUNKS; ++c) q[c] = load_stream_buffer(rs, vo, (uint32_t)(t * DIRECT_CHUNKS + c) * (NT * 16u));
   };
-  DirectState<DT, NT> s;
+  DirectState<NT> s;
   s.a = s.lane_max = -INFINITY; s.Z = s.S = 0.0; s.bad = false;
   s.tau = -3.402823466e38f;                                  // the lowest finite value: masked logits (-inf) are not listed
   load(qa, 0);
   if (n_tiles > 1) load(qb, 1);
   for (int t = 0; t < n_tiles; t += 2) {
-    if ((t + 1) * TILE > n_whole) blank_tile<DT, NT>(qa, sg, t * TILE);
-    direct_tile<DT, NT>(qa, t, sg, V, K, s, sh, sel);
+    if ((t + 1) * TILE > n_whole) blank_tile<NT>(qa, sg, t * TILE);
+    direct_tile<NT>(qa, t, sg, V, K, s, sh, sel);
     if (t + 1 >= n_tiles) break;
     if (t + 2 < n_tiles) load(qa, t + 2);
-    if ((t + 2) * TILE > n_whole) blank_tile<DT, NT>(qb, sg, (t + 1) * TILE);
-    direct_tile<DT, NT>(qb, t + 1, sg, V, K, s, sh, sel);
+    if ((t + 2) * TILE > n_whole) blank_tile<NT>(qb, sg, (t + 1) * TILE);
+    direct_tile<NT>(qb, t + 1, sg, V, K, s, sh, sel);
     if (t + 3 < n_tiles) load(qb, t + 3);
   }
   C2T_PT(PT_STREAM_END);
@@ -332,8 +326,8 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   __syncthreads();
   C2T_PT(PT_HIST_COMPLETE);
   int n_el = sh.n_list;
-  if (n_el > 2 * WAVE || n_el < K) n_el = settle_list<DT, NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, sel.cell_cap, (DirectSharedLds<NT>)&sh);
-  if (n_el == UNSETTLED) generic_segment<DT, NT, DIRECT_CPC>(rowp, V, K, 0, sg, sel.list, sel, rr, 0u);   // (its cell map overlays the list)
+  if (__builtin_expect(n_el > 2 * WAVE || n_el < K, 0)) n_el = settle_list<NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, sel.cell_cap, (DirectSharedLds<NT>)&sh);
+  if (__builtin_expect(n_el == UNSETTLED, 0)) generic_segment<0, NT>(rowp, V, K, 0, sg, sel.list, sel, rr, 0u);   // (its cell map overlays the list)
   return SegmentTop{n_el, false};
 }
 // The segment's record from the wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.
@@ -363,11 +357,11 @@ __device__ __forceinline__ void combine_waves(const DirectShared<NT>& sh, RowRes
 
 // grid: rows_launched * nsplit workgroups of NT threads.
 // Dynamic LDS (sp.lds_bytes): the list of the selection, over the cell map of generic_segment (cps keys); reused by the tail.
-template <int DT, int NT>
+template <int NT>
 __global__ __launch_bounds__(NT, 4) void k_logits_direct(
     const void* __restrict__ logits, int64_t row_stride_elems, int V, int cps, const float* __restrict__ cls,
     TreeState st, ScoreParams sp) {
-  typedef LogitTraits<DT> T;
+  typedef LogitTraits<0> T;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   touch_kernel_arguments<32 + (int)sizeof(TreeState) + (int)sizeof(ScoreParams)>();
   const int nsplit = sp.nsplit, K = sp.K;
@@ -376,13 +370,13 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
   const int b = rw.b, f = rw.f, rl = b * sp.rows_per_seq + f, nf = rw.nf;
   if (f >= nf) { if (nf == 0) end_of_sequence(st, sp, b, f, split); return; }   // uniform for the workgroup
   const int64_t row = (int64_t)b * sp.F + f;
-  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_elems * (DT == 1 ? 2 : 4));
+  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_elems * 4);
   const Segment sg = make_segment<T::EPC>(V, split, cps);
   __shared__ RowResult rr;
   C2T_PT(PT_START);
   __shared__ DirectShared<NT> sh;
-  const ClassifierStage cst = stage_classifier(cls, sp.h, sp.w_lds_off >= 0 ? (float*)(dyn_lds + sp.w_lds_off) : nullptr);
-  const SelectLds sel = make_select_lds<NT, DIRECT_CPC, T::EPC>(dyn_lds, sp.lds_bytes);
+  const ClassifierStage cst = stage_classifier(cls, sp.h, (float*)(dyn_lds + sp.w_lds_off));
+  const SelectLds sel = make_select_lds<NT, T::EPC>(dyn_lds, sp.lds_bytes);
   SegmentTop top{RANKED_IN_RR, false};
   bool have_record = true;                                 // (uniform) rr.part is complete
   if (sg.ncell == 0) {
@@ -390,10 +384,10 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
     if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
     __syncthreads();
   } else {
-    top = direct_segment<DT, NT>(rowp, V, K, sg, sel, cst, sh, &rr);
+    top = direct_segment<NT>(rowp, V, K, sg, sel, cst, sh, &rr);
     have_record = top.n_el < 0;
   }
-  const auto top_m = [&](RowResult& r) { top_m_of_split_row<DT, NT>(rowp, V, sp.M, r); };
+  const auto top_m = [&](RowResult& r) { top_m_of_whole_row<0, NT>(rowp, V, sp.M, r); };
   if (nsplit == 1 && sp.M > 0) {
     if (!have_record && threadIdx.x < WAVE) combine_waves(sh, rr);
     __syncthreads();

@@ -95,18 +95,16 @@ __device__ __forceinline__ Segment make_segment(int V, int split, int cps) {
   return s;
 }
 
-// Cells of a segment of n chunks.  CPC = 4: sweep s of the workgroup reads chunks [s*NT, (s+1)*NT);
+// Cells of a segment of n chunks, CPC chunks each: sweep s of the workgroup reads chunks [s*NT, (s+1)*NT);
 // cell (s/4)*NT + t holds the chunks that lane t reads in sweeps 4*(s/4) .. 4*(s/4)+3.
-template <int NT, int CPC>
+template <int NT>
 __host__ __device__ inline int cells_in_segment(int n) {
-  if (CPC == 1) return n;
   const int full = n / (4 * NT), rem = n - full * 4 * NT;
   return full * NT + (rem < NT ? rem : NT);
 }
 // chunk j (0 <= j < CPC) of a cell, as an index into the segment; may lie past its end
-template <int NT, int CPC>
+template <int NT>
 __device__ __forceinline__ int chunk_of_cell(int cell, int j) {
-  if (CPC == 1) return cell;
   const int grp = cell / NT, t = cell - grp * NT;
   return grp * 4 * NT + j * NT + t;
 }
@@ -140,7 +138,7 @@ __device__ __forceinline__ int list_cells(const typename LogitTraits<DT>::key_t*
 // put a barrier after the last read of the map and after setting *sh_cnt = 0.  Ends with a barrier.
 // BY_WAVE: one addition to the counter a wavefront (append_places) instead of one per step and element: a workgroup alone on its
 // CU waits out fewer round trips (1.3 % of a phase), four a CU issue more instructions (0.6 % slower).
-template <int DT, int NT, int CPC, bool BY_WAVE>
+template <int DT, int NT, bool BY_WAVE>
 __device__ __forceinline__ void collect_cells(const uint4* __restrict__ rowp, int c0, int c1, int V, float tau, bool strict,
                                               const int32_t* cell_list, int n_cells, const SelectLds& sel, int32_t* sh_cnt) {
   typedef LogitTraits<DT> T;
@@ -150,7 +148,7 @@ __device__ __forceinline__ void collect_cells(const uint4* __restrict__ rowp, in
   int my_chunk = -1;
   uint4 q = make_uint4(0, 0, 0, 0);
   if (tid < n_cells * CPC) {                                 // n_cells <= cell_cap <= NT / CPC
-    const int ch = c0 + chunk_of_cell<NT, CPC>(cell_list[tid / CPC], tid % CPC);
+    const int ch = c0 + chunk_of_cell<NT>(cell_list[tid / CPC], tid % CPC);
     if (ch < c1) { my_chunk = ch; q = rowp[ch]; }
   }
   if (!BY_WAVE) {
@@ -329,12 +327,11 @@ __device__ __forceinline__ void top_m_sums(const uint4* __restrict__ rowp, const
   block_sum2<NT>(Z, S, red, out);
 }
 
-// A row that was split over several workgroups: the M largest logits of the ROW cannot be told from
-// the splits' own sums, so the workgroup that merged the row goes over the whole row once more
-// (five passes of one workgroup: a rare configuration, fp32 rows of more than 49152 logits or bf16
-// rows of more than 262144, with the entropy over the M largest).  Sums relative to the row maximum.
+// The sums over the M largest logits of a whole row, by one workgroup in five passes: every fp32 row with M > 0 (its one pass does
+// not find them), and rows that were split (they cannot be told from the splits' own sums), by the workgroup that merged the
+// row.  Sums relative to the row maximum.
 template <int DT, int NT>
-__device__ __forceinline__ void top_m_of_split_row(const uint4* __restrict__ rowp, int V, int M, RowResult& rr) {
+__device__ __forceinline__ void top_m_of_whole_row(const uint4* __restrict__ rowp, int V, int M, RowResult& rr) {
   if (M <= 0) return;
   __shared__ double red_t[2][NT / WAVE], sum_t[2];
   const bool usable = !(rr.part.flags & 1u) && rr.part.Z > 0.0 && rr.part.ref > -INFINITY && rr.part.ref < INFINITY;
@@ -349,15 +346,15 @@ __device__ __forceinline__ void top_m_of_split_row(const uint4* __restrict__ row
 }
 
 // map_lds: one key per cell.
-template <int DT, int NT, int CPC>
+template <int DT, int NT>
 __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int V, int K, int top_m, const Segment sg,
                                 unsigned char* map_lds, const SelectLds sel, RowResult* rr, uint32_t info_flags) {
   typedef LogitTraits<DT> T;
   typedef typename T::key_t key_t;
   constexpr int NW = NT / WAVE;
-  static_assert(CPC == 1 || CPC == 4, "a cell is one chunk or four sweeps of a lane");
+  static_assert(CPC == 4, "a cell is four sweeps of a lane");
   key_t* map = (key_t*)map_lds;
-  const int ncells = cells_in_segment<NT, CPC>(sg.ncell);
+  const int ncells = cells_in_segment<NT>(sg.ncell);
   __shared__ double red_d[2][NW], sum_d[2], sum_m[2];
   __shared__ float red_f[NW];
   __shared__ uint32_t lane_keys[NT];
@@ -385,11 +382,8 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
       if (j < nv) { bad |= !(x[j] < INFINITY); cm = fmaxf(cm, x[j]); }
     }
     M = fmaxf(M, cm);
-    if (CPC == 1) map[g - sg.c0] = T::to_key(cm);
-    else {
-      cell_max = fmaxf(cell_max, cm);
-      if ((sweep & 3) == 3 || g + NT >= sg.c1) { map[(sweep >> 2) * NT + tid] = T::to_key(cell_max); cell_max = -INFINITY; }
-    }
+    cell_max = fmaxf(cell_max, cm);
+    if ((sweep & 3) == 3 || g + NT >= sg.c1) { map[(sweep >> 2) * NT + tid] = T::to_key(cell_max); cell_max = -INFINITY; }
     any = true;
   }
   lane_keys[tid] = any ? sortable_key(M) : 0u;
@@ -476,7 +470,7 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
   if (tid == 0) sh_cnt = 0;
   __syncthreads();
   C2T_PT(PT_CELLS_LISTED);
-  collect_cells<DT, NT, CPC, true>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
+  collect_cells<DT, NT, true>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
   if (ties) tie_scan<DT, NT>(rowp, sg, V, tau, K, sel, &sh_cnt, scan_tmp);
   C2T_PT(PT_CELLS_READ);
   const int n_el = min(sh_cnt, sel.list_cap), n_top = min(n_el, K);
@@ -568,7 +562,6 @@ __device__ __forceinline__ RowOfWorkgroup row_of_workgroup(const TreeState& st, 
 // ---------------------------------------------------------------------------------------
 constexpr int HP_BINS = 8192;                 // sign(1) | exponent mod 32 (5) | mantissa (7)
 constexpr int HP_WORDS = HP_BINS / 2;         // LDS words: low half counts +|v|, high half counts -|v|
-constexpr int HP_CPC = 4;                     // chunks per cell of the map: four sweeps of a lane
 constexpr uint32_t HP_MAG_LO = 102u << 7;     // |x| >= 2^-25
 constexpr uint32_t HP_MAG_SPAN = 32u << 7;    // 32 binades: |x| < 2^7
 constexpr uint32_t HP_WORD_ROT = HP_MAG_LO & (HP_WORDS - 1);   // word of magnitude index i: (i + ROT) mod 4096
@@ -676,6 +669,7 @@ struct OutsideAcc {
                                     // wavefront adds to word l, in the half a negative value's count goes to (folded into n_masked)
 };
 typedef __attribute__((address_space(3))) OutsideAcc* OutsideAccLds;
+typedef __attribute__((address_space(3))) uint32_t* LdsWords;
 
 // Chunks that hold a logit outside the window, and a row's partial last chunk (n_valid < 8).  Out
 // of line: typical rows never get here, and inlined at each of the streaming loop's sites this
@@ -710,7 +704,6 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
       // lane's own word of masked_by_lane instead of the histogram (one address select per logit: no
       // branches, no ballots, and the 64 words lie in 64 different places, so masked logits pile up nowhere).
       // The stand-in value is negative, so the count lands in the word's upper half.
-      typedef __attribute__((address_space(3))) uint32_t* LdsWords;
       const LdsWords own = &acc->masked_by_lane[lane_id()], hl = (LdsWords)hist;   // LDS addresses: the selects stay 32-bit, the atomics ds_add
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -785,7 +778,6 @@ __device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uin
 // not swallow, codes in (-2^10, -2^7] and negative NaN, shows in `seen` (packed maximum of the codes, packed minimum of
 // codes - 0xC300), which the caller looks at once per row.
 struct CodesSeen { uint32_t hi, lo; };
-typedef __attribute__((address_space(3))) uint32_t* LdsWords;
 __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& M2, LdsWords hist, LdsWords own, OutsideAcc* acc, CodesSeen& seen) {
   constexpr uint32_t TWO2 = 0x00020002u, BIAS2 = ((0x10000u - 2u * HP_MAG_LO) & 0xffffu) * 0x00010001u;
   constexpr uint32_t LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1), FIRST_MASKED = 0xC480u;       // see hp_masked
@@ -933,8 +925,8 @@ __device__ __forceinline__ bool share_row(const ScoreParams& sp, int split, int6
     const c2t_uint4v u0 = {t0.x, t0.y, t0.z, t0.w}, u1 = {t1.x, t1.y, t1.z, t1.w};
     __builtin_amdgcn_raw_buffer_store_b128(u0, rh, w0 * 4u, (uint32_t)split * SLOT_BYTES, COHERENT);
     __builtin_amdgcn_raw_buffer_store_b128(u1, rh, w0 * 4u + 16u, (uint32_t)split * SLOT_BYTES, COHERENT);
-    const int ncells = cells_in_segment<NT, HP_CPC>(sg.ncell);
-    const uint32_t first_key_byte = (uint32_t)sg.c0 / HP_CPC * 2u;     // sg.c0 is a multiple of HP_CPC * NT chunks
+    const int ncells = cells_in_segment<NT>(sg.ncell);
+    const uint32_t first_key_byte = (uint32_t)sg.c0 / CPC * 2u;        // sg.c0 is a multiple of CPC * NT chunks
     for (int i = tid * 8; i < ncells; i += NT * 8) {                    // (a store that reaches past the row's keys is dropped by the bounds check)
       const uint4 k = *(const uint4*)(map + i);
       const c2t_uint4v kv = {k.x, k.y, k.z, k.w};
@@ -1314,7 +1306,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       (n_ninf > 0 && sh_tau_rank < 0) ||
       (TOPM && n_tiny > 0 && tot_p < M && M < tot_p + n_tiny)) {
     __syncthreads();
-    generic_segment<1, NT, HP_CPC>(rowp, V, K, M, sg, map_lds, sel, rr, 2u);
+    generic_segment<1, NT>(rowp, V, K, M, sg, map_lds, sel, rr, 2u);
     return SegmentTop{RANKED_IN_RR, false};
   }
   if (TOPM) {
@@ -1365,7 +1357,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   // ---------------- cells that can hold a top-K element ----------------
   // Fewer than K cells exceed tau; cells equal to tau are all taken when they fit (the exact
   // ranking below keeps the lowest ids).
-  const int ncells = cells_in_segment<NT, HP_CPC>(sg.ncell);
+  const int ncells = cells_in_segment<NT>(sg.ncell);
   if (WPS == 8) {                                        // (see collect_cells)
 #pragma unroll 1
     for (int c8 = tid * 8; c8 < ncells; c8 += NT * 8) {  // eight keys per read (the map is padded to 16 bytes)
@@ -1420,7 +1412,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     if (lane == 0) { RowPartial r; r.ref = (double)m; r.a = 0.0; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = 0; r.flags = 0u; rr->part = r; }
     if (entropy) row_entropy(st, sp, b, slot, (double)m, 0.0, sum_d[0], sum_d[1], 0u, *rr);
   }
-  collect_cells<1, NT, HP_CPC, WPS != 8>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
+  collect_cells<1, NT, WPS != 8>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
   if (ties) {
     tie_scan<1, NT>(rowp, sg, V, tau, eq_limit, sel, &sh_cnt, scan_tmp);
     __syncthreads();
@@ -1452,8 +1444,8 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
   C2T_PT(PT_START);
   // The classifier's parameters (5h+1 <= 1281 floats) are copied to LDS for the scoring step: the
   // loads are issued now, four floats a thread, and stored behind the streaming loop.
-  const ClassifierStage cst = stage_classifier(cls, sp.h, (!TOPM && sp.w_lds_off >= 0) ? (float*)(dyn_lds + sp.w_lds_off) : nullptr);
-  const SelectLds sel = make_select_lds<NT, HP_CPC, 8>(dyn_lds, sp.lds_bytes);
+  const ClassifierStage cst = stage_classifier(cls, sp.h, TOPM ? nullptr : (float*)(dyn_lds + sp.w_lds_off));
+  const SelectLds sel = make_select_lds<NT, 8>(dyn_lds, sp.lds_bytes);
   SegmentTop top{RANKED_IN_RR, false};
   if (sg.ncell == 0) {                                     // (loaded again here: the copy above must not stay in registers for this)
     store_classifier(stage_classifier(cls, sp.h, cst.dst));
@@ -1465,7 +1457,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
   finish_layer<NT, false>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst, [] {},
-                   [&](RowResult& r) { if (TOPM) top_m_of_split_row<1, NT>(rowp, V, sp.M, r); });
+                   [&](RowResult& r) { if (TOPM) top_m_of_whole_row<1, NT>(rowp, V, sp.M, r); });
 }
 
 // Plain streaming read: the practical HBM ceiling.

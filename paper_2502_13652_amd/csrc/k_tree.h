@@ -159,7 +159,7 @@ struct ScoreParams {
   int nsplit, rows_per_seq, B, F, K, N, h, layer, D;
   int M;                                                     // 0: entropy over the whole row; M > 0: over the M largest logits
   int lds_bytes;                                             // dynamic LDS of the launch
-  int w_lds_off;                                             // byte offset of the classifier's copy in dynamic LDS, -1: none
+  int w_lds_off;                                             // byte offset of the classifier's copy in dynamic LDS
   int compact;                                               // 1: workgroup w takes the w-th live row (see row_of_workgroup)
   uint32_t k_inverse;                                        // ceil(2^20 / K): (i * k_inverse) >> 20 is i / K for i < 2048, K <= 64
   int spread_min;                                            // hidden units from which on the whole workgroup evaluates the classifier
@@ -199,6 +199,7 @@ __device__ __forceinline__ int sum_of_lanes(int tshift, int v) {
 // LDS of the selection of a segment's (or a row's) K largest logits: the element list ((value, id), 8 bytes an
 // entry, overlaying histogram and cell map) and the number of cells a launch may keep:
 // min(SEL_CELL_CAP, NT / CPC, list entries / elements per cell), which the host keeps >= 2K - 1.
+constexpr int CPC = 4;                         // chunks per cell of the cell map: four sweeps of a lane
 constexpr int SEL_CELL_CAP = 256;              // size of the candidate-cell list
 struct SelectLds {
   unsigned char* list;
@@ -207,7 +208,7 @@ struct SelectLds {
   __device__ __forceinline__ float* values() const { return (float*)list; }
   __device__ __forceinline__ int32_t* ids() const { return (int32_t*)(list + (size_t)list_cap * 4); }
 };
-template <int NT, int CPC, int EPC>
+template <int NT, int EPC>
 __device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int bytes) {
   SelectLds s;
   s.list = base; s.list_cap = bytes / 8;
