@@ -810,7 +810,7 @@ __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& 
 
 // The streaming loop of such a row: `whole` chunks from `base` and, with tail_valid > 0, a partial one behind them.  Out of
 // line, so that rows that mask nothing keep their registers.  Returns the packed maximum.
-// A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 43 us when every chunk took hist_chunk_outside, 37.
+// A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 41 us when every chunk took hist_chunk_outside, 30.
 template <int NT>
 __device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, LdsWords hist,
                                                     __attribute__((address_space(3))) uint16_t* keys, OutsideAcc* acc) {
