@@ -564,7 +564,6 @@ constexpr int HP_BINS = 8192;                 // sign(1) | exponent mod 32 (5) |
 constexpr int HP_WORDS = HP_BINS / 2;         // LDS words: low half counts +|v|, high half counts -|v|
 constexpr uint32_t HP_MAG_LO = 102u << 7;     // |x| >= 2^-25
 constexpr uint32_t HP_MAG_SPAN = 32u << 7;    // 32 binades: |x| < 2^7
-constexpr uint32_t HP_WORD_ROT = HP_MAG_LO & (HP_WORDS - 1);   // word of magnitude index i: (i + ROT) mod 4096
 constexpr uint32_t HP_F16_NEG_INF2 = 0xFC00FC00u;              // identity of the packed maximum
 
 // value-ordered rank r in [0, 8192): larger r = larger value.  r -> bf16 code.
@@ -631,17 +630,31 @@ __device__ __forceinline__ uint32_t pk_mad_u16(uint32_t a, uint32_t b_sgpr, uint
   asm("v_pk_mad_u16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "s"(b_sgpr), "v"(c));
   return d;
 }
-// bits 16..27 of w: the histogram word of the upper bf16 (written out because the compiler turns the
-// bit-field extract into shift, mask and a separate add of the array base: one instruction more)
-__device__ __forceinline__ uint32_t bits_16_27(uint32_t w) {
+// (lower, upper 16 bits of a) * 2 + base, one instruction: the LDS address of a histogram word from twice its index.
+// UNIFORM: base is the same for every lane
+template <bool UNIFORM>
+__device__ __forceinline__ uint32_t twice_lower(uint32_t a, uint32_t base) {
   uint32_t d;
-  asm("v_bfe_u32 %0, %1, 16, 12" : "=v"(d) : "v"(w));
+  if (UNIFORM) asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(d) : "v"(a), "s"(base));
+  else asm("v_mad_u32_u16 %0, %1, 2, %2" : "=v"(d) : "v"(a), "v"(base));
   return d;
 }
-// mask ? 65536 : 1 for mask = 0 or ~0: the histogram increment of a negative / positive value
-__device__ __forceinline__ uint32_t hist_increment(int32_t sign_mask, uint32_t c65536_sgpr) {
+template <bool UNIFORM>
+__device__ __forceinline__ uint32_t twice_upper(uint32_t a, uint32_t base) {
   uint32_t d;
-  asm("v_bfi_b32 %0, %1, %2, 1" : "=v"(d) : "v"(sign_mask), "s"(c65536_sgpr));
+  if (UNIFORM) asm("v_mad_u32_u16 %0, %1, 2, %2 op_sel:[1,0,0,0]" : "=v"(d) : "v"(a), "s"(base));
+  else asm("v_mad_u32_u16 %0, %1, 2, %2 op_sel:[1,0,0,0]" : "=v"(d) : "v"(a), "v"(base));
+  return d;
+}
+// the histogram increment of a positive value, 1, or of a negative one, 65536, from its sign (0 or 1) in the lower or upper half
+__device__ __forceinline__ uint32_t increment_lower(uint32_t signs, uint32_t c65535_sgpr) {
+  uint32_t d;
+  asm("v_mad_u32_u16 %0, %1, %2, 1" : "=v"(d) : "v"(signs), "s"(c65535_sgpr));
+  return d;
+}
+__device__ __forceinline__ uint32_t increment_upper(uint32_t signs, uint32_t c65535_sgpr) {
+  uint32_t d;
+  asm("v_mad_u32_u16 %0, %1, %2, 1 op_sel:[1,0,0,0]" : "=v"(d) : "v"(signs), "s"(c65535_sgpr));
   return d;
 }
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
@@ -653,6 +666,9 @@ __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
 
 __device__ __forceinline__ uint32_t pk_sub_sat_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(c2t_ushort2, a), __builtin_bit_cast(c2t_ushort2, b)));
+}
+__device__ __forceinline__ uint32_t pk_shr_u16(uint32_t a, int n) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(c2t_ushort2, a) >> (unsigned short)n);
 }
 __device__ __forceinline__ uint32_t pk_sub_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_bit_cast(c2t_ushort2, a) - __builtin_bit_cast(c2t_ushort2, b));
@@ -670,6 +686,17 @@ struct OutsideAcc {
 };
 typedef __attribute__((address_space(3))) OutsideAcc* OutsideAccLds;
 typedef __attribute__((address_space(3))) uint32_t* LdsWords;
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p; }
+__device__ __forceinline__ void lds_add(uint32_t address, uint32_t v) {
+  __hip_atomic_fetch_add((LdsWords)(uintptr_t)address, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// Of two packed bf16 codes w, d = 2 |code| - 2 LO (mod 2^16), with the sign shifted out by the doubling: the value lies in the
+// window iff d < 2 SPAN = 8192, i.e. iff bits 13..15 of d are clear; then d is twice the index of its histogram word.
+constexpr uint32_t HP_OUTSIDE2 = 0xE000E000u;
+static_assert(2 * HP_MAG_SPAN == 8192 && HP_WORDS == 4096, "window test and index");
+__device__ __forceinline__ uint32_t twice_index(uint32_t w) {
+  return pk_mad_u16(w, 0x00020002u, ((0x10000u - 2u * HP_MAG_LO) & 0xffffu) * 0x00010001u);
+}
 
 // Chunks that hold a logit outside the window, and a row's partial last chunk (n_valid < 8).  Out
 // of line: typical rows never get here, and inlined at each of the streaming loop's sites this
@@ -683,34 +710,33 @@ typedef __attribute__((address_space(3))) uint32_t* LdsWords;
 // exactly 0 in fp64 (which underflows to 0 below -745.2): such a logit adds nothing to Z or S, and
 // it ranks after every window value.  NaN codes (above 0xff80) are not in the range.
 __device__ __forceinline__ bool hp_masked(uint32_t code16) { return code16 - 0xc480u <= 0xff80u - 0xc480u; }
-__device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32_t* __restrict__ hist, OutsideAcc* acc_generic) {
-  constexpr uint32_t TWO2 = 0x00020002u, BIAS2 = ((0x10000u - 2u * HP_MAG_LO) & 0xffffu) * 0x00010001u;
+__device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32_t hist, OutsideAcc* acc_generic) {     // hist: LDS address
   constexpr uint32_t LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1);   // the lowest value of the window stands in for a masked logit
   const OutsideAccLds acc = (OutsideAccLds)acc_generic;
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
   if (n_valid == 8) {
     // codes from 0xC300 on are clamped to the window's lowest value; what must not be, codes in (-2^10, -2^7] and negative
     // NaN, shows in the packed extremes
-    uint32_t w2[4], dm = 0u, hi = 0u, lo = 0xffffffffu;
+    uint32_t w2[4], d[4], dm = 0u, hi = 0u, lo = 0xffffffffu;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       hi = pk_max_u16(hi, w[j]);
       lo = pk_min_u16(lo, pk_sub_u16(w[j], 0xC300C300u));
       w2[j] = pk_min_u16(w[j], LOWEST * 0x00010001u);
-      dm = pk_max_u16(dm, pk_mad_u16(w2[j], TWO2, BIAS2));
+      d[j] = twice_index(w2[j]);
+      dm |= d[j];
     }
-    if (((dm & 0xE000E000u) | pk_sub_sat_u16(hi, 0xFF80FF80u) | pk_sub_sat_u16(0x01800180u, lo)) == 0u) {
+    if (((dm & HP_OUTSIDE2) | pk_sub_sat_u16(hi, 0xFF80FF80u) | pk_sub_sat_u16(0x01800180u, lo)) == 0u) {
       // Every lane issues all eight atomics, as for a chunk inside the window; a masked logit's goes to the
       // lane's own word of masked_by_lane instead of the histogram (one address select per logit: no
       // branches, no ballots, and the 64 words lie in 64 different places, so masked logits pile up nowhere).
       // The stand-in value is negative, so the count lands in the word's upper half.
-      const LdsWords own = &acc->masked_by_lane[lane_id()], hl = (LdsWords)hist;   // LDS addresses: the selects stay 32-bit, the atomics ds_add
+      const uint32_t own = lds_address(&acc_generic->masked_by_lane[lane_id()]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const LdsWords a_hi = w[j] >= 0xC4800000u ? own : hl + bits_16_27(w2[j]);
-        const LdsWords a_lo = (uint16_t)w[j] >= (uint16_t)0xC480u ? own : hl + (w2[j] & (HP_WORDS - 1));
-        __hip_atomic_fetch_add(a_hi, hist_increment((int32_t)w2[j] >> 31, 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(a_lo, hist_increment(__builtin_amdgcn_sbfe((int32_t)w2[j], 15, 1), 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t sg = pk_shr_u16(w2[j], 15);
+        lds_add(w[j] >= 0xC4800000u ? own : twice_upper<false>(d[j], hist), increment_upper(sg, 0xffffu));
+        lds_add((uint16_t)w[j] >= (uint16_t)0xC480u ? own : twice_lower<false>(d[j], hist), increment_lower(sg, 0xffffu));
       }
       return pk_max_f16(pk_max_f16(w2[0], w2[1]), pk_max_f16(w2[2], w2[3]));
     }
@@ -729,7 +755,7 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
         mag_max = max(mag_max, mag);
         cm = fmaxf(cm, x);
         if (mag < HP_MAG_LO) { n_tiny += 1; s_tiny += (double)x; }
-        else atomicAdd(&hist[code & (HP_WORDS - 1)], (code & 0x8000u) ? 0x10000u : 1u);
+        else lds_add(hist + 4u * ((mag - HP_MAG_LO) & (HP_WORDS - 1)), (code & 0x8000u) ? 0x10000u : 1u);   // (above the window: counted anywhere, the row leaves this path)
       }
     }
   }
@@ -743,20 +769,17 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
   return c16 | (c16 << 16);
 }
 
-// Counts the values of a whole chunk; returns the chunk maximum as a packed pattern (both halves
-// <= max, one of them equal to it).
-__device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uint32_t* __restrict__ hist, OutsideAcc* acc) {
+// Counts the values of a whole chunk into the histogram at LDS address `hist`; returns the chunk maximum as a packed pattern (both
+// halves <= max, one of them equal to it).  32 vector instructions beside the eight additions: the address and the increment of a
+// value take one each (v_mad_u32_u16 picks its half, scales and adds the lane's base), the window test three a chunk beyond the indices.
+template <bool ONE_COPY>
+__device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uint32_t hist, OutsideAcc* acc) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-  // Per half d = 2 |code| - 2 LO (mod 2^16), with the sign shifted out by the doubling: the value
-  // lies in the window iff d < 2 SPAN = 8192, i.e. iff bits 13..15 of d are clear.
-  constexpr uint32_t TWO2 = 0x00020002u, BIAS2 = ((0x10000u - 2u * HP_MAG_LO) & 0xffffu) * 0x00010001u;
-  static_assert(2 * HP_MAG_SPAN == 8192 && HP_WORDS == 4096, "window test and 12-bit word index below");
-  const uint32_t dm = pk_max_u16(pk_max_u16(pk_mad_u16(w[0], TWO2, BIAS2), pk_mad_u16(w[1], TWO2, BIAS2)),
-                                 pk_max_u16(pk_mad_u16(w[2], TWO2, BIAS2), pk_mad_u16(w[3], TWO2, BIAS2)));
+  const uint32_t d[4] = {twice_index(w[0]), twice_index(w[1]), twice_index(w[2]), twice_index(w[3])};
   uint32_t pat;
   // rare: a logit outside the window.  The whole wave then takes the out-of-line routine (it counts
   // in-window chunks as well): cheaper than running both paths one after the other.
-  if (__builtin_amdgcn_ballot_w64((dm & 0xE000E000u) != 0u) != 0ull) {   // (a hint that this is rare made the loop 10 % slower)
+  if (__builtin_amdgcn_ballot_w64(((d[0] | d[1] | d[2] | d[3]) & HP_OUTSIDE2) != 0u) != 0ull) {   // (a hint that this is rare made the loop 10 % slower)
     pat = hist_chunk_outside(q, 8, hist, acc);
   } else {
     // inside the window bf16 bit patterns order exactly like fp16 bit patterns
@@ -764,8 +787,9 @@ __device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uin
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       // +1 into the low half for a positive value, into the high half for a negative one
-      atomicAdd(&hist[bits_16_27(w[j])], hist_increment((int32_t)w[j] >> 31, 0x10000u));
-      atomicAdd(&hist[w[j] & (HP_WORDS - 1)], hist_increment(__builtin_amdgcn_sbfe((int32_t)w[j], 15, 1), 0x10000u));
+      const uint32_t sg = pk_shr_u16(w[j], 15);
+      lds_add(twice_upper<ONE_COPY>(d[j], hist), increment_upper(sg, 0xffffu));
+      lds_add(twice_lower<ONE_COPY>(d[j], hist), increment_lower(sg, 0xffffu));
     }
   }
   M2 = pk_max_f16_raw(M2, pat);
@@ -778,8 +802,7 @@ __device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uin
 // not swallow, codes in (-2^10, -2^7] and negative NaN, shows in `seen` (packed maximum of the codes, packed minimum of
 // codes - 0xC300), which the caller looks at once per row.
 struct CodesSeen { uint32_t hi, lo; };
-__device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& M2, LdsWords hist, LdsWords own, OutsideAcc* acc, CodesSeen& seen) {
-  constexpr uint32_t TWO2 = 0x00020002u, BIAS2 = ((0x10000u - 2u * HP_MAG_LO) & 0xffffu) * 0x00010001u;
+__device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& M2, uint32_t hist, uint32_t own, OutsideAcc* acc, CodesSeen& seen) {
   constexpr uint32_t LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1), FIRST_MASKED = 0xC480u;       // see hp_masked
   const uint32_t raw[4] = {q.x, q.y, q.z, q.w};
   uint32_t w[4];
@@ -789,19 +812,17 @@ __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& 
     seen.lo = pk_min_u16(seen.lo, pk_sub_u16(raw[j], 0xC300C300u));
     w[j] = pk_min_u16(raw[j], LOWEST * 0x00010001u);
   }
-  const uint32_t dm = pk_max_u16(pk_max_u16(pk_mad_u16(w[0], TWO2, BIAS2), pk_mad_u16(w[1], TWO2, BIAS2)),
-                                 pk_max_u16(pk_mad_u16(w[2], TWO2, BIAS2), pk_mad_u16(w[3], TWO2, BIAS2)));
+  const uint32_t d[4] = {twice_index(w[0]), twice_index(w[1]), twice_index(w[2]), twice_index(w[3])};
   uint32_t pat;
-  if (__builtin_amdgcn_ballot_w64((dm & 0xE000E000u) != 0u) != 0ull) {
-    pat = hist_chunk_outside(q, 8, (uint32_t*)hist, acc);
+  if (__builtin_amdgcn_ballot_w64(((d[0] | d[1] | d[2] | d[3]) & HP_OUTSIDE2) != 0u) != 0ull) {
+    pat = hist_chunk_outside(q, 8, hist, acc);
   } else {
     pat = pk_max_f16_raw(pk_max_f16_raw(w[0], w[1]), pk_max_f16_raw(w[2], w[3]));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const LdsWords a_hi = raw[j] >= (FIRST_MASKED << 16) ? own : hist + bits_16_27(w[j]);
-      const LdsWords a_lo = (uint16_t)raw[j] >= (uint16_t)FIRST_MASKED ? own : hist + (w[j] & (HP_WORDS - 1));
-      __hip_atomic_fetch_add(a_hi, hist_increment((int32_t)w[j] >> 31, 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      __hip_atomic_fetch_add(a_lo, hist_increment(__builtin_amdgcn_sbfe((int32_t)w[j], 15, 1), 0x10000u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const uint32_t sg = pk_shr_u16(w[j], 15);
+      lds_add(raw[j] >= (FIRST_MASKED << 16) ? own : twice_upper<false>(d[j], hist), increment_upper(sg, 0xffffu));
+      lds_add((uint16_t)raw[j] >= (uint16_t)FIRST_MASKED ? own : twice_lower<false>(d[j], hist), increment_lower(sg, 0xffffu));
     }
   }
   M2 = pk_max_f16_raw(M2, pat);
@@ -812,13 +833,13 @@ __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& 
 // line, so that rows that mask nothing keep their registers.  Returns the packed maximum.
 // A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 41 us when every chunk took hist_chunk_outside, 30.
 template <int NT>
-__device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, LdsWords hist,
+__device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, uint32_t hist,
                                                     __attribute__((address_space(3))) uint16_t* keys, OutsideAcc* acc) {
   const uint64_t base_u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
                           ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32);
   const int whole = __builtin_amdgcn_readfirstlane(whole_chunks), tail = tail_valid > 0 ? whole : -1;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, (whole + (tail >= 0 ? 1 : 0)) * 16, 0x00020000);
-  const LdsWords own = (LdsWords)&((OutsideAccLds)acc)->masked_by_lane[lane_id()];
+  const uint32_t own = lds_address(&acc->masked_by_lane[lane_id()]);
   const int n = whole / (4 * NT);
   uint32_t M2 = HP_F16_NEG_INF2, so = 0u;
   uint4 q[4];
@@ -841,7 +862,7 @@ __device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chu
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (g + k * NT < whole) key = pk_max_f16_raw(key, hist_chunk_masked(q[k], M2, hist, own, acc, seen));
-      else if (g + k * NT == tail) key = pk_max_f16(key, hist_chunk_outside(q[k], tail_valid, (uint32_t*)hist, acc));
+      else if (g + k * NT == tail) key = pk_max_f16(key, hist_chunk_outside(q[k], tail_valid, hist, acc));
     }
     keys[n * NT] = (uint16_t)pk_max_f16(key, key >> 16);
     M2 = pk_max_f16(M2, key);
@@ -1054,8 +1075,8 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     // hold the same value (common: few hundred values carry most of a row) then add to different
     // words, which the LDS does not have to serialise.  The copies are folded after the loop.
     static_assert(REPL == 1 || REPL == 2 || REPL == 4 || REPL == 8, "a lane picks its copy with a mask");
-    uint32_t* __restrict__ histl = hist + (REPL > 1 ? (tid & (REPL - 1)) * HP_WORDS : 0);
-#define C2T_COUNT(q) hist_chunk(q, M2, histl, &sh_out)
+    const uint32_t histl = lds_address(hist) + (REPL > 1 ? (uint32_t)(tid & (REPL - 1)) * (HP_WORDS * 4u) : 0u);
+#define C2T_COUNT(q) hist_chunk<REPL == 1>(q, M2, histl, &sh_out)
     uint4 q[DEPTH];
 #pragma unroll
     for (int k = 0; k < DEPTH; ++k) q[k] = C2T_LOAD(k);
@@ -1084,7 +1105,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     }
     vo_after = vo;
     if (masks != 0) {                                    // (nothing of this path is live across the call: what is would be spilled for every row)
-      M2 = hist_stream_masked<NT>(base_u, whole, sg.tail_chunk >= 0 ? sg.tail_valid : 0, vo, (LdsWords)histl,
+      M2 = hist_stream_masked<NT>(base_u, whole, sg.tail_chunk >= 0 ? sg.tail_valid : 0, vo, histl,
                                   (__attribute__((address_space(3))) uint16_t*)mp, &sh_out);
       C2T_PT(PT_STREAM_END);
       __builtin_amdgcn_s_setprio(0);
@@ -1113,11 +1134,11 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     for (int c = 0; c < DEPTH / 4; ++c) {
       const int g = g0 + 4 * c * NT;
       if (g < c1 || g == tail) {
-        uint32_t key = g < c1 ? C2T_COUNT(q[4 * c]) : hist_chunk_outside(rowp[tail], sg.tail_valid, hist, &sh_out);
+        uint32_t key = g < c1 ? C2T_COUNT(q[4 * c]) : hist_chunk_outside(rowp[tail], sg.tail_valid, histl, &sh_out);
 #pragma unroll
         for (int k = 1; k < 4; ++k) {
           if (g + k * NT < c1) key = pk_max_f16_raw(key, C2T_COUNT(q[4 * c + k]));
-          else if (g + k * NT == tail) key = pk_max_f16(key, hist_chunk_outside(rowp[tail], sg.tail_valid, hist, &sh_out));
+          else if (g + k * NT == tail) key = pk_max_f16(key, hist_chunk_outside(rowp[tail], sg.tail_valid, histl, &sh_out));
         }
         mp[c * NT] = (uint16_t)pk_max_f16(key, key >> 16);
         M2 = pk_max_f16(M2, key);                         // the partial chunk's maximum is in no other running value
@@ -1159,7 +1180,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   double Z = 0.0, S = 0.0, Zp = 0.0, Sp = 0.0;
   int lane_pos = 0, lane_neg = 0;
   float vtop = -INFINITY;                               // value of the lane's highest non-empty bin
-  const uint32_t w0 = ((uint32_t)(WPL * tid) + HP_WORD_ROT) & (HP_WORDS - 1);   // the lane's words; WPL-aligned: no wrap inside
+  const uint32_t w0 = (uint32_t)(WPL * tid);            // the lane's words
   if (REPL > 1) {                                       // fold the copies into the first: only this lane touches these words
 #pragma unroll
     for (int j = 0; j < WPL; j += 4) {
