@@ -62,8 +62,6 @@ constexpr int SPLITS_F32 = 4, MAX_SPLITS_F32 = 8, SPLIT_CHUNKS_F32 = 2700, MERGE
 #ifndef C2T_COOP_MIN_GROUPS
 #define C2T_COOP_MIN_GROUPS 4
 #endif
-constexpr int COOP_MAX_WORKGROUPS = 256;       // workgroups of such a launch: one per CU at most
-constexpr int COOP_MAX_ROWS = COOP_MAX_WORKGROUPS / 2;
 constexpr int COOP_MAX_SHARE = C2T_COOP_MAX_SHARE;     // workgroups per row at most
 constexpr int COOP_MIN_GROUPS = C2T_COOP_MIN_GROUPS;   // shortest row that is shared, in groups of CPC sweeps (32 KB)
 constexpr int COOP_GROUP_CHUNKS = CPC * HP_NT;         // segments are whole groups: the row's cell map is then the segments' maps end to end
@@ -132,9 +130,9 @@ Layout make_layout(const c2t_config& c) {
   L.tab_e = take((size_t)HP_TAB_DOUBLES * 8);
   L.coop_hist = L.coop_map = L.coop_acc = 0; L.coop_map_stride = 0;
   if (c.logits_dtype == C2T_BF16 && min_splits(c) == 1 && (chunks_of(c) + COOP_GROUP_CHUNKS - 1) / COOP_GROUP_CHUNKS >= COOP_MIN_GROUPS) {
-    L.coop_map_stride = (cells_in_segment<HP_NT>(chunks_of(c)) + 7) / 8 * 8;
+    L.coop_map_stride = quad_cells_in_segment<HP_NT>(chunks_of(c));
     L.coop_hist = take((size_t)COOP_MAX_WORKGROUPS * HP_WORDS * 4);
-    L.coop_map = take((size_t)COOP_MAX_ROWS * L.coop_map_stride * 2);
+    L.coop_map = take((size_t)COOP_MAX_ROWS * L.coop_map_stride * 2 + (size_t)COOP_MAX_WORKGROUPS * WAVE * 4);
     L.coop_acc = take((size_t)COOP_MAX_WORKGROUPS * sizeof(CoopAcc));
   }
   L.fr_hidx = L.fr_s = L.h_tok = L.h_par = L.h_P = L.h_H = L.h_z = L.h_s = L.h_ncand = L.h_pos = 0;
@@ -231,10 +229,10 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   const int per_row = share.n > 1 ? share.n : nsplit;       // workgroups per row
   const int cps = share.n > 1 ? share.groups_each * COOP_GROUP_CHUNKS : (chunks_of(c) + nsplit - 1) / nsplit;
   // the cell map in LDS: the workgroup's segment; the whole row where rows are shared (the workgroup that finishes the row loads it)
-  const int cells = cells_in_segment<HP_NT>(share.n > 1 ? chunks_of(c) : cps);
+  const int cells = quad_cells_in_segment<HP_NT>(share.n > 1 ? chunks_of(c) : cps);   // (at least as many as generic_segment's)
   const size_t map_lds = ((size_t)cells * keybytes_of(c) + 15) / 16 * 16;
-  // element list of the selection: (2K-1) cells of CPC chunks, 8 bytes per element
-  const size_t list_lds = (size_t)(2 * c.top_k - 1) * CPC * epc_of(c) * 8;
+  // element list of generic_segment, over the map: (2K-1) cells of CPC chunks, 8 bytes per element
+  const size_t list_lds = (size_t)(2 * c.top_k - 1) * CPC * epc_of(c) * 8, generic_lds = std::max(map_lds, list_lds) + SEL_AUX_BYTES;
   const size_t score_lds = score_lds_bytes<HP_NT>(c.max_frontier * c.top_k);
   const unsigned grid = (unsigned)((int64_t)c.batch * rows_per_seq * per_row);
   ScoreParams sp;
@@ -257,7 +255,7 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
     const int64_t cus = x->n_cus;
     const bool four_per_cu = (int64_t)grid > cus;
     const int repl = four_per_cu ? 1 : HP_REPL_ALONE;       // copies of the histogram in LDS
-    const size_t lds_work = (std::max(std::max((size_t)HP_WORDS * 4 * repl + map_lds, list_lds), score_lds) + 15) / 16 * 16;
+    const size_t lds_work = (std::max(std::max(hist_lds_bytes<HP_NT>(repl) + std::max(map_lds, (size_t)HP_NT * 16), generic_lds), score_lds) + 15) / 16 * 16;
     sp.lds_bytes = (int)lds_work;
     sp.w_lds_off = (int)lds_work;                           // behind it: the classifier's parameters, padded to 16 bytes
     const size_t lds = lds_work + ((size_t)(5 * c.hidden + 1) * 4 + 15) / 16 * 16;
@@ -292,7 +290,7 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
 #undef C2T_LAUNCH_HIST_BUILD
 #undef C2T_LAUNCH_HIST
   } else {
-    const size_t lds_work = (std::max(std::max(std::max(map_lds, list_lds), score_lds), LIST_BYTES_F32) + 15) / 16 * 16;
+    const size_t lds_work = (std::max(std::max(generic_lds, score_lds), LIST_BYTES_F32 + SEL_AUX_BYTES) + 15) / 16 * 16;
     sp.lds_bytes = (int)lds_work;
     sp.w_lds_off = (int)lds_work;                           // the classifier's parameters, padded to 16 bytes
     const size_t lds = lds_work + ((size_t)(5 * c.hidden + 1) * 4 + 15) / 16 * 16;

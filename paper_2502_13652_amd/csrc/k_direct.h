@@ -198,12 +198,11 @@ __device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int
 // More than LIST_RANK_MAX logits above T lie in fewer than K lanes (of 512), which only rows with a period of 2048 logits have:
 // they are generic_segment's (UNSETTLED).
 // Returns the list's length.  Out of line: inlined, its code stood between the loop and the tail of every row (0.7 us a layer).
-constexpr int LIST_RANK_MAX = 512, UNSETTLED = RANKED_IN_RR;
+constexpr int LIST_RANK_MAX = 512;
 template <int NT> using DirectSharedLds = __attribute__((address_space(3))) DirectShared<NT>*;
 typedef __attribute__((address_space(3))) unsigned char* LdsBytes;
 template <int NT>
-__device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsBytes lds, int list_cap, int cell_cap,
-                                        DirectSharedLds<NT> shl) {
+__device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsBytes lds, int list_cap, DirectSharedLds<NT> shl) {
   typedef LogitTraits<0> T;
   const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
   const int K = uniform(top_k);
@@ -211,7 +210,7 @@ __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, i
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
   DirectShared<NT>& sh = *(DirectShared<NT>*)shl;
   SelectLds sel;
-  sel.list = (unsigned char*)lds; sel.list_cap = uniform(list_cap); sel.cell_cap = uniform(cell_cap);
+  sel.list = (unsigned char*)lds; sel.list_cap = uniform(list_cap); sel.aux = nullptr; sel.cell_cap = 0;
   float* el_v = sel.values();
   int32_t* el_i = sel.ids();
   int n = uniform(sh.n_list);
@@ -282,7 +281,7 @@ __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, i
   }
   const int n_elems = sg.tail_chunk >= 0 ? (sg.ncell - 1) * T::EPC + sg.tail_valid : sg.ncell * T::EPC, need = min(K, n_elems) - n;
   if (need > 0 && !sh.bad) {
-    tie_scan<0, NT>(rowp, sg, V, tie, need, sel, &sh.n_list, sh.scan_tmp);
+    tie_scan<0, NT>((int)threadIdx.x, rowp, sg, V, tie, need, sel, &sh.n_list, sh.scan_tmp);
     n += need;
   }
   return n;
@@ -320,16 +319,16 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
     if (t + 3 < n_tiles) load(qb, t + 3);
   }
   C2T_PT(PT_STREAM_END);
-  store_classifier(cst);                                     // published by the barriers below
+  store_classifier((int)threadIdx.x, cst);                                     // published by the barriers below
   s.Z = wave_sum(s.Z); s.S = wave_sum(s.S);
   if (lane == 0) { sh.wave_z[wid] = s.Z; sh.wave_s[wid] = s.S; sh.wave_a[wid] = s.a; }
   if (s.bad) sh.bad = 1;
   __syncthreads();
   C2T_PT(PT_HIST_COMPLETE);
   int n_el = sh.n_list;
-  if (__builtin_expect(n_el > 2 * WAVE || n_el < K, 0)) n_el = settle_list<NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, sel.cell_cap, (DirectSharedLds<NT>)&sh);
-  if (__builtin_expect(n_el == UNSETTLED, 0)) generic_segment<0, NT>(rowp, V, K, 0, sg, sel.list, sel, rr, 0u);   // (its cell map overlays the list)
-  return SegmentTop{n_el, false};
+  if (__builtin_expect(n_el > 2 * WAVE || n_el < K, 0)) n_el = settle_list<NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, (DirectSharedLds<NT>)&sh);
+  if (__builtin_expect(n_el == UNSETTLED, 0)) generic_segment<0, NT>((int)threadIdx.x, rowp, V, K, 0, sg, sel.list, sel, rr, 0u);   // (its cell map overlays the list)
+  return SegmentTop{n_el};
 }
 // The segment's record from the wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.
 template <int NT>
@@ -376,26 +375,27 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
   __shared__ RowResult rr;
   C2T_PT(PT_START);
   __shared__ DirectShared<NT> sh;
-  const ClassifierStage cst = stage_classifier(cls, sp.h, (float*)(dyn_lds + sp.w_lds_off));
+  const ClassifierStage cst = stage_classifier((int)threadIdx.x, cls, sp.h, (float*)(dyn_lds + sp.w_lds_off));
   const SelectLds sel = make_select_lds<NT, T::EPC>(dyn_lds, sp.lds_bytes);
-  SegmentTop top{RANKED_IN_RR, false};
+  SegmentTop top{RANKED_IN_RR};
   bool have_record = true;                                 // (uniform) rr.part is complete
   if (sg.ncell == 0) {
-    store_classifier(cst);
+    store_classifier((int)threadIdx.x, cst);
     if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
     __syncthreads();
   } else {
     top = direct_segment<NT>(rowp, V, K, sg, sel, cst, sh, &rr);
     have_record = top.n_el < 0;
   }
-  const auto top_m = [&](RowResult& r) { top_m_of_whole_row<0, NT>(rowp, V, sp.M, r); };
+  const auto top_m = [&](RowResult& r) { top_m_of_whole_row<0, NT>((int)threadIdx.x, rowp, V, sp.M, r, sel); };
   if (nsplit == 1 && sp.M > 0) {
     if (!have_record && threadIdx.x < WAVE) combine_waves(sh, rr);
     __syncthreads();
     have_record = true;
     top_m(rr);
   }
-  finish_layer<NT, true>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst,     // split records are indexed by launched row
+  const TailArguments& ta = tail_arguments<32>();
+  finish_layer<NT>((int)threadIdx.x, ta.st, ta.sp, b, f, nf, split, rl, rr, top, sel, sel, dyn_lds, cls, cst.dst,     // split records are indexed by launched row
                    [&] { if (!have_record) combine_waves(sh, rr); }, top_m);
 }
 

@@ -116,13 +116,13 @@ __device__ __forceinline__ int chunk_of_cell(int cell, int j) {
 // Cells whose key reaches tau (exceeds it, if strict) are pushed to cell_list, in any order.
 // Returns how many there are; if that is more than cell_cap the list is incomplete.
 template <int DT, int NT>
-__device__ __forceinline__ int list_cells(const typename LogitTraits<DT>::key_t* map, int ncells, float tau, bool strict,
+__device__ __forceinline__ int list_cells(int tid, const typename LogitTraits<DT>::key_t* map, int ncells, float tau, bool strict,
                                           int cell_cap, int32_t* cell_list, int32_t* sh_n) {
   typedef LogitTraits<DT> T;
-  if (threadIdx.x == 0) *sh_n = 0;
+  if (tid == 0) *sh_n = 0;
   __syncthreads();
 #pragma unroll 1
-  for (int c = threadIdx.x; c < ncells; c += NT) {
+  for (int c = tid; c < ncells; c += NT) {
     const float kv = T::from_key(map[c]);
     if (strict ? kv > tau : kv >= tau) {
       const int slot = atomicAdd(sh_n, 1);
@@ -136,13 +136,10 @@ __device__ __forceinline__ int list_cells(const typename LogitTraits<DT>::key_t*
 // Re-read the listed cells (CPC chunks each, one chunk per thread) and append their elements that
 // reach tau (exceed it, if strict) to the element list, which overlays the cell map: the caller has
 // put a barrier after the last read of the map and after setting *sh_cnt = 0.  Ends with a barrier.
-// BY_WAVE: one addition to the counter a wavefront (append_places) instead of one per step and element: a workgroup alone on its
-// CU waits out fewer round trips (1.3 % of a phase), four a CU issue more instructions (0.6 % slower).
-template <int DT, int NT, bool BY_WAVE>
-__device__ __forceinline__ void collect_cells(const uint4* __restrict__ rowp, int c0, int c1, int V, float tau, bool strict,
+template <int DT, int NT>
+__device__ __forceinline__ void collect_cells(int tid, const uint4* __restrict__ rowp, int c0, int c1, int V, float tau, bool strict,
                                               const int32_t* cell_list, int n_cells, const SelectLds& sel, int32_t* sh_cnt) {
   typedef LogitTraits<DT> T;
-  const int tid = threadIdx.x;
   float* el_v = sel.values();
   int32_t* el_i = sel.ids();
   int my_chunk = -1;
@@ -151,20 +148,7 @@ __device__ __forceinline__ void collect_cells(const uint4* __restrict__ rowp, in
     const int ch = c0 + chunk_of_cell<NT>(cell_list[tid / CPC], tid % CPC);
     if (ch < c1) { my_chunk = ch; q = rowp[ch]; }
   }
-  if (!BY_WAVE) {
-    if (my_chunk >= 0) {
-      float x[T::EPC];
-      T::unpack(q, x);
-#pragma unroll
-      for (int j = 0; j < T::EPC; ++j) {
-        const int id = my_chunk * T::EPC + j;
-        if (id < V && (strict ? x[j] > tau : x[j] >= tau)) {
-          const int slot = atomicAdd(sh_cnt, 1);
-          if (slot < sel.list_cap) { el_v[slot] = x[j]; el_i[slot] = id; }
-        }
-      }
-    }
-  } else if ((tid & ~(WAVE - 1)) < n_cells * CPC) {                 // wavefronts with a cell
+  if ((tid & ~(WAVE - 1)) < n_cells * CPC) {                 // wavefronts with a cell
     float x[T::EPC];
     T::unpack(q, x);
     uint32_t hit = 0u;
@@ -185,11 +169,11 @@ __device__ __forceinline__ void collect_cells(const uint4* __restrict__ rowp, in
 // Massive ties: append the `need` lowest-id elements equal to tau, found by sweeping the segment in
 // id order (one chunk per thread and sweep, prefix counts across the workgroup) until enough are seen.
 template <int DT, int NT>
-__device__ __forceinline__ void tie_scan(const uint4* __restrict__ rowp, const Segment& sg, int V, float tau, int need,
+__device__ __forceinline__ void tie_scan(int tid, const uint4* __restrict__ rowp, const Segment& sg, int V, float tau, int need,
                                          const SelectLds& sel, int32_t* sh_cnt, int32_t (*scan_tmp)[NT / WAVE]) {
   typedef LogitTraits<DT> T;
   constexpr int NW = NT / WAVE;
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
+  const int lane = tid & (WAVE - 1), wid = tid >> 6;
   float* el_v = sel.values();
   int32_t* el_i = sel.ids();
   int found = 0;                                             // uniform
@@ -225,12 +209,12 @@ __device__ __forceinline__ void tie_scan(const uint4* __restrict__ rowp, const S
 // Only thread 0 needs the totals: it leaves them in out[0..1] (LDS), so no lane keeps the
 // per-wave partials alive in registers.
 template <int NT>
-__device__ __forceinline__ void block_sum2(double Z, double S, double (*red)[NT / WAVE], double* out) {
+__device__ __forceinline__ void block_sum2(int tid, double Z, double S, double (*red)[NT / WAVE], double* out) {
   constexpr int NW = NT / WAVE;
   Z = wave_sum(Z); S = wave_sum(S);
-  if ((threadIdx.x & (WAVE - 1)) == 0) { red[0][threadIdx.x >> 6] = Z; red[1][threadIdx.x >> 6] = S; }
+  if ((tid & (WAVE - 1)) == 0) { red[0][tid >> 6] = Z; red[1][tid >> 6] = S; }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     double tz = 0.0, ts = 0.0;
 #pragma unroll 1
     for (int w = 0; w < NW; ++w) { tz += red[0][w]; ts += red[1][w]; }
@@ -238,11 +222,11 @@ __device__ __forceinline__ void block_sum2(double Z, double S, double (*red)[NT 
   }
 }
 template <int NT>
-__device__ __forceinline__ float block_max(float v, float* red /*[NT/WAVE]*/) {
+__device__ __forceinline__ float block_max(int tid, float v, float* red /*[NT/WAVE]*/) {
   constexpr int NW = NT / WAVE;
   v = wave_max(v);
   __syncthreads();
-  if ((threadIdx.x & (WAVE - 1)) == 0) red[threadIdx.x >> 6] = v;
+  if ((tid & (WAVE - 1)) == 0) red[tid >> 6] = v;
   __syncthreads();
   float t = red[0];
 #pragma unroll
@@ -259,12 +243,11 @@ __device__ __forceinline__ float block_max(float v, float* red /*[NT/WAVE]*/) {
 // (an LDS histogram of the digit among the elements that match the prefix so far); one more pass
 // sums the terms above it.  out[0..1] in LDS, valid after the caller's next barrier.
 template <int DT, int NT>
-__device__ __forceinline__ void top_m_sums(const uint4* __restrict__ rowp, const Segment& sg, int M, float m,
-                                           double (*red)[NT / WAVE], double* out) {
+__device__ __forceinline__ void top_m_sums(int tid, const uint4* __restrict__ rowp, const Segment& sg, int M, float m,
+                                           double (*red)[NT / WAVE], double* out, uint32_t* dig /*[256]*/) {
   typedef LogitTraits<DT> T;
-  __shared__ uint32_t dig[256];
   __shared__ int32_t sh_digit, sh_above, sh_total;
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+  const int lane = tid & (WAVE - 1);
   uint32_t prefix = 0, care = 0;
   int remaining = M;
   bool take_all = false;
@@ -324,30 +307,30 @@ __device__ __forceinline__ void top_m_sums(const uint4* __restrict__ rowp, const
     const float xt = key_to_float(prefix);
     if (xt > -INFINITY) { const double t = (double)xt - md, e = exp(t); Z += remaining * e; if (e > 0.0) S += remaining * (t * e); }
   }
-  block_sum2<NT>(Z, S, red, out);
+  block_sum2<NT>(tid, Z, S, red, out);
 }
 
 // The sums over the M largest logits of a whole row, by one workgroup in five passes: every fp32 row with M > 0 (its one pass does
 // not find them), and rows that were split (they cannot be told from the splits' own sums), by the workgroup that merged the
 // row.  Sums relative to the row maximum.
 template <int DT, int NT>
-__device__ __forceinline__ void top_m_of_whole_row(const uint4* __restrict__ rowp, int V, int M, RowResult& rr) {
+__device__ __forceinline__ void top_m_of_whole_row(int tid, const uint4* __restrict__ rowp, int V, int M, RowResult& rr, const SelectLds& sel) {
   if (M <= 0) return;
   __shared__ double red_t[2][NT / WAVE], sum_t[2];
   const bool usable = !(rr.part.flags & 1u) && rr.part.Z > 0.0 && rr.part.ref > -INFINITY && rr.part.ref < INFINITY;
   if (usable) {
     constexpr int EPC = LogitTraits<DT>::EPC;
     const Segment whole = make_segment<EPC>(V, 0, (V + EPC - 1) / EPC);
-    top_m_sums<DT, NT>(rowp, whole, M, (float)rr.part.ref, red_t, sum_t);
+    top_m_sums<DT, NT>(tid, rowp, whole, M, (float)rr.part.ref, red_t, sum_t, (uint32_t*)sel.aux);
   }
   __syncthreads();
-  if (threadIdx.x == 0) { rr.ZM = usable ? sum_t[0] : 0.0; rr.SM = usable ? sum_t[1] : 0.0; }
+  if (tid == 0) { rr.ZM = usable ? sum_t[0] : 0.0; rr.SM = usable ? sum_t[1] : 0.0; }
   __syncthreads();
 }
 
 // map_lds: one key per cell.
 template <int DT, int NT>
-__device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int V, int K, int top_m, const Segment sg,
+__device__ __noinline__ void generic_segment(int tid, const uint4* __restrict__ rowp, int V, int K, int top_m, const Segment sg,
                                 unsigned char* map_lds, const SelectLds sel, RowResult* rr, uint32_t info_flags) {
   typedef LogitTraits<DT> T;
   typedef typename T::key_t key_t;
@@ -357,12 +340,13 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
   const int ncells = cells_in_segment<NT>(sg.ncell);
   __shared__ double red_d[2][NW], sum_d[2], sum_m[2];
   __shared__ float red_f[NW];
-  __shared__ uint32_t lane_keys[NT];
-  __shared__ int32_t cell_list[SEL_CELL_CAP];
+  uint32_t* const lane_keys = (uint32_t*)sel.aux;           // [NT]
+  int32_t* const cell_list = (int32_t*)(lane_keys + NT);    // [SEL_CELL_CAP]; before the cells are listed: the digits of top_m_sums
+  static_assert(NT * 4 + SEL_CELL_CAP * 4 == SEL_AUX_BYTES && SEL_CELL_CAP == 256, "they fill the place");
   __shared__ int32_t scan_tmp[2][NW];
   __shared__ uint32_t sh_tau;
   __shared__ int32_t sh_cnt, sh_bad;
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
+  const int lane = tid & (WAVE - 1), wid = tid >> 6;
   if (tid == 0) sh_bad = 0;
   __syncthreads();
 
@@ -388,7 +372,7 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
   }
   lane_keys[tid] = any ? sortable_key(M) : 0u;
   if (bad) sh_bad = 1;
-  const float m = block_max<NT>(M, red_f);          // barriers inside also publish map, lane_keys, sh_bad
+  const float m = block_max<NT>(tid, M, red_f);          // barriers inside also publish map, lane_keys, sh_bad
   const bool seg_bad = sh_bad != 0;
   C2T_PT(PT_STREAM_END);                            // (the marks of the histogram path, at the corresponding steps)
 
@@ -412,11 +396,11 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
       }
     }
   }
-  block_sum2<NT>(Z, S, red_d, sum_d);
+  block_sum2<NT>(tid, Z, S, red_d, sum_d);
   C2T_PT(PT_SUMS);
   if (top_m > 0) {
     __syncthreads();
-    if (!seg_bad && m > -INFINITY) top_m_sums<DT, NT>(rowp, sg, top_m, m, red_d, sum_m);
+    if (!seg_bad && m > -INFINITY) top_m_sums<DT, NT>(tid, rowp, sg, top_m, m, red_d, sum_m, (uint32_t*)cell_list);
     else if (tid == 0) { sum_m[0] = 0.0; sum_m[1] = 0.0; }
     __syncthreads();
   }
@@ -438,7 +422,7 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
   uint32_t tau_key = sh_tau;
   float tau = tau_key ? key_to_float(tau_key) : -INFINITY;
   bool ties = false;
-  int n_cells = list_cells<DT, NT>(map, ncells, tau, false, sel.cell_cap, cell_list, &sh_cnt);
+  int n_cells = list_cells<DT, NT>(tid, map, ncells, tau, false, sel.cell_cap, cell_list, &sh_cnt);
   if (n_cells > sel.cell_cap) {
     // Too many cells reach the bound (maxima clustered in few lanes): take the exact K-th
     // largest cell key by radix select over the whole map; fewer than K cells exceed it.
@@ -461,20 +445,20 @@ __device__ __noinline__ void generic_segment(const uint4* __restrict__ rowp, int
       care = cmask;
     }
     tau = prefix ? key_to_float(prefix) : -INFINITY;
-    n_cells = list_cells<DT, NT>(map, ncells, tau, false, sel.cell_cap, cell_list, &sh_cnt);
+    n_cells = list_cells<DT, NT>(tid, map, ncells, tau, false, sel.cell_cap, cell_list, &sh_cnt);
     if (n_cells > sel.cell_cap) {                            // massive ties at tau: the cells above it, then a tie scan
-      n_cells = list_cells<DT, NT>(map, ncells, tau, true, sel.cell_cap, cell_list, &sh_cnt);
+      n_cells = list_cells<DT, NT>(tid, map, ncells, tau, true, sel.cell_cap, cell_list, &sh_cnt);
       ties = true;
     }
   }
   if (tid == 0) sh_cnt = 0;
   __syncthreads();
   C2T_PT(PT_CELLS_LISTED);
-  collect_cells<DT, NT, true>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
-  if (ties) tie_scan<DT, NT>(rowp, sg, V, tau, K, sel, &sh_cnt, scan_tmp);
+  collect_cells<DT, NT>(tid, rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
+  if (ties) tie_scan<DT, NT>(tid, rowp, sg, V, tau, K, sel, &sh_cnt, scan_tmp);
   C2T_PT(PT_CELLS_READ);
   const int n_el = min(sh_cnt, sel.list_cap), n_top = min(n_el, K);
-  rank_list<NT, false>(K, sel, n_el, rr->topv, rr->topi);
+  rank_list<NT>(tid, K, sel, n_el, rr->topv, rr->topi);
   if (tid == 0) {
     RowPartial r;
     r.ref = (double)m; r.a = (double)m; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = seg_bad ? 0 : n_top; r.flags = (seg_bad ? 1u : 0u) | info_flags;
@@ -553,7 +537,7 @@ __device__ __forceinline__ RowOfWorkgroup row_of_workgroup(const TreeState& st, 
   const bool slot_major = 4 * st.layer_rows[sp.layer] >= 3 * sp.B * sp.rows_per_seq;
   r.b = slot_major ? b_slot : b_seq;
   r.f = slot_major ? w / sp.B : w % sp.rows_per_seq;
-  r.nf = slot_major ? nf_slot : nf_seq;
+  r.nf = __builtin_amdgcn_readfirstlane(slot_major ? nf_slot : nf_seq);   // (loaded by a vector instruction: a spill in the launch that has no register for it)
   return r;
 }
 
@@ -773,7 +757,7 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
 // halves <= max, one of them equal to it).  32 vector instructions beside the eight additions: the address and the increment of a
 // value take one each (v_mad_u32_u16 picks its half, scales and adds the lane's base), the window test three a chunk beyond the indices.
 template <bool ONE_COPY>
-__device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uint32_t hist, OutsideAcc* acc) {
+__device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t hist, OutsideAcc* acc) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
   const uint32_t d[4] = {twice_index(w[0]), twice_index(w[1]), twice_index(w[2]), twice_index(w[3])};
   uint32_t pat;
@@ -792,7 +776,6 @@ __device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uin
       lds_add(twice_lower<ONE_COPY>(d[j], hist), increment_lower(sg, 0xffffu));
     }
   }
-  M2 = pk_max_f16_raw(M2, pat);
   return pat;
 }
 
@@ -802,7 +785,7 @@ __device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t& M2, uin
 // not swallow, codes in (-2^10, -2^7] and negative NaN, shows in `seen` (packed maximum of the codes, packed minimum of
 // codes - 0xC300), which the caller looks at once per row.
 struct CodesSeen { uint32_t hi, lo; };
-__device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& M2, uint32_t hist, uint32_t own, OutsideAcc* acc, CodesSeen& seen) {
+__device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t hist, uint32_t own, OutsideAcc* acc, CodesSeen& seen) {
   constexpr uint32_t LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1), FIRST_MASKED = 0xC480u;       // see hp_masked
   const uint32_t raw[4] = {q.x, q.y, q.z, q.w};
   uint32_t w[4];
@@ -825,51 +808,167 @@ __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t& 
       lds_add((uint16_t)raw[j] >= (uint16_t)FIRST_MASKED ? own : twice_lower<false>(d[j], hist), increment_lower(sg, 0xffffu));
     }
   }
-  M2 = pk_max_f16_raw(M2, pat);
   return pat;
 }
 
-// The streaming loop of such a row: `whole` chunks from `base` and, with tail_valid > 0, a partial one behind them.  Out of
-// line, so that rows that mask nothing keep their registers.  Returns the packed maximum.
-// A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 41 us when every chunk took hist_chunk_outside, 30.
+// ---- a lower bound of the K-th largest logit (K <= COLUMNS_MAX_K), from the maxima of 64 columns of lanes: each row of 16 lanes is sorted
+// (bitonic, a lane permutation and a v_med3 a stage), and the smallest of the four rows' ceil(K / 4)-th largest maxima is reached by
+// K of them.  Of randomly placed logits 27 reach it for K = 16 (18 the exact K-th largest of the 64).  A tenth of a microsecond,
+// where a search by ballots takes half of one: its rounds are chains of scalar instructions.  For K = 32 it would be 59 logits and now and
+// then more than the 128 cells that can be listed: 8192 rows of 152064 494 us a layer, with the exact K-th largest logit 464.
+constexpr int COLUMNS_MAX_K = 16;
+constexpr uint32_t HP_NONE2 = HP_F16_NEG_INF2;                          // pattern of a lane without a chunk
+constexpr uint32_t HP_LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1);  // the window's lowest value, which also stands in for masked logits
+#define C2T_DPP_QUAD_XOR3 0x1B      /* quad_perm [3,2,1,0] */
+#define C2T_DPP_ROW_SHL(n) (0x100 | (n))
+__device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t d;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+// every row of 16 lanes descending
+__device__ __forceinline__ uint32_t sort_rows_of_16(uint32_t v) {
+  const int lane = lane_id();
+  // of a pair the lane with the bit clear takes the maximum: the median with the largest or the smallest number
+  const uint32_t c0 = (uint32_t)((lane & 1) - 1), c1 = (uint32_t)(((lane >> 1) & 1) - 1), c2 = (uint32_t)(((lane >> 2) & 1) - 1), c3 = (uint32_t)(((lane >> 3) & 1) - 1);
+  const auto xor4 = [](uint32_t x) {
+    const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, C2T_DPP_ROW_SHL(4), 0xf, 0x5, false);      // quads 0 and 2: from the lanes above
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)up, (int)x, C2T_DPP_ROW_SHR(4), 0xf, 0xa, false);                   // quads 1 and 3: from the lanes below
+  };
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR3, 0xf>(0u, v), c1);
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
+  v = med3_u32(v, dpp_u32<C2T_DPP_ROW_HALF_MIRROR, 0xf>(0u, v), c2);
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, v), c1);
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
+  v = med3_u32(v, dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, v), c3);
+  v = med3_u32(v, xor4(v), c2);
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, v), c1);
+  return med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
+}
+// 16-bit keys that order like the values of the patterns
+__device__ __forceinline__ uint32_t key_of_pattern(uint32_t c) { return (c & 0x8000u) ? c ^ 0xffffu : c | 0x8000u; }
+// column: packed pattern, the lane's column maximum over the whole row; uniform result: a value that K logits at least reach, or the window's
+// lowest where fewer columns hold a logit of the window.
+__device__ __forceinline__ float bound_of_columns16(uint32_t column, int K) {
+  const uint32_t v = sort_rows_of_16(max(key_of_pattern(column & 0xffffu), key_of_pattern(column >> 16)));
+  uint32_t key;
+  if (K == 1) {                                                         // (uniform) the maximum itself
+    key = max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+              max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+  } else {
+    const int j = (K - 1) >> 2;
+    key = min(min((uint32_t)__builtin_amdgcn_readlane((int)v, j), (uint32_t)__builtin_amdgcn_readlane((int)v, 16 + j)),
+              min((uint32_t)__builtin_amdgcn_readlane((int)v, 32 + j), (uint32_t)__builtin_amdgcn_readlane((int)v, 48 + j)));
+  }
+  key = max(key, key_of_pattern(HP_LOWEST));
+  return __uint_as_float(((key & 0x8000u) ? key & 0x7fffu : key ^ 0xffffu) << 16);
+}
+
+// Cells of the histogram path: four neighbouring chunks, 64 bytes of one or two lines, so that one which holds a large logit is read again at
+// the price of its lines (a cell of four chunks of one lane, four sweeps apart, costs four: with K = 32
+// 4096 rows of 152064 took 255 us a layer, with K = 1 193).  Cell g * NT + t of a segment: chunks (4 g + t mod 4) * NT + t - t mod 4 and the next three; a group g of four sweeps has NT cells.
 template <int NT>
-__device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, uint32_t hist,
-                                                    __attribute__((address_space(3))) uint16_t* keys, OutsideAcc* acc) {
+__host__ __device__ inline int quad_cells_in_segment(int n) { return (n + 4 * NT - 1) / (4 * NT) * NT; }
+template <int NT>
+__device__ __forceinline__ int chunk_of_quad_cell(int cell, int j) {
+  const int grp = cell / NT, t = cell - grp * NT;
+  return (grp * 4 + (t & 3)) * NT + (t & ~3) + j;
+}
+// The keys of a group's cells: of the maxima p[k] of the chunks that the lane has read in sweep k of the group, lane t of a quad gets the
+// largest of the quad's p[t].  Two exchanges between neighbours, each lane giving away half of what it holds.
+__device__ __forceinline__ uint32_t quad_exchange_1(uint32_t even, uint32_t odd, bool is_odd) {
+  return pk_max_f16_raw(is_odd ? odd : even, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, is_odd ? even : odd));
+}
+__device__ __forceinline__ uint32_t quad_exchange_2(uint32_t lower, uint32_t upper, bool is_upper) {
+  return pk_max_f16_raw(is_upper ? upper : lower, dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, is_upper ? lower : upper));
+}
+
+// The streaming loop: `whole` chunks of the segment that rs covers and, with tail_valid > 0, a partial one behind them; q: the lane's first
+// DEPTH chunks, on their way; keys: LDS, the cells' keys, the lane's first.  MASKED: see hist_chunk_masked.
+typedef __attribute__((address_space(3))) uint16_t* LdsHalves;
+struct StreamInput { __amdgpu_buffer_rsrc_t rs; int whole, tail_valid; uint32_t vo, hist; LdsHalves keys; OutsideAcc* acc; };
+template <int NT, int DEPTH, bool MASKED, bool ONE_COPY>
+__device__ __forceinline__ uint32_t hist_stream(const StreamInput& in, uint4 (&q)[DEPTH]) {
+  static_assert(DEPTH % 4 == 0 && CPC == 4, "whole cells");
+  const uint32_t own = MASKED ? lds_address(&in.acc->masked_by_lane[lane_id()]) : 0u;
+  const int whole = in.whole, tail = in.tail_valid > 0 ? whole : -1, n = whole / (DEPTH * NT);
+  CodesSeen seen{0u, 0xffffffffu};
+  uint32_t M2 = HP_NONE2, so = 0u;
+  LdsHalves mp = in.keys;
+  const auto count = [&](const uint4& c) {
+    if (MASKED) return hist_chunk_masked(c, in.hist, own, in.acc, seen);
+    return hist_chunk<ONE_COPY>(c, in.hist, in.acc);
+  };
+  const bool odd = (lane_id() & 1) != 0, upper = (lane_id() & 2) != 0;
+  for (int it = n; it > 0; --it, so += (uint32_t)DEPTH * NT * 16u, mp += (DEPTH / 4) * NT) {
+#pragma unroll
+    for (int c = 0; c < DEPTH; c += 4) {
+      uint32_t half[2];
+#pragma unroll
+      for (int k = 0; k < 4; k += 2) {
+        const uint32_t pe = count(q[c + k]);
+        q[c + k] = load_stream_buffer(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k) * (NT * 16u));
+        const uint32_t po = count(q[c + k + 1]);
+        q[c + k + 1] = load_stream_buffer(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k + 1) * (NT * 16u));
+        half[k / 2] = quad_exchange_1(pe, po, odd);
+      }
+      const uint32_t key = quad_exchange_2(half[0], half[1], upper);
+      M2 = pk_max_f16_raw(M2, key);
+      mp[c / 4 * NT] = (uint16_t)pk_max_f16_raw(key, key >> 16);
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
+  // the last, partial group: up to DEPTH chunks of this lane, the row's partial last chunk among them
+  uint32_t vo = in.vo;
+  asm volatile("" : "+v"(vo));                                          // (not a copy that has been spilled over the loop)
+  const int g0 = n * (DEPTH * NT), g = g0 + (int)(vo >> 4), end = whole + (tail >= 0 ? 1 : 0);
+#pragma unroll
+  for (int c = 0; c < DEPTH; c += 4) {
+    if (g0 + c * NT >= end) break;                                      // (uniform)
+    uint32_t half[2];
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {
+      uint32_t p[2] = {HP_NONE2, HP_NONE2};
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (g + (c + k + i) * NT < whole) p[i] = count(q[c + k + i]);
+        else if (g + (c + k + i) * NT == tail) p[i] = hist_chunk_outside(q[c + k + i], in.tail_valid, in.hist, in.acc);
+      }
+      half[k / 2] = quad_exchange_1(p[0], p[1], odd);
+    }
+    const uint32_t key = quad_exchange_2(half[0], half[1], upper);
+    M2 = pk_max_f16(M2, key);
+    mp[c / 4 * NT] = (uint16_t)pk_max_f16(key, key >> 16);
+  }
+  if (MASKED && (pk_sub_sat_u16(seen.hi, 0xFF80FF80u) | pk_sub_sat_u16(0x01800180u, seen.lo)))             // neither in the window nor masked: two-pass path
+    __hip_atomic_fetch_max(&((OutsideAccLds)in.acc)->mag_max, 0x7fffu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return M2;
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_buffer(uint64_t base, int bytes) {      // (the builtin of readfirstlane returns int: no sign extension)
   const uint64_t base_u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |
                           ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32);
-  const int whole = __builtin_amdgcn_readfirstlane(whole_chunks), tail = tail_valid > 0 ? whole : -1;
-  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, (whole + (tail >= 0 ? 1 : 0)) * 16, 0x00020000);
-  const uint32_t own = lds_address(&acc->masked_by_lane[lane_id()]);
-  const int n = whole / (4 * NT);
-  uint32_t M2 = HP_F16_NEG_INF2, so = 0u;
-  uint4 q[4];
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
+// The loop of a row that masks part of its vocabulary.  Out of line, so that rows that mask nothing keep their registers.
+// A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 41 us when every chunk took hist_chunk_outside, 30.
+template <int NT>
+__device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, uint32_t hist, LdsHalves keys, OutsideAcc* acc) {
+  constexpr int DEPTH = 4;
+  const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
+  StreamInput in;
+  in.whole = uniform(whole_chunks); in.tail_valid = uniform(tail_valid); in.vo = vo; in.hist = hist; in.keys = keys; in.acc = acc;
+  in.rs = uniform_buffer(base, (in.whole + (in.tail_valid > 0 ? 1 : 0)) * 16);
+  uint4 q[DEPTH];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) q[k] = load_stream_buffer(rs, vo, (uint32_t)k * (NT * 16u));
-  CodesSeen seen{0u, 0xffffffffu};
-  for (int it = 0; it < n; ++it, so += 4u * NT * 16u) {
-    uint32_t key = HP_F16_NEG_INF2;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      key = pk_max_f16_raw(key, hist_chunk_masked(q[k], M2, hist, own, acc, seen));
-      q[k] = load_stream_buffer(rs, vo, so + (uint32_t)(4 + k) * (NT * 16u));
-    }
-    keys[it * NT] = (uint16_t)pk_max_f16_raw(key, key >> 16);
-  }
-  // the last, partial group: up to four chunks of this lane, the row's partial last chunk among them
-  const int g = (int)(vo >> 4) + n * 4 * NT;
-  if (g < whole || g == tail) {
-    uint32_t key = HP_F16_NEG_INF2;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (g + k * NT < whole) key = pk_max_f16_raw(key, hist_chunk_masked(q[k], M2, hist, own, acc, seen));
-      else if (g + k * NT == tail) key = pk_max_f16(key, hist_chunk_outside(q[k], tail_valid, hist, acc));
-    }
-    keys[n * NT] = (uint16_t)pk_max_f16(key, key >> 16);
-    M2 = pk_max_f16(M2, key);
-  }
-  if (pk_sub_sat_u16(seen.hi, 0xFF80FF80u) | pk_sub_sat_u16(0x01800180u, seen.lo))             // neither in the window nor masked: two-pass path
-    __hip_atomic_fetch_max(&((OutsideAccLds)acc)->mag_max, 0x7fffu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  return M2;
+  for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer(in.rs, vo, (uint32_t)k * (NT * 16u));
+  return hist_stream<NT, DEPTH, true, false>(in, q);
+}
+
+// 16 bytes a lane from global memory straight into LDS, to `address` (uniform over the wavefront) + 16 lane: no registers while it is on its way.
+__device__ __forceinline__ void lds_chunk_load(const uint4* p, uint32_t address) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p, (__attribute__((address_space(3))) void*)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)address), 16, 0, 0);
 }
 
 // The lane that holds the M-th largest logit: the sums over the logits it contributes to the top M
@@ -902,16 +1001,132 @@ __device__ __noinline__ TopMPart top_m_boundary_lane(int tid, LaneCounts<WPL> co
 
 // A thread's share of the classifier's parameters on its way from global memory to LDS.
 struct ClassifierStage { float4 q; float* dst; bool mine; };
-__device__ __forceinline__ ClassifierStage stage_classifier(const float* __restrict__ cls, int h, float* dst) {
+__device__ __forceinline__ ClassifierStage stage_classifier(int tid, const float* __restrict__ cls, int h, float* dst) {
   ClassifierStage c;
   c.dst = dst;
-  c.mine = dst != nullptr && (int)threadIdx.x * 4 < 5 * h + 1;     // the array is padded to a multiple of four floats
+  c.mine = dst != nullptr && tid * 4 < 5 * h + 1;     // the array is padded to a multiple of four floats
   c.q = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (c.mine) c.q = ((const float4*)cls)[threadIdx.x];
+  if (c.mine) c.q = ((const float4*)cls)[tid];
   return c;
 }
-__device__ __forceinline__ void store_classifier(const ClassifierStage& c) {
-  if (c.mine) ((float4*)c.dst)[threadIdx.x] = c.q;
+__device__ __forceinline__ void store_classifier(int tid, const ClassifierStage& c) {
+  if (c.mine) ((float4*)c.dst)[tid] = c.q;
+}
+
+constexpr int HANDED_OVER = -2, RANKED_IN_RR = -1, UNSETTLED = RANKED_IN_RR;     // SegmentTop::n_el
+
+// What a workgroup's wavefronts leave each other in LDS on the histogram path.
+template <int NT>
+struct HistShared {
+  static constexpr int NW = NT / WAVE;
+  double red_d[2][NW];              // the wavefronts' Z and S
+  double red_m_d[2][NW];            // ... over the M largest logits (TOPM)
+  uint32_t red_m[NW];               // their largest patterns
+  int32_t total[NW], scan_p[NW], scan_n[NW];
+  OutsideAcc out;
+  float m;                          // largest logit of the row
+  int32_t n_cells, n_el, tot_p;
+  int32_t cells[SEL_CELL_CAP];      // cells that hold a logit above the bound
+};
+constexpr int HIST_LIST = 256;                  // logits the element list holds
+template <int NT>
+__host__ __device__ inline size_t hist_lds_bytes(int repl) { return (size_t)HP_WORDS * 4 * repl + HIST_LIST * 8 + NT * 4; }   // histogram copies | element list | columns; the cell map behind
+__device__ __forceinline__ SelectLds hist_list(unsigned char* at) {
+  SelectLds s;
+  s.list = at; s.aux = nullptr; s.list_cap = HIST_LIST; s.cell_cap = 0;
+  return s;
+}
+
+// The exact K-th largest logit of a histogram, by the whole workgroup: the value-ordered rank of its bin (see hp_code_of_rank; -1: fewer
+// than K logits lie in the window) and how many logits exceed it.  Out of line: it is looked for where K > COLUMNS_MAX_K, and in rows that
+// settle_hist is asked about.
+struct KthOfCounts { int rank, n_gt; };
+template <int NT>
+__device__ __noinline__ KthOfCounts kth_of_counts(int tid, LdsWords hist, int top_k) {
+  const int K = __builtin_amdgcn_readfirstlane(top_k);
+  constexpr int NW = NT / WAVE, WPL = HP_WORDS / NT;
+  __shared__ int32_t scan[2][NW], found[2];
+  const int lane = tid & (WAVE - 1), wid = tid >> 6, w0 = WPL * tid;
+  int lane_pos = 0, lane_neg = 0;
+  for (int j = 0; j < WPL; ++j) { lane_pos += (int)(hist[w0 + j] & 0xffffu); lane_neg += (int)(hist[w0 + j] >> 16); }
+  const int incl_p = wave_scan_incl(lane_pos), incl_n = wave_scan_incl(lane_neg);
+  if (lane == WAVE - 1) { scan[0][wid] = incl_p; scan[1][wid] = incl_n; }
+  if (tid == 0) { found[0] = -1; found[1] = 0; }
+  __syncthreads();
+  int before_p = 0, before_n = 0, tot_p = 0;
+  for (int w = 0; w < NW; ++w) { if (w < wid) { before_p += scan[0][w]; before_n += scan[1][w]; } tot_p += scan[0][w]; }
+  // descending: positive values from the highest lane down, then negative ones from lane 0 up
+  const int above_p = tot_p - (before_p + incl_p), above_n = tot_p + before_n + incl_n - lane_neg;
+  if (above_p < K && above_p + lane_pos >= K) {              // at most one lane
+    int run = above_p;
+    for (int j = WPL - 1; j >= 0; --j) {
+      const int n = (int)(hist[w0 + j] & 0xffffu);
+      if (run < K && run + n >= K) { found[0] = HP_WORDS + w0 + j; found[1] = run; }
+      run += n;
+    }
+  }
+  if (above_n < K && above_n + lane_neg >= K) {
+    int run = above_n;
+    for (int j = 0; j < WPL; ++j) {
+      const int n = (int)(hist[w0 + j] >> 16);
+      if (run < K && run + n >= K) { found[0] = HP_WORDS - 1 - (w0 + j); found[1] = run; }
+      run += n;
+    }
+  }
+  __syncthreads();
+  return KthOfCounts{found[0], found[1]};
+}
+
+// The rows whose list of the largest logits did not come out, or that need a closer look: with the exact K-th largest logit tau
+// from the counts,
+//  * rows with logits below the window take the two-pass path unless tau is a positive value of it, those with fewer than K logits in the
+//    window and masked ones besides do so too (they could be among the top K, which the histogram cannot rank): UNSETTLED;
+//  * a list that is incomplete (too many cells or logits above the bound) or short of K is made again: the segment is read a second time for what
+//    exceeds tau (fewer than K logits), and the ties at tau of the lowest ids are added (tie_scan).
+// list_length: more than HIST_LIST if the list is incomplete.  Returns its length.  Out of line: see settle_list.
+template <int NT>
+__device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsWords hist, uint32_t list_address, int list_length,
+                                        int n_tiny, int n_masked) {
+  typedef LogitTraits<1> T;
+  __shared__ int32_t scan_tmp[1][NT / WAVE], sh_n;
+  const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
+  const int K = uniform(top_k), n_el = uniform(list_length);
+  const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
+  const SelectLds list = hist_list((unsigned char*)(__attribute__((address_space(3))) unsigned char*)(uintptr_t)(uint32_t)uniform((int)list_address));
+  const int n_elems = sg.tail_chunk >= 0 ? (sg.ncell - 1) * T::EPC + sg.tail_valid : sg.ncell * T::EPC, want = min(K, n_elems);
+  const KthOfCounts kth = kth_of_counts<NT>(tid, hist, K);
+  if ((uniform(n_tiny) > 0 && kth.rank < HP_WORDS) || (uniform(n_masked) > 0 && kth.rank < 0)) return UNSETTLED;
+  if (n_el >= want && n_el <= HIST_LIST) return n_el;
+  const float tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;    // (fewer than K logits: all of them)
+  float* el_v = list.values();
+  int32_t* el_i = list.ids();
+  if (tid == 0) sh_n = 0;
+  __syncthreads();
+  const __amdgpu_buffer_rsrc_t rs = uniform_buffer((uint64_t)(rowp + sg.c0), sg.ncell * 16);
+  constexpr int BATCH = 4;                                   // chunks a thread holds at once
+  for (int g0 = 0; g0 < sg.ncell; g0 += BATCH * NT) {
+    uint4 q[BATCH];
+#pragma unroll
+    for (int k = 0; k < BATCH; ++k) q[k] = load_stream_buffer(rs, (uint32_t)tid * 16u, (uint32_t)(g0 + k * NT) * 16u);
+#pragma unroll
+    for (int k = 0; k < BATCH; ++k) {
+      const int g = g0 + k * NT + tid;
+      float x[T::EPC];
+      T::unpack(q[k], x);
+#pragma unroll
+      for (int j = 0; j < T::EPC; ++j) {
+        const int id = (sg.c0 + g) * T::EPC + j;
+        if (x[j] > tau && g < sg.ncell && id < V) {
+          const int slot = atomicAdd(&sh_n, 1);
+          if (slot < HIST_LIST) { el_v[slot] = x[j]; el_i[slot] = id; }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const int n = sh_n;                                        // kth.n_gt, or all of fewer than K logits
+  if (want > n) tie_scan<1, NT>(tid, rowp, sg, V, tau, want - n, list, &sh_n, scan_tmp);
+  return want > n ? want : n;
 }
 
 // A row shared by sp.coop workgroups (launches that leave most of the chip idle: a single sequence,
@@ -919,61 +1134,67 @@ __device__ __forceinline__ void store_classifier(const ClassifierStage& c) {
 // workgroups on n CUs count a segment each, and their histograms, being sums, merge exactly.  Each
 // hands over through memory what the epilogue needs of its segment: the 4096 count words (copies
 // already folded), the keys of its cells (segments are whole groups of four sweeps, so the row's
-// map is the segments' maps laid end to end) and the few numbers of OutsideAcc.  The stores are
+// map is the segments' maps laid end to end), its columns' maxima and the few numbers of OutsideAcc.  The stores are
 // device-coherent and complete before the workgroup takes the row's ticket; the workgroup that takes
 // the last one adds the n histograms up in its own LDS, loads the row's map, and goes on as if it
-// had counted the whole row.  The sums, the K-th largest value and the selection therefore come
+// had counted the whole row.  The sums and the selection therefore come
 // out exactly as for an unshared row (the sum of the logits below the window is added up per
 // segment first: a different rounding order for a term of relative size 1e-16).
 // Every slot is written once and read once per launch: nothing has to be cleared between launches.
-// Returns true in the workgroup that goes on.  map: the segment's keys in LDS, with room for the row's.
+// Returns true in the workgroup that goes on.  map: the segment's keys in LDS, with room for the row's; column, m2: the lane's column maximum
+// and the largest pattern, of the segment, then of the row.
 constexpr int COOP_BATCH = 4;                   // other segments whose counts a lane has in flight at once (eight registers each)
 template <int NT>
-__device__ __forceinline__ bool share_row(const ScoreParams& sp, int split, int64_t row_launched, int32_t* row_ticket,
+__device__ __forceinline__ bool share_row(int tid, const ScoreParams& sp, int split, int64_t row_launched, int32_t* row_ticket,
                                           const Segment& sg, uint32_t* __restrict__ hist, uint32_t w0, uint16_t* map,
-                                          OutsideAcc* sh_out, uint32_t* red_m) {
+                                          OutsideAcc* sh_out, uint32_t& column, uint32_t& m2) {
   constexpr int NW = NT / WAVE;
   constexpr uint32_t SLOT_BYTES = HP_WORDS * 4, COHERENT = 16;          // cache policy sc1: served at the device's coherence point
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
+  const int lane = tid & (WAVE - 1), wid = tid >> 6;
   const int n = sp.coop;
   const __amdgpu_buffer_rsrc_t rh = __builtin_amdgcn_make_buffer_rsrc((void*)(sp.coop_hist + row_launched * n * HP_WORDS), 0,
                                                                       n * (int)SLOT_BYTES, 0x00020000);
   const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc((void*)(sp.coop_map + row_launched * sp.coop_map_stride), 0,
                                                                       sp.coop_map_stride * 2, 0x00020000);
   CoopAcc* const acc = sp.coop_acc + row_launched * n;
+  uint32_t* const columns = (uint32_t*)(sp.coop_map + (int64_t)COOP_MAX_ROWS * sp.coop_map_stride) + row_launched * n * WAVE;
   {
     const uint4 t0 = *(const uint4*)(hist + w0), t1 = *(const uint4*)(hist + w0 + 4);
     const c2t_uint4v u0 = {t0.x, t0.y, t0.z, t0.w}, u1 = {t1.x, t1.y, t1.z, t1.w};
     __builtin_amdgcn_raw_buffer_store_b128(u0, rh, w0 * 4u, (uint32_t)split * SLOT_BYTES, COHERENT);
     __builtin_amdgcn_raw_buffer_store_b128(u1, rh, w0 * 4u + 16u, (uint32_t)split * SLOT_BYTES, COHERENT);
-    const int ncells = cells_in_segment<NT>(sg.ncell);
+    const int ncells = quad_cells_in_segment<NT>(sg.ncell);
     const uint32_t first_key_byte = (uint32_t)sg.c0 / CPC * 2u;        // sg.c0 is a multiple of CPC * NT chunks
     for (int i = tid * 8; i < ncells; i += NT * 8) {                    // (a store that reaches past the row's keys is dropped by the bounds check)
       const uint4 k = *(const uint4*)(map + i);
       const c2t_uint4v kv = {k.x, k.y, k.z, k.w};
       __builtin_amdgcn_raw_buffer_store_b128(kv, rm, (uint32_t)i * 2u, first_key_byte, COHERENT);
     }
-    if (wid == NW - 1 && lane == 0) {                                   // the lane that has just folded masked_by_lane into n_masked
-      uint32_t m2 = HP_F16_NEG_INF2;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) m2 = pk_max_f16(m2, red_m[w]);
-      CoopAcc* a = acc + split;
-      st_dev(&a->s_tiny, sh_out->s_tiny);
-      st_dev(&a->n_tiny, sh_out->n_tiny); st_dev(&a->n_masked, sh_out->n_masked);
-      st_dev(&a->mag_max, sh_out->mag_max); st_dev(&a->max_pattern, m2);
+    if (wid == NW - 1) {
+      st_dev(columns + split * WAVE + lane, column);
+      if (lane == 0) {                                                  // the lane that has just folded masked_by_lane into n_masked
+        CoopAcc* a = acc + split;
+        st_dev(&a->s_tiny, sh_out->s_tiny);
+        st_dev(&a->n_tiny, sh_out->n_tiny); st_dev(&a->n_masked, sh_out->n_masked);
+        st_dev(&a->mag_max, sh_out->mag_max); st_dev(&a->max_pattern, m2);
+      }
     }
   }
   wait_vector_memory();                                                 // this wave's stores have reached the coherence point
   __syncthreads();                                                      // ... and every wave's; the reads of LDS above are done
-  if (!last_arrival(row_ticket, n)) return false;
+  if (!last_arrival(tid, row_ticket, n)) return false;
 
   // Every load of the first round trip is issued before anything waits: the segments' numbers
-  // (wave 0, one segment per lane), the row's keys (two loads a thread cover the largest map) and the
+  // (one segment per lane), their columns, the row's keys (two loads a thread cover the largest map) and the
   // first COOP_BATCH segments' counts.
-  const bool have = wid == 0 && lane < n;
-  const CoopAcc* a = acc + (have ? lane : 0);
-  double st = 0.0; int nt = 0, nm = 0; uint32_t mm = 0u, mp = HP_F16_NEG_INF2;
-  if (have) { st = ld_dev(&a->s_tiny); nt = ld_dev(&a->n_tiny); nm = ld_dev(&a->n_masked); mm = ld_dev(&a->mag_max); mp = ld_dev(&a->max_pattern); }
+  const bool have = lane < n;
+  const CoopAcc* a = acc + min(lane, n - 1);
+  const uint32_t mp = ld_dev(&a->max_pattern);
+  double st = 0.0; int nt = 0, nm = 0; uint32_t mm = 0u;
+  if (wid == 0) { st = ld_dev(&a->s_tiny); nt = ld_dev(&a->n_tiny); nm = ld_dev(&a->n_masked); mm = ld_dev(&a->mag_max); }
+  uint32_t col[COOP_BATCH];
+#pragma unroll
+  for (int j = 0; j < COOP_BATCH; ++j) col[j] = ld_dev(columns + min(j, n - 1) * WAVE + lane);
   const int k0 = tid * 8, k1 = k0 + NT * 8;
   const c2t_uint4v kv0 = __builtin_amdgcn_raw_buffer_load_b128(rm, (uint32_t)k0 * 2u, 0u, COHERENT);   // zeros past the row's keys
   const c2t_uint4v kv1 = __builtin_amdgcn_raw_buffer_load_b128(rm, (uint32_t)k1 * 2u, 0u, COHERENT);
@@ -1002,55 +1223,47 @@ __device__ __forceinline__ bool share_row(const ScoreParams& sp, int split, int6
     const c2t_uint4v kv = __builtin_amdgcn_raw_buffer_load_b128(rm, (uint32_t)i * 2u, 0u, COHERENT);
     *(uint4*)(map + i) = make_uint4(kv.x, kv.y, kv.z, kv.w);
   }
+#pragma unroll
+  for (int j = 0; j < COOP_BATCH; ++j) column = pk_max_f16_raw(column, col[j]);
+  for (int j = COOP_BATCH; j < n; ++j) column = pk_max_f16_raw(column, ld_dev(columns + j * WAVE + lane));
+  m2 = wave_reduce_u32(have ? mp : HP_NONE2, HP_NONE2, [](uint32_t x, uint32_t y) { return pk_max_f16(x, y); });
   if (wid == 0) {                                                       // fixed order of the sums
-    const double st_all = wave_sum(st);
-    const int nt_all = wave_sum_i(nt), nm_all = wave_sum_i(nm);
-    const uint32_t mm_all = wave_reduce_u32(mm, 0u, [](uint32_t x, uint32_t y) { return max(x, y); });
-    const uint32_t mp_all = wave_reduce_u32(mp, HP_F16_NEG_INF2, [](uint32_t x, uint32_t y) { return pk_max_f16(x, y); });
+    const double st_all = wave_sum(have ? st : 0.0);
+    const int nt_all = wave_sum_i(have ? nt : 0), nm_all = wave_sum_i(have ? nm : 0);
+    const uint32_t mm_all = wave_reduce_u32(have ? mm : 0u, 0u, [](uint32_t x, uint32_t y) { return max(x, y); });
     if (lane == 0) { sh_out->s_tiny = st_all; sh_out->n_tiny = nt_all; sh_out->n_masked = nm_all; sh_out->mag_max = mm_all; }
-    if (lane < NW) red_m[lane] = mp_all;
   }
-  return true;                                                          // the caller's next barrier publishes map, sh_out and red_m
+  return true;                                                          // the caller's next barrier publishes map and sh_out
 }
 
 // One (row, split) segment on the histogram path, run by a whole workgroup of NT threads.
-// hist: HP_WORDS words; map_lds: one 2-byte key per cell, padded to 16 bytes; sel: see SelectLds.
+// hist: HP_WORDS words a copy, then the element list, the columns and the map, one 2-byte key per cell, padded to 16 bytes
+// (hist_lds_bytes); sel: see SelectLds.
 // TOPM: built with the entropy over the M largest logits (a separate instantiation, so that the
 // default kernel carries none of its registers).
 // COOP: built with the hand-over of a shared row (see share_row); returns HANDED_OVER in the workgroups
 // that have handed their segment over and are done.
-constexpr int HANDED_OVER = -2, RANKED_IN_RR = -1;     // SegmentTop::n_el
 template <int NT, bool TOPM, int WPS, int REPL, bool COOP>
 __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ rowp, int V, int K, int M, const Segment& sg_own,
-                                             const double* __restrict__ tab_e, uint32_t* __restrict__ hist,
-                                             unsigned char* map_lds, const SelectLds& sel, RowResult* rr,
+                                             const double* __restrict__ tab_e, uint32_t* __restrict__ hist, const SelectLds& list, uint32_t* columns, uint16_t* map,
+                                             const SelectLds& sel, RowResult* rr, HistShared<NT>& hs,
                                              const ClassifierStage cst, const float* __restrict__ cls, const TreeState& st, const ScoreParams& sp, int split,
-                                             int64_t row_launched, int b, int64_t slot) {
+                                             int64_t row_launched, int64_t slot, int& tid) {
   constexpr int NW = NT / WAVE;
   constexpr int WPL = HP_WORDS / NT;                   // words per lane in the epilogue (8 at 512 threads)
   static_assert(NW <= 16 && WPL % 4 == 0, "one DPP row holds the per-wave partials; a lane reads whole 16-byte runs");
-  uint16_t* map = (uint16_t*)map_lds;
-  __shared__ double red_d[2][NW], sum_d[2];
-  __shared__ float red_v[NW];
-  __shared__ uint32_t red_m[NW];
-  __shared__ OutsideAcc sh_out;
-  __shared__ int32_t cell_list[SEL_CELL_CAP];
-  __shared__ int32_t scan_tmp[2][NW];
-  __shared__ int32_t sh_cnt, sh_ncell, sh_tau_rank, sh_n_gt;
-
-  int tid = threadIdx.x;
-  const int lane = tid & (WAVE - 1), wid = tid >> 6;
+  const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   Segment sg = sg_own;                                   // what the workgroup streams; the whole row once a shared row's counts are merged
 
 #pragma unroll
-  for (int j = 0; j < WPL * REPL; ++j) hist[tid + j * NT] = 0u;
-  if (tid == 0) { sh_tau_rank = -1; sh_n_gt = 0; sh_ncell = 0; sh_out.s_tiny = 0.0; sh_out.n_tiny = 0; sh_out.n_masked = 0; sh_out.mag_max = 0u; }
-  if (tid < WAVE) sh_out.masked_by_lane[tid] = 0u;
+  for (int j = 0; j < WPL * REPL / 4; ++j) *(uint4*)(hist + 4 * (tid + j * NT)) = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) { hs.n_cells = 0; hs.n_el = 0; hs.out.s_tiny = 0.0; hs.out.n_tiny = 0; hs.out.n_masked = 0; hs.out.mag_max = 0u; }
+  if (tid < WAVE) hs.out.masked_by_lane[tid] = 0u;
   __syncthreads();
 
   // ---------------- streaming loop: count values, record cell maxima ----------------
   uint32_t vo_after;
-  uint32_t M2 = HP_F16_NEG_INF2;                       // packed running maximum of the bf16 patterns (compared as fp16 patterns)
+  uint32_t M2;                                         // packed running maximum of the bf16 patterns (compared as fp16 patterns)
   {
     // DEPTH chunks per lane in flight: a workgroup that streams while its neighbours on the CU are
     // in their epilogues still covers the HBM latency.  Unrolled by DEPTH so that each buffer is
@@ -1058,34 +1271,27 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     // 80 registers, which has room for them (measured: no faster than four, also for a workgroup
     // that is alone on its CU: the CU's counting rate bounds it, not the latency of its loads).
     constexpr int DEPTH = WPS == 6 ? 8 : 4;
-    const int c1 = sg.tail_chunk >= 0 ? sg.c1 - 1 : sg.c1;   // whole chunks; a partial last chunk is counted below
-    // The whole chunks are read through a buffer descriptor over exactly their bytes: a lane whose
-    // chunk lies past the last whole one gets zeros from the bounds check instead of needing a
+    // The chunks are read through a buffer descriptor over exactly their bytes: a lane whose
+    // chunk lies past the last one gets zeros from the bounds check instead of needing a
     // compare and a select per load, and the address is the lane's fixed offset plus a scalar one:
     // no vector instruction per load (eight before, a seventh of the loop).
     const uint64_t base = (uint64_t)(rowp + sg.c0);      // the same for every lane: told to the compiler
-    const uint64_t base_u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base) |   // the builtin returns int:
-                            ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32);   // no sign extension
-    const int whole = __builtin_amdgcn_readfirstlane(max(c1 - sg.c0, 0));
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, whole * 16, 0x00020000);
-    const uint32_t vo = (uint32_t)tid * 16u;
-    uint32_t so = 0u;
-#define C2T_LOAD(k) load_stream_buffer(rs, vo, so + (uint32_t)(k) * (NT * 16u))
+    StreamInput in;
+    in.whole = __builtin_amdgcn_readfirstlane(max((sg.tail_chunk >= 0 ? sg.c1 - 1 : sg.c1) - sg.c0, 0));   // a partial last chunk is counted apart
+    in.tail_valid = __builtin_amdgcn_readfirstlane(sg.tail_chunk >= 0 ? sg.tail_valid : 0);
+    in.rs = uniform_buffer(base, sg.ncell * 16);
+    in.vo = (uint32_t)tid * 16u; in.keys = (LdsHalves)(map + tid); in.acc = &hs.out;
     // REPL copies of the histogram, a lane counting into copy (lane mod REPL): neighbouring lanes that
     // hold the same value (common: few hundred values carry most of a row) then add to different
     // words, which the LDS does not have to serialise.  The copies are folded after the loop.
     static_assert(REPL == 1 || REPL == 2 || REPL == 4 || REPL == 8, "a lane picks its copy with a mask");
-    const uint32_t histl = lds_address(hist) + (REPL > 1 ? (uint32_t)(tid & (REPL - 1)) * (HP_WORDS * 4u) : 0u);
-#define C2T_COUNT(q) hist_chunk<REPL == 1>(q, M2, histl, &sh_out)
+    in.hist = lds_address(hist) + (REPL > 1 ? (uint32_t)(tid & (REPL - 1)) * (HP_WORDS * 4u) : 0u);
     uint4 q[DEPTH];
 #pragma unroll
-    for (int k = 0; k < DEPTH; ++k) q[k] = C2T_LOAD(k);
-    uint16_t* mp = map + tid;
+    for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer(in.rs, in.vo, (uint32_t)k * (NT * 16u));
     // Streaming waves issue ahead of the waves of co-resident workgroups that are in their
     // (latency-bound) epilogue or tail: the memory pipeline stays fed.  Measured: 3 % per full layer.
     __builtin_amdgcn_s_setprio(3);
-    // groups of DEPTH sweeps in which every lane has a chunk; a cell is four sweeps
-    const int n_groups = whole / (DEPTH * NT);
     // A row that masks part of its vocabulary shows it in the wavefront's first chunks (of 512 logits each): where half of them hold
     // a masked logit, most chunks do.  Fewer, a few masked tokens or a masked stretch, are counted chunk by chunk, out of line.  256
     // rows of 128256 by the usual loop / by the masked one: no logit masked 21.4 us / -, one 21.4 / 26.8, the first 4096 22.1 / 30.2,
@@ -1094,7 +1300,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     int masks = 0;
     // Not with four workgroups per CU, where the decision alone costs rows that mask nothing 1 % and the call gains nothing; nor
     // for shared rows, whose segments are a group or two: root layer of 64 rows 26.7 us without it, 29.0 with it.
-    if (WPS != 8 && !COOP && n_groups > 0) {               // (shorter rows do not wait for all their loads here)
+    if (WPS != 8 && !COOP && in.whole >= DEPTH * NT) {     // (shorter rows do not wait for all their loads here)
       int n = 0;
 #pragma unroll
       for (int k = 0; k < DEPTH; ++k) {
@@ -1103,57 +1309,22 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       }
       masks = __builtin_amdgcn_readfirstlane(2 * n >= DEPTH ? 1 : 0);      // (a scalar branch: as a lane mask both sides' registers would be live at once)
     }
-    vo_after = vo;
+    vo_after = in.vo;
     if (masks != 0) {                                    // (nothing of this path is live across the call: what is would be spilled for every row)
-      M2 = hist_stream_masked<NT>(base_u, whole, sg.tail_chunk >= 0 ? sg.tail_valid : 0, vo, histl,
-                                  (__attribute__((address_space(3))) uint16_t*)mp, &sh_out);
+      M2 = hist_stream_masked<NT>(base, in.whole, in.tail_valid, in.vo, in.hist, in.keys, &hs.out);
       C2T_PT(PT_STREAM_END);
-      __builtin_amdgcn_s_setprio(0);
-      store_classifier(stage_classifier(cls, sp.h, cst.dst));
+      store_classifier(tid, stage_classifier(tid, cls, sp.h, cst.dst));
     } else {
-    for (int it = n_groups; it > 0; --it, so += (uint32_t)DEPTH * NT * 16u, mp += (DEPTH / 4) * NT) {
-#pragma unroll
-      for (int c = 0; c < DEPTH / 4; ++c) {
-        uint32_t key = C2T_COUNT(q[4 * c]);
-        q[4 * c] = C2T_LOAD(DEPTH + 4 * c);
-#pragma unroll
-        for (int k = 1; k < 4; ++k) {
-          key = pk_max_f16_raw(key, C2T_COUNT(q[4 * c + k]));
-          q[4 * c + k] = C2T_LOAD(DEPTH + 4 * c + k);
-        }
-        mp[c * NT] = (uint16_t)pk_max_f16_raw(key, key >> 16);
-      }
+      M2 = hist_stream<NT, DEPTH, false, REPL == 1>(in, q);
+      C2T_PT(PT_STREAM_END);
+      store_classifier(tid, cst);                               // published by the barriers below
     }
-    C2T_PT(PT_STREAM_END);
-    store_classifier(cst);                               // published by the barriers below
-    const int g0 = sg.c0 + (int)(vo >> 4) + n_groups * (DEPTH * NT);
-    __builtin_amdgcn_s_setprio(0);
-    // the last, partial group: up to DEPTH chunks of this lane, the row's partial last chunk among them
-    const int tail = sg.tail_chunk;
-#pragma unroll
-    for (int c = 0; c < DEPTH / 4; ++c) {
-      const int g = g0 + 4 * c * NT;
-      if (g < c1 || g == tail) {
-        uint32_t key = g < c1 ? C2T_COUNT(q[4 * c]) : hist_chunk_outside(rowp[tail], sg.tail_valid, histl, &sh_out);
-#pragma unroll
-        for (int k = 1; k < 4; ++k) {
-          if (g + k * NT < c1) key = pk_max_f16_raw(key, C2T_COUNT(q[4 * c + k]));
-          else if (g + k * NT == tail) key = pk_max_f16(key, hist_chunk_outside(rowp[tail], sg.tail_valid, histl, &sh_out));
-        }
-        mp[c * NT] = (uint16_t)pk_max_f16(key, key >> 16);
-        M2 = pk_max_f16(M2, key);                         // the partial chunk's maximum is in no other running value
-      }
-    }
-    }
-#undef C2T_COUNT
-#undef C2T_LOAD
   }
   // The thread index should not be kept in a register through the loop on top of the lane's
   // buffer offset: a spill that crosses the loop is reloaded behind all the logits in flight on the
-  // CU (microseconds, for every wave).  It is formed again here: from the offset, or, where the
-  // register allocation of that build comes out better, from the wave's index and the lane.
-  if (TOPM && WPS == 8) tid = __builtin_amdgcn_readfirstlane(wid) * WAVE + lane_id();
-  else tid = (int)(vo_after >> 4);
+  // CU (microseconds, for every wave).  It is formed again here, for everything that follows, from the offset.
+  asm volatile("" : "+v"(vo_after));
+  tid = (int)(vo_after >> 4);
 
   // The lane owns the magnitude indices WPL*tid .. WPL*tid + WPL-1, with both signs.  The table
   // loads for their e^v are issued now so that their latency hides behind the barrier.
@@ -1161,25 +1332,20 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   const bool shared_row = COOP && sp.coop > 1;          // (uniform) then the factors are loaded behind the hand-over: they would
   ExpFactors ef;                                        // only take registers from it
   if (!shared_row) ef = load_exp_factors(tab_e, tid);
-  // per-wave: maximum
+  columns[tid] = M2;                                    // the lane's maximum
   {
-    const uint32_t m2 = wave_reduce_u32(M2, HP_F16_NEG_INF2, [](uint32_t x, uint32_t y) { return pk_max_f16(x, y); });
-    if (lane == 0) red_m[wid] = m2;
+    const uint32_t m2 = wave_reduce_u32(M2, HP_NONE2, [](uint32_t x, uint32_t y) { return pk_max_f16(x, y); });
+    if (lane == 0) hs.red_m[wid] = m2;
   }
-  __syncthreads();                                     // histogram, cell map and wave results complete
+  __syncthreads();                                     // histogram, map, columns and wave results complete
   C2T_PT(PT_HIST_COMPLETE);
   if (wid == NW - 1) {                                  // masked logits counted by lane: folded into the one count (read after the next barrier)
-    const int nm = wave_sum_i((int)(sh_out.masked_by_lane[lane] >> 16));
-    if (lane == 0 && nm) sh_out.n_masked += nm;         // every other addition to it happened before the barrier above
+    const int nm = wave_sum_i((int)(hs.out.masked_by_lane[lane] >> 16));
+    if (lane == 0 && nm) hs.out.n_masked += nm;         // every other addition to it happened before the barrier above
   }
-
-  // ---------------- Z = sum n_v e^v and S = sum n_v (v - m) e^v ----------------
-  // S is accumulated against the largest value seen so far at each level (lane, wave, workgroup),
-  // so every term has the same sign and nothing cancels: rows whose entropy is tiny keep their
-  // relative accuracy.
-  double Z = 0.0, S = 0.0, Zp = 0.0, Sp = 0.0;
-  int lane_pos = 0, lane_neg = 0;
-  float vtop = -INFINITY;                               // value of the lane's highest non-empty bin
+  uint32_t m2 = HP_NONE2;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) m2 = pk_max_f16(m2, hs.red_m[w]);
   const uint32_t w0 = (uint32_t)(WPL * tid);            // the lane's words
   if (REPL > 1) {                                       // fold the copies into the first: only this lane touches these words
 #pragma unroll
@@ -1193,14 +1359,85 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       *(uint4*)(hist + w0 + j) = t;
     }
   }
+  // ---------------- cells that can hold one of the K largest ----------------
+  // All cells whose key reaches a lower bound of the K-th largest logit (for K > COLUMNS_MAX_K: that logit itself) are listed, and their chunks
+  // requested, one a thread; the sums below take as long as the answer.
+  uint32_t column = HP_NONE2;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) column = pk_max_f16_raw(column, columns[w * WAVE + lane]);
   if (shared_row) {
-    if (!share_row<NT>(sp, split, row_launched, st.row_tickets + slot, sg, hist, w0, map, &sh_out, red_m)) return SegmentTop{HANDED_OVER, false};
+    if (!share_row<NT>(tid, sp, split, row_launched, st.row_tickets + slot, sg, hist, w0, map, &hs.out, column, m2)) return SegmentTop{HANDED_OVER};
     sg = make_segment<8>(V, 0, (V + 7) / 8);             // the epilogue below is the whole row's
     ef = load_exp_factors(tab_e, tid);
+    __syncthreads();                                     // the row's map
   }
+  float tau;
+  if (__builtin_expect(K > COLUMNS_MAX_K, 0)) {
+    const KthOfCounts kth = kth_of_counts<NT>(tid, (LdsWords)hist, K);
+    tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;
+  } else {
+    tau = bound_of_columns16(column, K);
+  }
+  const int ncells = quad_cells_in_segment<NT>(sg.ncell);
+  if (WPS == 8) {                                        // four workgroups a CU: an addition per cell (by wavefront 0.6 % slower), one for all of a wavefront's
+#pragma unroll 1                                         // where a workgroup alone on its CU would wait out every round trip (1.3 % of a phase)
+    for (int c8 = tid * 8; c8 < ncells; c8 += NT * 8) {  // eight keys per read (the map is padded to 16 bytes)
+      const uint4 kq = *(const uint4*)(map + c8);
+      const uint32_t kw[4] = {kq.x, kq.y, kq.z, kq.w};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float kv = (j & 1) ? bf16_hi(kw[j >> 1]) : bf16_lo(kw[j >> 1]);
+        if (c8 + j < ncells && kv >= tau) {
+          const int at = atomicAdd(&hs.n_cells, 1);
+          if (at < sel.cell_cap) hs.cells[at] = c8 + j;
+        }
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int w8 = wid * (WAVE * 8); w8 < ncells; w8 += NT * 8) {
+      const int c8 = w8 + lane * 8;
+      uint32_t hit = 0u;
+      if (c8 < ncells) {
+        const uint4 kq = *(const uint4*)(map + c8);
+        const uint32_t kw[4] = {kq.x, kq.y, kq.z, kq.w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float kv = (j & 1) ? bf16_hi(kw[j >> 1]) : bf16_lo(kw[j >> 1]);
+          hit |= (c8 + j < ncells && kv >= tau ? 1u : 0u) << j;
+        }
+      }
+      int at = append_places(__popc(hit), &hs.n_cells);
+      while (hit) {
+        const int j = __ffs(hit) - 1; hit &= hit - 1;
+        if (at < sel.cell_cap) hs.cells[at] = c8 + j;
+        ++at;
+      }
+    }
+  }
+  __syncthreads();
+  C2T_PT(PT_CELLS_LISTED);
+  const int n_cells = hs.n_cells;
+  const bool listed = n_cells <= sel.cell_cap;           // (uniform) else settle_hist makes the list
+  int my_chunk = -1;
+  uint4 cell_q = make_uint4(0u, 0u, 0u, 0u);
+  if (listed && tid < n_cells * CPC) {                   // n_cells <= cell_cap <= NT / CPC
+    const int ch = sg.c0 + chunk_of_quad_cell<NT>(hs.cells[tid / CPC], tid % CPC);
+    if (ch < sg.c1) {
+      my_chunk = ch;
+      if (WPS == 8) lds_chunk_load(rowp + ch, lds_address(map) + (uint32_t)wid * (WAVE * 16u));   // the map has been read: its place takes a chunk a thread
+      else cell_q = rowp[ch];
+    }
+  }
+  const float m = fmaxf(bf16_lo(m2), bf16_hi(m2));      // largest logit; exact whenever the row stays on this path
+
+  // ---------------- Z = sum n_v e^v and S = sum n_v (v - m) e^v ----------------
+  // Every term of S has the same sign and nothing cancels: rows whose entropy is tiny keep their relative accuracy.
+  double Z = 0.0, S = 0.0, Zp = 0.0, Sp = 0.0;
+  int lane_pos = 0, lane_neg = 0;
+  const double md = (double)m;
   {
-    // low half: count of +|v_j|, high half: count of -|v_j|.  Not kept beyond the sums: the one or
-    // two lanes that need their counts again below read them from LDS again.
+    // low half: count of +|v_j|, high half: count of -|v_j|
     uint32_t cw[WPL];
 #pragma unroll
     for (int j = 0; j < WPL; j += 4) {
@@ -1211,13 +1448,6 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     for (int j = 0; j < WPL; ++j) { lane_pos += (int)(cw[j] & 0xffffu); lane_neg += (int)(cw[j] >> 16); }
     // typical rows leave the lanes (and whole waves) of the small magnitudes empty: they skip the fp64 work
     if (lane_pos | lane_neg) {
-#pragma unroll
-    for (int j = WPL - 1; j >= 0; --j)                  // lowest of the negative values last
-      if (cw[j] >> 16) vtop = hp_value_of_mag(WPL * tid + j, true);
-#pragma unroll
-    for (int j = 0; j < WPL; ++j)                       // highest of the positive values last
-      if (cw[j] & 0xffffu) vtop = hp_value_of_mag(WPL * tid + j, false);
-    const double vt = (double)vtop;
 #pragma unroll
     for (int j = 0; j < WPL; ++j)                       // 64-register build: the halves are unpacked again below rather than
       if (WPS == 8) asm volatile("" : "+v"(cw[j]));     // kept from above in sixteen registers (which spilled the thread index)
@@ -1233,111 +1463,100 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       const double tp = (double)(cw[j] & 0xffffu) * ep;            // n * e^v (0 for an empty bin)
       const double tn = (double)(cw[j] >> 16) * en;
       if (TOPM) {                                                  // the positive values' share kept apart
-        Zp += tp; Sp += (vp - vt) * tp;
-        Z += tn; S += (-vp - vt) * tn;
+        Zp += tp; Sp += (vp - md) * tp;
+        Z += tn; S += (-vp - md) * tn;
       } else {
-        Z += tp; S += (vp - vt) * tp;
-        Z += tn; S += (-vp - vt) * tn;
+        Z += tp; S += (vp - md) * tp;
+        Z += tn; S += (-vp - md) * tn;
       }
       __builtin_amdgcn_sched_barrier(0);                           // one bin pair at a time: keeps live registers low
     }
     }
   }
-  // TOPM: the lane's sums over its positive and over its negative values, relative to its top value
+  // TOPM: the lane's sums over its positive and over its negative values
   const double Zpos = Zp, Spos = Sp, Zneg = Z, Sneg = S;
   if (TOPM) { Z += Zp; S += Sp; }
-  const float vw = wave_max(vtop);                      // -inf only if the whole wave owns empty bins
-  if (lane_pos | lane_neg) S += ((double)vtop - (double)vw) * Z;
   Z = wave_sum(Z); S = wave_sum(S);
-  const int incl_p = wave_scan_incl(lane_pos), incl_n = wave_scan_incl(lane_neg);
-  if (lane == 0) { red_d[0][wid] = Z; red_d[1][wid] = S; red_v[wid] = vw; }
-  if (lane == WAVE - 1) { scan_tmp[0][wid] = incl_p; scan_tmp[1][wid] = incl_n; }
-  __syncthreads();
+  int incl_p = 0, incl_n = 0;
+  if (TOPM) {
+    incl_p = wave_scan_incl(lane_pos); incl_n = wave_scan_incl(lane_neg);
+    if (lane == WAVE - 1) { hs.scan_p[wid] = incl_p; hs.scan_n[wid] = incl_n; }
+  }
+  const int total = wave_sum_i(lane_pos + lane_neg);
   C2T_PT(PT_SUMS);
-
-  uint32_t m2 = HP_F16_NEG_INF2;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) m2 = pk_max_f16(m2, red_m[w]);
-  const uint32_t mag_hi = sh_out.mag_max;               // 0 unless a logit above the window (or a NaN) was met
-  const float m = fmaxf(bf16_lo(m2), bf16_hi(m2));      // exact whenever the row stays on this path
-  const int n_tiny = sh_out.n_tiny, n_ninf = sh_out.n_masked;
-  int before_p = 0, before_n = 0, tot_p = 0, tot_n = 0; // counts in lower lanes / in the whole segment
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    if (w < wid) { before_p += scan_tmp[0][w]; before_n += scan_tmp[1][w]; }
-    tot_p += scan_tmp[0][w]; tot_n += scan_tmp[1][w];
-  }
-  // The row's sums from its wavefronts' (lanes 0..NW-1 hold one each; fixed order), by one wavefront: sum_d
-  const auto combine = [&] {
-    double tz = 0.0, ts = 0.0;
-    if (lane < NW && red_d[0][lane] > 0.0) {
-      tz = red_d[0][lane];
-      ts = red_d[1][lane] + ((double)red_v[lane] - (double)m) * tz;
-    }
-    tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts);
-    if (lane == 0) {
-      if (n_tiny) {                                     // e^x = 1 + x, x e^x = x for |x| < 2^-25
-        const double zt = (double)n_tiny + sh_out.s_tiny;
-        tz += zt; ts += sh_out.s_tiny - (double)m * zt;
-      }
-      sum_d[0] = tz; sum_d[1] = ts;
-    }
-  };
-  constexpr bool COMBINE_LATE = !TOPM && WPS != 8;      // by the wavefront that forms the entropy, off the path to tau; with four workgroups per CU
-  if (!COMBINE_LATE && wid == 0) combine();             // that wavefront would be the last one (and with TOPM the sums' LDS is used again below)
-  // tau = exact K-th largest logit: first value (from the top) where the running count reaches K.
-  // Descending value order: positive values from the highest lane down, then negative values from
-  // lane 0 up.
+  // ---------------- their logits that reach the bound ----------------
   {
-    const int above_p = tot_p - (before_p + incl_p);                   // positive elements in higher lanes
-    if (above_p < K && above_p + lane_pos >= K) {                      // at most one lane
-      int run = above_p;
+    if (WPS == 8) { wait_vector_memory(); cell_q = *(const uint4*)((unsigned char*)map + tid * 16); }
+    float x[8];
+    LogitTraits<1>::unpack(cell_q, x);
+    float* el_v = list.values();
+    int32_t* el_i = list.ids();
+    if (WPS == 8) {
+      if (my_chunk >= 0) {
 #pragma unroll
-      for (int j = WPL - 1; j >= 0; --j) {
-        const int n = (int)(hist[w0 + j] & 0xffffu);
-        if (run < K && run + n >= K) { sh_tau_rank = HP_WORDS + WPL * tid + j; sh_n_gt = run; }
-        run += n;
+        for (int j = 0; j < 8; ++j) {
+          const int id = my_chunk * 8 + j;
+          if (id < V && x[j] >= tau) {
+            const int at = atomicAdd(&hs.n_el, 1);
+            if (at < HIST_LIST) { el_v[at] = x[j]; el_i[at] = id; }
+          }
+        }
       }
-    }
-    const int above_n = tot_p + before_n + incl_n - lane_neg;          // everything positive, and negatives in lower lanes
-    if (above_n < K && above_n + lane_neg >= K) {
-      int run = above_n;
+    } else if (listed && wid * WAVE < n_cells * CPC) {   // wavefronts with a cell
+      uint32_t hit = 0u;
 #pragma unroll
-      for (int j = 0; j < WPL; ++j) {
-        const int n = (int)(hist[w0 + j] >> 16);
-        if (run < K && run + n >= K) { sh_tau_rank = HP_WORDS - 1 - (WPL * tid + j); sh_n_gt = run; }
-        run += n;
+      for (int j = 0; j < 8; ++j) hit |= (my_chunk >= 0 && my_chunk * 8 + j < V && x[j] >= tau ? 1u : 0u) << j;
+      int at = append_places(__popc(hit), &hs.n_el);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if ((hit >> j) & 1u) {
+          if (at < HIST_LIST) { el_v[at] = x[j]; el_i[at] = my_chunk * 8 + j; }
+          ++at;
+        }
       }
     }
   }
-  __syncthreads();
-  C2T_PT(PT_TAU);
-  // Leave this path (uniformly) if a logit that is not masked lies above the window (|x| >= 2^7, +inf, NaN), if a
-  // 16-bit counter overflowed (the total is then off by a multiple of 65535 or 65536), if logits
-  // below the window exist and the K-th largest logit is not a positive window value (then they
-  // could be among the top K, which the histogram cannot rank), or if fewer than K logits lie
-  // in the window while some are masked (the top K then ends with masked entries).
+  if (lane == 0) { hs.red_d[0][wid] = Z; hs.red_d[1][wid] = S; hs.total[wid] = total; }
+  if (tid == 0) hs.m = m;
+  __syncthreads();                                       // sums and list complete
+  C2T_PT(PT_CELLS_READ);
+
+  int counted = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) counted += hs.total[w];
+  const int n_tiny = hs.out.n_tiny, n_ninf = hs.out.n_masked;
   const int n_elems = (sg.tail_chunk >= 0 ? (sg.ncell - 1) * 8 + sg.tail_valid : sg.ncell * 8);
-  // With the entropy over the M largest logits: also if some but not all of the logits below the
-  // window are among them (which ones cannot be told from the histogram).
-  if (mag_hi >= HP_MAG_LO + HP_MAG_SPAN || tot_p + tot_n + n_tiny + n_ninf != n_elems || (n_tiny > 0 && sh_tau_rank < HP_WORDS) ||
-      (n_ninf > 0 && sh_tau_rank < 0) ||
-      (TOPM && n_tiny > 0 && tot_p < M && M < tot_p + n_tiny)) {
+  int n_el = listed ? hs.n_el : HIST_LIST + 1;
+  // Leave this path (uniformly) if a logit that is not masked lies above the window (|x| >= 2^7, +inf, NaN), or if a
+  // 16-bit counter overflowed (the total is then off by a multiple of 65535 or 65536).
+  bool leave = hs.out.mag_max >= HP_MAG_LO + HP_MAG_SPAN || counted + n_tiny + n_ninf != n_elems;
+  int before_p = 0, before_n = 0, tot_p = 0;            // TOPM: counts in lower lanes / in the whole segment
+  if (TOPM) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w < wid) { before_p += hs.scan_p[w]; before_n += hs.scan_n[w]; }
+      tot_p += hs.scan_p[w];
+    }
+    // ... or if some but not all of the logits below the window are among the M largest (which ones cannot be told from the histogram)
+    leave = leave || (n_tiny > 0 && tot_p < M && M < tot_p + n_tiny);
+  }
+  if (__builtin_expect(!leave && (n_tiny > 0 || n_el > HIST_LIST || n_el < min(K, n_elems)), 0)) {
+    n_el = settle_hist<NT>(tid, rowp, V, K, sg, (LdsWords)hist, lds_address(list.list), n_el, n_tiny, n_ninf);
+    leave = n_el == UNSETTLED;
+    __syncthreads();                                     // the list is complete
+  }
+  if (__builtin_expect(leave, 0)) {
     __syncthreads();
-    generic_segment<1, NT>(rowp, V, K, M, sg, map_lds, sel, rr, 2u);
-    return SegmentTop{RANKED_IN_RR, false};
+    generic_segment<1, NT>(tid, rowp, V, K, M, sg, (unsigned char*)hist, sel, rr, 2u);
+    return SegmentTop{RANKED_IN_RR};
   }
   if (TOPM) {
     // Eq. 2, second line: Z and S restricted to the M largest logits.  A lane's values, from the
     // top: its positive magnitudes descending, then its negative ones ascending; `above` of them
-    // lie in other lanes.  Same reference chain as for S (lane top, wave top, m): one sign throughout.
+    // lie in other lanes.
     double zm = 0.0, sm = 0.0;
     // (logits below the window, |x| < 2^-25, rank between the positive and the negative window values)
     const int above_p = tot_p - (before_p + incl_p), above_n = tot_p + n_tiny + before_n + incl_n - lane_neg;
-    const double vt = (double)vtop;
     // A lane whose positive (negative) values all rank within the first M contributes the sums it
     // already has; only the lane that holds the M-th largest logit walks its bins.
     const bool part_p = lane_pos > 0 && above_p < M && above_p + lane_pos > M;
@@ -1348,103 +1567,48 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       LaneCounts<WPL> counts;
 #pragma unroll
       for (int j = 0; j < WPL; ++j) counts.w[j] = hist[w0 + j];
-      const TopMPart part = top_m_boundary_lane<WPL>(tid, counts, part_p, part_p ? above_p : above_n, M, vt);
+      const TopMPart part = top_m_boundary_lane<WPL>(tid, counts, part_p, part_p ? above_p : above_n, M, md);
       zm += part.zm; sm += part.sm;
     }
-    if (lane_pos | lane_neg) sm += (vt - (double)vw) * zm;
     zm = wave_sum(zm); sm = wave_sum(sm);
-    if (lane == 0) { red_d[0][wid] = zm; red_d[1][wid] = sm; }     // red_v still holds the waves' top values
+    if (lane == 0) { hs.red_m_d[0][wid] = zm; hs.red_m_d[1][wid] = sm; }
+    if (tid == 0) hs.tot_p = tot_p;
     __syncthreads();
-    if (wid == 0) {
-      double tz = 0.0, ts = 0.0;
-      if (lane < NW && red_d[0][lane] > 0.0) { tz = red_d[0][lane]; ts = red_d[1][lane] + ((double)red_v[lane] - (double)m) * tz; }
-      tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
-      tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
-      tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
-      tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts);
-      if (lane == 0) {
-        if (n_tiny > 0 && tot_p < M) {                    // then M >= tot_p + n_tiny: all of them are among the M largest
-          const double zt = (double)n_tiny + sh_out.s_tiny;
-          tz += zt; ts += sh_out.s_tiny - (double)m * zt;
-        }
-        rr->ZM = tz; rr->SM = ts;
-      }
-    }
   }
-  float tau = -INFINITY;
-  int eq_limit = K;
-  if (sh_tau_rank >= 0) { tau = __uint_as_float(hp_code_of_rank(sh_tau_rank) << 16); eq_limit = K - sh_n_gt; }
+  return SegmentTop{n_el};
+}
 
-  // ---------------- cells that can hold a top-K element ----------------
-  // Fewer than K cells exceed tau; cells equal to tau are all taken when they fit (the exact
-  // ranking below keeps the lowest ids).
-  const int ncells = cells_in_segment<NT>(sg.ncell);
-  if (WPS == 8) {                                        // (see collect_cells)
-#pragma unroll 1
-    for (int c8 = tid * 8; c8 < ncells; c8 += NT * 8) {  // eight keys per read (the map is padded to 16 bytes)
-      const uint4 kq = *(const uint4*)(map + c8);
-      const uint32_t kw[4] = {kq.x, kq.y, kq.z, kq.w};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float kv = (j & 1) ? bf16_hi(kw[j >> 1]) : bf16_lo(kw[j >> 1]);
-        if (c8 + j < ncells && kv >= tau) {
-          const int slot = atomicAdd(&sh_ncell, 1);
-          if (slot < sel.cell_cap) cell_list[slot] = c8 + j;
-        }
-      }
+// The record of a row (or split) from its wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.
+template <int NT, bool TOPM>
+__device__ __forceinline__ void combine_hist(const HistShared<NT>& hs, int M, RowResult& rr) {
+  constexpr int NW = NT / WAVE;
+  static_assert(NW <= 16, "one DPP row holds the per-wave sums");
+  const int lane = lane_id(), n_tiny = hs.out.n_tiny;
+  const double md = (double)hs.m;
+  const auto sum = [&](const double (&red)[2][NW], bool with_tiny, double& z, double& s) {
+    double tz = lane < NW ? red[0][lane] : 0.0, ts = lane < NW ? red[1][lane] : 0.0;
+    tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
+    tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
+    tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
+    if (NW > 8) { tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts); }
+    if (with_tiny && n_tiny) {                          // e^x = 1 + x, x e^x = x for |x| < 2^-25
+      const double zt = (double)n_tiny + hs.out.s_tiny;
+      tz += zt; ts += hs.out.s_tiny - md * zt;
     }
-  } else {
-#pragma unroll 1
-  for (int w8 = wid * (WAVE * 8); w8 < ncells; w8 += NT * 8) {   // eight keys per read (the map is padded to 16 bytes)
-    const int c8 = w8 + lane * 8;
-    uint32_t hit = 0u;
-    if (c8 < ncells) {
-      const uint4 kq = *(const uint4*)(map + c8);
-      const uint32_t kw[4] = {kq.x, kq.y, kq.z, kq.w};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float kv = (j & 1) ? bf16_hi(kw[j >> 1]) : bf16_lo(kw[j >> 1]);
-        hit |= (c8 + j < ncells && kv >= tau ? 1u : 0u) << j;
-      }
-    }
-    int slot = append_places(__popc(hit), &sh_ncell);
-    while (hit) {
-      const int j = __ffs(hit) - 1; hit &= hit - 1;
-      if (slot < sel.cell_cap) cell_list[slot] = c8 + j;
-      ++slot;
-    }
+    z = tz; s = ts;
+  };
+  double Z, S, ZM = 0.0, SM = 0.0;
+  sum(hs.red_d, true, Z, S);
+  if (TOPM) sum(hs.red_m_d, hs.tot_p < M, ZM, SM);       // (where the tiny ones are among the M largest, all of them are)
+  if (lane == 0) {
+    RowPartial r; r.ref = md; r.a = 0.0; r.Z = Z; r.S = S; r.n_top = 0; r.flags = 0u;
+    rr.part = r;
+    if (TOPM) { rr.ZM = ZM; rr.SM = SM; }
   }
-  }
-  if (tid == 0) sh_cnt = 0;
-  __syncthreads();
-  C2T_PT(PT_CELLS_LISTED);
-  int n_cells = sh_ncell;
-  const bool ties = n_cells > sel.cell_cap;                  // massive ties at tau: the cells above it, then a tie scan
-  if (ties) {
-    n_cells = list_cells<1, NT>(map, ncells, tau, true, sel.cell_cap, cell_list, &sh_ncell);
-    if (tid == 0) sh_cnt = 0;
-    __syncthreads();
-  }
-  // While the first wavefronts wait for the cells they read again (n_cells is K to 2K, four chunks each), the last one
-  // forms the row's entropy from the sums: fp64 log, exp and divide, half a microsecond and more off the tail.
-  const bool entropy = sp.nsplit == 1;
-  if (wid == NW - 1) {
-    if (COMBINE_LATE) combine();
-    if (lane == 0) { RowPartial r; r.ref = (double)m; r.a = 0.0; r.Z = sum_d[0]; r.S = sum_d[1]; r.n_top = 0; r.flags = 0u; rr->part = r; }
-    if (entropy) row_entropy(st, sp, b, slot, (double)m, 0.0, sum_d[0], sum_d[1], 0u, *rr);
-  }
-  collect_cells<1, NT, WPS != 8>(rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
-  if (ties) {
-    tie_scan<1, NT>(rowp, sg, V, tau, eq_limit, sel, &sh_cnt, scan_tmp);
-    __syncthreads();
-  }
-  C2T_PT(PT_CELLS_READ);
-  return SegmentTop{min(sh_cnt, sel.list_cap), entropy};
 }
 
 // grid: rows_launched * nsplit workgroups of NT threads.
-// Dynamic LDS (sp.lds_bytes): [HP_WORDS counters | cell map, padded to 16 bytes]; the selection's
-// element list and the tail reuse all of it.
+// Dynamic LDS (sp.lds_bytes): see hist_lds_bytes; generic_segment and the tail reuse all of it.
 // WPS: waves per SIMD the kernel is built for.  8 = four workgroups per CU on 64 registers a lane;
 // 6 = three workgroups per CU on 80 registers, which needs no spills.
 template <int NT, bool TOPM, int WPS, int REPL, bool COOP>
@@ -1462,23 +1626,27 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
   const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_elems * 2);
   const Segment sg = make_segment<8>(V, split, cps);
   __shared__ RowResult rr;
+  __shared__ HistShared<NT> hs;
   C2T_PT(PT_START);
   // The classifier's parameters (5h+1 <= 1281 floats) are copied to LDS for the scoring step: the
   // loads are issued now, four floats a thread, and stored behind the streaming loop.
-  const ClassifierStage cst = stage_classifier(cls, sp.h, TOPM ? nullptr : (float*)(dyn_lds + sp.w_lds_off));
-  const SelectLds sel = make_select_lds<NT, 8>(dyn_lds, sp.lds_bytes);
-  SegmentTop top{RANKED_IN_RR, false};
+  const ClassifierStage cst = stage_classifier(threadIdx.x, cls, sp.h, TOPM ? nullptr : (float*)(dyn_lds + sp.w_lds_off));
+  const SelectLds sel = make_select_lds<NT, 8>(dyn_lds, sp.lds_bytes), list = hist_list(dyn_lds + HP_WORDS * 4 * REPL);
+  SegmentTop top{RANKED_IN_RR};
+  int tid = threadIdx.x;
   if (sg.ncell == 0) {                                     // (loaded again here: the copy above must not stay in registers for this)
-    store_classifier(stage_classifier(cls, sp.h, cst.dst));
-    if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
+    store_classifier(tid, stage_classifier(tid, cls, sp.h, cst.dst));
+    if (tid == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
     __syncthreads();
   } else {
-    top = hist_segment<NT, TOPM, WPS, REPL, COOP>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, dyn_lds + HP_WORDS * 4 * REPL,
-                                                  sel, &rr, cst, cls, st, sp, split, rl, b, row);
+    top = hist_segment<NT, TOPM, WPS, REPL, COOP>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, list, (uint32_t*)(dyn_lds + HP_WORDS * 4 * REPL + HIST_LIST * 8),
+                                                  (uint16_t*)(dyn_lds + hist_lds_bytes<NT>(REPL)), sel, &rr, hs, cst, cls, st, sp, split, rl, row, tid);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
-  finish_layer<NT, false>(st, sp, b, f, nf, split, rl, rr, top, sel, dyn_lds, cls, cst.dst, [] {},
-                   [&](RowResult& r) { if (TOPM) top_m_of_whole_row<1, NT>(rowp, V, sp.M, r); });
+  const TailArguments& ta = tail_arguments<40>();
+  finish_layer<NT>(tid, ta.st, ta.sp, b, f, nf, split, rl, rr, top, list, sel, dyn_lds, cls, cst.dst,
+                   [&] { if (top.n_el >= 0) combine_hist<NT, TOPM>(hs, sp.M, rr); },
+                   [&](RowResult& r) { if (TOPM) top_m_of_whole_row<1, NT>(tid, rowp, V, sp.M, r, sel); });
 }
 
 // Plain streaming read: the practical HBM ceiling.

@@ -116,9 +116,8 @@ __device__ __forceinline__ float mlp_logit_lds(LdsFloats w, int h, float P, floa
 // Same operations in the same order.  P: LDS, the candidates' joint probabilities; act: scratch of act_bytes;
 // entry behind a barrier that publishes P.  Returns z in lanes tid < K.
 template <int NT>
-__device__ __forceinline__ float mlp_logit_spread(LdsFloats w, int h, const float* P, float H, float d, int K, uint32_t k_inverse,
+__device__ __forceinline__ float mlp_logit_spread(int tid, LdsFloats w, int h, const float* P, float H, float d, int K, uint32_t k_inverse,
                                                   float* act, int act_bytes) {
-  const int tid = threadIdx.x;
   LdsFloats W1 = w; LdsFloats b1 = w + 3 * h; LdsFloats w2 = w + 4 * h;
   const int step = NT / K, first = (int)(((uint32_t)tid * k_inverse) >> 20), cand = tid - first * K;      // first = tid / K
   const int block = min(h, act_bytes / (4 * K));             // units whose activations fit the scratch
@@ -149,7 +148,9 @@ constexpr int SP_MAX_F = 64;
 constexpr int C2T_MAX_BUDGET_DEV = 1024;                  // n_out limit of the reranking
 constexpr int C2T_MAX_CANDIDATES_DEV = 2048;              // F*K limit of the per-sequence step
 
-// What a workgroup that shares a row hands over besides its counts and cell keys.
+// What a workgroup that shares a row hands over besides its counts, its cell keys and its columns' maxima.
+constexpr int COOP_MAX_WORKGROUPS = 256;                  // workgroups of such a launch: one per CU at most
+constexpr int COOP_MAX_ROWS = COOP_MAX_WORKGROUPS / 2;
 struct __attribute__((aligned(32))) CoopAcc {
   double s_tiny; int32_t n_tiny, n_masked; uint32_t mag_max, max_pattern;   // see OutsideAcc; max_pattern: packed maximum of the segment's bf16 patterns
 };
@@ -169,9 +170,22 @@ struct ScoreParams {
   int coop;
   int coop_map_stride;                                       // keys per row in coop_map (a multiple of 8)
   uint32_t* coop_hist;                                       // [launched row][coop][HP_WORDS] counts of a segment
-  uint16_t* coop_map;                                        // [launched row][coop_map_stride] cell keys of the whole row
+  uint16_t* coop_map;                                        // [launched row][coop_map_stride] cell keys of the whole row; behind all COOP_MAX_ROWS of
+                                                             // them [launched row][coop][WAVE] uint32: the segments' columns
   CoopAcc* coop_acc;                                         // [launched row][coop]
 };
+
+// The last two arguments of the layer kernels, at byte OFFSET of the argument segment, read again for the tail: the compiler loads what it
+// can reach early and keeps it in scalar registers through the streaming loop, or, there being too few, in lanes of vector registers.
+struct TailArguments { TreeState st; ScoreParams sp; };
+template <int OFFSET>
+__device__ __forceinline__ const TailArguments& tail_arguments() {
+  static_assert(OFFSET % 8 == 0 && sizeof(TreeState) % 8 == 0, "both lie where the kernel's argument list has them");
+  typedef const __attribute__((address_space(4))) char* Arguments;
+  Arguments p = (Arguments)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const TailArguments*)(const __attribute__((address_space(4))) TailArguments*)(p + OFFSET);
+}
 
 // What one workgroup of the logits pass leaves in LDS for its (row, split): the record, the segment's
 // top-K list (value desc, id asc) where it has been ranked, and what scoring the row needs besides.
@@ -201,8 +215,10 @@ __device__ __forceinline__ int sum_of_lanes(int tshift, int v) {
 // min(SEL_CELL_CAP, NT / CPC, list entries / elements per cell), which the host keeps >= 2K - 1.
 constexpr int CPC = 4;                         // chunks per cell of the cell map: four sweeps of a lane
 constexpr int SEL_CELL_CAP = 256;              // size of the candidate-cell list
+constexpr int SEL_AUX_BYTES = 2048 + SEL_CELL_CAP * 4;   // behind the list: the lanes' maxima and the cells of generic_segment
 struct SelectLds {
   unsigned char* list;
+  unsigned char* aux;
   int list_cap;       // entries
   int cell_cap;
   __device__ __forceinline__ float* values() const { return (float*)list; }
@@ -211,55 +227,51 @@ struct SelectLds {
 template <int NT, int EPC>
 __device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int bytes) {
   SelectLds s;
-  s.list = base; s.list_cap = bytes / 8;
+  s.list = base; s.list_cap = (bytes - SEL_AUX_BYTES) / 8; s.aux = base + bytes - SEL_AUX_BYTES;
   s.cell_cap = min(min(SEL_CELL_CAP, NT / CPC), s.list_cap / (CPC * EPC));
   return s;
 }
 
-// ---- ranking of the element list by (logit desc, id asc), exactly; the best K go to topv, topi.
-// Short lists (the usual case: K to 2K-1 elements): T lanes per element, each compares it with every T-th entry, one
-// value per step; the partial ranks are summed over the T lanes.  nt threads take part: all of them, or the first RANK_NT where
-// another wavefront forms the row's entropy meanwhile.
-constexpr int RANK_NT = 256;
-__device__ __forceinline__ void rank_short(int K, const SelectLds& sel, int n_el, int nt, float* topv, int32_t* topi) {
-  const int tid = threadIdx.x;
-  const float* el_v = sel.values(); const int32_t* el_i = sel.ids();
-  if (tid >= nt) return;                                     // whole wavefronts
-  int tshift = 0;
-  while (tshift < 4 && (n_el << (tshift + 1)) <= nt) ++tshift;
-  const int T = 1 << tshift, e = tid >> tshift, sub = tid & (T - 1);
-  const bool mine = e < n_el;
-  int rank = 0, id = 0; float v = 0.f;
-  if (mine) {
-    v = el_v[e]; id = el_i[e];
-    for (int o = sub; o < n_el; o += T) {
-      const float q = el_v[o];
-      if (q > v) rank += 1;
-      else if (q == v && o != e) rank += el_i[o] < id;
-    }
-  }
-  rank = sum_of_lanes(tshift, rank);
-  if (mine && sub == 0 && rank < K) { topv[rank] = v; topi[rank] = id; }
-}
-// Any length, all threads: the best K to topv, topi.
+// ---- ranking of the element list by (logit desc, id asc), exactly; the best K go to topv, topi.  By every wavefront but the last, which
+// forms the row's entropy meanwhile: T lanes per element (four at least), each compares it with four entries per LDS read, of every
+// T-th group of four; the partial ranks are summed over the T lanes.  Equal logits are told apart by id where a count shows them.
 template <int NT>
-__device__ __forceinline__ void rank_long(int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
+__device__ __forceinline__ void rank_list(int tid, int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
+  constexpr int nt = NT - WAVE;
   const float* el_v = sel.values(); const int32_t* el_i = sel.ids();
+  if (tid >= nt) return;                                     // a whole wavefront
+  int tshift = 2;
+  while (tshift < 4 && (n_el << (tshift + 1)) <= nt) ++tshift;
+  const int T = 1 << tshift, sub = tid & (T - 1);
 #pragma unroll 1
-  for (int e = threadIdx.x; e < n_el; e += NT) {
-    const float v = el_v[e]; const int id = el_i[e];
-    // every dependent LDS read is slow while the neighbouring workgroups fill their histograms
-    const int rank = count_ahead4(el_v, n_el, 0, 4, v, e, [&](int o) { return el_i[o] < id; });
-    if (rank < K) { topv[rank] = v; topi[rank] = id; }
+  for (int e0 = 0; e0 < n_el; e0 += nt >> tshift) {
+    const int e = e0 + (tid >> tshift);
+    const bool mine = e < n_el;
+    int rank = 0, id = 0; float v = 0.f;                     // rank: greater ones; equal ones (itself among them) in the upper half
+    if (mine) {
+      v = el_v[e]; id = el_i[e];
+#pragma unroll 2
+      for (int o = sub * 4; o < n_el; o += T * 4) {          // (values past the last, three at most, are read and not counted)
+        const float4 q = *(const float4*)(el_v + o);
+        const int past = max(o + 4 - n_el, 0);               // of the group's four
+        const uint32_t gt = (q.x > v ? 1u : 0u) | (q.y > v ? 2u : 0u) | (q.z > v ? 4u : 0u) | (q.w > v ? 8u : 0u);
+        const uint32_t eq = (q.x == v ? 1u : 0u) | (q.y == v ? 2u : 0u) | (q.z == v ? 4u : 0u) | (q.w == v ? 8u : 0u), in = 15u >> past;
+        rank += __popc(gt & in) + (__popc(eq & in) << 16);
+      }
+    }
+    rank = sum_of_lanes(tshift, rank);
+    const bool tied = mine && (rank >> 16) > 1 && (rank & 0xffff) < K;   // (the same in the element's T lanes)
+    rank &= 0xffff;
+    if (__builtin_amdgcn_ballot_w64(tied) != 0ull) {         // (uniform)
+      int ahead = 0;
+      if (tied) {
+#pragma unroll 4
+        for (int o = sub; o < n_el; o += T) ahead += (int)(el_v[o] == v && el_i[o] < id);
+      }
+      rank += sum_of_lanes(tshift, ahead);
+    }
+    if (mine && sub == 0 && rank < K) { topv[rank] = v; topi[rank] = id; }
   }
-}
-// Short: four lanes or more to an element.  K to 2K-1 elements with four workgroups on a CU, by all threads: K = 32 0.77 us, K = 64
-// 1.74 (by 256 of them 1.06 and, one lane to an element, 2.9).
-template <int NT, bool LAST_WAVE_BUSY>
-__device__ __forceinline__ void rank_list(int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
-  constexpr int nt = LAST_WAVE_BUSY ? RANK_NT : NT;
-  if (n_el <= nt / 4) rank_short(K, sel, n_el, nt, topv, topi);
-  else rank_long<NT>(K, sel, n_el, topv, topi);
 }
 
 // ---- row level: entropy (Eq. 2) from the row's sums, and what the row's frontier node hands down; by one wavefront.
@@ -290,9 +302,9 @@ struct Candidate { float z, P, H; int32_t tok; uint32_t info; };   // as lane t 
 // `w`: the classifier parameters in global memory, read-only for the whole kernel: every lane
 // reads the same addresses, so the loads are scalar and touch neither LDS nor the vector memory path.
 template <int NT>
-__device__ __forceinline__ Candidate score_row(const TreeState& s, const ScoreParams& sp, int b, int f, RowResult& rr, int n,
+__device__ __forceinline__ Candidate score_row(int tid, const TreeState& s, const ScoreParams& sp, int b, int f, RowResult& rr, int n,
                                           const float* __restrict__ w, const float* w_lds, unsigned char* lds) {
-  const int tid = threadIdx.x, K = sp.K, FK = sp.F * K;
+  const int K = sp.K, FK = sp.F * K;
   const float H = rr.H;
   const bool spread = w_lds && sp.h >= sp.spread_min;        // (uniform)
   float z = -INFINITY, p32 = 0.f, P32 = 0.f; int tok = -1;
@@ -305,7 +317,7 @@ __device__ __forceinline__ Candidate score_row(const TreeState& s, const ScorePa
   if (spread) {
     if (tid < K) rr.topv[tid] = P32;                         // each lane overwrites the logit it has just read
     __syncthreads();
-    z = mlp_logit_spread<NT>((LdsFloats)w_lds, sp.h, rr.topv, H, (float)sp.layer, K, sp.k_inverse, (float*)lds, sp.lds_bytes);
+    z = mlp_logit_spread<NT>(tid, (LdsFloats)w_lds, sp.h, rr.topv, H, (float)sp.layer, K, sp.k_inverse, (float*)lds, sp.lds_bytes);
     if (!mine) z = -INFINITY;
   }
   const uint32_t info = (rr.bad ? 1u : 0u) | (rr.part.flags & 2u);
@@ -367,12 +379,12 @@ __device__ __forceinline__ RowSums merge_records(const RowPartial* rp, int nspli
   m.R = (double)Rf; m.flags = fl; m.Z = wave_sum(Z); m.S = wave_sum(S);
   return m;
 }
-__device__ __forceinline__ void stage_lists(const ScoreParams& sp, int64_t row_launched, const SelectLds& sel) {
+__device__ __forceinline__ void stage_lists(int tid, const ScoreParams& sp, int64_t row_launched, const SelectLds& sel) {
   const int nsplit = sp.nsplit, K = sp.K, per_row = nsplit * K, nt = blockDim.x;
   const RowPartial* rp = sp.part + row_launched * nsplit;
   const float* tv = sp.part_topv + row_launched * per_row;
   const int32_t* ti = sp.part_topi + row_launched * per_row;
-  for (int ent = threadIdx.x; ent < per_row; ent += nt) {
+  for (int ent = tid; ent < per_row; ent += nt) {
     const int n_top = ld_dev(&rp[ent / K].n_top);
     const float v = ld_dev(tv + ent); const int32_t id = ld_dev(ti + ent);
     const bool ok = ent % K < n_top;
@@ -381,12 +393,12 @@ __device__ __forceinline__ void stage_lists(const ScoreParams& sp, int64_t row_l
   }
 }
 // Lists that exceed the element list (very many splits): ranked from global memory, the best K to rr.topv, rr.topi.
-__device__ __forceinline__ void rank_lists_from_memory(const ScoreParams& sp, int64_t row_launched, RowResult& rr) {
+__device__ __forceinline__ void rank_lists_from_memory(int tid, const ScoreParams& sp, int64_t row_launched, RowResult& rr) {
   const int nsplit = sp.nsplit, K = sp.K, per_row = nsplit * K, nt = blockDim.x;
   const RowPartial* rp = sp.part + row_launched * nsplit;
   const float* tv = sp.part_topv + row_launched * per_row;
   const int32_t* ti = sp.part_topi + row_launched * per_row;
-  for (int ent = threadIdx.x; ent < per_row; ent += nt) {
+  for (int ent = tid; ent < per_row; ent += nt) {
     const int q = ent / K, e = ent % K;
     if (e >= ld_dev(&rp[q].n_top)) continue;
     const float v = ld_dev(tv + ent); const int vi = ld_dev(ti + ent);
@@ -477,7 +489,7 @@ __host__ __device__ inline size_t score_lds_bytes(int FK) {
 
 // PER: candidates per thread; F * K <= PER * NT.
 template <int NT, int PER>
-__device__ __forceinline__ void prune_sequence(const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps) {
+__device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, const ScoreParams& sp, int b, int nf, unsigned char* lds, PruneShared<NT>& ps) {
   constexpr int NW = NT / WAVE;
   constexpr bool BY_DIGITS = PER > 1;                        // long lists are cut by the radix select at once
   const int F = sp.F, K = sp.K, N = sp.N, layer = sp.layer;
@@ -495,7 +507,7 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
   float* list_P = (float*)(hist + NW * WAVE); float* list_H = list_P + PRUNE_RANK_MAX;
   static_assert(NW * WAVE + 2 * PRUNE_RANK_MAX <= PRUNE_HIST_WORDS, "they fit there");
 
-  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
+  const int lane = tid & (WAVE - 1), wid = tid >> 6;
   const int64_t cb = (int64_t)b * FK, fb = (int64_t)b * F;   // uniform bases: the lanes' offsets stay 32 bits wide
   // the candidates of all F*K slots are requested up front: one memory round trip
   float my_z[PER], my_P[PER], my_H[PER]; int32_t my_tok[PER];
@@ -741,8 +753,8 @@ __device__ __forceinline__ void prune_sequence(const TreeState& s, const ScorePa
 // 14.1 -> 12.4 us, K = 64 (all survive) 16.1 -> 14.4.  (A walk over the survivors' ballot with three compares a
 // survivor: 1.5 us slower at K = 64.)
 template <int NT>
-__device__ __forceinline__ void prune_lone_row(const TreeState& s, const ScoreParams& sp, int b, const RowResult& rr, const Candidate& c) {
-  const int tid = threadIdx.x, F = sp.F, K = sp.K, FK = F * K, layer = sp.layer;
+__device__ __forceinline__ void prune_lone_row(int tid, const TreeState& s, const ScoreParams& sp, int b, const RowResult& rr, const Candidate& c) {
+  const int F = sp.F, K = sp.K, FK = F * K, layer = sp.layer;
   const int64_t cb = (int64_t)b * FK, fb = (int64_t)b * F;
   for (int i = tid < WAVE ? tid + NT : tid; i < FK; i += NT) s.c_kept[cb + i] = 0;
   if (tid >= WAVE) return;
@@ -785,11 +797,11 @@ __device__ __forceinline__ void prune_lone_row(const TreeState& s, const ScorePa
 // workgroup that took the last of `expected` (it resets the counter for the next layer).  Every
 // store the ticket publishes is issued by wave 0 (at most 64 candidates or list entries, lanes
 // 0..63), whose own wait covers them; the other waves only meet at the barrier.
-__device__ __forceinline__ bool last_arrival(int32_t* ticket, int expected) {
+__device__ __forceinline__ bool last_arrival(int tid, int32_t* ticket, int expected) {
   __shared__ int32_t sh_last;
-  if (threadIdx.x < WAVE) {
+  if (tid < WAVE) {
     wait_vector_memory();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       sh_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expected - 1;
       if (sh_last) st_dev(ticket, 0);
     }
@@ -798,31 +810,31 @@ __device__ __forceinline__ bool last_arrival(int32_t* ticket, int expected) {
   return sh_last != 0;
 }
 
-// How a workgroup leaves its segment's largest logits: n_el elements in the element list, not ranked yet, or (n_el < 0)
-// ranked in rr.topv, rr.topi with rr.part.n_top of them.  entropy: row_entropy has been run on an unsplit row.
-struct SegmentTop { int n_el; bool entropy; };
+// How a workgroup leaves its segment's largest logits: n_el elements in its element list, not ranked yet, or (n_el < 0)
+// ranked in rr.topv, rr.topi with rr.part.n_top of them.
+struct SegmentTop { int n_el; };
 
 // Tail of the logits pass for the workgroup that owned (sequence b, frontier slot f, split).  The workgroup
 // that completes a row scores the row's candidates; the workgroup that completes a sequence's last row prunes
 // and appends.  Both overlap with the other workgroups' streaming, so the whole layer is one launch.
 // On entry a barrier lies behind the last write to the list and to rr, except that `record()`, called by the last
 // wavefront while the others rank the list, completes rr.part (sums, flags; its lane 0 writes).
-// LATE_ENTROPY: lists come with the entropy still to be formed (by the last wavefront, while the others rank).
+// list: the segment's element list; sel: the one that merged rows are ranked in.
 // after_merge(rr): called by the whole workgroup that has merged a split row, before the row is scored
 // (the entropy over the M largest logits of a split row is computed there, over the whole row).
-template <int NT, bool LATE_ENTROPY, typename Record, typename AfterMerge>
-__device__ __forceinline__ void finish_layer(const TreeState& s, const ScoreParams& sp, int b, int f, int nf, int split,
-                                             int64_t row_launched, RowResult& rr, SegmentTop top, const SelectLds& sel, unsigned char* lds,
+template <int NT, typename Record, typename AfterMerge>
+__device__ __forceinline__ void finish_layer(int tid, const TreeState& s, const ScoreParams& sp, int b, int f, int nf, int split,
+                                             int64_t row_launched, RowResult& rr, SegmentTop top, const SelectLds& list, const SelectLds& sel, unsigned char* lds,
                                              const float* __restrict__ cls, const float* cls_lds, Record record, AfterMerge after_merge) {
   constexpr int NW = NT / WAVE;
-  const int tid = threadIdx.x, K = sp.K;
+  const int K = sp.K;
   const bool last_wave = (tid >> 6) == NW - 1;
   const int64_t slot = (int64_t)b * sp.F + f;
   if (last_wave) {
     record();
-    if (sp.nsplit == 1 && !top.entropy) row_entropy(s, sp, b, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
+    if (sp.nsplit == 1) row_entropy(s, sp, b, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
   }
-  if (top.n_el >= 0) rank_list<NT, LATE_ENTROPY>(K, sel, top.n_el, rr.topv, rr.topi);
+  if (top.n_el >= 0) rank_list<NT>(tid, K, list, top.n_el, rr.topv, rr.topi);
   __syncthreads();                                           // rr is complete
   int n = top.n_el >= 0 ? min(top.n_el, K) : rr.part.n_top;
   C2T_PT(PT_RANKED);
@@ -832,12 +844,12 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
     if (rr.part.flags & 1u) n = 0;
     if (tid < n) { st_dev(sp.part_topv + po * K + tid, rr.topv[tid]); st_dev(sp.part_topi + po * K + tid, rr.topi[tid]); }
     if (tid == 0) { RowPartial r = rr.part; r.n_top = n; st_dev(sp.part + po, r); }
-    if (!last_arrival(s.row_tickets + slot, nsplit)) { C2T_PT_FLUSH(); return; }
+    if (!last_arrival(tid, s.row_tickets + slot, nsplit)) { C2T_PT_FLUSH(); return; }
     const bool staged = per_row <= sel.list_cap;             // the lists fit the element list
     const RowPartial* rp = sp.part + row_launched * nsplit;
     RowSums m;
     if (last_wave) m = merge_records(rp, nsplit);
-    if (staged) stage_lists(sp, row_launched, sel); else rank_lists_from_memory(sp, row_launched, rr);
+    if (staged) stage_lists(tid, sp, row_launched, sel); else rank_lists_from_memory(tid, sp, row_launched, rr);
     __syncthreads();
     if (last_wave) {
       if (lane_id() == 0) {
@@ -846,7 +858,7 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
       }
       if (sp.M <= 0) row_entropy(s, sp, b, slot, m.R, m.R, m.Z, m.S, m.flags, rr);
     }
-    if (staged) rank_list<NT, true>(K, sel, per_row, rr.topv, rr.topi);
+    if (staged) rank_list<NT>(tid, K, sel, per_row, rr.topv, rr.topi);
     __syncthreads();
     if (sp.M > 0) {
       after_merge(rr);
@@ -856,21 +868,21 @@ __device__ __forceinline__ void finish_layer(const TreeState& s, const ScorePara
     n = rr.part.n_top;
     C2T_PT(PT_MERGED);
   }
-  const Candidate c = score_row<NT>(s, sp, b, f, rr, n, cls, cls_lds, lds);
+  const Candidate c = score_row<NT>(tid, s, sp, b, f, rr, n, cls, cls_lds, lds);
   C2T_PT(PT_PUBLISHED);
   if (nf == 1) {                                             // (uniform) the only row: nothing is handed over
     C2T_PT(PT_TICKET);
-    prune_lone_row<NT>(s, sp, b, rr, c);
+    prune_lone_row<NT>(tid, s, sp, b, rr, c);
     C2T_PT(PT_PRUNED);
     C2T_PT_FLUSH();
     return;
   }
-  if (!last_arrival(s.tickets + b, nf)) { C2T_PT_FLUSH(); return; }   // nf: the sequence's frontier size, known since the workgroup started
+  if (!last_arrival(tid, s.tickets + b, nf)) { C2T_PT_FLUSH(); return; }   // nf: the sequence's frontier size, known since the workgroup started
   C2T_PT(PT_TICKET);
   // one candidate a thread wherever that is enough: an eighth of the instructions of the general form
   PruneShared<NT>& ps = *(PruneShared<NT>*)(lds + prune_list_bytes(sp.F * K));
-  if (sp.F * K <= NT) prune_sequence<NT, 1>(s, sp, b, nf, lds, ps);
-  else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(s, sp, b, nf, lds, ps);
+  if (sp.F * K <= NT) prune_sequence<NT, 1>(tid, s, sp, b, nf, lds, ps);
+  else prune_sequence<NT, C2T_MAX_CANDIDATES_DEV / NT>(tid, s, sp, b, nf, lds, ps);
   C2T_PT(PT_PRUNED);
   C2T_PT_FLUSH();
 }
