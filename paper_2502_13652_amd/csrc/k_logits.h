@@ -63,12 +63,15 @@ template <> struct LogitTraits<0> {     // fp32
   static __device__ __forceinline__ float from_key(key_t k) { return k; }
 };
 
-// A logits chunk is read once per layer: a non-temporal load keeps the stream from evicting what
-// the workgroups reuse (the e^v table, the classifier) from the L2.
+// A logits chunk is read once per layer, but for the cells that hold one of the row's largest.  STREAMED: a non-temporal load keeps the
+// stream from evicting what the workgroups reuse (the e^v table, the classifier) from the L2.  Launches of at most one workgroup a CU read with the
+// usual policy: of their few rows the cells are still in the L2 when they are read again (16 sequences of 128256, masked, 174.3 -> 171.7 us a
+// phase, one of 128256 117.7 -> 116.9).
 typedef uint32_t c2t_uint4v __attribute__((ext_vector_type(4)));
-// 16 bytes at descriptor base + lane offset + scalar offset, non-temporal; zeros past the descriptor's size
+// 16 bytes at descriptor base + lane offset + scalar offset; zeros past the descriptor's size
+template <bool STREAMED = true>
 __device__ __forceinline__ uint4 load_stream_buffer(__amdgpu_buffer_rsrc_t rs, uint32_t lane_off, uint32_t scalar_off) {
-  const c2t_uint4v v = __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, scalar_off, 2);
+  const c2t_uint4v v = __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, scalar_off, STREAMED ? 2 : 0);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ uint4 load_stream(const uint4* p) {
@@ -885,7 +888,8 @@ __device__ __forceinline__ uint32_t quad_exchange_2(uint32_t lower, uint32_t upp
 }
 
 // The streaming loop: `whole` chunks of the segment that rs covers and, with tail_valid > 0, a partial one behind them; q: the lane's first
-// DEPTH chunks, on their way; keys: LDS, the cells' keys, the lane's first.  MASKED: see hist_chunk_masked.
+// DEPTH chunks, on their way; keys: LDS, the cells' keys, the lane's first.  MASKED: see hist_chunk_masked.  ONE_COPY: of the histogram,
+// with four workgroups a CU.
 typedef __attribute__((address_space(3))) uint16_t* LdsHalves;
 struct StreamInput { __amdgpu_buffer_rsrc_t rs; int whole, tail_valid; uint32_t vo, hist; LdsHalves keys; OutsideAcc* acc; };
 template <int NT, int DEPTH, bool MASKED, bool ONE_COPY>
@@ -908,9 +912,9 @@ __device__ __forceinline__ uint32_t hist_stream(const StreamInput& in, uint4 (&q
 #pragma unroll
       for (int k = 0; k < 4; k += 2) {
         const uint32_t pe = count(q[c + k]);
-        q[c + k] = load_stream_buffer(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k) * (NT * 16u));
+        q[c + k] = load_stream_buffer<ONE_COPY>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k) * (NT * 16u));
         const uint32_t po = count(q[c + k + 1]);
-        q[c + k + 1] = load_stream_buffer(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k + 1) * (NT * 16u));
+        q[c + k + 1] = load_stream_buffer<ONE_COPY>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k + 1) * (NT * 16u));
         half[k / 2] = quad_exchange_1(pe, po, odd);
       }
       const uint32_t key = quad_exchange_2(half[0], half[1], upper);
@@ -962,7 +966,7 @@ __device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chu
   in.rs = uniform_buffer(base, (in.whole + (in.tail_valid > 0 ? 1 : 0)) * 16);
   uint4 q[DEPTH];
 #pragma unroll
-  for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer(in.rs, vo, (uint32_t)k * (NT * 16u));
+  for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<false>(in.rs, vo, (uint32_t)k * (NT * 16u));
   return hist_stream<NT, DEPTH, true, false>(in, q);
 }
 
@@ -1288,7 +1292,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     in.hist = lds_address(hist) + (REPL > 1 ? (uint32_t)(tid & (REPL - 1)) * (HP_WORDS * 4u) : 0u);
     uint4 q[DEPTH];
 #pragma unroll
-    for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer(in.rs, in.vo, (uint32_t)k * (NT * 16u));
+    for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<REPL == 1>(in.rs, in.vo, (uint32_t)k * (NT * 16u));
     // Streaming waves issue ahead of the waves of co-resident workgroups that are in their
     // (latency-bound) epilogue or tail: the memory pipeline stays fed.  Measured: 3 % per full layer.
     __builtin_amdgcn_s_setprio(3);
