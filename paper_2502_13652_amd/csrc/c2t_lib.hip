@@ -35,6 +35,7 @@ constexpr int HP_NT = 512;                     // workgroup size of the histogra
 #define C2T_HP_REPL_ALONE 4
 #endif
 constexpr int HP_REPL_ALONE = C2T_HP_REPL_ALONE;   // histogram copies of a workgroup that has its CU to itself (launches of at most one workgroup per CU)
+constexpr int64_t STREAMED_BYTES = 24 << 20;       // logits of a launch beyond which they are not kept in the L2s (eight of 4 MB)
 constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
 constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
@@ -183,7 +184,7 @@ struct c2t_ctx {
   bool have_cls, finalized;
   int ns_first, ns_other;      // row splits in use
   bool share_first, share_other;   // rows may be shared by workgroups (the default; off where the caller has set the splits itself)
-  size_t lds_raised[3];        // dynamic LDS this context has asked the runtime to allow each build of its layer kernel so far
+  size_t lds_raised[4];        // dynamic LDS this context has asked the runtime to allow each build of its layer kernel so far
   int n_cus;                   // compute units of the device the context was created on
   // optional event timing of the logits pass
   std::vector<hipEvent_t> ev;
@@ -266,25 +267,29 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
     // 2048: 114 / 120, 3072: 166 / 163, 4096: 209 / 215, 8192: 388 / 393.  Four per CU whenever a CU
     // gets more than one workgroup; a workgroup that is alone on its CU is 2-3 % faster on 80 registers.
     const bool coop = share.n > 1;                           // (never with four per CU: see share_of)
-#define C2T_HIST_KERNEL(TOPM)                                                                                   \
-  (four_per_cu ? (const void*)k_logits_hist<HP_NT, TOPM, 8, 1, false>                                            \
-               : coop ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, true> : (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, false>)
+    const bool streamed = (int64_t)c.batch * rows_per_seq * c.vocab * 2 > STREAMED_BYTES;    // see load_stream_buffer; shared rows are few, and never streamed
+#define C2T_HIST_KERNEL(TOPM)                                                           \
+  (four_per_cu ? (const void*)k_logits_hist<HP_NT, TOPM, 8, 1, false, true>             \
+   : coop      ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, true, false> \
+   : streamed  ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, false, true> \
+               : (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, false, false>)
     const void* fn = topm ? C2T_HIST_KERNEL(true) : C2T_HIST_KERNEL(false);
 #undef C2T_HIST_KERNEL
-    size_t& raised = x->lds_raised[four_per_cu ? 1 : coop ? 2 : 0];
+    size_t& raised = x->lds_raised[four_per_cu ? 1 : coop ? 2 : streamed ? 3 : 0];
     if (lds > raised) {                                     // beyond the 48 KB a kernel may use without asking
       hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
       raised = lds;
     }
-#define C2T_LAUNCH_HIST(TOPM, WPS, REPL, COOP)                                                                                      \
-  hipExtLaunchKernelGGL((k_logits_hist<HP_NT, TOPM, WPS, REPL, COOP>), dim3(grid), dim3(HP_NT), lds, s, ev0, ev1, 0, logits, stride, \
+#define C2T_LAUNCH_HIST(TOPM, WPS, REPL, COOP, STREAMED)                                                                                      \
+  hipExtLaunchKernelGGL((k_logits_hist<HP_NT, TOPM, WPS, REPL, COOP, STREAMED>), dim3(grid), dim3(HP_NT), lds, s, ev0, ev1, 0, logits, stride, \
                         c.vocab, cps, (const double*)x->tab_e, (const float*)x->st.cls, x->st, sp)
-#define C2T_LAUNCH_HIST_BUILD(TOPM)                                      \
-  do {                                                                   \
-    if (four_per_cu) C2T_LAUNCH_HIST(TOPM, 8, 1, false);                 \
-    else if (coop) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, true);        \
-    else C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, false);                 \
+#define C2T_LAUNCH_HIST_BUILD(TOPM)                                          \
+  do {                                                                       \
+    if (four_per_cu) C2T_LAUNCH_HIST(TOPM, 8, 1, false, true);               \
+    else if (coop) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, true, false);     \
+    else if (streamed) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, false, true); \
+    else C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, false, false);              \
   } while (0)
     if (topm) C2T_LAUNCH_HIST_BUILD(true); else C2T_LAUNCH_HIST_BUILD(false);
 #undef C2T_LAUNCH_HIST_BUILD
@@ -367,7 +372,7 @@ int c2t_create(const c2t_config* cfg, void* ws, size_t bytes, c2t_ctx** out) {
   x->tab_e = (double*)(w + L.tab_e);
   x->z_beta = cfg->beta <= 0.0f ? -INFINITY : (float)std::log((double)cfg->beta / (1.0 - (double)cfg->beta));
   x->layer = -1; x->have_cls = false; x->finalized = false; x->ev_used = 0; x->sample_every = 1; x->sample_first = 0; x->phase_no = -1;
-  x->lds_raised[0] = x->lds_raised[1] = x->lds_raised[2] = 48 * 1024;
+  x->lds_raised[0] = x->lds_raised[1] = x->lds_raised[2] = x->lds_raised[3] = 48 * 1024;
   {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)

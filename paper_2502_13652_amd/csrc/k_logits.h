@@ -64,9 +64,9 @@ template <> struct LogitTraits<0> {     // fp32
 };
 
 // A logits chunk is read once per layer, but for the cells that hold one of the row's largest.  STREAMED: a non-temporal load keeps the
-// stream from evicting what the workgroups reuse (the e^v table, the classifier) from the L2.  Launches of at most one workgroup a CU read with the
-// usual policy: of their few rows the cells are still in the L2 when they are read again (16 sequences of 128256, masked, 174.3 -> 171.7 us a
-// phase, one of 128256 117.7 -> 116.9).
+// stream from evicting what the workgroups reuse (the e^v table, the classifier) from the L2.  Launches of at most one workgroup a CU
+// whose rows fit the L2s read with the usual policy: the cells are still there when they are read again (phases: one sequence of 128256
+// 123.5 -> 121.1 us, four of 20011 with 64 rows each 261.7 -> 258.2; 256 rows of 128256 a layer, 64 MB, 177.3 -> 178.9: those are STREAMED).
 typedef uint32_t c2t_uint4v __attribute__((ext_vector_type(4)));
 // 16 bytes at descriptor base + lane offset + scalar offset; zeros past the descriptor's size
 template <bool STREAMED = true>
@@ -889,10 +889,10 @@ __device__ __forceinline__ uint32_t quad_exchange_2(uint32_t lower, uint32_t upp
 
 // The streaming loop: `whole` chunks of the segment that rs covers and, with tail_valid > 0, a partial one behind them; q: the lane's first
 // DEPTH chunks, on their way; keys: LDS, the cells' keys, the lane's first.  MASKED: see hist_chunk_masked.  ONE_COPY: of the histogram,
-// with four workgroups a CU.
+// with four workgroups a CU.  STREAMED: see load_stream_buffer.
 typedef __attribute__((address_space(3))) uint16_t* LdsHalves;
 struct StreamInput { __amdgpu_buffer_rsrc_t rs; int whole, tail_valid; uint32_t vo, hist; LdsHalves keys; OutsideAcc* acc; };
-template <int NT, int DEPTH, bool MASKED, bool ONE_COPY>
+template <int NT, int DEPTH, bool MASKED, bool ONE_COPY, bool STREAMED>
 __device__ __forceinline__ uint32_t hist_stream(const StreamInput& in, uint4 (&q)[DEPTH]) {
   static_assert(DEPTH % 4 == 0 && CPC == 4, "whole cells");
   const uint32_t own = MASKED ? lds_address(&in.acc->masked_by_lane[lane_id()]) : 0u;
@@ -912,9 +912,9 @@ __device__ __forceinline__ uint32_t hist_stream(const StreamInput& in, uint4 (&q
 #pragma unroll
       for (int k = 0; k < 4; k += 2) {
         const uint32_t pe = count(q[c + k]);
-        q[c + k] = load_stream_buffer<ONE_COPY>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k) * (NT * 16u));
+        q[c + k] = load_stream_buffer<STREAMED>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k) * (NT * 16u));
         const uint32_t po = count(q[c + k + 1]);
-        q[c + k + 1] = load_stream_buffer<ONE_COPY>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k + 1) * (NT * 16u));
+        q[c + k + 1] = load_stream_buffer<STREAMED>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k + 1) * (NT * 16u));
         half[k / 2] = quad_exchange_1(pe, po, odd);
       }
       const uint32_t key = quad_exchange_2(half[0], half[1], upper);
@@ -957,7 +957,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_buffer(uint64_t base, 
 
 // The loop of a row that masks part of its vocabulary.  Out of line, so that rows that mask nothing keep their registers.
 // A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 41 us when every chunk took hist_chunk_outside, 30.
-template <int NT>
+template <int NT, bool STREAMED>
 __device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, uint32_t hist, LdsHalves keys, OutsideAcc* acc) {
   constexpr int DEPTH = 4;
   const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
@@ -966,8 +966,8 @@ __device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chu
   in.rs = uniform_buffer(base, (in.whole + (in.tail_valid > 0 ? 1 : 0)) * 16);
   uint4 q[DEPTH];
 #pragma unroll
-  for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<false>(in.rs, vo, (uint32_t)k * (NT * 16u));
-  return hist_stream<NT, DEPTH, true, false>(in, q);
+  for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<STREAMED>(in.rs, vo, (uint32_t)k * (NT * 16u));
+  return hist_stream<NT, DEPTH, true, false, STREAMED>(in, q);
 }
 
 // 16 bytes a lane from global memory straight into LDS, to `address` (uniform over the wavefront) + 16 lane: no registers while it is on its way.
@@ -1247,7 +1247,7 @@ __device__ __forceinline__ bool share_row(int tid, const ScoreParams& sp, int sp
 // default kernel carries none of its registers).
 // COOP: built with the hand-over of a shared row (see share_row); returns HANDED_OVER in the workgroups
 // that have handed their segment over and are done.
-template <int NT, bool TOPM, int WPS, int REPL, bool COOP>
+template <int NT, bool TOPM, int WPS, int REPL, bool COOP, bool STREAMED>
 __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ rowp, int V, int K, int M, const Segment& sg_own,
                                              const double* __restrict__ tab_e, uint32_t* __restrict__ hist, const SelectLds& list, uint32_t* columns, uint16_t* map,
                                              const SelectLds& sel, RowResult* rr, HistShared<NT>& hs,
@@ -1292,7 +1292,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     in.hist = lds_address(hist) + (REPL > 1 ? (uint32_t)(tid & (REPL - 1)) * (HP_WORDS * 4u) : 0u);
     uint4 q[DEPTH];
 #pragma unroll
-    for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<REPL == 1>(in.rs, in.vo, (uint32_t)k * (NT * 16u));
+    for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<STREAMED>(in.rs, in.vo, (uint32_t)k * (NT * 16u));
     // Streaming waves issue ahead of the waves of co-resident workgroups that are in their
     // (latency-bound) epilogue or tail: the memory pipeline stays fed.  Measured: 3 % per full layer.
     __builtin_amdgcn_s_setprio(3);
@@ -1315,11 +1315,11 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     }
     vo_after = in.vo;
     if (masks != 0) {                                    // (nothing of this path is live across the call: what is would be spilled for every row)
-      M2 = hist_stream_masked<NT>(base, in.whole, in.tail_valid, in.vo, in.hist, in.keys, &hs.out);
+      M2 = hist_stream_masked<NT, STREAMED>(base, in.whole, in.tail_valid, in.vo, in.hist, in.keys, &hs.out);
       C2T_PT(PT_STREAM_END);
       store_classifier(tid, stage_classifier(tid, cls, sp.h, cst.dst));
     } else {
-      M2 = hist_stream<NT, DEPTH, false, REPL == 1>(in, q);
+      M2 = hist_stream<NT, DEPTH, false, REPL == 1, STREAMED>(in, q);
       C2T_PT(PT_STREAM_END);
       store_classifier(tid, cst);                               // published by the barriers below
     }
@@ -1615,7 +1615,7 @@ __device__ __forceinline__ void combine_hist(const HistShared<NT>& hs, int M, Ro
 // Dynamic LDS (sp.lds_bytes): see hist_lds_bytes; generic_segment and the tail reuse all of it.
 // WPS: waves per SIMD the kernel is built for.  8 = four workgroups per CU on 64 registers a lane;
 // 6 = three workgroups per CU on 80 registers, which needs no spills.
-template <int NT, bool TOPM, int WPS, int REPL, bool COOP>
+template <int NT, bool TOPM, int WPS, int REPL, bool COOP, bool STREAMED>
 __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     const void* __restrict__ logits, int64_t row_stride_elems, int V, int cps, const double* __restrict__ tab_e,
     const float* __restrict__ cls, TreeState st, ScoreParams sp) {
@@ -1643,7 +1643,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     if (tid == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
     __syncthreads();
   } else {
-    top = hist_segment<NT, TOPM, WPS, REPL, COOP>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, list, (uint32_t*)(dyn_lds + HP_WORDS * 4 * REPL + HIST_LIST * 8),
+    top = hist_segment<NT, TOPM, WPS, REPL, COOP, STREAMED>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, list, (uint32_t*)(dyn_lds + HP_WORDS * 4 * REPL + HIST_LIST * 8),
                                                   (uint16_t*)(dyn_lds + hist_lds_bytes<NT>(REPL)), sel, &rr, hs, cst, cls, st, sp, split, rl, row, tid);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
