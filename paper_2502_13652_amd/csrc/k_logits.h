@@ -975,34 +975,6 @@ __device__ __forceinline__ void lds_chunk_load(const uint4* p, uint32_t address)
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p, (__attribute__((address_space(3))) void*)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)address), 16, 0, 0);
 }
 
-// The lane that holds the M-th largest logit: the sums over the logits it contributes to the top M
-// (from its top value down: positive magnitudes descending, or negative ones ascending), relative to
-// its top value vt.  Out of line: one lane per row gets here, and inlined its registers would be
-// charged to every workgroup's epilogue.  e^v is computed here (at most WPL values) rather than
-// fetched from the tables again: a load issued at this point waits behind all the logits in flight
-// on the CU, several microseconds that the whole workgroup would spend at its next barrier.
-template <int WPL> struct LaneCounts { uint32_t w[WPL]; };      // by value: a reference would put the counts in scratch memory
-struct TopMPart { double zm, sm; };
-template <int WPL>
-__device__ __noinline__ TopMPart top_m_boundary_lane(int tid, LaneCounts<WPL> counts, bool positive, int above, int M, double vt) {
-  const uint32_t (&cw)[WPL] = counts.w;
-  double zm = 0.0, sm = 0.0;
-  int run = above;
-#pragma unroll 1
-  for (int jj = 0; jj < WPL; ++jj) {
-    const int j = positive ? WPL - 1 - jj : jj;
-    const int n = positive ? (int)(cw[j] & 0xffffu) : (int)(cw[j] >> 16), take = max(0, min(n, M - run));
-    run += n;
-    if (take) {
-      const double v = (double)hp_value_of_mag(WPL * tid + j, !positive);
-      const double t = (double)take * exp(v);
-      zm += t; sm += (v - vt) * t;
-    }
-  }
-  TopMPart r; r.zm = zm; r.sm = sm;
-  return r;
-}
-
 // A thread's share of the classifier's parameters on its way from global memory to LDS.
 struct ClassifierStage { float4 q; float* dst; bool mine; };
 __device__ __forceinline__ ClassifierStage stage_classifier(int tid, const float* __restrict__ cls, int h, float* dst) {
@@ -1562,17 +1534,27 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     // (logits below the window, |x| < 2^-25, rank between the positive and the negative window values)
     const int above_p = tot_p - (before_p + incl_p), above_n = tot_p + n_tiny + before_n + incl_n - lane_neg;
     // A lane whose positive (negative) values all rank within the first M contributes the sums it
-    // already has; only the lane that holds the M-th largest logit walks its bins.
+    // already has.  The bins of the one lane that holds the M-th largest logit are told apart by WPL lanes of its wavefront, one
+    // exponential each at the same time instead of WPL one after the other (by that lane alone, out of line, 32 sequences of 128256 with M = 1000
+    // took 207.5 us a phase, 194.8 so).  They are computed rather than fetched from the tables again: a load issued at this point waits behind all the logits in flight
+    // on the CU, several microseconds that the whole workgroup would spend at its next barrier.
     const bool part_p = lane_pos > 0 && above_p < M && above_p + lane_pos > M;
     const bool part_n = lane_neg > 0 && above_n < M && above_n + lane_neg > M;
     if (lane_pos > 0 && above_p + lane_pos <= M) { zm += Zpos; sm += Spos; }
     if (lane_neg > 0 && above_n + lane_neg <= M) { zm += Zneg; sm += Sneg; }
-    if (part_p || part_n) {
-      LaneCounts<WPL> counts;
-#pragma unroll
-      for (int j = 0; j < WPL; ++j) counts.w[j] = hist[w0 + j];
-      const TopMPart part = top_m_boundary_lane<WPL>(tid, counts, part_p, part_p ? above_p : above_n, M, md);
-      zm += part.zm; sm += part.sm;
+    const uint64_t boundary = __builtin_amdgcn_ballot_w64(part_p || part_n);
+    if (boundary != 0ull) {                              // (uniform) one lane of the workgroup at most
+      const int owner = (int)__builtin_ctzll(boundary);
+      const bool positive = __builtin_amdgcn_readlane(part_p ? 1 : 0, owner) != 0;
+      const int above = __builtin_amdgcn_readlane(part_p ? above_p : above_n, owner);
+      const int mag = WPL * (wid * WAVE + owner) + (positive ? WPL - 1 - lane : lane);       // lane 0: the largest of its values
+      int n = 0;
+      if (lane < WPL) n = (int)(positive ? hist[mag] & 0xffffu : hist[mag] >> 16);
+      const int take = min(n, M - (above + wave_scan_incl(n) - n));
+      if (take > 0) {
+        const double v = (double)hp_value_of_mag((uint32_t)mag, !positive), t = (double)take * exp(v);
+        zm += t; sm += (v - md) * t;
+      }
     }
     zm = wave_sum(zm); sm = wave_sum(sm);
     if (lane == 0) { hs.red_m_d[0][wid] = zm; hs.red_m_d[1][wid] = sm; }
