@@ -1463,32 +1463,26 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   // ---------------- their logits that reach the bound ----------------
   {
     if (WPS == 8) { wait_vector_memory(); cell_q = *(const uint4*)((unsigned char*)map + tid * 16); }
-    float x[8];
-    LogitTraits<1>::unpack(cell_q, x);
     float* el_v = list.values();
     int32_t* el_i = list.ids();
-    if (WPS == 8) {
-      if (my_chunk >= 0) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int id = my_chunk * 8 + j;
-          if (id < V && x[j] >= tau) {
-            const int at = atomicAdd(&hs.n_el, 1);
-            if (at < HIST_LIST) { el_v[at] = x[j]; el_i[at] = id; }
-          }
-        }
-      }
-    } else if (listed && wid * WAVE < n_cells * CPC) {   // wavefronts with a cell
+    if (wid * WAVE < n_cells * CPC) {                    // wavefronts with a cell
+      float x[8];
+      LogitTraits<1>::unpack(cell_q, x);
       uint32_t hit = 0u;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) hit |= (my_chunk >= 0 && my_chunk * 8 + j < V && x[j] >= tau ? 1u : 0u) << j;
-      int at = append_places(__popc(hit), &hs.n_el);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        if ((hit >> j) & 1u) {
-          if (at < HIST_LIST) { el_v[at] = x[j]; el_i[at] = my_chunk * 8 + j; }
-          ++at;
-        }
+      for (int j = 0; j < 8; ++j) hit |= (x[j] >= tau ? 1u : 0u) << j;
+      if (my_chunk < 0) hit = 0u;
+      else if (my_chunk * 8 + 8 > V) hit &= (1u << (V - my_chunk * 8)) - 1u;
+      int at = 0;
+      if (WPS != 8) at = append_places(__popc(hit), &hs.n_el);
+      // One pass a logit that reaches the bound, of which few chunks hold a second one: a branch for each of the eight places was a
+      // hundred instructions of a wavefront that issues one every four cycles (2.3 % of a phase of one sequence).
+      while (hit) {
+        const int j = __ffs(hit) - 1; hit &= hit - 1;
+        const uint32_t w = (j & 4) ? ((j & 2) ? cell_q.w : cell_q.z) : (j & 2) ? cell_q.y : cell_q.x;
+        if (WPS == 8) at = atomicAdd(&hs.n_el, 1);
+        if (at < HIST_LIST) { el_v[at] = (j & 1) ? bf16_hi(w) : bf16_lo(w); el_i[at] = my_chunk * 8 + j; }
+        ++at;
       }
     }
   }
