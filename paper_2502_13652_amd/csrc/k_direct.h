@@ -1,21 +1,22 @@
 // Logits pass without a histogram: every logit's exponential is evaluated in fp64 as it is read, in one
 // pass over the segment.  The path of fp32 rows (whose values are too many to be counted).
 //
-// What bounds it: instruction issue.  About nineteen vector instructions a logit, fourteen of them fp64 at 5.3 cycles
-// each: 2048 rows of 65536 run at 3.95 TB/s, half of what HBM delivers.  The two-pass form that it replaces read
+// What bounds it: instruction issue.  About seventeen vector instructions a logit, thirteen of them fp64: 2048 rows of 65536
+// take 121 us, 4.4 TB/s, two thirds of what HBM delivers (with a table of 32, one more fp64 instruction, a move of the logit and its own test
+// for NaN 127 us; 320 rows of 32000 25.6 -> 24.3).  The two-pass form that it replaces read
 // the segment twice (the maximum first) and spent about fifty instructions in the library's exp.
 //
 // Sums.  Each wavefront keeps Z = sum e^(x-a) and S = sum (x-a) e^(x-a) against its own largest logit so far, a
 // (uniform over the wave; re-referenced when a tile raises it, which happens a few times a segment), so
 // every term of S has one sign and nothing overflows.  No barrier is needed for any of it.
 //
-// Exponential.  e^t = 2^(k/32) e^r with k = rint(32 t / ln 2), |r| <= ln 2 / 64 (Cody and Waite's reduction, Tang's
-// table): 2^(j/32) for j = 0..31 from a 256-byte LDS table (32 doubles fill the 64 banks once: equal banks mean
-// equal addresses, so the random reads of a wave never conflict), e^r from a polynomial of degree 5
-// interpolated at Chebyshev nodes (1.4e-16 relative with rounded coefficients); the exponent k div 32 is added to the table entry's
+// Exponential.  e^t = 2^(k/256) e^r with k = rint(256 t / ln 2), |r| <= ln 2 / 512 (Cody and Waite's reduction, Tang's
+// table): 2^(j/256) for j = 0..255 from a 2 KB LDS table (of 32 entries the random reads of a wave would never conflict, but the
+// polynomial needs a degree more, and it is issue that binds), e^r from a polynomial of degree 4 whose upper three coefficients interpolate
+// (e^r - 1 - r) / r^2 at Chebyshev nodes (9.5e-18 relative); the exponent k div 256 is added to the table entry's
 // upper word, from which the entry's own share has been taken off beforehand, as table-driven exponentials commonly do.  In all e^t is
-// good to about 4.2e-16 + 3.3e-17 |t| relative (20000 points against 60 digits): the rounding of the table entry and of the product, and the one-constant
-// reduction's |k| 7e-19.  t <= 0 here, so the last matters only as |t| e^t, at most e^-1.
+// good to about 3.0e-16 + 3.8e-17 |t| relative (20000 points against 50 digits): the rounding of the table entry and of the product, and the one-constant
+// reduction's.  t <= 0 here, so the last matters only as |t| e^t, at most e^-1.
 //
 // Top K without reading anything twice: the K-th largest of the maxima of 64 lane columns (128 for large K) is
 // a lower bound of the K-th largest logit from the first tile on; the few finite logits that reach it are appended
@@ -28,13 +29,13 @@
 
 namespace c2t {
 
-constexpr int EXP_TAB = 32;
+constexpr int EXP_TAB_BITS = 8, EXP_TAB = 1 << EXP_TAB_BITS;
 constexpr int DIRECT_CHUNKS = 4;               // chunks a lane reads per tile: 64 bytes, two tiles in flight
 
-// 2^(j/32) with j << 15 taken off its upper word: adding k << 15 for any k = 32 q + j then gives 2^(k/32)
+// 2^(j/256) with j << 12 taken off its upper word: adding k << 12 for any k = 256 q + j then gives 2^(k/256)
 __device__ __forceinline__ double exp_tab_entry(int j) {
-  const uint64_t u = (uint64_t)__double_as_longlong(exp2((double)j * 0.03125));
-  return __longlong_as_double((long long)(u - ((uint64_t)j << 47)));
+  const uint64_t u = (uint64_t)__double_as_longlong(exp2((double)j / EXP_TAB));
+  return __longlong_as_double((long long)(u - ((uint64_t)j << (52 - EXP_TAB_BITS))));
 }
 __device__ __forceinline__ float max3_raw(float a, float b, float c) {     // without the canonicalising copies fmaxf adds per operand
   float d;
@@ -44,16 +45,18 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c) {     // wi
 // e^t for t <= 0 (clamped at -700: 1e-304, nothing beside the largest term, which is 1)
 __device__ __forceinline__ double exp_nonpositive(double t, const double* tab) {
   constexpr double SHIFT = 6755399441055744.0;               // 1.5 * 2^52: the sum's low word is the rounded integer
-  const double kf = __builtin_fma(t, 0x1.71547652b82fep+5, SHIFT);
+  const double kf = __builtin_fma(t, 0x1.71547652b82fep+8, SHIFT);
   const int k = __double2loint(kf);
-  const double r = __builtin_fma(kf - SHIFT, -0x1.62e42fefa39efp-6, t);
+  const double r = __builtin_fma(kf - SHIFT, -0x1.62e42fefa39efp-9, t);
   const double e = tab[k & (EXP_TAB - 1)];
-  double p = __builtin_fma(0x1.11115c0928b20p-7, r, 0x1.5555d887832fap-5);
-  p = __builtin_fma(p, r, 0x1.5555555547d38p-3);
-  p = __builtin_fma(p, r, 0x1.ffffffffd0b99p-2);
+  double p = __builtin_fma(0x1.5555565bb9890p-5, r, 0x1.555556deeba30p-3);
+  p = __builtin_fma(p, r, 0.5);
   p = __builtin_fma(p, r, 1.0);
   p = __builtin_fma(p, r, 1.0);
-  return __hiloint2double(__double2hiint(e) + (int)((uint32_t)k << 15), __double2loint(e)) * p;
+  typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+  uint2v w = __builtin_bit_cast(uint2v, e);
+  w.y += (uint32_t)k << (20 - EXP_TAB_BITS);
+  return __builtin_bit_cast(double, w) * p;
 }
 
 template <int NT>
@@ -124,7 +127,7 @@ __device__ __forceinline__ void blank_tile(uint4 (&q)[DIRECT_CHUNKS], const Segm
 
 // One tile: sums, and the logits that reach the bound.  t: the tile's number.
 template <int NT>
-__device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int t, const Segment& sg, int V, int K,
+__device__ __forceinline__ void direct_tile(uint4 (&q)[DIRECT_CHUNKS], int t, const Segment& sg, int V, int K,
                                             DirectState<NT>& s, DirectShared<NT>& sh, const SelectLds& sel) {
   typedef LogitTraits<0> T;
   const int tid = threadIdx.x;
@@ -151,13 +154,12 @@ __device__ __forceinline__ void direct_tile(const uint4 (&q)[DIRECT_CHUNKS], int
   const double ad = (double)s.a;
 #pragma unroll
   for (int c = 0; c < DIRECT_CHUNKS; ++c) {
-    uint4 qc = q[c];
-    asm volatile("" : "+v"(qc.x), "+v"(qc.y), "+v"(qc.z), "+v"(qc.w));     // (conversions of later chunks are not hoisted: they would spill)
+    asm volatile("" : "+v"(q[c].x), "+v"(q[c].y), "+v"(q[c].z), "+v"(q[c].w));     // (conversions of later chunks are not hoisted: they would spill; of a copy: a move a logit)
     float x[T::EPC];
-    T::unpack(qc, x);
+    T::unpack(q[c], x);
 #pragma unroll
     for (int j = 0; j < T::EPC; ++j) {
-      s.bad |= !(x[j] < INFINITY);
+      if (j & 1) s.bad |= __builtin_isunordered(x[j - 1], x[j]);           // (+inf shows in the maximum)
       const double d = fmax((double)x[j] - ad, -700.0);
       const double e = exp_nonpositive(d, sh.exp_tab);
       s.Z += e; s.S = __builtin_fma(d, e, s.S);
@@ -293,9 +295,6 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
                                                      const SelectLds& sel, const ClassifierStage cst, DirectShared<NT>& sh, RowResult* rr) {
   constexpr int TILE = DIRECT_CHUNKS * NT;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
-  if (tid < EXP_TAB) sh.exp_tab[tid] = exp_tab_entry(tid);
-  if (tid == 0) { sh.n_list = 0; sh.bad = 0; sh.n_reach = 0; }
-  __syncthreads();
   const int n_tiles = (sg.ncell + TILE - 1) / TILE, n_whole = sg.tail_chunk >= 0 ? sg.ncell - 1 : sg.ncell;
   const __amdgpu_buffer_rsrc_t rs = segment_buffer(rowp, sg);
   const uint32_t vo = (uint32_t)tid * 16u;
@@ -309,6 +308,10 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   s.tau = -3.402823466e38f;                                  // the lowest finite value: masked logits (-inf) are not listed
   load(qa, 0);
   if (n_tiles > 1) load(qb, 1);
+  static_assert(EXP_TAB <= NT, "an entry a thread, while the first tiles are on their way");
+  if (tid < EXP_TAB) sh.exp_tab[tid] = exp_tab_entry(tid);
+  if (tid == 0) { sh.n_list = 0; sh.bad = 0; sh.n_reach = 0; }
+  __syncthreads();
   for (int t = 0; t < n_tiles; t += 2) {
     if ((t + 1) * TILE > n_whole) blank_tile<NT>(qa, sg, t * TILE);
     direct_tile<NT>(qa, t, sg, V, K, s, sh, sel);
@@ -322,7 +325,7 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   store_classifier((int)threadIdx.x, cst);                                     // published by the barriers below
   s.Z = wave_sum(s.Z); s.S = wave_sum(s.S);
   if (lane == 0) { sh.wave_z[wid] = s.Z; sh.wave_s[wid] = s.S; sh.wave_a[wid] = s.a; }
-  if (s.bad) sh.bad = 1;
+  if (s.bad || !(s.lane_max < INFINITY)) sh.bad = 1;
   __syncthreads();
   C2T_PT(PT_HIST_COMPLETE);
   int n_el = sh.n_list;
