@@ -814,30 +814,33 @@ __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t h
   return pat;
 }
 
-// ---- a lower bound of the K-th largest logit (K <= COLUMNS_MAX_K), from the maxima of 64 columns of lanes: each row of 16 lanes is sorted
-// (bitonic, a lane permutation and a v_med3 a stage), and the smallest of the four rows' ceil(K / 4)-th largest maxima is reached by
-// K of them.  Of randomly placed logits 27 reach it for K = 16 (18 the exact K-th largest of the 64).  A tenth of a microsecond,
-// where a search by ballots takes half of one: its rounds are chains of scalar instructions.  For K = 32 it would be 59 logits and now and
-// then more than the 128 cells that can be listed: 8192 rows of 152064 494 us a layer, with the exact K-th largest logit 464.
-constexpr int COLUMNS_MAX_K = 16;
+// ---- a lower bound of the K-th largest logit (K <= COLUMNS_MAX_K), from the maxima of 64 columns of lanes: sorted in rows of 16 lanes
+// (bitonic, a lane permutation and a v_med3 a stage).  K <= 16: the smallest of the four rows' ceil(K / 4)-th largest maxima is reached by
+// K of them; of randomly placed logits 27 reach it for K = 16 (18 the exact K-th largest of the 64).  A tenth of a microsecond,
+// where a search by ballots takes half of one: its rounds are chains of scalar instructions.  17 to 32: that bound would let 59 logits pass for K = 32,
+// now and then more than the 128 cells that can be listed; the rows are merged on, and the bound is the 32nd largest of the 64 maxima,
+// which 44 logits reach (63 at most in 300 rows).  The exact K-th largest logit of the counts (kth_of_counts) takes a microsecond more a row:
+// four sequences of 20011 with 64 x 32 candidates took 237.3 us a phase with it, 230.4 so, 256 of 152064 with 32 x 32 1820 and 1803.
+constexpr int COLUMNS_MAX_K = 32;
 constexpr uint32_t HP_NONE2 = HP_F16_NEG_INF2;                          // pattern of a lane without a chunk
 constexpr uint32_t HP_LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1);  // the window's lowest value, which also stands in for masked logits
 #define C2T_DPP_QUAD_XOR3 0x1B      /* quad_perm [3,2,1,0] */
 #define C2T_DPP_ROW_SHL(n) (0x100 | (n))
+#define C2T_DPP_ROW_ROR(n) (0x120 | (n))
 __device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c) {
   uint32_t d;
   asm("v_med3_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
   return d;
 }
+__device__ __forceinline__ uint32_t xor4_of_row(uint32_t x) {
+  const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, C2T_DPP_ROW_SHL(4), 0xf, 0x5, false);      // quads 0 and 2: from the lanes above
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)up, (int)x, C2T_DPP_ROW_SHR(4), 0xf, 0xa, false);                   // quads 1 and 3: from the lanes below
+}
+// of a pair of lanes that differ in bit b the one with the bit clear takes the maximum: the median with the largest number, the other with the smallest
+__device__ __forceinline__ uint32_t takes_max(int bit) { return (uint32_t)(((lane_id() >> bit) & 1) - 1); }
 // every row of 16 lanes descending
 __device__ __forceinline__ uint32_t sort_rows_of_16(uint32_t v) {
-  const int lane = lane_id();
-  // of a pair the lane with the bit clear takes the maximum: the median with the largest or the smallest number
-  const uint32_t c0 = (uint32_t)((lane & 1) - 1), c1 = (uint32_t)(((lane >> 1) & 1) - 1), c2 = (uint32_t)(((lane >> 2) & 1) - 1), c3 = (uint32_t)(((lane >> 3) & 1) - 1);
-  const auto xor4 = [](uint32_t x) {
-    const uint32_t up = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, C2T_DPP_ROW_SHL(4), 0xf, 0x5, false);      // quads 0 and 2: from the lanes above
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)up, (int)x, C2T_DPP_ROW_SHR(4), 0xf, 0xa, false);                   // quads 1 and 3: from the lanes below
-  };
+  const uint32_t c0 = takes_max(0), c1 = takes_max(1), c2 = takes_max(2), c3 = takes_max(3);
   v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
   v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR3, 0xf>(0u, v), c1);
   v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
@@ -845,24 +848,46 @@ __device__ __forceinline__ uint32_t sort_rows_of_16(uint32_t v) {
   v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, v), c1);
   v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
   v = med3_u32(v, dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, v), c3);
-  v = med3_u32(v, xor4(v), c2);
+  v = med3_u32(v, xor4_of_row(v), c2);
   v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, v), c1);
   return med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
+}
+// The 32nd largest of the wavefront's 64 values; uniform.  Two falling runs, one of them reversed: the lane-wise maxima are the larger half, the minima the
+// smaller, each of them rising and then falling or the other way round.  So the rows are merged to two falling runs of 32, and the
+// smallest of the larger half of these is the answer.
+__device__ __forceinline__ uint32_t largest_32nd(uint32_t v) {
+  const uint32_t c0 = takes_max(0), c1 = takes_max(1), c2 = takes_max(2), c3 = takes_max(3), c4 = takes_max(4);
+  v = sort_rows_of_16(v);
+  const auto rows = __builtin_amdgcn_permlane16_swap(v, v, false, false);        // the even rows, twice each; the odd rows
+  v = med3_u32((uint32_t)rows[0], dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, (uint32_t)rows[1]), c4);
+  v = med3_u32(v, dpp_u32<C2T_DPP_ROW_ROR(8), 0xf>(0u, v), c3);
+  v = med3_u32(v, xor4_of_row(v), c2);
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR2, 0xf>(0u, v), c1);
+  v = med3_u32(v, dpp_u32<C2T_DPP_QUAD_XOR1, 0xf>(0u, v), c0);
+  const auto runs = __builtin_amdgcn_permlane32_swap(v, v, false, false);        // the lower run, twice; the upper run
+  const auto upper = __builtin_amdgcn_permlane16_swap((uint32_t)runs[1], (uint32_t)runs[1], false, false);       // its first row; its second row
+  const uint32_t reversed = dpp_u32<C2T_DPP_ROW_MIRROR, 0xf>(0u, c4 ? (uint32_t)upper[1] : (uint32_t)upper[0]);
+  return wave_reduce_u32(max((uint32_t)runs[0], reversed), 0xffffffffu, [](uint32_t x, uint32_t y) { return min(x, y); });
 }
 // 16-bit keys that order like the values of the patterns
 __device__ __forceinline__ uint32_t key_of_pattern(uint32_t c) { return (c & 0x8000u) ? c ^ 0xffffu : c | 0x8000u; }
 // column: packed pattern, the lane's column maximum over the whole row; uniform result: a value that K logits at least reach, or the window's
 // lowest where fewer columns hold a logit of the window.
-__device__ __forceinline__ float bound_of_columns16(uint32_t column, int K) {
-  const uint32_t v = sort_rows_of_16(max(key_of_pattern(column & 0xffffu), key_of_pattern(column >> 16)));
+__device__ __forceinline__ float bound_of_patterns(uint32_t column, int K) {
+  const uint32_t own = max(key_of_pattern(column & 0xffffu), key_of_pattern(column >> 16));
   uint32_t key;
-  if (K == 1) {                                                         // (uniform) the maximum itself
-    key = max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
-              max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+  if (K > 16) {                                                         // (uniform)
+    key = largest_32nd(own);
   } else {
-    const int j = (K - 1) >> 2;
-    key = min(min((uint32_t)__builtin_amdgcn_readlane((int)v, j), (uint32_t)__builtin_amdgcn_readlane((int)v, 16 + j)),
-              min((uint32_t)__builtin_amdgcn_readlane((int)v, 32 + j), (uint32_t)__builtin_amdgcn_readlane((int)v, 48 + j)));
+    const uint32_t v = sort_rows_of_16(own);
+    if (K == 1) {                                                       // the maximum itself
+      key = max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+                max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+    } else {
+      const int j = (K - 1) >> 2;
+      key = min(min((uint32_t)__builtin_amdgcn_readlane((int)v, j), (uint32_t)__builtin_amdgcn_readlane((int)v, 16 + j)),
+                min((uint32_t)__builtin_amdgcn_readlane((int)v, 32 + j), (uint32_t)__builtin_amdgcn_readlane((int)v, 48 + j)));
+    }
   }
   key = max(key, key_of_pattern(HP_LOWEST));
   return __uint_as_float(((key & 0x8000u) ? key & 0x7fffu : key ^ 0xffffu) << 16);
@@ -1352,7 +1377,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     const KthOfCounts kth = kth_of_counts<NT>(tid, (LdsWords)hist, K);
     tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;
   } else {
-    tau = bound_of_columns16(column, K);
+    tau = bound_of_patterns(column, K);
   }
   const int ncells = quad_cells_in_segment<NT>(sg.ncell);
   if (WPS == 8) {                                        // four workgroups a CU: an addition per cell (by wavefront 0.6 % slower), one for all of a wavefront's
