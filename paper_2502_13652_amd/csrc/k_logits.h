@@ -1477,13 +1477,15 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   // TOPM: the lane's sums over its positive and over its negative values
   const double Zpos = Zp, Spos = Sp, Zneg = Z, Sneg = S;
   if (TOPM) { Z += Zp; S += Sp; }
-  Z = wave_sum(Z); S = wave_sum(S);
+  // (uniform) wavefronts without a count, six of eight in typical rows, have nothing to add up: they go on to the listed logits
+  const bool counts = TOPM || __builtin_amdgcn_ballot_w64((lane_pos | lane_neg) != 0) != 0ull;
+  if (counts) { Z = wave_sum(Z); S = wave_sum(S); }
   int incl_p = 0, incl_n = 0;
   if (TOPM) {
     incl_p = wave_scan_incl(lane_pos); incl_n = wave_scan_incl(lane_neg);
     if (lane == WAVE - 1) { hs.scan_p[wid] = incl_p; hs.scan_n[wid] = incl_n; }
   }
-  const int total = wave_sum_i(lane_pos + lane_neg);
+  const int total = counts ? wave_sum_i(lane_pos + lane_neg) : 0;
   C2T_PT(PT_SUMS);
   // ---------------- their logits that reach the bound ----------------
   {
