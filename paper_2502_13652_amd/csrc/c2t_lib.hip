@@ -31,10 +31,11 @@ static_assert(C2T_MAX_BUDGET == C2T_MAX_BUDGET_DEV && C2T_MAX_CANDIDATES == C2T_
 // Cell map of one workgroup.  bf16: four workgroups of 512 threads share the CU's 160 KB, each with the
 // 16 KB histogram, its static LDS (under 8 KB) and the map (2 bytes per 4 chunks): 16 KB at most.
 constexpr int HP_NT = 512;                     // workgroup size of the histogram kernel
-#ifndef C2T_HP_REPL_ALONE
-#define C2T_HP_REPL_ALONE 4
-#endif
-constexpr int HP_REPL_ALONE = C2T_HP_REPL_ALONE;   // histogram copies of a workgroup that has its CU to itself (launches of at most one workgroup per CU)
+// Copies of the histogram of a workgroup that has its CU to itself: neighbouring lanes which hold the same value add to different words.  What they
+// save grows with the row, folding them costs the same for all.  Four / two: a layer of 256 rows of 128256 of spread logits 24.1 / 23.4 us, of
+// logits round -40 (steps of 1/4) 26.3 / 27.4, round -100 29.5 / 31.9; phases of short rows, or of segments of a shared one: four sequences of
+// 20011 230.3 / 223.8, one of 128256 118.7 / 117.3, of 32000 93.0 / 92.1.  (One: 222.6, 117.2 and 92.2, and the long rows 23.7, 28.4 and 33.1.)
+constexpr int HP_REPL_LONG = 4, HP_REPL_SHORT = 2;
 constexpr int64_t STREAMED_BYTES = 24 << 20;       // logits of a launch beyond which they are not kept in the L2s (eight of 4 MB)
 constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
@@ -255,7 +256,9 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   if (c.logits_dtype == C2T_BF16) {
     const int64_t cus = x->n_cus;
     const bool four_per_cu = (int64_t)grid > cus;
-    const int repl = four_per_cu ? 1 : HP_REPL_ALONE;       // copies of the histogram in LDS
+    const bool coop = share.n > 1;                           // (never with four per CU: see share_of)
+    const bool streamed = (int64_t)c.batch * rows_per_seq * c.vocab * 2 > STREAMED_BYTES;    // see load_stream_buffer; shared rows are few, and never streamed
+    const int repl = four_per_cu ? 1 : streamed && !coop ? HP_REPL_LONG : HP_REPL_SHORT;     // copies of the histogram in LDS
     const size_t lds_work = (std::max(std::max(hist_lds_bytes<HP_NT>(repl) + std::max(map_lds, (size_t)HP_NT * 16), generic_lds), score_lds) + 15) / 16 * 16;
     sp.lds_bytes = (int)lds_work;
     sp.w_lds_off = (int)lds_work;                           // behind it: the classifier's parameters, padded to 16 bytes
@@ -266,13 +269,11 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
     // 256 rows 32.4 / 31.6, 512: 38.8 / 39.8, 1024: 61.0 / 73.1, 1280: 82.7 / 86.6, 1536: 95.3 / 91.6,
     // 2048: 114 / 120, 3072: 166 / 163, 4096: 209 / 215, 8192: 388 / 393.  Four per CU whenever a CU
     // gets more than one workgroup; a workgroup that is alone on its CU is 2-3 % faster on 80 registers.
-    const bool coop = share.n > 1;                           // (never with four per CU: see share_of)
-    const bool streamed = (int64_t)c.batch * rows_per_seq * c.vocab * 2 > STREAMED_BYTES;    // see load_stream_buffer; shared rows are few, and never streamed
 #define C2T_HIST_KERNEL(TOPM)                                                           \
   (four_per_cu ? (const void*)k_logits_hist<HP_NT, TOPM, 8, 1, false, true>             \
-   : coop      ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, true, false> \
-   : streamed  ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, false, true> \
-               : (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_ALONE, false, false>)
+   : coop      ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_SHORT, true, false> \
+   : streamed  ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_LONG, false, true>  \
+               : (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_SHORT, false, false>)
     const void* fn = topm ? C2T_HIST_KERNEL(true) : C2T_HIST_KERNEL(false);
 #undef C2T_HIST_KERNEL
     size_t& raised = x->lds_raised[four_per_cu ? 1 : coop ? 2 : streamed ? 3 : 0];
@@ -284,12 +285,12 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
 #define C2T_LAUNCH_HIST(TOPM, WPS, REPL, COOP, STREAMED)                                                                                      \
   hipExtLaunchKernelGGL((k_logits_hist<HP_NT, TOPM, WPS, REPL, COOP, STREAMED>), dim3(grid), dim3(HP_NT), lds, s, ev0, ev1, 0, logits, stride, \
                         c.vocab, cps, (const double*)x->tab_e, (const float*)x->st.cls, x->st, sp)
-#define C2T_LAUNCH_HIST_BUILD(TOPM)                                          \
-  do {                                                                       \
-    if (four_per_cu) C2T_LAUNCH_HIST(TOPM, 8, 1, false, true);               \
-    else if (coop) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, true, false);     \
-    else if (streamed) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, false, true); \
-    else C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_ALONE, false, false);              \
+#define C2T_LAUNCH_HIST_BUILD(TOPM)                                         \
+  do {                                                                      \
+    if (four_per_cu) C2T_LAUNCH_HIST(TOPM, 8, 1, false, true);              \
+    else if (coop) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_SHORT, true, false);    \
+    else if (streamed) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_LONG, false, true); \
+    else C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_SHORT, false, false);             \
   } while (0)
     if (topm) C2T_LAUNCH_HIST_BUILD(true); else C2T_LAUNCH_HIST_BUILD(false);
 #undef C2T_LAUNCH_HIST_BUILD
