@@ -7,7 +7,7 @@ import torch
 import workloads as W
 from _harness import close, make_gpu, make_oracle, run_both, to_np, ORACLE_THREADS
 from test_gpu_configs import _compare_reranked
-from test_gpu_rows import adversarial_rows, test_rows_against_oracle as rows_against_oracle
+from test_gpu_rows import adversarial_rows, test_entropy_over_the_top_m_against_oracle as top_m_against_oracle, test_rows_against_oracle as rows_against_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -22,6 +22,39 @@ def test_fp32_rows_at_tile_edges(V, K):
 @pytest.mark.parametrize("K", [16, 17, 32, 33, 63, 64])
 def test_bf16_lists_at_the_ranking_s_edges(K):
     rows_against_oracle("bf16", 8191, K, 1)
+
+
+# The bound of the K-th largest bf16 logit: column maxima, the largest, four rows of them or two merged runs; the exact K-th largest above 32.  Rows shorter
+# than a sweep of the workgroup, a cell and a group of four sweeps, and beyond
+@pytest.mark.parametrize("V,K", [(4099, 1), (72, 2), (4097, 4), (520, 5), (32771, 15), (16385, 16), (200, 17), (65541, 17), (4099, 31), (32776, 32), (49163, 33)])
+def test_bf16_rows_where_the_bound_changes(V, K):
+    rows_against_oracle("bf16", V, K, 0)
+
+
+# The entropy's M-th largest logit among the first and the last bins of a lane, and past the row's positive values
+@pytest.mark.parametrize("V,M", [(4099, 2), (4099, 9), (32771, 512), (520, 519)])
+def test_top_m_at_a_lane_s_bins(V, M):
+    top_m_against_oracle("bf16", V, M, 0)
+
+
+# NaN is looked for in pairs of an fp32 row's logits, +inf in its maximum: each place of a chunk, the padding of the last one not among them
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_bad_fp32_logits_at_each_place_of_a_chunk(bad):
+    from paper_2502_13652_amd import C2TContext
+    V, places = 8197, [0, 1, 2, 3, 2047, 8190, 8191, 8192, 8195, 8196]
+    x = torch.full((len(places) + 1, 1, 8200), float(bad))
+    x[:, 0, :V] = torch.from_numpy(np.random.default_rng(8).standard_normal((len(places) + 1, V)).astype(np.float32))
+    for r, at in enumerate(places):
+        x[r, 0, at] = float(bad)
+    ctx = C2TContext(len(places) + 1, V, 1, 4, 1, 4, 2, 0, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    ctx.set_row_splits(1, 1)
+    ctx.reset()
+    ctx.expand_layer(x.cuda())
+    out = to_np(ctx.finalize_tree())
+    np.testing.assert_array_equal(out["status"] & 1, [1] * len(places) + [0])
+    np.testing.assert_array_equal(out["n_nodes"], [0] * len(places) + [1])
 
 
 # Long fp32 rows of a launch with more rows than CUs: one workgroup each up to 196608 logits, and split above.  The rows are dealt out ten times and more: equal rows give equal results.
@@ -147,6 +180,12 @@ def test_sequence_step_at_its_edges(F, K, h, N, dtype):
         go, oo, _ = run_both(cfg, W.classifier(cfg, seed), _layers(cfg), tag="F=%d K=%d h=%d seed %d" % (F, K, h, seed))
         total += int(go["n_nodes"].sum())
     assert total > 0
+
+
+# classifiers of a multiple of four units, evaluated by the workgroup: one and more blocks of activations, an odd number of fours in one, one candidate
+@pytest.mark.parametrize("F,K,h,N,dtype", [(4, 64, 256, 60, "bf16"), (5, 33, 52, 60, "f32"), (3, 1, 48, 8, "bf16"), (7, 20, 252, 60, "f32")])
+def test_wide_classifiers_by_fours(F, K, h, N, dtype):
+    test_sequence_step_at_its_edges(F, K, h, N, dtype)
 
 
 # the mask is written sixteen bytes a store in slices of 16384 bytes: budgets around multiples of sixteen and slice edges
