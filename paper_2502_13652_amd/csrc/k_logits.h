@@ -26,10 +26,10 @@
 //  * fp32 rows: one pass with an fp64 exponential per element (k_direct.h).
 //
 // Top-K without data-dependent work in the streaming loop: the loop records the maximum of each
-// cell as a "cell key" in an LDS map.  A cell is the four chunks a lane reads
-// in four consecutive sweeps of the workgroup (chunks i, i+NT, i+2NT, i+3NT of the segment).
-// Afterwards a bound tau <= K-th largest logit is known (exactly, from the histogram; or as the
-// K-th largest per-lane maximum), only cells whose key reaches tau can hold a top-K element, and
+// cell of four chunks as a "cell key" in an LDS map.  On the histogram path a cell is four neighbouring chunks (64 bytes); on the
+// two-pass path it is the four chunks a lane reads in four consecutive sweeps of the workgroup (chunks i, i+NT, i+2NT, i+3NT of the segment).
+// Afterwards a bound tau <= K-th largest logit is known (from the maxima of columns of lanes, or exactly, from the histogram),
+// only cells whose key reaches tau can hold a top-K element, and
 // those few cells are re-read and their elements ranked exactly by (logit desc, id asc).
 #pragma once
 #include "k_common.h"

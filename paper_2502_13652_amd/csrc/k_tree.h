@@ -4,6 +4,8 @@
 // and the small kernels: reset, emission of the tree mask, position ids and parent links, and the
 // EAGLE-2-style reranked emission (Sec. 2.2).
 #pragma once
+#include <type_traits>
+
 #include "k_common.h"
 
 namespace c2t {
@@ -107,6 +109,45 @@ __device__ __forceinline__ float mlp_logit_lds(LdsFloats w, int h, float P, floa
     a = a > 0.0f ? a : 0.0f;
     z = __fmaf_rn(w2[j], a, z);
   }
+  return z;
+}
+
+// The same by four neighbouring lanes a candidate (h a multiple of four, at most 16 candidates): each forms every fourth activation, and the
+// chain takes them from the four in turn, by lane permutation; all four run it.  Eight vector instructions for four units instead of twenty, in the
+// one wavefront that everything waits for: phases with 32 units, one sequence of 128256 115.5 -> 113.5 us, 64 sequences 264.0 -> 262.1.
+template <int LANE>
+__device__ __forceinline__ float of_quad(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), LANE * 0x55, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float mlp_logit_quads(LdsFloats w, int h, float P, float H, float d) {
+  typedef float float4v __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) const float4v* LdsFloat4s;
+  const int q = lane_id() & 3;
+  LdsFloats W1 = w + 3 * q; LdsFloats b1 = w + 3 * h + q; LdsFloats w2 = w + 4 * h;
+  float z = w[5 * h];
+  const auto fours = [&](int j, auto groups) {               // the reads of all groups ahead of the first use
+    constexpr int G = decltype(groups)::value;
+    float x[G], y[G], t[G], a[G]; float4v v[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int u = j + 4 * g;
+      x[g] = W1[3 * u]; y[g] = W1[3 * u + 1]; t[g] = W1[3 * u + 2]; a[g] = b1[u]; v[g] = *(LdsFloat4s)(w2 + u);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      a[g] = __fmaf_rn(x[g], P, a[g]); a[g] = __fmaf_rn(y[g], H, a[g]); a[g] = __fmaf_rn(t[g], d, a[g]);
+      a[g] = a[g] > 0.0f ? a[g] : 0.0f;
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      z = __fmaf_rn(v[g].x, of_quad<0>(a[g]), z); z = __fmaf_rn(v[g].y, of_quad<1>(a[g]), z);
+      z = __fmaf_rn(v[g].z, of_quad<2>(a[g]), z); z = __fmaf_rn(v[g].w, of_quad<3>(a[g]), z);
+    }
+  };
+  int j = 0;
+  for (; j + 16 <= h; j += 16) fours(j, std::integral_constant<int, 4>());
+  if (j + 8 <= h) { fours(j, std::integral_constant<int, 2>()); j += 8; }
+  if (j < h) fours(j, std::integral_constant<int, 1>());
   return z;
 }
 
@@ -340,24 +381,26 @@ __device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParam
   }
 }
 
-struct Candidate { float z, P, H; int32_t tok; uint32_t info; };   // as lane t of the first wavefront scored it; info: the row's flags
+struct Candidate { float z, P, H; int32_t tok; uint32_t info; };   // candidate t of a lone row, in lane t of the first wavefront; info: the row's flags
 
 // ---- row level: generation and joint probability (Eq. 1) and classifier logit (Eq. 3) of the row's n candidates, from
-// the complete row result in `rr`; one lane of the first wavefront per candidate (a wavefront issues the classifier's
+// the complete row result in `rr`; one lane of the first wavefront per candidate, or four where there are so many (a wavefront issues the classifier's
 // chain once for all of them).
 // `w`: the classifier parameters in global memory, read-only for the whole kernel: every lane
 // reads the same addresses, so the loads are scalar and touch neither LDS nor the vector memory path.
 template <int NT>
-__device__ __forceinline__ Candidate score_row(int tid, const TreeState& s, const ScoreParams& sp, int b, int f, RowResult& rr, int n,
+__device__ __forceinline__ Candidate score_row(int tid, const TreeState& s, const ScoreParams& sp, int b, int f, bool lone, RowResult& rr, int n,
                                           const float* __restrict__ w, const float* w_lds, unsigned char* lds) {
   const int K = sp.K, FK = sp.F * K;
   const float H = rr.H;
   const bool spread = w_lds && sp.h >= sp.spread_min;        // (uniform)
+  const bool quads = !spread && w_lds && K <= WAVE / 4 && (sp.h & 3) == 0;       // (uniform) four lanes a candidate
+  const int cand = quads ? tid >> 2 : tid;
   float z = -INFINITY, p32 = 0.f, P32 = 0.f; int tok = -1;
-  const bool mine = !rr.bad && tid < n;                      // n <= K
+  const bool mine = !rr.bad && cand < n;                     // n <= K
   if (mine) {
-    tok = rr.topi[tid];
-    p32 = (float)(exp((double)rr.topv[tid] - rr.part.ref) / rr.Zr);
+    tok = rr.topi[cand];
+    p32 = (float)(exp((double)rr.topv[cand] - rr.part.ref) / rr.Zr);
     P32 = rr.parent_P * p32;
   }
   if (spread) {
@@ -367,19 +410,29 @@ __device__ __forceinline__ Candidate score_row(int tid, const TreeState& s, cons
     if (!mine) z = -INFINITY;
   }
   const uint32_t info = (rr.bad ? 1u : 0u) | (rr.part.flags & 2u);
-  if (tid >= K) return Candidate{-INFINITY, 0.f, 0.f, -1, 0u};
+  if (tid >= (quads ? WAVE : K)) return Candidate{-INFINITY, 0.f, 0.f, -1, 0u};
   if (mine && !spread) {
-    z = w_lds ? mlp_logit_lds((LdsFloats)w_lds, sp.h, P32, H, (float)sp.layer) : mlp_logit(w, sp.h, P32, H, (float)sp.layer);
+    z = quads ? mlp_logit_quads((LdsFloats)w_lds, sp.h, P32, H, (float)sp.layer)
+        : w_lds ? mlp_logit_lds((LdsFloats)w_lds, sp.h, P32, H, (float)sp.layer) : mlp_logit(w, sp.h, P32, H, (float)sp.layer);
   }
   const int64_t row = (int64_t)b * FK + (int64_t)f * K;     // uniform; the lane's offset stays 32 bits wide
-  st_dev(s.c_tok + row + tid, tok); st_dev(s.c_p + row + tid, p32); st_dev(s.c_P + row + tid, P32);
-  st_dev(s.c_H + row + tid, H); st_dev(s.c_z + row + tid, z);
-  if (tid == 0) st_dev(s.row_info + (int64_t)b * sp.F + f, info);
-  if (s.h_tok) {                                             // keep the candidate for the reranking
-    const int64_t h = ((int64_t)b * sp.D + sp.layer) * FK + (int64_t)f * K;
-    s.h_tok[h + tid] = tok; s.h_par[h + tid] = rr.parent_hidx;
-    s.h_P[h + tid] = P32; s.h_H[h + tid] = H; s.h_z[h + tid] = z;
-    s.h_s[h + tid] = fminf(rr.parent_s, z);
+  if (!quads || ((tid & 3) == 0 && cand < K)) {
+    st_dev(s.c_tok + row + cand, tok); st_dev(s.c_p + row + cand, p32); st_dev(s.c_P + row + cand, P32);
+    st_dev(s.c_H + row + cand, H); st_dev(s.c_z + row + cand, z);
+    if (tid == 0) st_dev(s.row_info + (int64_t)b * sp.F + f, info);
+    if (s.h_tok) {                                           // keep the candidate for the reranking
+      const int64_t h = ((int64_t)b * sp.D + sp.layer) * FK + (int64_t)f * K;
+      s.h_tok[h + cand] = tok; s.h_par[h + cand] = rr.parent_hidx;
+      s.h_P[h + cand] = P32; s.h_H[h + cand] = H; s.h_z[h + cand] = z;
+      s.h_s[h + cand] = fminf(rr.parent_s, z);
+    }
+  }
+  if (quads && lone) {                                       // (uniform) for the caller a lane a candidate again
+    const int from = tid * 16;
+    z = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)__float_as_uint(z)));
+    P32 = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)__float_as_uint(P32)));
+    tok = __builtin_amdgcn_ds_bpermute(from, tok);
+    if (tid >= K) return Candidate{-INFINITY, 0.f, 0.f, -1, 0u};
   }
   return Candidate{z, P32, H, tok, info};
 }
@@ -914,7 +967,7 @@ __device__ __forceinline__ void finish_layer(int tid, const TreeState& s, const 
     n = rr.part.n_top;
     C2T_PT(PT_MERGED);
   }
-  const Candidate c = score_row<NT>(tid, s, sp, b, f, rr, n, cls, cls_lds, lds);
+  const Candidate c = score_row<NT>(tid, s, sp, b, f, nf == 1, rr, n, cls, cls_lds, lds);
   C2T_PT(PT_PUBLISHED);
   if (nf == 1) {                                             // (uniform) the only row: nothing is handed over
     C2T_PT(PT_TICKET);

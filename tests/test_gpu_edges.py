@@ -182,6 +182,12 @@ def test_sequence_step_at_its_edges(F, K, h, N, dtype):
     assert total > 0
 
 
+# classifiers of a multiple of four units by four lanes a candidate, up to 16 candidates: groups of 16, 8 and 4 units, lone rows (F = 1) too
+@pytest.mark.parametrize("F,K,h,N,dtype", [(10, 16, 28, 60, "bf16"), (7, 15, 4, 60, "f32"), (1, 16, 20, 4, "bf16"), (1, 1, 12, 3, "f32"), (16, 3, 44, 60, "bf16")])
+def test_classifiers_by_four_lanes(F, K, h, N, dtype):
+    test_sequence_step_at_its_edges(F, K, h, N, dtype)
+
+
 # classifiers of a multiple of four units, evaluated by the workgroup: one and more blocks of activations, an odd number of fours in one, one candidate
 @pytest.mark.parametrize("F,K,h,N,dtype", [(4, 64, 256, 60, "bf16"), (5, 33, 52, 60, "f32"), (3, 1, 48, 8, "bf16"), (7, 20, 252, 60, "f32")])
 def test_wide_classifiers_by_fours(F, K, h, N, dtype):
