@@ -518,8 +518,9 @@ __device__ __forceinline__ void rank_lists_from_memory(int tid, const ScoreParam
 //
 // What bounds it: latency; a handful of dependent steps on at most 2048 candidates.  Everything the step reads is requested
 // at once.  Only the n_keep best survivors of the first pruning matter: of 64 (or 128) groups of candidates, one
-// per lane, the n_keep-th largest group maximum is a lower bound of the n_keep-th largest z, found by a wavefront from
-// ballots; what reaches it (two dozen candidates where 16 are kept) is listed in LDS and ranked exactly.  The
+// per lane, the n_keep-th largest group maximum is a lower bound of the n_keep-th largest z, found by every wavefront from sorted rows of
+// 16 (n_keep <= 16; from ballots, rounds of scalar instructions, 32 sequences of 10 x 10 candidates with every one a survivor took 113.7 us a phase, 111.0
+// so, 16 of 16 x 16 173.2 and 172.4) or from ballots; what reaches it (two dozen candidates where 16 are kept) is listed in LDS and ranked exactly.  The
 // ranking gives each listed candidate to T = 2^tshift lanes, which split the list between them, two keys per LDS read.
 // Lists that stay long, layers of equal z above all, are first cut by a radix select on the whole keys; so are, without a
 // bound, more than 64 survivors of more than 512 candidates (several a thread), whose bound is slower to find and lets more
@@ -661,7 +662,8 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
     uint32_t m[2] = {0u, 0u};
 #pragma unroll
     for (int v = 0; v < NW; ++v) m[v & 1] = max(m[v & 1], lane_max[v * WAVE + lane]);
-    if (n_keep <= 32) { const uint32_t m1[1] = {max(m[0], m[1])}; bound = bound_from_maxima<1>(m1, n_keep, n_keep + 24); }
+    if (n_keep <= 16) bound = nth_largest16(max(m[0], m[1]), n_keep);
+    else if (n_keep <= 32) { const uint32_t m1[1] = {max(m[0], m[1])}; bound = bound_from_maxima<1>(m1, n_keep, n_keep + 24); }
     else bound = bound_from_maxima<2>(m, n_keep, n_keep + 24);
     bound = max(bound, 1u);
   }

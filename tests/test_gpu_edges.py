@@ -182,6 +182,12 @@ def test_sequence_step_at_its_edges(F, K, h, N, dtype):
     assert total > 0
 
 
+# more than 64 survivors in one candidate a thread, of which 1 to 16 are kept: the bound from sorted maxima, and the ballots beyond
+@pytest.mark.parametrize("F,K,N", [(2, 50, 12), (3, 64, 7), (15, 30, 50), (16, 31, 60), (17, 30, 60)])
+def test_sequence_step_where_the_bound_changes(F, K, N):
+    test_sequence_step_at_its_edges(F, K, 8, N, "bf16")
+
+
 # classifiers of a multiple of four units by four lanes a candidate, up to 16 candidates: groups of 16, 8 and 4 units, lone rows (F = 1) too
 @pytest.mark.parametrize("F,K,h,N,dtype", [(10, 16, 28, 60, "bf16"), (7, 15, 4, 60, "f32"), (1, 16, 20, 4, "bf16"), (1, 1, 12, 3, "f32"), (16, 3, 44, 60, "bf16")])
 def test_classifiers_by_four_lanes(F, K, h, N, dtype):
