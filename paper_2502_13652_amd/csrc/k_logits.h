@@ -1328,7 +1328,9 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     __syncthreads();                                     // the row's map
   }
   float tau;
-  if (__builtin_expect(K > COLUMNS_MAX_K, 0)) {
+  // (A lane's column holds the chunks of one sweep in four: with fewer than three sweeps less than 48 columns hold any, and the 32nd largest would be
+  // hardly a bound: three sequences of 8279 with K = 31 48.8 us a phase by the counts, 59 by the columns.)
+  if (__builtin_expect(K > COLUMNS_MAX_K || (K > 16 && sg.ncell < 3 * NT), 0)) {
     const KthOfCounts kth = kth_of_counts<NT>(tid, (LdsWords)hist, K);
     tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;
   } else {

@@ -26,7 +26,8 @@ def test_bf16_lists_at_the_ranking_s_edges(K):
 
 # The bound of the K-th largest bf16 logit: column maxima, the largest, four rows of them or two merged runs; the exact K-th largest above 32.  Rows shorter
 # than a sweep of the workgroup, a cell and a group of four sweeps, and beyond
-@pytest.mark.parametrize("V,K", [(4099, 1), (72, 2), (4097, 4), (520, 5), (32771, 15), (16385, 16), (200, 17), (65541, 17), (4099, 31), (32776, 32), (49163, 33)])
+@pytest.mark.parametrize("V,K", [(4099, 1), (72, 2), (4097, 4), (520, 5), (32771, 15), (16385, 16), (200, 17), (65541, 17), (4099, 31), (32776, 32), (49163, 33), (8279, 31),
+                                 (12280, 32), (12288, 32), (12289, 17)])
 def test_bf16_rows_where_the_bound_changes(V, K):
     rows_against_oracle("bf16", V, K, 0)
 
