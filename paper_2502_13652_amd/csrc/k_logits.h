@@ -112,6 +112,17 @@ __device__ __forceinline__ int chunk_of_cell(int cell, int j) {
   return grp * 4 * NT + j * NT + t;
 }
 
+// Cells of the histogram path: four neighbouring chunks, 64 bytes of one or two lines, so that one which holds a large logit is read again at
+// the price of its lines (a cell of four chunks of one lane, four sweeps apart, costs four: with K = 32
+// 4096 rows of 152064 took 255 us a layer, with K = 1 193).  Cell g * NT + t of a segment: chunks (4 g + t mod 4) * NT + t - t mod 4 and the next three; a group g of four sweeps has NT cells.
+template <int NT>
+__host__ __device__ inline int quad_cells_in_segment(int n) { return (n + 4 * NT - 1) / (4 * NT) * NT; }
+template <int NT>
+__device__ __forceinline__ int chunk_of_quad_cell(int cell, int j) {
+  const int grp = cell / NT, t = cell - grp * NT;
+  return (grp * 4 + (t & 3)) * NT + (t & ~3) + j;
+}
+
 // ---------------------------------------------------------------------------------------
 // Selection, shared by both paths.
 // ---------------------------------------------------------------------------------------
@@ -137,9 +148,10 @@ __device__ __forceinline__ int list_cells(int tid, const typename LogitTraits<DT
 }
 
 // Re-read the listed cells (CPC chunks each, one chunk per thread) and append their elements that
-// reach tau (exceed it, if strict) to the element list, which overlays the cell map: the caller has
+// reach tau (exceed it, if strict) to the element list, which may overlay the cell map: the caller has
 // put a barrier after the last read of the map and after setting *sh_cnt = 0.  Ends with a barrier.
-template <int DT, int NT>
+// QUAD: the cells of the histogram path.
+template <int DT, int NT, bool QUAD>
 __device__ __forceinline__ void collect_cells(int tid, const uint4* __restrict__ rowp, int c0, int c1, int V, float tau, bool strict,
                                               const int32_t* cell_list, int n_cells, const SelectLds& sel, int32_t* sh_cnt) {
   typedef LogitTraits<DT> T;
@@ -148,7 +160,7 @@ __device__ __forceinline__ void collect_cells(int tid, const uint4* __restrict__
   int my_chunk = -1;
   uint4 q = make_uint4(0, 0, 0, 0);
   if (tid < n_cells * CPC) {                                 // n_cells <= cell_cap <= NT / CPC
-    const int ch = c0 + chunk_of_cell<NT>(cell_list[tid / CPC], tid % CPC);
+    const int ch = c0 + (QUAD ? chunk_of_quad_cell<NT>(cell_list[tid / CPC], tid % CPC) : chunk_of_cell<NT>(cell_list[tid / CPC], tid % CPC));
     if (ch < c1) { my_chunk = ch; q = rowp[ch]; }
   }
   if ((tid & ~(WAVE - 1)) < n_cells * CPC) {                 // wavefronts with a cell
@@ -457,7 +469,7 @@ __device__ __noinline__ void generic_segment(int tid, const uint4* __restrict__ 
   if (tid == 0) sh_cnt = 0;
   __syncthreads();
   C2T_PT(PT_CELLS_LISTED);
-  collect_cells<DT, NT>(tid, rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
+  collect_cells<DT, NT, false>(tid, rowp, sg.c0, sg.c1, V, tau, ties, cell_list, n_cells, sel, &sh_cnt);
   if (ties) tie_scan<DT, NT>(tid, rowp, sg, V, tau, K, sel, &sh_cnt, scan_tmp);
   C2T_PT(PT_CELLS_READ);
   const int n_el = min(sh_cnt, sel.list_cap), n_top = min(n_el, K);
@@ -848,16 +860,6 @@ __device__ __forceinline__ float bound_of_patterns(uint32_t column, int K) {
   return __uint_as_float(((key & 0x8000u) ? key & 0x7fffu : key ^ 0xffffu) << 16);
 }
 
-// Cells of the histogram path: four neighbouring chunks, 64 bytes of one or two lines, so that one which holds a large logit is read again at
-// the price of its lines (a cell of four chunks of one lane, four sweeps apart, costs four: with K = 32
-// 4096 rows of 152064 took 255 us a layer, with K = 1 193).  Cell g * NT + t of a segment: chunks (4 g + t mod 4) * NT + t - t mod 4 and the next three; a group g of four sweeps has NT cells.
-template <int NT>
-__host__ __device__ inline int quad_cells_in_segment(int n) { return (n + 4 * NT - 1) / (4 * NT) * NT; }
-template <int NT>
-__device__ __forceinline__ int chunk_of_quad_cell(int cell, int j) {
-  const int grp = cell / NT, t = cell - grp * NT;
-  return (grp * 4 + (t & 3)) * NT + (t & ~3) + j;
-}
 // The keys of a group's cells: of the maxima p[k] of the chunks that the lane has read in sweep k of the group, lane t of a quad gets the
 // largest of the quad's p[t].  Two exchanges between neighbours, each lane giving away half of what it holds.
 __device__ __forceinline__ uint32_t quad_exchange_1(uint32_t even, uint32_t odd, bool is_odd) {
@@ -982,6 +984,7 @@ struct HistShared {
   OutsideAcc out;
   float m;                          // largest logit of the row
   int32_t n_cells, n_el, tot_p;
+  int32_t kth[3];                   // KthOfCounts: rank, n_gt, n_ge
   int32_t cells[SEL_CELL_CAP];      // cells that hold a logit above the bound
 };
 constexpr int HIST_LIST = 256;                  // logits the element list holds
@@ -994,20 +997,22 @@ __device__ __forceinline__ SelectLds hist_list(unsigned char* at) {
 }
 
 // The exact K-th largest logit of a histogram, by the whole workgroup: the value-ordered rank of its bin (see hp_code_of_rank; -1: fewer
-// than K logits lie in the window) and how many logits exceed it.  Out of line: it is looked for where K > COLUMNS_MAX_K, and in rows that
+// than K logits lie in the window), how many logits exceed it and how many reach it.  Out of line: it is looked for where K > COLUMNS_MAX_K, and in rows that
 // settle_hist is asked about.
-struct KthOfCounts { int rank, n_gt; };
+struct KthOfCounts { int rank, n_gt, n_ge; };
+template <int NT> using HistSharedLds = __attribute__((address_space(3))) HistShared<NT>*;
 template <int NT>
-__device__ __noinline__ KthOfCounts kth_of_counts(int tid, LdsWords hist, int top_k) {
+__device__ __noinline__ KthOfCounts kth_of_counts(int tid, LdsWords hist, int top_k, HistSharedLds<NT> hs) {
   const int K = __builtin_amdgcn_readfirstlane(top_k);
   constexpr int NW = NT / WAVE, WPL = HP_WORDS / NT;
-  __shared__ int32_t scan[2][NW], found[2];
+  __shared__ int32_t scan[2][NW];
+  __attribute__((address_space(3))) int32_t* const found = hs->kth;
   const int lane = tid & (WAVE - 1), wid = tid >> 6, w0 = WPL * tid;
   int lane_pos = 0, lane_neg = 0;
   for (int j = 0; j < WPL; ++j) { lane_pos += (int)(hist[w0 + j] & 0xffffu); lane_neg += (int)(hist[w0 + j] >> 16); }
   const int incl_p = wave_scan_incl(lane_pos), incl_n = wave_scan_incl(lane_neg);
   if (lane == WAVE - 1) { scan[0][wid] = incl_p; scan[1][wid] = incl_n; }
-  if (tid == 0) { found[0] = -1; found[1] = 0; }
+  if (tid == 0) { found[0] = -1; found[1] = found[2] = 0; }
   __syncthreads();
   int before_p = 0, before_n = 0, tot_p = 0;
   for (int w = 0; w < NW; ++w) { if (w < wid) { before_p += scan[0][w]; before_n += scan[1][w]; } tot_p += scan[0][w]; }
@@ -1017,7 +1022,7 @@ __device__ __noinline__ KthOfCounts kth_of_counts(int tid, LdsWords hist, int to
     int run = above_p;
     for (int j = WPL - 1; j >= 0; --j) {
       const int n = (int)(hist[w0 + j] & 0xffffu);
-      if (run < K && run + n >= K) { found[0] = HP_WORDS + w0 + j; found[1] = run; }
+      if (run < K && run + n >= K) { found[0] = HP_WORDS + w0 + j; found[1] = run; found[2] = run + n; }
       run += n;
     }
   }
@@ -1025,64 +1030,62 @@ __device__ __noinline__ KthOfCounts kth_of_counts(int tid, LdsWords hist, int to
     int run = above_n;
     for (int j = 0; j < WPL; ++j) {
       const int n = (int)(hist[w0 + j] >> 16);
-      if (run < K && run + n >= K) { found[0] = HP_WORDS - 1 - (w0 + j); found[1] = run; }
+      if (run < K && run + n >= K) { found[0] = HP_WORDS - 1 - (w0 + j); found[1] = run; found[2] = run + n; }
       run += n;
     }
   }
   __syncthreads();
-  return KthOfCounts{found[0], found[1]};
+  return KthOfCounts{found[0], found[1], found[2]};
 }
 
 // The rows whose list of the largest logits did not come out, or that need a closer look: with the exact K-th largest logit tau
 // from the counts,
 //  * rows with logits below the window take the two-pass path unless tau is a positive value of it, those with fewer than K logits in the
 //    window and masked ones besides do so too (they could be among the top K, which the histogram cannot rank): UNSETTLED;
-//  * a list that is incomplete (too many cells or logits above the bound) or short of K is made again: the segment is read a second time for what
-//    exceeds tau (fewer than K logits), and the ties at tau of the lowest ids are added (tie_scan).
-// list_length: more than HIST_LIST if the list is incomplete.  Returns its length.  Out of line: see settle_list.
+//  * a list that is incomplete (too many cells or logits reach the bound) or short of K is made again from the cells that reach tau: those listed, if
+//    all were, else from the map, which is still in place then.  Where too many logits equal tau, only what exceeds it is listed (fewer than K
+//    logits), and the ties of the lowest ids are added (tie_scan).
+// Reading the whole segment a second time for what exceeds tau took longer than the first time: layers of 256 rows of 128256 with K = 32, 400 to 4000
+// neighbouring logits of each far above the others, 69 us (26 to 37 from the cells); of nine values 69 (53).
+// Returns the list's length.  Out of line: see settle_list.
 template <int NT>
-__device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsWords hist, uint32_t list_address, int list_length,
-                                        int n_tiny, int n_masked) {
+__device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsWords hist, uint32_t list_address,
+                                        LdsHalves cell_map, int cells_max, HistSharedLds<NT> shl) {
   typedef LogitTraits<1> T;
-  __shared__ int32_t scan_tmp[1][NT / WAVE], sh_n;
+  __shared__ int32_t scan_tmp[1][NT / WAVE];
   const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
-  const int K = uniform(top_k), n_el = uniform(list_length);
+  HistShared<NT>& hs = *(HistShared<NT>*)shl;
+  const int K = uniform(top_k), cell_cap = uniform(cells_max);
   const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
   const SelectLds list = hist_list((unsigned char*)(__attribute__((address_space(3))) unsigned char*)(uintptr_t)(uint32_t)uniform((int)list_address));
   const int n_elems = sg.tail_chunk >= 0 ? (sg.ncell - 1) * T::EPC + sg.tail_valid : sg.ncell * T::EPC, want = min(K, n_elems);
-  const KthOfCounts kth = kth_of_counts<NT>(tid, hist, K);
-  if ((uniform(n_tiny) > 0 && kth.rank < HP_WORDS) || (uniform(n_masked) > 0 && kth.rank < 0)) return UNSETTLED;
-  if (n_el >= want && n_el <= HIST_LIST) return n_el;
+  int n_cells = uniform(hs.n_cells);
+  const int n_el = uniform(hs.n_el);
+  KthOfCounts kth{hs.kth[0], hs.kth[1], hs.kth[2]};
+  if (K <= COLUMNS_MAX_K) kth = kth_of_counts<NT>(tid, hist, K, shl);
+  __syncthreads();                                             // everybody has read the lengths
+  if ((uniform(hs.out.n_tiny) > 0 && kth.rank < HP_WORDS) || (uniform(hs.out.n_masked) > 0 && kth.rank < 0)) return UNSETTLED;
+  if (n_cells <= cell_cap && n_el >= want && n_el <= HIST_LIST) return n_el;
   const float tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;    // (fewer than K logits: all of them)
-  float* el_v = list.values();
-  int32_t* el_i = list.ids();
-  if (tid == 0) sh_n = 0;
-  __syncthreads();
-  const __amdgpu_buffer_rsrc_t rs = uniform_buffer((uint64_t)(rowp + sg.c0), sg.ncell * 16);
-  constexpr int BATCH = 4;                                   // chunks a thread holds at once
-  for (int g0 = 0; g0 < sg.ncell; g0 += BATCH * NT) {
-    uint4 q[BATCH];
-#pragma unroll
-    for (int k = 0; k < BATCH; ++k) q[k] = load_stream_buffer(rs, (uint32_t)tid * 16u, (uint32_t)(g0 + k * NT) * 16u);
-#pragma unroll
-    for (int k = 0; k < BATCH; ++k) {
-      const int g = g0 + k * NT + tid;
-      float x[T::EPC];
-      T::unpack(q[k], x);
-#pragma unroll
-      for (int j = 0; j < T::EPC; ++j) {
-        const int id = (sg.c0 + g) * T::EPC + j;
-        if (x[j] > tau && g < sg.ncell && id < V) {
-          const int slot = atomicAdd(&sh_n, 1);
-          if (slot < HIST_LIST) { el_v[slot] = x[j]; el_i[slot] = id; }
-        }
-      }
+  bool strict = kth.n_ge > HIST_LIST;                          // only what exceeds tau
+  if (strict && kth.n_gt == 0) {
+    n_cells = 0;
+  } else if (n_cells > cell_cap) {
+    const uint16_t* const map = (const uint16_t*)cell_map;
+    const int ncells = quad_cells_in_segment<NT>(sg.ncell);
+    if (!strict) n_cells = list_cells<1, NT>(tid, map, ncells, tau, false, cell_cap, hs.cells, &hs.n_cells);
+    if (strict || n_cells > cell_cap) {
+      strict = true;
+      __syncthreads();                                         // everybody has read the length
+      n_cells = list_cells<1, NT>(tid, map, ncells, tau, true, cell_cap, hs.cells, &hs.n_cells);
     }
   }
+  if (tid == 0) hs.n_el = 0;
   __syncthreads();
-  const int n = sh_n;                                        // kth.n_gt, or all of fewer than K logits
-  if (want > n) tie_scan<1, NT>(tid, rowp, sg, V, tau, want - n, list, &sh_n, scan_tmp);
-  return want > n ? want : n;
+  if (n_cells > 0) collect_cells<1, NT, true>(tid, rowp, sg.c0, sg.c1, V, tau, strict, hs.cells, n_cells, list, &hs.n_el);
+  const int n = hs.n_el, need = want - n;                      // (need > 0 only where it is strict)
+  if (need > 0) tie_scan<1, NT>(tid, rowp, sg, V, tau, need, list, &hs.n_el, scan_tmp);
+  return need > 0 ? want : n;
 }
 
 // A row shared by sp.coop workgroups (launches that leave most of the chip idle: a single sequence,
@@ -1331,7 +1334,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   // (A lane's column holds the chunks of one sweep in four: with fewer than three sweeps less than 48 columns hold any, and the 32nd largest would be
   // hardly a bound: three sequences of 8279 with K = 31 48.8 us a phase by the counts, 59 by the columns.)
   if (__builtin_expect(K > COLUMNS_MAX_K || (K > 16 && sg.ncell < 3 * NT), 0)) {
-    const KthOfCounts kth = kth_of_counts<NT>(tid, (LdsWords)hist, K);
+    const KthOfCounts kth = kth_of_counts<NT>(tid, (LdsWords)hist, K, (HistSharedLds<NT>)&hs);
     tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;
   } else {
     tau = bound_of_patterns(column, K);
@@ -1494,17 +1497,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     // ... or if some but not all of the logits below the window are among the M largest (which ones cannot be told from the histogram)
     leave = leave || (n_tiny > 0 && tot_p < M && M < tot_p + n_tiny);
   }
-  if (__builtin_expect(!leave && (n_tiny > 0 || n_el > HIST_LIST || n_el < min(K, n_elems)), 0)) {
-    n_el = settle_hist<NT>(tid, rowp, V, K, sg, (LdsWords)hist, lds_address(list.list), n_el, n_tiny, n_ninf);
-    leave = n_el == UNSETTLED;
-    __syncthreads();                                     // the list is complete
-  }
-  if (__builtin_expect(leave, 0)) {
-    __syncthreads();
-    generic_segment<1, NT>(tid, rowp, V, K, M, sg, (unsigned char*)hist, sel, rr, 2u);
-    return SegmentTop{RANKED_IN_RR};
-  }
-  if (TOPM) {
+  if (TOPM && !leave) {                                  // (uniform; ahead of the calls below: little is live across them)
     // Eq. 2, second line: Z and S restricted to the M largest logits.  A lane's values, from the
     // top: its positive magnitudes descending, then its negative ones ascending; `above` of them
     // lie in other lanes.
@@ -1538,6 +1531,16 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     if (lane == 0) { hs.red_m_d[0][wid] = zm; hs.red_m_d[1][wid] = sm; }
     if (tid == 0) hs.tot_p = tot_p;
     __syncthreads();
+  }
+  if (__builtin_expect(!leave && (n_tiny > 0 || n_el > HIST_LIST || n_el < min(K, n_elems)), 0)) {
+    n_el = settle_hist<NT>(tid, rowp, V, K, sg, (LdsWords)hist, lds_address(list.list), (LdsHalves)map, sel.cell_cap, (HistSharedLds<NT>)&hs);
+    leave = n_el == UNSETTLED;
+    __syncthreads();                                     // the list is complete
+  }
+  if (__builtin_expect(leave, 0)) {
+    __syncthreads();
+    generic_segment<1, NT>(tid, rowp, V, K, M, sg, (unsigned char*)hist, sel, rr, 2u);
+    return SegmentTop{RANKED_IN_RR};
   }
   return SegmentTop{n_el};
 }

@@ -32,6 +32,83 @@ def test_bf16_rows_where_the_bound_changes(V, K):
     rows_against_oracle("bf16", V, K, 0)
 
 
+# Rows whose large logits lie next to each other: likely ids that are neighbours, a stretch of ids that is allowed, ids in order of frequency; few values
+def neighbouring_rows(V, rng):
+    rows = {}
+    for w in (100, 400, 1000, 4000):
+        at = int(rng.integers(0, V - w))
+        rows["likely_%d" % w] = r = 3 * rng.standard_normal(V); r[at:at + w] += 25
+        rows["allowed_%d" % w] = r = np.full(V, -np.inf); r[at:at + w] = 3 * rng.standard_normal(w)
+    rows["by_frequency"] = 2 * rng.standard_normal(V) - 1.05 * np.log(np.arange(1, V + 1))
+    rows["nine_values"] = 0.5 * rng.integers(0, 9, V) - 3.25
+    return list(rows), np.stack(list(rows.values())).astype(np.float32)
+
+
+# bf16 rows dealt out to B sequences (one row each) against the oracle: every one of the equal rows
+def dealt_rows_against_oracle(names, rows, K, B, M=0):
+    from oracle import ref_entropy_top_m, ref_row
+    from paper_2502_13652_amd import C2TContext
+    n, V = rows.shape
+    x = torch.full((n, 1, (V + 7) // 8 * 8 + 8), float("inf"), dtype=torch.bfloat16)
+    x[:, 0, :V] = torch.from_numpy(rows).to(torch.bfloat16)
+    ctx = C2TContext(B, V, 1, K, 1, 1, 2, 1, 0.0, entropy_top_m=M)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    print("%d rows, %d of them different, V=%d K=%d M=%d" % (B, n, V, K, M), flush=True)
+    ctx.reset()
+    ctx.expand_layer(x.cuda()[torch.arange(B, device="cuda") % n].contiguous())
+    c = to_np(ctx.candidates())
+    bits = x[:, 0, :V].contiguous().view(torch.int16).numpy().view(np.uint16)
+    for b, name in enumerate(names[:B]):
+        r = ref_row(bits[b], K)
+        k, H = len(r["ids"]), ref_entropy_top_m(bits[b], M) if M else r["H"]
+        for e in range(b, B, n):
+            np.testing.assert_array_equal(c["token"][e, :k], r["ids"], err_msg=name)
+            assert close(c["p"][e, :k], r["p"].astype(np.float32), atol=1e-37).all(), name
+            assert close(c["H"][e, 0], np.float32(H), atol=V * 2.0 ** -53).all(), name            # (as in test_gpu_rows.py)
+
+
+# ... in the kernel's builds for shared rows, rows alone on a CU, and four workgroups a CU
+@pytest.mark.parametrize("V,K,B", [(128256, 32, 10), (128256, 16, 10), (128256, 33, 60), (8279, 31, 10), (32000, 10, 200), (32000, 32, 200), (32000, 64, 200),
+                                   (20011, 1, 300), (32000, 16, 300), (65541, 20, 300), (32000, 32, 300), (32000, 64, 300)])
+def test_rows_with_neighbouring_large_logits(V, K, B):
+    names, rows = neighbouring_rows(V, np.random.default_rng(V + K))
+    dealt_rows_against_oracle(names, rows, K, B)
+
+
+# Where a row's large logits lie must not decide over its time (kernel times, medians of turns): rows against the same values in random places, and
+# tied rows against such with K larger logits in random places.  A second read of such rows took them 1.3 to 3 times as long
+@pytest.mark.parametrize("B,K", [(256, 32), (512, 32), (300, 16), (40, 16), (1, 32)])
+def test_the_place_of_large_logits_does_not_cost_a_second_read(B, K):
+    from paper_2502_13652_amd import C2TContext
+    V, n, turns = 128256, min(B, 16), 30
+    g = torch.Generator(device="cuda").manual_seed(5)
+    noise, places = 3 * torch.randn((n, V), generator=g, device="cuda"), torch.randperm(V, generator=g, device="cuda")
+    block = noise.clone(); block[:, 70000:71000] += 25
+    few = noise.clone(); few[:, 5000:5400] += 25
+    ties = 0.5 * torch.randint(0, 9, (n, V), generator=g, device="cuda") - 3.25
+    headed = ties.clone(); headed[:, places[:K]] = 5 + 0.125 * torch.arange(K, device="cuda")
+    ctx = C2TContext(B, V, 1, K, 1, 1, 2, 1, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+
+    def times(*inputs):
+        xs = [x.to(torch.bfloat16)[torch.arange(B, device="cuda") % n].view(B, 1, V) for x in inputs]
+        for _ in range(2):                                   # (the first turns warm up)
+            ctx.profile_enable(turns * len(xs))
+            for i in range(turns * len(xs)):
+                ctx.reset(); ctx.expand_layer(xs[i % len(xs)]); ctx.finalize_tree()
+            torch.cuda.synchronize()
+        t = np.array(ctx.profile_read(turns * len(xs))).reshape(turns, len(xs))
+        return np.median(t, axis=0)
+
+    for x, limit in ((block, 1.6), (few, 1.6)):
+        together, apart = times(x, x[:, places])
+        assert together < limit * apart, (together, apart)
+    tied, free = times(ties, headed)
+    assert tied < 1.15 * free, (tied, free)
+
+
 # The entropy's M-th largest logit among the first and the last bins of a lane, and past the row's positive values
 @pytest.mark.parametrize("V,M", [(4099, 2), (4099, 9), (32771, 512), (520, 519)])
 def test_top_m_at_a_lane_s_bins(V, M):
