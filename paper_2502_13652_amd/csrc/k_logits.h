@@ -623,6 +623,11 @@ __device__ __forceinline__ uint32_t pk_max_f16_raw(uint32_t a, uint32_t b) {
   asm("v_pk_max_f16 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
   return d;
 }
+__device__ __forceinline__ uint32_t pk_max3_f16_raw(uint32_t a, uint32_t b, uint32_t c) {     // (a NaN pattern, of a logit far outside the window, wins)
+  uint32_t d;
+  asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
 // per 16-bit half: a * b + c (mod 2^16)
 __device__ __forceinline__ uint32_t pk_mad_u16(uint32_t a, uint32_t b_sgpr, uint32_t c) {
   uint32_t d;
@@ -826,36 +831,28 @@ __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t h
   return pat;
 }
 
-// ---- a lower bound of the K-th largest logit (K <= COLUMNS_MAX_K), from the maxima of 64 columns of lanes: sorted in rows of 16 lanes
-// (bitonic, a lane permutation and a v_med3 a stage).  K <= 16: the smallest of the four rows' ceil(K / 4)-th largest maxima is reached by
-// K of them; of randomly placed logits 27 reach it for K = 16 (18 the exact K-th largest of the 64).  A tenth of a microsecond,
-// where a search by ballots takes half of one: its rounds are chains of scalar instructions.  17 to 32: that bound would let 59 logits pass for K = 32,
-// now and then more than the 128 cells that can be listed; the rows are merged on, and the bound is the 32nd largest of the 64 maxima,
-// which 44 logits reach (63 at most in 300 rows).  The exact K-th largest logit of the counts (kth_of_counts) takes a microsecond more a row:
-// four sequences of 20011 with 64 x 32 candidates took 237.3 us a phase with it, 230.4 so, 256 of 152064 with 32 x 32 1820 and 1803.
+// ---- a lower bound of the K-th largest logit (K <= COLUMNS_MAX_K): the K-th largest of the maxima of 64 columns of lanes (K <= 16), or the 32nd; sorted in
+// rows of 16 lanes (bitonic, a lane permutation and a v_med3 a stage).  A tenth of a microsecond, where a search by ballots takes half of one: its
+// rounds are chains of scalar instructions.  Lane l's column holds the chunks l, l + 64, .. of 8 logits, so that neighbouring ids
+// lie in different columns: of randomly placed logits 18 reach the bound for K = 16 and 44 for K = 32, where the ids are ordered by frequency 20 and 48
+// (95 at most in 300 rows), and of a stretch of 512 ids that are likely ones all 64 columns hold some.  (Columns of whole cells put 512 ids into 16 of
+// them: the bound fell to what lies around them, and layers of 256 rows of 128256 whose likely ids are neighbours, 400 to 4000, took 26 to 37 us with K = 32,
+// 23 so; by frequency 31.6 and 24.1, with K = 16 23.8 and 21.8.  The smallest of the four rows' ceil(K / 4)-th, two lane permutations shorter: 400 neighbours,
+// which are 50 lanes, 27.0 with K = 16, 22.0 so.)  Fewer neighbours than that, 100 to 256, may all reach the bound: 100 of them 24.8 (4 sequences of 20011 with
+// K = 32 16.2, 12.7 without them).
+// The exact K-th largest logit of the counts (kth_of_counts) takes a microsecond more a row:
+// four sequences of 20011 with 64 x 32 candidates took 237.3 us a phase with it, 230.4 so, 256 of 152064 with 32 x 32 1820 and 1803, a layer of three rows
+// of 8279 with K = 31 12.5 and 11.7.
 constexpr int COLUMNS_MAX_K = 32;
 constexpr uint32_t HP_NONE2 = HP_F16_NEG_INF2;                          // pattern of a lane without a chunk
 constexpr uint32_t HP_LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1);  // the window's lowest value, which also stands in for masked logits
 // 16-bit keys that order like the values of the patterns
 __device__ __forceinline__ uint32_t key_of_pattern(uint32_t c) { return (c & 0x8000u) ? c ^ 0xffffu : c | 0x8000u; }
-// column: packed pattern, the lane's column maximum over the whole row; uniform result: a value that K logits at least reach, or the window's
+// column: packed pattern, the maximum of the lane's column over the whole row; uniform result: a value that K logits at least reach, or the window's
 // lowest where fewer columns hold a logit of the window.
 __device__ __forceinline__ float bound_of_patterns(uint32_t column, int K) {
   const uint32_t own = max(key_of_pattern(column & 0xffffu), key_of_pattern(column >> 16));
-  uint32_t key;
-  if (K > 16) {                                                         // (uniform)
-    key = largest_32nd(own);
-  } else {
-    const uint32_t v = sort_rows_of_16(own);
-    if (K == 1) {                                                       // the maximum itself
-      key = max(max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
-                max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
-    } else {
-      const int j = (K - 1) >> 2;
-      key = min(min((uint32_t)__builtin_amdgcn_readlane((int)v, j), (uint32_t)__builtin_amdgcn_readlane((int)v, 16 + j)),
-                min((uint32_t)__builtin_amdgcn_readlane((int)v, 32 + j), (uint32_t)__builtin_amdgcn_readlane((int)v, 48 + j)));
-    }
-  }
+  uint32_t key = K > 16 ? largest_32nd(own) : nth_largest16(own, K);     // (uniform)
   key = max(key, key_of_pattern(HP_LOWEST));
   return __uint_as_float(((key & 0x8000u) ? key & 0x7fffu : key ^ 0xffffu) << 16);
 }
@@ -897,10 +894,10 @@ __device__ __forceinline__ uint32_t hist_stream(const StreamInput& in, uint4 (&q
         q[c + k] = load_stream_buffer<STREAMED>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k) * (NT * 16u));
         const uint32_t po = count(q[c + k + 1]);
         q[c + k + 1] = load_stream_buffer<STREAMED>(in.rs, in.vo, so + (uint32_t)(DEPTH + c + k + 1) * (NT * 16u));
+        M2 = pk_max3_f16_raw(M2, pe, po);
         half[k / 2] = quad_exchange_1(pe, po, odd);
       }
       const uint32_t key = quad_exchange_2(half[0], half[1], upper);
-      M2 = pk_max_f16_raw(M2, key);
       mp[c / 4 * NT] = (uint16_t)pk_max_f16_raw(key, key >> 16);
     }
   }
@@ -921,10 +918,10 @@ __device__ __forceinline__ uint32_t hist_stream(const StreamInput& in, uint4 (&q
         if (g + (c + k + i) * NT < whole) p[i] = count(q[c + k + i]);
         else if (g + (c + k + i) * NT == tail) p[i] = hist_chunk_outside(q[c + k + i], in.tail_valid, in.hist, in.acc);
       }
+      M2 = pk_max3_f16_raw(M2, p[0], p[1]);
       half[k / 2] = quad_exchange_1(p[0], p[1], odd);
     }
     const uint32_t key = quad_exchange_2(half[0], half[1], upper);
-    M2 = pk_max_f16(M2, key);
     mp[c / 4 * NT] = (uint16_t)pk_max_f16(key, key >> 16);
   }
   if (MASKED && (pk_sub_sat_u16(seen.hi, 0xFF80FF80u) | pk_sub_sat_u16(0x01800180u, seen.lo)))             // neither in the window nor masked: two-pass path
@@ -1331,9 +1328,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     __syncthreads();                                     // the row's map
   }
   float tau;
-  // (A lane's column holds the chunks of one sweep in four: with fewer than three sweeps less than 48 columns hold any, and the 32nd largest would be
-  // hardly a bound: three sequences of 8279 with K = 31 48.8 us a phase by the counts, 59 by the columns.)
-  if (__builtin_expect(K > COLUMNS_MAX_K || (K > 16 && sg.ncell < 3 * NT), 0)) {
+  if (__builtin_expect(K > COLUMNS_MAX_K, 0)) {
     const KthOfCounts kth = kth_of_counts<NT>(tid, (LdsWords)hist, K, (HistSharedLds<NT>)&hs);
     tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;
   } else {
