@@ -1527,7 +1527,9 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     if (tid == 0) hs.tot_p = tot_p;
     __syncthreads();
   }
-  if (__builtin_expect(!leave && (n_tiny > 0 || n_el > HIST_LIST || n_el < min(K, n_elems)), 0)) {
+  // (A bound among the window's positive values is reached by K logits, so that the K-th largest is one of them too: logits below the window change
+  // nothing then.  Asked about each row with such a logit, settle_hist took a layer of three rows of 8279 from 11.8 us to 13.6, one of 128256 from 15.9 to 17.4.)
+  if (__builtin_expect(!leave && ((n_tiny > 0 && !(tau >= hp_value_of_mag(0u, false))) || n_el > HIST_LIST || n_el < min(K, n_elems)), 0)) {
     n_el = settle_hist<NT>(tid, rowp, V, K, sg, (LdsWords)hist, lds_address(list.list), (LdsHalves)map, sel.cell_cap, (HistSharedLds<NT>)&hs);
     leave = n_el == UNSETTLED;
     __syncthreads();                                     // the list is complete

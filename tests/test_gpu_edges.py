@@ -76,12 +76,27 @@ def test_rows_with_neighbouring_large_logits(V, K, B):
     dealt_rows_against_oracle(names, rows, K, B)
 
 
-# Where a row's large logits lie must not decide over its time (kernel times, medians of turns): rows against the same values in random places, and
+# Medians of the kernel times of one-row layers, a turn for each of the inputs [n][V] (bf16, dealt out to B rows)
+def layer_times(B, K, inputs, turns):
+    from paper_2502_13652_amd import C2TContext
+    n, V = inputs[0].shape
+    ctx = C2TContext(B, V, 1, K, 1, 1, 2, 1, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    xs = [torch.nn.functional.pad(x.to(torch.bfloat16), (0, -V % 8))[torch.arange(B, device="cuda") % n].unsqueeze(1) for x in inputs]
+    for _ in range(2):                                       # (the first turns warm up)
+        ctx.profile_enable(turns * len(xs))
+        for i in range(turns * len(xs)):
+            ctx.reset(); ctx.expand_layer(xs[i % len(xs)]); ctx.finalize_tree()
+        torch.cuda.synchronize()
+    return np.median(np.array(ctx.profile_read(turns * len(xs))).reshape(turns, len(xs)), axis=0)
+
+
+# Where a row's large logits lie must not decide over its time: rows against the same values in random places, and
 # tied rows against such with K larger logits in random places.  A second read of such rows took them 1.3 to 3 times as long
 @pytest.mark.parametrize("B,K", [(256, 32), (512, 32), (300, 16), (40, 16), (1, 32)])
 def test_the_place_of_large_logits_does_not_cost_a_second_read(B, K):
-    from paper_2502_13652_amd import C2TContext
-    V, n, turns = 128256, min(B, 16), 30
+    V, n = 128256, min(B, 16)
     g = torch.Generator(device="cuda").manual_seed(5)
     noise, places = 3 * torch.randn((n, V), generator=g, device="cuda"), torch.randperm(V, generator=g, device="cuda")
     block = noise.clone(); block[:, 70000:71000] += 25
@@ -89,25 +104,19 @@ def test_the_place_of_large_logits_does_not_cost_a_second_read(B, K):
     frequency = noise - 1.05 * torch.log(torch.arange(1, V + 1, device="cuda").float())
     ties = 0.5 * torch.randint(0, 9, (n, V), generator=g, device="cuda") - 3.25
     headed = ties.clone(); headed[:, places[:K]] = 5 + 0.125 * torch.arange(K, device="cuda")
-    ctx = C2TContext(B, V, 1, K, 1, 1, 2, 1, 0.0)
-    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
-    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
-
-    def times(*inputs):
-        xs = [x.to(torch.bfloat16)[torch.arange(B, device="cuda") % n].view(B, 1, V) for x in inputs]
-        for _ in range(2):                                   # (the first turns warm up)
-            ctx.profile_enable(turns * len(xs))
-            for i in range(turns * len(xs)):
-                ctx.reset(); ctx.expand_layer(xs[i % len(xs)]); ctx.finalize_tree()
-            torch.cuda.synchronize()
-        t = np.array(ctx.profile_read(turns * len(xs))).reshape(turns, len(xs))
-        return np.median(t, axis=0)
-
     for x in (block, few, frequency):
-        together, apart = times(x, x[:, places])
+        together, apart = layer_times(B, K, [x, x[:, places]], 30)
         assert together < 1.15 * apart, (together, apart)
-    tied, free = times(ties, headed)
+    tied, free = layer_times(B, K, [ties, headed], 30)
     assert tied < 1.15 * free, (tied, free)
+
+
+# Logits of zero (padding of the vocabulary) below K positive ones: nothing has to be counted again for them (a tenth of a short row's time)
+def test_zeros_below_the_top_k_cost_nothing():
+    x = 3 * torch.randn((3, 8279), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
+    zeros = x.clone(); zeros[:, 4000:4004] = 0
+    with_zeros, without = layer_times(3, 10, [zeros, x], 200)
+    assert with_zeros < 1.05 * without, (with_zeros, without)
 
 
 # The entropy's M-th largest logit among the first and the last bins of a lane, and past the row's positive values
