@@ -852,7 +852,10 @@ __device__ __forceinline__ uint32_t key_of_pattern(uint32_t c) { return (c & 0x8
 // lowest where fewer columns hold a logit of the window.
 __device__ __forceinline__ float bound_of_patterns(uint32_t column, int K) {
   const uint32_t own = max(key_of_pattern(column & 0xffffu), key_of_pattern(column >> 16));
-  uint32_t key = K > 16 ? largest_32nd(own) : nth_largest16(own, K);     // (uniform)
+  uint32_t key;                                                         // (K is uniform)
+  if (K > 16) key = largest_32nd(own);
+  else if (K > 1) key = nth_largest16(own, K);
+  else key = wave_reduce_u32(own, 0u, [](uint32_t x, uint32_t y) { return max(x, y); });
   key = max(key, key_of_pattern(HP_LOWEST));
   return __uint_as_float(((key & 0x8000u) ? key & 0x7fffu : key ^ 0xffffu) << 16);
 }
