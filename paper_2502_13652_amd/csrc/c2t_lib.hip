@@ -32,11 +32,17 @@ static_assert(C2T_MAX_BUDGET == C2T_MAX_BUDGET_DEV && C2T_MAX_CANDIDATES == C2T_
 // 16 KB histogram, its static LDS (under 8 KB) and the map (2 bytes per 4 chunks): 16 KB at most.
 constexpr int HP_NT = 512;                     // workgroup size of the histogram kernel
 // Copies of the histogram of a workgroup that has its CU to itself: neighbouring lanes which hold the same value add to different words.  What they
-// save grows with the row, folding them costs the same for all.  Four / two: a layer of 256 rows of 128256 of spread logits 24.1 / 23.4 us, of
-// logits round -40 (steps of 1/4) 26.3 / 27.4, round -100 29.5 / 31.9; phases of short rows, or of segments of a shared one: four sequences of
-// 20011 230.3 / 223.8, one of 128256 118.7 / 117.3, of 32000 93.0 / 92.1.  (One: 222.6, 117.2 and 92.2, and the long rows 23.7, 28.4 and 33.1.)
-constexpr int HP_REPL_LONG = 4, HP_REPL_SHORT = 2;
-constexpr int64_t STREAMED_BYTES = 24 << 20;       // logits of a launch beyond which they are not kept in the L2s (eight of 4 MB)
+// save grows with the row and with how few its values are, folding them costs the same for all.  Layers in us, with two copies / four, of
+// spread logits, of some round -40 (steps of 1/4) and of some round -100 (of 1/2): 250 rows of 20011 14.7 / 15.2, 17.2 / 16.8, 22.0 / 21.4;
+// 200 of 32000 14.5 / 14.8, 20.4 / 19.6, 26.1 / 25.3; 250 of 36000 16.0 / 16.1, 25.7 / 24.6, 27.5 / 25.8; 250 of 50000 17.0 / 17.2, 27.8 / 25.5, 33.2 / 30.5;
+// 150 of 80000 17.4 / 17.2, 35.4 / 31.5, 43.3 / 37.4.  Shared rows have two: of spread logits 128 of 128256 take 20.2 / 21.0, 64 of 262144 20.9 / 21.5, one of
+// 128256 15.0 / 15.2 (round -40 34.6 / 33.5, 211 / 209 and 16.1 / 15.9).
+constexpr int HP_REPL_LONG = 4, HP_REPL_SHORT = 2, HP_SHORT_CHUNKS = 4096;
+// Logits of a launch beyond which they are not kept in the L2s (eight of 4 MB, which the tables and the handed-over data share): 150 rows of 80000, 24 MB,
+// 17.3 us a layer with the usual policy and 17.8 without, 250 of 50000, 25 MB, 17.2 and 17.5; phases of 16 sequences of 128256 with 16 rows each,
+// 64 MB a layer, 178.9 and 177.3.  Shared rows have the usual policy at any size: their workgroups have a quarter of a row and less to stream
+// and wait longer for the cells: 128 rows of 128256 20.2 / 20.3, 64 of 262144 21.4 / 21.8 (128 of them, the largest such launch, 28.4 / 27.7).
+constexpr int64_t STREAMED_BYTES = 24 << 20;
 constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
 constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
@@ -169,6 +175,20 @@ int32_t* scratch_on_current_device(hipError_t* err) {
   return (int32_t*)sym;
 }
 
+// Builds of the histogram kernel, see launch_logits
+enum HistBuild { HB_FOUR_PER_CU, HB_SHARED, HB_SHORT, HB_LONG, HB_LONG_STREAMED, HB_COUNT };
+typedef void (*HistKernel)(const void*, int64_t, int, int, const double*, const float*, TreeState, ScoreParams);
+template <bool TOPM>
+HistKernel hist_kernel(int build) {
+  switch (build) {
+    case HB_FOUR_PER_CU: return k_logits_hist<HP_NT, TOPM, 8, 1, false, true>;
+    case HB_SHARED: return k_logits_hist<HP_NT, TOPM, 6, HP_REPL_SHORT, true, false>;
+    case HB_SHORT: return k_logits_hist<HP_NT, TOPM, 6, HP_REPL_SHORT, false, false>;
+    case HB_LONG_STREAMED: return k_logits_hist<HP_NT, TOPM, 6, HP_REPL_LONG, false, true>;
+    default: return k_logits_hist<HP_NT, TOPM, 6, HP_REPL_LONG, false, false>;
+  }
+}
+
 }  // namespace
 
 struct c2t_ctx {
@@ -185,7 +205,7 @@ struct c2t_ctx {
   bool have_cls, finalized;
   int ns_first, ns_other;      // row splits in use
   bool share_first, share_other;   // rows may be shared by workgroups (the default; off where the caller has set the splits itself)
-  size_t lds_raised[4];        // dynamic LDS this context has asked the runtime to allow each build of its layer kernel so far
+  size_t lds_raised[HB_COUNT];       // dynamic LDS this context has asked the runtime to allow each build of its layer kernel so far
   int n_cus;                   // compute units of the device the context was created on
   // optional event timing of the logits pass
   std::vector<hipEvent_t> ev;
@@ -257,44 +277,27 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
     const int64_t cus = x->n_cus;
     const bool four_per_cu = (int64_t)grid > cus;
     const bool coop = share.n > 1;                           // (never with four per CU: see share_of)
-    const bool streamed = (int64_t)c.batch * rows_per_seq * c.vocab * 2 > STREAMED_BYTES;    // see load_stream_buffer; shared rows are few, and never streamed
-    const int repl = four_per_cu ? 1 : streamed && !coop ? HP_REPL_LONG : HP_REPL_SHORT;     // copies of the histogram in LDS
+    const bool long_rows = !coop && cps > HP_SHORT_CHUNKS;
+    const bool streamed = (int64_t)c.batch * rows_per_seq * c.vocab * 2 > STREAMED_BYTES;
+    const int repl = four_per_cu ? 1 : long_rows ? HP_REPL_LONG : HP_REPL_SHORT;             // copies of the histogram in LDS
     const size_t lds_work = (std::max(std::max(hist_lds_bytes<HP_NT>(repl) + std::max(map_lds, (size_t)HP_NT * 16), generic_lds), score_lds) + 15) / 16 * 16;
     sp.lds_bytes = (int)lds_work;
     sp.w_lds_off = (int)lds_work;                           // behind it: the classifier's parameters, padded to 16 bytes
     const size_t lds = lds_work + ((size_t)(5 * c.hidden + 1) * 4 + 15) / 16 * 16;
-    const int topm = c.entropy_top_m > 0;
     // Two builds of the kernel.  Four workgroups per CU on 64 registers a lane, or three per CU on
     // 80 registers.  Measured on full layers of V = 128256 (us per layer, four / three per CU):
     // 256 rows 32.4 / 31.6, 512: 38.8 / 39.8, 1024: 61.0 / 73.1, 1280: 82.7 / 86.6, 1536: 95.3 / 91.6,
     // 2048: 114 / 120, 3072: 166 / 163, 4096: 209 / 215, 8192: 388 / 393.  Four per CU whenever a CU
     // gets more than one workgroup; a workgroup that is alone on its CU is 2-3 % faster on 80 registers.
-#define C2T_HIST_KERNEL(TOPM)                                                           \
-  (four_per_cu ? (const void*)k_logits_hist<HP_NT, TOPM, 8, 1, false, true>             \
-   : coop      ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_SHORT, true, false> \
-   : streamed  ? (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_LONG, false, true>  \
-               : (const void*)k_logits_hist<HP_NT, TOPM, 6, HP_REPL_SHORT, false, false>)
-    const void* fn = topm ? C2T_HIST_KERNEL(true) : C2T_HIST_KERNEL(false);
-#undef C2T_HIST_KERNEL
-    size_t& raised = x->lds_raised[four_per_cu ? 1 : coop ? 2 : streamed ? 3 : 0];
+    const int build = four_per_cu ? HB_FOUR_PER_CU : coop ? HB_SHARED : !long_rows ? HB_SHORT : streamed ? HB_LONG_STREAMED : HB_LONG;
+    const HistKernel fn = c.entropy_top_m == 0 ? hist_kernel<false>(build) : hist_kernel<true>(build);
+    size_t& raised = x->lds_raised[build];
     if (lds > raised) {                                     // beyond the 48 KB a kernel may use without asking
-      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
       raised = lds;
     }
-#define C2T_LAUNCH_HIST(TOPM, WPS, REPL, COOP, STREAMED)                                                                                      \
-  hipExtLaunchKernelGGL((k_logits_hist<HP_NT, TOPM, WPS, REPL, COOP, STREAMED>), dim3(grid), dim3(HP_NT), lds, s, ev0, ev1, 0, logits, stride, \
-                        c.vocab, cps, (const double*)x->tab_e, (const float*)x->st.cls, x->st, sp)
-#define C2T_LAUNCH_HIST_BUILD(TOPM)                                         \
-  do {                                                                      \
-    if (four_per_cu) C2T_LAUNCH_HIST(TOPM, 8, 1, false, true);              \
-    else if (coop) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_SHORT, true, false);    \
-    else if (streamed) C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_LONG, false, true); \
-    else C2T_LAUNCH_HIST(TOPM, 6, HP_REPL_SHORT, false, false);             \
-  } while (0)
-    if (topm) C2T_LAUNCH_HIST_BUILD(true); else C2T_LAUNCH_HIST_BUILD(false);
-#undef C2T_LAUNCH_HIST_BUILD
-#undef C2T_LAUNCH_HIST
+    hipExtLaunchKernelGGL(fn, dim3(grid), dim3(HP_NT), lds, s, ev0, ev1, 0, logits, stride, c.vocab, cps, (const double*)x->tab_e, (const float*)x->st.cls, x->st, sp);
   } else {
     const size_t lds_work = (std::max(std::max(generic_lds, score_lds), LIST_BYTES_F32 + SEL_AUX_BYTES) + 15) / 16 * 16;
     sp.lds_bytes = (int)lds_work;
@@ -373,7 +376,7 @@ int c2t_create(const c2t_config* cfg, void* ws, size_t bytes, c2t_ctx** out) {
   x->tab_e = (double*)(w + L.tab_e);
   x->z_beta = cfg->beta <= 0.0f ? -INFINITY : (float)std::log((double)cfg->beta / (1.0 - (double)cfg->beta));
   x->layer = -1; x->have_cls = false; x->finalized = false; x->ev_used = 0; x->sample_every = 1; x->sample_first = 0; x->phase_no = -1;
-  x->lds_raised[0] = x->lds_raised[1] = x->lds_raised[2] = x->lds_raised[3] = 48 * 1024;
+  for (size_t& r : x->lds_raised) r = 48 * 1024;
   {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)

@@ -119,6 +119,16 @@ def test_zeros_below_the_top_k_cost_nothing():
     assert with_zeros < 1.05 * without, (with_zeros, without)
 
 
+# How a row's equal values are kept apart goes by its own length: a layer of fewer rows is not slower than one of more (150 rows of 80000, round -100, were
+# slower by a seventh than 165)
+@pytest.mark.parametrize("V,few,more", [(80000, 150, 165)])
+def test_fewer_rows_with_few_values_are_not_slower(V, few, more):
+    x = torch.randn((16, V), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
+    x = torch.round(2 * (x - 100)) / 2
+    t_few, t_more = (layer_times(B, 10, [x], 60)[0] for B in (few, more))
+    assert t_few < 1.06 * t_more, (t_few, t_more)
+
+
 # The entropy's M-th largest logit among the first and the last bins of a lane, and past the row's positive values
 @pytest.mark.parametrize("V,M", [(4099, 2), (4099, 9), (32771, 512), (520, 519)])
 def test_top_m_at_a_lane_s_bins(V, M):
