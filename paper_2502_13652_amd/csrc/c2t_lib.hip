@@ -28,9 +28,8 @@ namespace {
 constexpr size_t ALIGN = 256;
 static_assert(C2T_MAX_BUDGET == C2T_MAX_BUDGET_DEV && C2T_MAX_CANDIDATES == C2T_MAX_CANDIDATES_DEV && C2T_MAX_FRONTIER == SP_MAX_F && C2T_MAX_TOP_K == 64,
               "limits of the C ABI and of the kernels must agree");
-// Cell map of one workgroup.  bf16: four workgroups of 512 threads share the CU's 160 KB, each with the
-// 16 KB histogram, its static LDS (under 8 KB) and the map (2 bytes per 4 chunks): 16 KB at most.
-constexpr int HP_NT = 512;                     // workgroup size of the histogram kernel
+// Workgroup size of the histogram kernel
+constexpr int HP_NT = 512;
 // Copies of the histogram of a workgroup that has its CU to itself: neighbouring lanes which hold the same value add to different words.  What they
 // save grows with the row and with how few its values are, folding them costs the same for all.  Layers in us, with two copies / four, of
 // spread logits, of some round -40 (steps of 1/4) and of some round -100 (of 1/2): 250 rows of 20011 14.7 / 15.2, 17.2 / 16.8, 22.0 / 21.4;
@@ -40,9 +39,10 @@ constexpr int HP_NT = 512;                     // workgroup size of the histogra
 constexpr int HP_REPL_LONG = 4, HP_REPL_SHORT = 2, HP_SHORT_CHUNKS = 4096;
 // Logits of a launch beyond which they are not kept in the L2s (eight of 4 MB, which the tables and the handed-over data share): 150 rows of 80000, 24 MB,
 // 17.3 us a layer with the usual policy and 17.8 without, 250 of 50000, 25 MB, 17.2 and 17.5; phases of 16 sequences of 128256 with 16 rows each,
-// 64 MB a layer, 178.9 and 177.3.  Shared rows have the usual policy at any size: their workgroups have a quarter of a row and less to stream
-// and wait longer for the cells: 128 rows of 128256 20.2 / 20.3, 64 of 262144 21.4 / 21.8 (128 of them, the largest such launch, 28.4 / 27.7).
+// 64 MB a layer, 178.9 and 177.3.  Shared rows have the usual policy at any size: their workgroups stream half a row
+// or less, and the cells are read again by one of them: 128 rows of 128256 20.2 / 20.3, 64 of 262144 21.4 / 21.8 (128 of them, the largest such launch, 28.4 / 27.7).
 constexpr int64_t STREAMED_BYTES = 24 << 20;
+// Cell map of one workgroup, at most: 262144 bf16 logits (2 bytes per 4 chunks).
 constexpr int MAX_MAP_BYTES_BF16 = 16 * 1024;
 constexpr int MAX_MAP_BYTES_F32 = 48 * 1024;
 constexpr size_t LIST_BYTES_F32 = 32 * 1024;   // of the fp32 list at least: 4096 logits (two workgroups a CU have 80 KB each)
@@ -175,6 +175,13 @@ int32_t* scratch_on_current_device(hipError_t* err) {
   return (int32_t*)sym;
 }
 
+// Four workgroups share the CU's 160 KB: 40960 bytes each for the histogram and the list, the map, the classifier's copy and the static LDS.  With
+// the widest classifier that holds for rows of up to 229376 logits, at the largest map for classifiers of up to 163 units; beyond, three share it.  1024 rows of 198000
+// with 256 units 106 us where 2 KB more were taken for the columns, which is three, 83 so.
+constexpr size_t HP_STATIC_LDS = 2880;         // of the build for four workgroups a CU, as compiled
+constexpr size_t hist_lds_of_workgroup(int map_bytes, int hidden) { return hist_lds_bytes<HP_NT>(1) + map_bytes + ((5 * hidden + 1) * 4 + 15) / 16 * 16 + HP_STATIC_LDS; }
+static_assert(4 * hist_lds_of_workgroup(229376 / 16, C2T_MAX_HIDDEN) <= 160 * 1024 && 4 * hist_lds_of_workgroup(MAX_MAP_BYTES_BF16, 163) <= 160 * 1024,
+              "four workgroups a CU");
 // Builds of the histogram kernel, see launch_logits
 enum HistBuild { HB_FOUR_PER_CU, HB_SHARED, HB_SHORT, HB_LONG, HB_LONG_STREAMED, HB_COUNT };
 typedef void (*HistKernel)(const void*, int64_t, int, int, const double*, const float*, TreeState, ScoreParams);

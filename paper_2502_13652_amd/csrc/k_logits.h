@@ -65,7 +65,7 @@ template <> struct LogitTraits<0> {     // fp32
 
 // A logits chunk is read once per layer, but for the cells that hold one of the row's largest.  STREAMED: a non-temporal load keeps the
 // stream from evicting what the workgroups reuse (the e^v table, the classifier) from the L2.  Launches of at most one workgroup a CU
-// whose rows fit the L2s read with the usual policy: the cells are still there when they are read again (phases: one sequence of 128256
+// whose rows fit the L2s, and shared rows, read with the usual policy: the cells are still there when they are read again (phases: one sequence of 128256
 // 123.5 -> 121.1 us, four of 20011 with 64 rows each 261.7 -> 258.2; 256 rows of 128256 a layer, 64 MB, 177.3 -> 178.9: those are STREAMED).
 typedef uint32_t c2t_uint4v __attribute__((ext_vector_type(4)));
 // 16 bytes at descriptor base + lane offset + scalar offset; zeros past the descriptor's size
@@ -989,7 +989,10 @@ struct HistShared {
 };
 constexpr int HIST_LIST = 256;                  // logits the element list holds
 template <int NT>
-__host__ __device__ inline size_t hist_lds_bytes(int repl) { return (size_t)HP_WORDS * 4 * repl + HIST_LIST * 8 + NT * 4; }   // histogram copies | element list | columns; the cell map behind
+__host__ __device__ constexpr size_t hist_lds_bytes(int repl) {   // histogram copies | columns, then (a barrier later) the element list; the cell map behind
+  static_assert(NT * 4 <= HIST_LIST * 8, "the columns fit the list's place");
+  return (size_t)HP_WORDS * 4 * repl + HIST_LIST * 8;
+}
 __device__ __forceinline__ SelectLds hist_list(unsigned char* at) {
   SelectLds s;
   s.list = at; s.aux = nullptr; s.list_cap = HIST_LIST; s.cell_cap = 0;
@@ -1196,7 +1199,7 @@ __device__ __forceinline__ bool share_row(int tid, const ScoreParams& sp, int sp
 }
 
 // One (row, split) segment on the histogram path, run by a whole workgroup of NT threads.
-// hist: HP_WORDS words a copy, then the element list, the columns and the map, one 2-byte key per cell, padded to 16 bytes
+// hist: HP_WORDS words a copy, then the columns and, in their place, the element list, and the map, one 2-byte key per cell, padded to 16 bytes
 // (hist_lds_bytes); sel: see SelectLds.
 // TOPM: built with the entropy over the M largest logits (a separate instantiation, so that the
 // default kernel carries none of its registers).
@@ -1204,7 +1207,7 @@ __device__ __forceinline__ bool share_row(int tid, const ScoreParams& sp, int sp
 // that have handed their segment over and are done.
 template <int NT, bool TOPM, int WPS, int REPL, bool COOP, bool STREAMED>
 __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ rowp, int V, int K, int M, const Segment& sg_own,
-                                             const double* __restrict__ tab_e, uint32_t* __restrict__ hist, const SelectLds& list, uint32_t* columns, uint16_t* map,
+                                             const double* __restrict__ tab_e, uint32_t* __restrict__ hist, const SelectLds& list, uint16_t* map,
                                              const SelectLds& sel, RowResult* rr, HistShared<NT>& hs,
                                              const ClassifierStage cst, const float* __restrict__ cls, const TreeState& st, const ScoreParams& sp, int split,
                                              int64_t row_launched, int64_t slot, int& tid) {
@@ -1291,6 +1294,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   const bool shared_row = COOP && sp.coop > 1;          // (uniform) then the factors are loaded behind the hand-over: they would
   ExpFactors ef;                                        // only take registers from it
   if (!shared_row) ef = load_exp_factors(tab_e, tid);
+  uint32_t* const columns = (uint32_t*)list.list;       // (read before the next barrier; the list's entries come after it)
   columns[tid] = M2;                                    // the lane's maximum
   {
     const uint32_t m2 = wave_reduce_u32(M2, HP_NONE2, [](uint32_t x, uint32_t y) { return pk_max_f16(x, y); });
@@ -1606,7 +1610,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     if (tid == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
     __syncthreads();
   } else {
-    top = hist_segment<NT, TOPM, WPS, REPL, COOP, STREAMED>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, list, (uint32_t*)(dyn_lds + HP_WORDS * 4 * REPL + HIST_LIST * 8),
+    top = hist_segment<NT, TOPM, WPS, REPL, COOP, STREAMED>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, list,
                                                   (uint16_t*)(dyn_lds + hist_lds_bytes<NT>(REPL)), sel, &rr, hs, cst, cls, st, sp, split, rl, row, tid);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
