@@ -314,14 +314,15 @@ struct SelectLds {
 template <int NT, int EPC>
 __device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int bytes) {
   SelectLds s;
-  s.list = base; s.list_cap = (bytes - SEL_AUX_BYTES) / 8; s.aux = base + bytes - SEL_AUX_BYTES;
+  s.list = base; s.list_cap = (bytes - SEL_AUX_BYTES) / 8 & ~3; s.aux = base + bytes - SEL_AUX_BYTES;     // (values and ids on 16 bytes)
   s.cell_cap = min(min(SEL_CELL_CAP, NT / CPC), s.list_cap / (CPC * EPC));
   return s;
 }
 
 // ---- ranking of the element list by (logit desc, id asc), exactly; the best K go to topv, topi.  By every wavefront but the last, which
 // forms the row's entropy meanwhile: T lanes per element (four at least), each compares it with four entries per LDS read, of every
-// T-th group of four; the partial ranks are summed over the T lanes.  Equal logits are told apart by id where a count shows them.
+// T-th group of four; the partial ranks are summed over the T lanes.  Equal logits are told apart by id where a count shows them, four a read as
+// well (one at a time, a layer of four rows of 20011 whose list holds 160 equal logits took 21.8 us, 17.8 so).
 template <int NT>
 __device__ __forceinline__ void rank_list(int tid, int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
   constexpr int nt = NT - WAVE;
@@ -352,8 +353,13 @@ __device__ __forceinline__ void rank_list(int tid, int K, const SelectLds& sel, 
     if (__builtin_amdgcn_ballot_w64(tied) != 0ull) {         // (uniform)
       int ahead = 0;
       if (tied) {
-#pragma unroll 4
-        for (int o = sub; o < n_el; o += T) ahead += (int)(el_v[o] == v && el_i[o] < id);
+#pragma unroll 2
+        for (int o = sub * 4; o < n_el; o += T * 4) {
+          const float4 q = *(const float4*)(el_v + o);
+          const int4 i = *(const int4*)(el_i + o);
+          const uint32_t hit = (q.x == v && i.x < id ? 1u : 0u) | (q.y == v && i.y < id ? 2u : 0u) | (q.z == v && i.z < id ? 4u : 0u) | (q.w == v && i.w < id ? 8u : 0u);
+          ahead += __popc(hit & (15u >> max(o + 4 - n_el, 0)));
+        }
       }
       rank += sum_of_lanes(tshift, ahead);
     }
