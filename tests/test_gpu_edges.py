@@ -79,6 +79,33 @@ def test_rows_with_neighbouring_large_logits(V, K, B):
     dealt_rows_against_oracle(names, rows, K, B)
 
 
+# The rows of test_gpu_rows.py in the builds for four workgroups a CU (more rows than CUs) and for long rows alone on a CU, with the usual cache policy
+# (up to 24 MB) and without: equal rows give equal results
+@pytest.mark.parametrize("V,K,B,M", [(4099, 1, 300, 0), (4099, 17, 300, 0), (8191, 64, 300, 0), (71003, 16, 300, 0), (71003, 33, 300, 0), (32771, 32, 1100, 0), (5003, 4, 300, 37),
+                                     (71003, 16, 300, 1000), (71003, 16, 150, 0), (71003, 32, 150, 1000), (128256, 17, 200, 0), (128256, 64, 200, 0), (128256, 1, 200, 1000)])
+def test_adversarial_rows_in_the_builds_for_many_rows(V, K, B, M):
+    names, rows = adversarial_rows(V, np.random.default_rng(V + K), True)
+    dealt_rows_against_oracle(names, rows, K, B, M)
+
+
+# NaN, +inf and rows without a finite logit in these builds
+@pytest.mark.parametrize("V,B", [(4104, 300), (71003, 150), (128256, 200)])
+def test_bad_rows_in_the_builds_for_many_rows(V, B):
+    from paper_2502_13652_amd import C2TContext
+    rows = (2 * np.random.default_rng(V).standard_normal((6, V))).astype(np.float32)
+    rows[1, V // 2], rows[2, V - 1], rows[3, :], rows[4, 0] = np.nan, np.inf, -np.inf, -np.nan
+    x = torch.nn.functional.pad(torch.from_numpy(rows).to(torch.bfloat16), (0, -V % 8), value=float("nan"))
+    ctx = C2TContext(B, V, 1, 4, 1, 4, 2, 1, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    ctx.reset()
+    ctx.expand_layer(x.cuda()[torch.arange(B, device="cuda") % 6].unsqueeze(1))
+    out = to_np(ctx.finalize_tree())
+    bad = np.array([0, 1, 1, 1, 1, 0])[np.arange(B) % 6]
+    np.testing.assert_array_equal(out["status"] & 1, bad)
+    np.testing.assert_array_equal(out["n_nodes"], 1 - bad)
+
+
 # Medians of the kernel times of one-row layers, a turn for each of the inputs [n][V] (bf16, dealt out to B rows)
 def layer_times(B, K, inputs, turns):
     from paper_2502_13652_amd import C2TContext
