@@ -123,10 +123,6 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t identity, uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)identity, (int)v, CTRL, ROW_MASK, 0xf, false);
 }
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_f32(float identity, float v) {
-  return __uint_as_float(dpp_u32<CTRL, ROW_MASK>(__float_as_uint(identity), __float_as_uint(v)));
-}
-template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ double dpp_f64(double v) {      // identity 0.0
   const uint64_t u = (uint64_t)__double_as_longlong(v);
   const uint32_t lo = dpp_u32<CTRL, ROW_MASK>(0u, (uint32_t)u), hi = dpp_u32<CTRL, ROW_MASK>(0u, (uint32_t)(u >> 32));
@@ -245,32 +241,6 @@ __device__ __forceinline__ int append_places(int n, int32_t* counter) {
   int base = 0;
   if (lane_id() == WAVE - 1) base = atomicAdd(counter, incl);
   return __builtin_amdgcn_readlane(base, WAVE - 1) + incl - n;
-}
-
-// Partial rank of an entry with value v (its own index: self) in a list of n values in LDS: how many of the
-// entries first4, first4 + 1, .. first4 + 3, first4 + step4, ... come before it in the order (value desc, then
-// `ahead_at_tie(index)` among equal values).  Four values per LDS read, the reads independent of each other, where a
-// read per value has every step wait out the LDS latency (a merge of 40 list entries: 1.5 us).
-// vals 16-byte aligned, first4 and step4 multiples of 4; up to three floats past the n-th are read and ignored.
-template <typename AheadAtTie>
-__device__ __forceinline__ int count_ahead4(const float* vals, int n, int first4, int step4, float v, int self, AheadAtTie ahead_at_tie) {
-  int rank = 0;
-  for (int o = first4; o < n; o += step4) {
-    const float4 q = *(const float4*)(vals + o);
-    const float qa[4] = {q.x, q.y, q.z, q.w};
-    uint32_t eq = 0;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const bool in = o + t < n;
-      rank += in && qa[t] > v; eq |= (in && qa[t] == v ? 1u : 0u) << t;
-    }
-    if (self >= o && self < o + 4) eq &= ~(1u << (self - o));   // not the entry itself
-    while (eq) {                                                // ties: rare
-      const int t = __ffs(eq) - 1; eq &= eq - 1;
-      rank += ahead_at_tie(o + t) ? 1 : 0;
-    }
-  }
-  return rank;
 }
 
 // K-th largest (k >= 1) of the keys held by one wave, NV keys per lane (invalid keys = 0,

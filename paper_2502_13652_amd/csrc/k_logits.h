@@ -563,7 +563,8 @@ constexpr int HP_BINS = 8192;                 // sign(1) | exponent mod 32 (5) |
 constexpr int HP_WORDS = HP_BINS / 2;         // LDS words: low half counts +|v|, high half counts -|v|
 constexpr uint32_t HP_MAG_LO = 102u << 7;     // |x| >= 2^-25
 constexpr uint32_t HP_MAG_SPAN = 32u << 7;    // 32 binades: |x| < 2^7
-constexpr uint32_t HP_F16_NEG_INF2 = 0xFC00FC00u;              // identity of the packed maximum
+constexpr uint32_t HP_LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1);  // the window's lowest value, which also stands in for masked logits
+constexpr uint32_t HP_NONE2 = 0xFC00FC00u;    // identity of the packed maximum (fp16's -inf twice): a lane without a chunk
 
 // value-ordered rank r in [0, 8192): larger r = larger value.  r -> bf16 code.
 __device__ __forceinline__ uint32_t hp_code_of_rank(int r) {
@@ -715,7 +716,6 @@ __device__ __forceinline__ uint32_t twice_index(uint32_t w) {
 // it ranks after every window value.  NaN codes (above 0xff80) are not in the range.
 __device__ __forceinline__ bool hp_masked(uint32_t code16) { return code16 - 0xc480u <= 0xff80u - 0xc480u; }
 __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32_t hist, OutsideAcc* acc_generic) {     // hist: LDS address
-  constexpr uint32_t LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1);   // the lowest value of the window stands in for a masked logit
   const OutsideAccLds acc = (OutsideAccLds)acc_generic;
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
   if (n_valid == 8) {
@@ -726,7 +726,7 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
     for (int j = 0; j < 4; ++j) {
       hi = pk_max_u16(hi, w[j]);
       lo = pk_min_u16(lo, pk_sub_u16(w[j], 0xC300C300u));
-      w2[j] = pk_min_u16(w[j], LOWEST * 0x00010001u);
+      w2[j] = pk_min_u16(w[j], HP_LOWEST * 0x00010001u);
       d[j] = twice_index(w2[j]);
       dm |= d[j];
     }
@@ -769,7 +769,7 @@ __device__ __noinline__ uint32_t hist_chunk_outside(uint4 q, int n_valid, uint32
     __hip_atomic_fetch_add(&acc->s_tiny, s_tiny, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   if (mag_max >= HP_MAG_LO + HP_MAG_SPAN) __hip_atomic_fetch_max(&acc->mag_max, mag_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  const uint32_t c16 = cm == -INFINITY ? (HP_F16_NEG_INF2 & 0xffffu) : __float_as_uint(cm) >> 16;
+  const uint32_t c16 = cm == -INFINITY ? (HP_NONE2 & 0xffffu) : __float_as_uint(cm) >> 16;
   return c16 | (c16 << 16);
 }
 
@@ -806,14 +806,14 @@ __device__ __forceinline__ uint32_t hist_chunk(const uint4& q, uint32_t hist, Ou
 // codes - 0xC300), which the caller looks at once per row.
 struct CodesSeen { uint32_t hi, lo; };
 __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t hist, uint32_t own, OutsideAcc* acc, CodesSeen& seen) {
-  constexpr uint32_t LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1), FIRST_MASKED = 0xC480u;       // see hp_masked
+  constexpr uint32_t FIRST_MASKED = 0xC480u;       // see hp_masked
   const uint32_t raw[4] = {q.x, q.y, q.z, q.w};
   uint32_t w[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     seen.hi = pk_max_u16(seen.hi, raw[j]);
     seen.lo = pk_min_u16(seen.lo, pk_sub_u16(raw[j], 0xC300C300u));
-    w[j] = pk_min_u16(raw[j], LOWEST * 0x00010001u);
+    w[j] = pk_min_u16(raw[j], HP_LOWEST * 0x00010001u);
   }
   const uint32_t d[4] = {twice_index(w[0]), twice_index(w[1]), twice_index(w[2]), twice_index(w[3])};
   uint32_t pat;
@@ -844,8 +844,6 @@ __device__ __forceinline__ uint32_t hist_chunk_masked(const uint4& q, uint32_t h
 // four sequences of 20011 with 64 x 32 candidates took 237.3 us a phase with it, 230.4 so, 256 of 152064 with 32 x 32 1820 and 1803, a layer of three rows
 // of 8279 with K = 31 12.5 and 11.7.
 constexpr int COLUMNS_MAX_K = 32;
-constexpr uint32_t HP_NONE2 = HP_F16_NEG_INF2;                          // pattern of a lane without a chunk
-constexpr uint32_t HP_LOWEST = 0x8000u | (HP_MAG_LO + HP_MAG_SPAN - 1);  // the window's lowest value, which also stands in for masked logits
 // 16-bit keys that order like the values of the patterns
 __device__ __forceinline__ uint32_t key_of_pattern(uint32_t c) { return (c & 0x8000u) ? c ^ 0xffffu : c | 0x8000u; }
 // column: packed pattern, the maximum of the lane's column over the whole row; uniform result: a value that K logits at least reach, or the window's
