@@ -298,9 +298,10 @@ __device__ __forceinline__ int sum_of_lanes(int tshift, int v) {
 }
 
 // LDS of the selection of a segment's (or a row's) K largest logits: the element list ((value, id), 8 bytes an
-// entry, overlaying histogram and cell map) and the number of cells a launch may keep:
-// min(SEL_CELL_CAP, NT / CPC, list entries / elements per cell), which the host keeps >= 2K - 1.
-constexpr int CPC = 4;                         // chunks per cell of the cell map: four sweeps of a lane
+// entry; the histogram path's own lies behind its counts, generic_segment's, the fp32 path's and that of merged rows at the start of
+// the dynamic LDS) and the number of cells a launch may list: min(SEL_CELL_CAP, NT / CPC, list entries / elements per cell), which the
+// host keeps >= 2K - 1.
+constexpr int CPC = 4;                         // chunks per cell of the cell map: four neighbouring ones (histogram path), or four sweeps of a lane (generic_segment)
 constexpr int SEL_CELL_CAP = 256;              // size of the candidate-cell list
 constexpr int SEL_AUX_BYTES = 2048 + SEL_CELL_CAP * 4;   // behind the list: the lanes' maxima and the cells of generic_segment
 struct SelectLds {
