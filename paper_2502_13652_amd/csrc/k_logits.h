@@ -1001,6 +1001,8 @@ __device__ __forceinline__ SelectLds hist_list(unsigned char* at) {
 // than K logits lie in the window), how many logits exceed it and how many reach it.  Out of line: it is looked for where K > COLUMNS_MAX_K, and in rows that
 // settle_hist is asked about.
 struct KthOfCounts { int rank, n_gt, n_ge; };
+// As a bound: where fewer than K logits lie in the window, its lowest value, which all of them reach and cells without a chunk do not
+__device__ __forceinline__ float bound_of_counts(const KthOfCounts& k) { return __uint_as_float(hp_code_of_rank(max(k.rank, 0)) << 16); }
 template <int NT> using HistSharedLds = __attribute__((address_space(3))) HistShared<NT>*;
 template <int NT>
 __device__ __noinline__ KthOfCounts kth_of_counts(int tid, LdsWords hist, int top_k, HistSharedLds<NT> hs) {
@@ -1067,7 +1069,7 @@ __device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp,
   __syncthreads();                                             // everybody has read the lengths
   if ((uniform(hs.out.n_tiny) > 0 && kth.rank < HP_WORDS) || (uniform(hs.out.n_masked) > 0 && kth.rank < 0)) return UNSETTLED;
   if (n_cells <= cell_cap && n_el >= want && n_el <= HIST_LIST) return n_el;
-  const float tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;    // (fewer than K logits: all of them)
+  const float tau = bound_of_counts(kth);
   // Only what exceeds tau: then fewer than K cells do, else no more than n_ge reach it, but for cells of masked logits, whose keys are the lowest value
   const bool strict = kth.n_ge > (n_cells > cell_cap ? cell_cap : HIST_LIST) || kth.rank == 0;
   if (strict && kth.n_gt == 0) n_cells = 0;
@@ -1326,8 +1328,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   }
   float tau;
   if (__builtin_expect(K > COLUMNS_MAX_K, 0)) {
-    const KthOfCounts kth = kth_of_counts<NT>(tid, (LdsWords)hist, K, (HistSharedLds<NT>)&hs);
-    tau = kth.rank >= 0 ? __uint_as_float(hp_code_of_rank(kth.rank) << 16) : -INFINITY;
+    tau = bound_of_counts(kth_of_counts<NT>(tid, (LdsWords)hist, K, (HistSharedLds<NT>)&hs));
   } else {
     tau = bound_of_patterns(column, K);
   }

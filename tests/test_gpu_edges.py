@@ -32,6 +32,12 @@ def test_bf16_rows_where_the_bound_changes(V, K):
     rows_against_oracle("bf16", V, K, 0)
 
 
+# Splits of short bf16 rows that hold fewer than K logits: all of them are listed, wherever the bound comes from, and none of the cells without a chunk
+@pytest.mark.parametrize("V,K,splits", [(100, 64, 2), (70, 33, 4), (1030, 64, 33), (40, 32, 3)])
+def test_bf16_segments_of_fewer_than_k_logits(V, K, splits):
+    rows_against_oracle("bf16", V, K, splits)
+
+
 # Rows whose large logits lie next to each other: likely ids that are neighbours, a stretch of ids that is allowed, ids in order of frequency; few values
 def neighbouring_rows(V, rng):
     rows = {}
