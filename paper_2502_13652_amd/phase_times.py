@@ -4,7 +4,7 @@ per phase boundary of the layer kernel, when the workgroups pass it (microsecond
 workgroup's start), the mean time between boundaries and the timeline of the workgroup that finishes last.
 
     python -m paper_2502_13652_amd.phase_times cfg4 2 --full     # a full layer (beta = 0) of cfg4
-    python -m paper_2502_13652_amd.phase_times cfg3 2            # 16 rows, five workgroups each, all alone on their CUs
+    python -m paper_2502_13652_amd.phase_times cfg3 2            # 16 rows, four workgroups each, all alone on their CUs
     python -m paper_2502_13652_amd.phase_times cfg3 2 --unshared # 16 workgroups, one per row
 """
 import argparse
@@ -17,10 +17,12 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 sys.path.insert(0, _ROOT)
 
+# in the order of the marks' slots; the rows of the histogram path pass those of ROW in that order (the bound's own mark is the two-pass path's)
 MARKS = ["start", "own stream ends", "histogram complete", "sums", "K-th largest known", "cells listed", "cells re-read",
          "top K ranked", "row scored, handed over", "sequence ticket", "sequence pruned",
          "  candidates loaded", "  first pruning done", "  preselected", "  ranked and appended",
          "  (split rows) row merged"]
+ROW = [0, 1, 2, 5, 3, 6, 7, 8]
 
 
 def build():
@@ -81,17 +83,17 @@ def main():
     us = (t - t0) / 100.0
     print("%s layer %d%s: %d rows consumed, %d workgroups with a row (%d per row)" % (a.workload, a.layer, " (full)" if a.full else "", rows, len(us), per_row))
     if per_row > 1:
-        print("(the workgroups that hand a segment's counts over end after 'histogram complete'; 'sums' includes the hand-over)")
+        print("(the workgroups that hand a segment's counts over end after 'histogram complete'; 'cells listed' includes the hand-over)")
     print("%-26s %8s %8s %8s %6s" % ("boundary", "mean us", "min", "max", "n"))
-    for i, nm in enumerate(MARKS):
-        c = us[:, i]
+    for i in ROW + [4] + list(range(9, len(MARKS))):
+        c, nm = us[:, i], MARKS[i]
         if np.all(np.isnan(c)):
             continue
         print("%-26s %8.2f %8.2f %8.2f %6d" % (nm, np.nanmean(c), np.nanmin(c), np.nanmax(c), int(np.sum(~np.isnan(c)))))
-    d = np.diff(us[:, :9], axis=1)   # the row's own boundaries
+    d = np.diff(us[:, [i for i in ROW if not np.all(np.isnan(us[:, i]))]], axis=1)   # the row's own boundaries
     print("mean time between boundaries (start .. handed over):", np.round(np.nanmean(d, axis=0), 2).tolist())
     last = int(np.nanargmax(us[:, 8]))
-    print("workgroup that hands its row over last:", np.round(us[last], 2).tolist())
+    print("workgroup that hands its row over last:", np.round(us[last, ROW + list(range(9, len(MARKS)))], 2).tolist())
     pr = ~np.isnan(us[:, 10])
     if pr.any():
         print("pruning workgroups (%d): handed over -> ticket %.2f us, ticket -> pruned %.2f us (means)"

@@ -171,7 +171,7 @@ def test_equal_logits_of_a_list(B, V):
     x = torch.randn((4, V), generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
     tied = x.clone(); tied[:, 8000:8160] = 24.0              # in 20 chunks: all of them are listed
     t_tied, t_free = layer_times(B, 32, [tied, x], 100)
-    assert t_tied < 1.55 * t_free, (t_tied, t_free)          # (1.42 at most, seen in turns of both)
+    assert t_tied < 1.6 * t_free, (t_tied, t_free)           # (1.38 to 1.50 in a dozen turns of both)
 
 
 # The entropy's M-th largest logit among the first and the last bins of a lane, and past the row's positive values
