@@ -128,7 +128,8 @@ __device__ __forceinline__ int chunk_of_quad_cell(int cell, int j) {
 // ---------------------------------------------------------------------------------------
 
 // Cells whose key reaches tau (exceeds it, if strict) are pushed to cell_list, in any order.
-// Returns how many there are; if that is more than cell_cap the list is incomplete.
+// Returns how many there are; if that is more than cell_cap the list is incomplete.  Ends with a barrier behind the read of the count, which callers
+// set to 0 again: a wavefront that read it late took none of the cells, or the other side of a branch with barriers in it.
 template <int DT, int NT>
 __device__ __forceinline__ int list_cells(int tid, const typename LogitTraits<DT>::key_t* map, int ncells, float tau, bool strict,
                                           int cell_cap, int32_t* cell_list, int32_t* sh_n) {
@@ -144,7 +145,9 @@ __device__ __forceinline__ int list_cells(int tid, const typename LogitTraits<DT
     }
   }
   __syncthreads();
-  return *sh_n;
+  const int n = *sh_n;
+  __syncthreads();
+  return n;
 }
 
 // Re-read the listed cells (CPC chunks each, one chunk per thread) and append their elements that
