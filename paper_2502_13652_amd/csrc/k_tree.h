@@ -701,7 +701,9 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
     }
   }
   __syncthreads();
-  int ns = ps.n_list;
+  // Counts are told to be uniform: the loop that finds the entries' lanes (tshift) is scalar then.  Masked, with more than 256 entries no lane ran it, and
+  // the build for four workgroups a CU, as compiled, copied the thread index behind it before the lanes were switched on again: nothing was kept.
+  int ns = __builtin_amdgcn_readfirstlane(ps.n_list);
   const bool listed_order = !BY_DIGITS && ns <= PRUNE_RANK_MAX;       // list_P, list_H hold the entries' P and H
   if (n_keep > 0 && (BY_DIGITS ? to_digits : !listed_order)) {
     // Radix select on the 64-bit keys, twelve bits a level, from the top: the histogram of the level's digit over
@@ -748,9 +750,9 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
       if (tid == 0) ps.n_red = 0;
       __syncthreads();
       // cut the list down, in place: read, barrier, write
-      const uint64_t cut = (prefix << 12) | (uint64_t)(uint32_t)ps.sel_bin;
-      const int undecided = ps.sel_count;
-      need -= ps.sel_above;
+      const uint64_t cut = (prefix << 12) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(ps.sel_bin);
+      const int undecided = __builtin_amdgcn_readfirstlane(ps.sel_count);
+      need -= __builtin_amdgcn_readfirstlane(ps.sel_above);
       uint64_t rk[PER]; int32_t ri[PER];
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
@@ -768,7 +770,7 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
       }
       for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u;   // for the next level, if there is one
       __syncthreads();
-      ns = ps.n_red;
+      ns = __builtin_amdgcn_readfirstlane(ps.n_red);
       if (undecided <= PRUNE_UNDECIDED_MAX || shift < 12) break;      // (uniform) few enough to rank; or the last whole digit done
       prefix = cut; shift -= 12;
 #pragma unroll

@@ -555,3 +555,16 @@ def test_reranking_time_with_ties():
         took.append(float(np.median(us)))
     print("60 out %.1f us, 161 out %.1f us" % tuple(took), flush=True)
     assert took[0] < 2 * took[1]
+
+
+# Candidates of equal confidence whose rows hold the same few tokens: hundreds of equal keys are left to rank, by one, two or four lanes each
+@pytest.mark.parametrize("B,V,F,K,D", [(20, 34, 32, 33, 2), (20, 33, 17, 31, 2), (20, 60, 32, 33, 2), (20, 100, 32, 33, 2), (20, 65, 32, 64, 2), (9, 33, 64, 32, 3), (20, 33, 16, 32, 2),
+                                       (2, 34, 32, 33, 2)])
+@pytest.mark.parametrize("dtype,M", [("bf16", 0), ("bf16", 37), ("f32", 0)])
+def test_equal_confidences_of_the_same_tokens(B, V, F, K, D, dtype, M):
+    cfg = dict(B=B, V=V, F=F, K=K, D=D, N=512, h=2, beta=0.3, dtype=dtype, entropy_top_m=M)
+    cls = np.zeros((2, 3), np.float32), np.zeros(2, np.float32), np.zeros(2, np.float32), 0.1
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = 2 * torch.randn((D, B, F, V), generator=g, device="cuda")
+    x = torch.nn.functional.pad(x, (0, -V % 8), value=float("inf")).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    run_both(cfg, cls, lambda l: x[l], tag="equal")
