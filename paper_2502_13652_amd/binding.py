@@ -17,7 +17,8 @@ F32, BF16 = 0, 1
 _ERR = {-1: "invalid argument", -2: "unsupported", -3: "workspace", -4: "state", -5: "hip", -6: "out of host memory"}
 
 HIPCC_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
-               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+               "-mllvm", "-amdgpu-kernarg-preload-count=11"]      # the layer kernels' first arguments arrive in registers
 
 
 class C2TError(RuntimeError):

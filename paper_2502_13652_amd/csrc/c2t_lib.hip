@@ -184,7 +184,7 @@ static_assert(4 * hist_lds_of_workgroup(229376 / 16, C2T_MAX_HIDDEN) <= 160 * 10
               "four workgroups a CU");
 // Builds of the histogram kernel, see launch_logits
 enum HistBuild { HB_FOUR_PER_CU, HB_SHARED, HB_SHORT, HB_LONG, HB_LONG_STREAMED, HB_COUNT };
-typedef void (*HistKernel)(const void*, int64_t, int, int, const double*, const float*, TreeState, ScoreParams);
+typedef void (*HistKernel)(const void*, const int32_t*, int64_t, int, int, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, const double*, const float*, TreeState, ScoreParams);
 template <bool TOPM>
 HistKernel hist_kernel(int build) {
   switch (build) {
@@ -266,14 +266,18 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
   const unsigned grid = (unsigned)((int64_t)c.batch * rows_per_seq * per_row);
   ScoreParams sp;
   sp.part = x->part; sp.part_topv = x->part_topv; sp.part_topi = x->part_topi;
-  sp.nsplit = nsplit; sp.rows_per_seq = rows_per_seq; sp.B = c.batch; sp.F = c.max_frontier; sp.K = c.top_k; sp.N = c.budget;
+  sp.nsplit = nsplit; sp.F = c.max_frontier; sp.K = c.top_k; sp.N = c.budget;
   sp.coop = share.n; sp.coop_map_stride = x->lay.coop_map_stride;
   sp.coop_hist = (uint32_t*)(x->ws + x->lay.coop_hist); sp.coop_map = (uint16_t*)(x->ws + x->lay.coop_map);
   sp.coop_acc = (CoopAcc*)(x->ws + x->lay.coop_acc);
   // one round of workgroups (static placement), more of them than CUs, and few enough sequences:
   // deal the live rows round the CUs
-  sp.compact = (rows_per_seq > 1 && (int64_t)grid > (int64_t)x->n_cus && (int64_t)grid <= 4 * (int64_t)x->n_cus &&
-                c.batch <= COMPACT_MAX_B) ? 1 : 0;
+  const bool compact = rows_per_seq > 1 && (int64_t)grid > (int64_t)x->n_cus && (int64_t)grid <= 4 * (int64_t)x->n_cus && c.batch <= COMPACT_MAX_B;
+  const uint32_t shape = (uint32_t)rows_per_seq | (uint32_t)c.max_frontier << 8 | (compact ? SHAPE_COMPACT : 0u);
+  const auto inverse = [](int64_t n) { return n == 1 ? 0u : (uint32_t)((((int64_t)1 << 32) + n - 1) / n); };
+  const uint32_t inv_per_row = inverse(per_row), inv_rows = inverse(rows_per_seq), inv_B = inverse(c.batch);
+  const int32_t* nfs = x->st.nf[x->layer & 1];
+  const int64_t stride_bytes = stride * (c.logits_dtype == C2T_BF16 ? 2 : 4);
   sp.k_inverse = (uint32_t)(((1u << 20) + c.top_k - 1) / c.top_k);
   // The classifier by the whole workgroup where it has its CU to itself: shorter for the row (64 units: 20.1 us a root layer
   // against 20.6, 256 units 26.0 against 27.0), but more instructions in all, which neighbours on the CU pay for: 8192 rows
@@ -304,7 +308,8 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
       if (e != hipSuccess) return e;
       raised = lds;
     }
-    hipExtLaunchKernelGGL(fn, dim3(grid), dim3(HP_NT), lds, s, ev0, ev1, 0, logits, stride, c.vocab, cps, (const double*)x->tab_e, (const float*)x->st.cls, x->st, sp);
+    hipExtLaunchKernelGGL(fn, dim3(grid), dim3(HP_NT), lds, s, ev0, ev1, 0, logits, nfs, stride_bytes, c.vocab, cps, (uint32_t)c.batch, shape, (uint32_t)per_row,
+                          inv_per_row, inv_rows, inv_B, (const double*)x->tab_e, (const float*)x->st.cls, x->st, sp);
   } else {
     const size_t lds_work = (std::max(std::max(generic_lds, score_lds), LIST_BYTES_F32 + SEL_AUX_BYTES) + 15) / 16 * 16;
     sp.lds_bytes = (int)lds_work;
@@ -316,8 +321,8 @@ hipError_t launch_logits(c2t_ctx* x, const void* logits, int64_t stride, int row
       if (e != hipSuccess) return e;
       raised = lds;
     }
-    hipExtLaunchKernelGGL(k_logits_direct<NT_F32>, dim3(grid), dim3(NT_F32), lds, s, ev0, ev1, 0, logits, stride,
-                          c.vocab, cps, (const float*)x->st.cls, x->st, sp);
+    hipExtLaunchKernelGGL(k_logits_direct<NT_F32>, dim3(grid), dim3(NT_F32), lds, s, ev0, ev1, 0, logits, nfs, stride_bytes,
+                          c.vocab, cps, (uint32_t)c.batch, shape, (uint32_t)per_row, inv_per_row, inv_rows, inv_B, (const float*)x->st.cls, x->st, sp);
   }
   return hipGetLastError();
 }

@@ -80,11 +80,11 @@ __device__ __forceinline__ void wait_vector_memory() { asm volatile("s_waitcnt v
 template <int BYTES>
 __device__ __forceinline__ void touch_kernel_arguments() {
   const __attribute__((address_space(4))) char* p = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
-  static_assert(BYTES > 384 && BYTES <= 448, "seven lines");
-  uint32_t a, b, c, d, e, f, g;
-  asm volatile("s_load_dword %0, %7, 0\n s_load_dword %1, %7, 64\n s_load_dword %2, %7, 128\n s_load_dword %3, %7, 192\n"
-               "s_load_dword %4, %7, 256\n s_load_dword %5, %7, 320\n s_load_dword %6, %7, 384\n s_waitcnt lgkmcnt(0)"
-               : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d), "=&s"(e), "=&s"(f), "=&s"(g) : "s"(p));
+  static_assert(BYTES > 448 && BYTES <= 512, "eight lines");
+  uint32_t a, b, c, d, e, f, g, h;
+  asm volatile("s_load_dword %0, %8, 0\n s_load_dword %1, %8, 64\n s_load_dword %2, %8, 128\n s_load_dword %3, %8, 192\n"
+               "s_load_dword %4, %8, 256\n s_load_dword %5, %8, 320\n s_load_dword %6, %8, 384\n s_load_dword %7, %8, 448\n s_waitcnt lgkmcnt(0)"
+               : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d), "=&s"(e), "=&s"(f), "=&s"(g), "=&s"(h) : "s"(p));
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }

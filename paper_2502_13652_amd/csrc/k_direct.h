@@ -289,10 +289,18 @@ __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, i
   return n;
 }
 
+// The table and what the tiles add to: an entry a thread.
+template <int NT>
+__device__ __forceinline__ void start_direct(int tid, DirectShared<NT>& sh) {
+  static_assert(EXP_TAB <= NT - WAVE, "also by the wavefronts that do not look for the row");
+  if (tid < EXP_TAB) sh.exp_tab[tid] = exp_tab_entry(tid);
+  if (tid == 0) { sh.n_list = 0; sh.bad = 0; sh.n_reach = 0; }
+}
+
 // One segment, by a whole workgroup.  The per-wave sums stay in `sh` (see combine_waves).
 template <int NT>
 __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ rowp, int V, int K, const Segment& sg,
-                                                     const SelectLds& sel, const ClassifierStage cst, DirectShared<NT>& sh, RowResult* rr) {
+                                                     const SelectLds& sel, const ClassifierStage cst, DirectShared<NT>& sh, bool started, RowResult* rr) {
   constexpr int TILE = DIRECT_CHUNKS * NT;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wid = tid >> 6;
   const int n_tiles = (sg.ncell + TILE - 1) / TILE, n_whole = sg.tail_chunk >= 0 ? sg.ncell - 1 : sg.ncell;
@@ -308,10 +316,10 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   s.tau = -3.402823466e38f;                                  // the lowest finite value: masked logits (-inf) are not listed
   load(qa, 0);
   if (n_tiles > 1) load(qb, 1);
-  static_assert(EXP_TAB <= NT, "an entry a thread, while the first tiles are on their way");
-  if (tid < EXP_TAB) sh.exp_tab[tid] = exp_tab_entry(tid);
-  if (tid == 0) { sh.n_list = 0; sh.bad = 0; sh.n_reach = 0; }
-  __syncthreads();
+  if (!started) {                                            // (uniform) while the first tiles are on their way
+    start_direct(tid, sh);
+    __syncthreads();
+  }
   for (int t = 0; t < n_tiles; t += 2) {
     if ((t + 1) * TILE > n_whole) blank_tile<NT>(qa, sg, t * TILE);
     direct_tile<NT>(qa, t, sg, V, K, s, sh, sel);
@@ -362,22 +370,38 @@ __device__ __forceinline__ void combine_waves(const DirectShared<NT>& sh, RowRes
 // Dynamic LDS (sp.lds_bytes): the list of the selection, over the cell map of generic_segment (cps keys); reused by the tail.
 template <int NT>
 __global__ __launch_bounds__(NT, 4) void k_logits_direct(
-    const void* __restrict__ logits, int64_t row_stride_elems, int V, int cps, const float* __restrict__ cls,
-    TreeState st, ScoreParams sp) {
+    C2T_START_PARAMETERS, const float* __restrict__ cls, TreeState st, ScoreParams sp) {
   typedef LogitTraits<0> T;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
-  touch_kernel_arguments<32 + (int)sizeof(TreeState) + (int)sizeof(ScoreParams)>();
-  const int nsplit = sp.nsplit, K = sp.K;
-  const int split = blockIdx.x % nsplit;
-  const RowOfWorkgroup rw = row_of_workgroup(st, sp, blockIdx.x / nsplit);
-  const int b = rw.b, f = rw.f, rl = b * sp.rows_per_seq + f, nf = rw.nf;
-  if (f >= nf) { if (nf == 0) end_of_sequence(st, sp, b, f, split); return; }   // uniform for the workgroup
-  const int64_t row = (int64_t)b * sp.F + f;
-  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_elems * 4);
-  const Segment sg = make_segment<T::EPC>(V, split, cps);
   __shared__ RowResult rr;
-  C2T_PT(PT_START);
   __shared__ DirectShared<NT> sh;
+  constexpr int REST = START_BYTES + 8, ARGUMENT_BYTES = REST + (int)sizeof(TreeState) + (int)sizeof(ScoreParams);
+  const uint32_t rows_per_seq = shape & 0xffu, F = (shape >> 8) & 0xffu;
+  const QuotientRemainder wg = divide(blockIdx.x, Division{per_row, inv_per_row});
+  const int split = (int)wg.r;
+  RowOfWorkgroup rw;
+  const bool dealt = (shape & SHAPE_COMPACT) != 0u;          // (uniform)
+  if (dealt) {
+    if (threadIdx.x < WAVE) {
+      rw = dealt_row(nfs, (int)B, (int)wg.q);
+      if (threadIdx.x == 0) { sh.scan_tmp[0][0] = rw.b; sh.scan_tmp[0][1] = rw.f; sh.scan_tmp[0][2] = rw.nf; }
+    } else {
+      touch_kernel_arguments<ARGUMENT_BYTES>();
+      start_direct((int)threadIdx.x - WAVE, sh);
+    }
+    __syncthreads();
+    rw.b = __builtin_amdgcn_readfirstlane(sh.scan_tmp[0][0]); rw.f = __builtin_amdgcn_readfirstlane(sh.scan_tmp[0][1]); rw.nf = __builtin_amdgcn_readfirstlane(sh.scan_tmp[0][2]);
+  } else {
+    rw = row_of_workgroup(nfs, st, sp.layer, B, inv_B, rows_per_seq, inv_rows, wg.q);
+    touch_kernel_arguments<ARGUMENT_BYTES>();
+  }
+  const int nsplit = sp.nsplit, K = sp.K;
+  const int b = rw.b, f = rw.f, rl = b * (int)rows_per_seq + f, nf = rw.nf;
+  if (f >= nf) { if (nf == 0) end_of_sequence(st, sp, b, f, split); return; }   // uniform for the workgroup
+  const int64_t row = (int64_t)b * F + f;
+  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_bytes);
+  const Segment sg = make_segment<T::EPC>(V, split, cps);
+  C2T_PT(PT_START);
   const ClassifierStage cst = stage_classifier((int)threadIdx.x, cls, sp.h, (float*)(dyn_lds + sp.w_lds_off));
   const SelectLds sel = make_select_lds<NT, T::EPC>(dyn_lds, sp.lds_bytes);
   SegmentTop top{RANKED_IN_RR};
@@ -387,7 +411,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
     if (threadIdx.x == 0) { rr.part = empty_partial(); rr.ZM = 0.0; rr.SM = 0.0; }
     __syncthreads();
   } else {
-    top = direct_segment<NT>(rowp, V, K, sg, sel, cst, sh, &rr);
+    top = direct_segment<NT>(rowp, V, K, sg, sel, cst, sh, dealt, &rr);
     have_record = top.n_el < 0;
   }
   const auto top_m = [&](RowResult& r) { top_m_of_whole_row<0, NT>((int)threadIdx.x, rowp, V, sp.M, r, sel); };
@@ -397,7 +421,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
     have_record = true;
     top_m(rr);
   }
-  const TailArguments& ta = tail_arguments<32>();
+  const TailArguments& ta = tail_arguments<REST>();
   finish_layer<NT>((int)threadIdx.x, ta.st, ta.sp, b, f, nf, split, rl, rr, top, sel, sel, dyn_lds, cls, cst.dst,     // split records are indexed by launched row
                    [&] { if (!have_record) combine_waves(sh, rr); }, top_m);
 }

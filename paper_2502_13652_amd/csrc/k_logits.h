@@ -499,9 +499,8 @@ __device__ __forceinline__ void end_of_sequence(const TreeState& st, const Score
 // consecutive sequences: 2 % faster at B = 64 and B = 256 than sequence-major).  In a thinned-out
 // layer the frontiers are of very different lengths (many sequences have used their budget up,
 // others are still full), and a fixed order leaves some CUs with four live rows and others with
-// none: the layer then takes as long as a full one.  With `compact` the workgroup takes the w-th
-// LIVE row in slot-major order instead, which it finds from the frontier sizes alone (every wave
-// by itself: one load per lane and at most launched/64 ballots, no atomics, no barrier): the live
+// none: the layer then takes as long as a full one.  Such launches (SHAPE_COMPACT) deal the rows instead: the workgroup takes the w-th
+// LIVE row in slot-major order, which follows from the frontier sizes alone (no atomics): the live
 // rows are dealt round the CUs, at most one more on one CU than on another.  Workgroups past the
 // live rows take the sequences without a frontier (one each, for the loop guard) or exit.
 struct RowOfWorkgroup { int b, f, nf; };
@@ -512,50 +511,78 @@ __device__ __forceinline__ int nth_set_bit(uint64_t m, int n) {
   const uint64_t hit = __builtin_amdgcn_ballot_w64(((m >> lane) & 1ull) != 0ull && below == n);
   return (int)__builtin_ctzll(hit);
 }
+//
+// Dealt by the first wavefront for its workgroup, while the others clear its counts: lane f forms the set of sequences that have a row in slot f, from
+// ballots over the bits of the frontier sizes; the slot follows from a prefix sum of their numbers.  About a hundred instructions whatever the
+// shape.  (Every wavefront for itself, a scalar loop over the slots with a search in each: the last of 1024 workgroups started 4.8 us after the first,
+// and a layer of 64 sequences that have ended, 1024 workgroups, took 7.1 us.)
 constexpr int COMPACT_MAX_B = 256;            // frontier sizes held by one wave: four per lane
-__device__ __forceinline__ RowOfWorkgroup row_of_workgroup(const TreeState& st, const ScoreParams& sp, int w) {
-  const int* nfs = st.nf[sp.layer & 1];
-  RowOfWorkgroup r;
-  if (sp.compact) {
-    const int lane = lane_id();
-    int nfv[COMPACT_MAX_B / WAVE];
+__device__ __forceinline__ RowOfWorkgroup dealt_row(const int32_t* __restrict__ nfs, int B, int w) {
+  constexpr int NB = COMPACT_MAX_B / WAVE;
+  static_assert(SP_MAX_F == WAVE, "a lane a slot, six bits a slot");
+  const int lane = lane_id();
+  int nfv[NB];
 #pragma unroll
-    for (int k = 0; k < COMPACT_MAX_B / WAVE; ++k) { const int i = lane + k * WAVE; nfv[k] = i < sp.B ? nfs[i] : -1; }
-    int run = 0, b = -1, f = 0, nf = 0;
-    for (int ff = 0; ff < sp.rows_per_seq && b < 0; ++ff) {
-#pragma unroll
-      for (int k = 0; k < COMPACT_MAX_B / WAVE; ++k) {
-        if (k * WAVE >= sp.B) break;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(nfv[k] > ff);
-        const int c = __builtin_popcountll(m);
-        if (b < 0 && w < run + c) {
-          const int bl = nth_set_bit(m, w - run);
-          b = k * WAVE + bl; f = ff; nf = __builtin_amdgcn_readlane(nfv[k], bl);
-        }
-        run += c;
-      }
-    }
-    if (b < 0) {                                          // run = all live rows of the layer
-      int d = w - run;
-#pragma unroll
-      for (int k = 0; k < COMPACT_MAX_B / WAVE; ++k) {
-        if (k * WAVE >= sp.B) break;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(nfv[k] == 0);
-        const int c = __builtin_popcountll(m);
-        if (b < 0 && d >= 0 && d < c) { b = k * WAVE + nth_set_bit(m, d); f = 0; nf = 0; }
-        d -= c;
-      }
-    }
-    if (b < 0) { b = 0; f = 1; nf = 1; }                 // nothing left for this workgroup
-    r.b = __builtin_amdgcn_readfirstlane(b); r.f = __builtin_amdgcn_readfirstlane(f); r.nf = __builtin_amdgcn_readfirstlane(nf);
-    return r;
+  for (int k = 0; k < NB; ++k) {
+    nfv[k] = -1;
+    if (k * WAVE < B) { const int i = lane + k * WAVE, n = nfs[min(i, B - 1)]; nfv[k] = i < B ? n : -1; }
   }
-  const int b_seq = w / sp.rows_per_seq, b_slot = w % sp.B;
-  const int nf_seq = nfs[b_seq], nf_slot = nfs[b_slot];         // both loads issued before the choice: no dependent round trip
-  const bool slot_major = 4 * st.layer_rows[sp.layer] >= 3 * sp.B * sp.rows_per_seq;
-  r.b = slot_major ? b_slot : b_seq;
-  r.f = slot_major ? w / sp.B : w % sp.rows_per_seq;
-  r.nf = __builtin_amdgcn_readfirstlane(slot_major ? nf_slot : nf_seq);   // (loaded by a vector instruction: a spill in the launch that has no register for it)
+  uint64_t in_slot[NB];                                    // lane f: the sequences whose frontier is longer than f
+  int rows = 0;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    in_slot[k] = 0ull;
+    if (k * WAVE < B) {
+      const int last = nfv[k] - 1;                         // its last slot; negative: none
+      uint64_t at_least = ~0ull;                           // the last slot's bits so far are at least f's
+#pragma unroll
+      for (int bit = 0; bit < 6; ++bit) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(((last >> bit) & 1) != 0);
+        at_least = ((lane >> bit) & 1) ? at_least & m : at_least | m;
+      }
+      in_slot[k] = at_least & __builtin_amdgcn_ballot_w64(last >= 0);
+      rows += __builtin_popcountll(in_slot[k]);
+    }
+  }
+  const int incl = wave_scan_incl(rows);
+  const uint64_t here = __builtin_amdgcn_ballot_w64(w < incl);
+  const bool has_row = here != 0ull;                        // (uniform, as all that follows) else a sequence without a frontier, if there are so many
+  const int f = has_row ? (int)__builtin_ctzll(here) : WAVE - 1;
+  int d = w - (__builtin_amdgcn_readlane(incl, f) - (has_row ? __builtin_amdgcn_readlane(rows, f) : 0));
+  RowOfWorkgroup r{0, 1, 1};                               // nothing left for this workgroup
+  bool found = false;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    if (k * WAVE < B && !found) {
+      const uint64_t m = has_row ? (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)in_slot[k], f) |
+                                   (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(in_slot[k] >> 32), f) << 32
+                                 : __builtin_amdgcn_ballot_w64(nfv[k] == 0);
+      const int c = __builtin_popcountll(m);
+      if (d < c) {
+        const int bl = nth_set_bit(m, d);
+        r.b = k * WAVE + bl; r.f = has_row ? f : 0; r.nf = __builtin_amdgcn_readlane(nfv[k], bl);
+        found = true;
+      }
+      d -= c;
+    }
+  }
+  return r;
+}
+// Rows in a fixed order.  What bounds the start of a layer is a chain of round trips ahead of the first logit: with the start's arguments in registers, the frontier size
+// requested at once and the first logits before the counts are cleared, phases of one sequence took 96.0 -> 89.2 us (32000, bf16, eight layers), 120.8 -> 113.1
+// (128256), 83.8 -> 80.2 (32000, fp32), 1024 chains 181.2 -> 177.1, 256 sequences of 152064 1782 -> 1762; with the rows dealt by one wavefront 64 sequences
+// of 128256 260.8 -> 259.2, 32 with 1000 top logits 178.8 -> 176.0.
+__device__ __forceinline__ RowOfWorkgroup row_of_workgroup(const int32_t* __restrict__ nfs, const TreeState& st, int layer, uint32_t B, uint32_t inv_B, uint32_t rows_per_seq,
+                                                           uint32_t inv_rows, uint32_t w) {
+  const QuotientRemainder by_seq = divide(w, Division{rows_per_seq, inv_rows});
+  RowOfWorkgroup r{(int)by_seq.q, (int)by_seq.r, 0};
+  if (B == 1u || rows_per_seq == 1u) { r.nf = nfs[r.b]; return r; }                      // both orders are the same
+  const QuotientRemainder by_slot = divide(w, Division{B, inv_B});
+  int nf_seq = nfs[by_seq.q], nf_slot = nfs[by_slot.r], live = st.layer_rows[layer];     // all loads issued before the choice: no dependent round trip
+  asm volatile("" : "+s"(nf_seq), "+s"(nf_slot));                       // (nor one load from a chosen address)
+  const bool slot_major = 4u * (uint32_t)__builtin_amdgcn_readfirstlane(live) >= 3u * B * rows_per_seq;
+  if (slot_major) { r.b = (int)by_slot.r; r.f = (int)by_slot.q; }
+  r.nf = slot_major ? nf_slot : nf_seq;
   return r;
 }
 
@@ -1193,6 +1220,16 @@ __device__ __forceinline__ bool share_row(int tid, const ScoreParams& sp, int sp
   return true;                                                          // the caller's next barrier publishes map and sh_out
 }
 
+// The histogram copies and what else the streaming loop adds to, by THREADS threads.
+template <int THREADS, int REPL, int NT>
+__device__ __forceinline__ void clear_counts(int tid, uint32_t* __restrict__ hist, HistShared<NT>& hs) {
+#pragma unroll
+  for (int j = 0; j < HP_WORDS * REPL / 4; j += THREADS)
+    if (HP_WORDS * REPL / 4 % THREADS == 0 || tid + j < HP_WORDS * REPL / 4) *(uint4*)(hist + 4 * (tid + j)) = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) { hs.n_cells = 0; hs.n_el = 0; hs.out.s_tiny = 0.0; hs.out.n_tiny = 0; hs.out.n_masked = 0; hs.out.mag_max = 0u; }
+  if (tid < WAVE) hs.out.masked_by_lane[tid] = 0u;
+}
+
 // One (row, split) segment on the histogram path, run by a whole workgroup of NT threads.
 // hist: HP_WORDS words a copy, then the columns and, in their place, the element list, and the map, one 2-byte key per cell, padded to 16 bytes
 // (hist_lds_bytes); sel: see SelectLds.
@@ -1205,18 +1242,12 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
                                              const double* __restrict__ tab_e, uint32_t* __restrict__ hist, const SelectLds& list, uint16_t* map,
                                              const SelectLds& sel, RowResult* rr, HistShared<NT>& hs,
                                              const ClassifierStage cst, const float* __restrict__ cls, const TreeState& st, const ScoreParams& sp, int split,
-                                             int64_t row_launched, int64_t slot, int& tid) {
+                                             int64_t row_launched, int64_t slot, bool cleared, int& tid) {
   constexpr int NW = NT / WAVE;
   constexpr int WPL = HP_WORDS / NT;                   // words per lane in the epilogue (8 at 512 threads)
   static_assert(NW <= 16 && WPL % 4 == 0, "one DPP row holds the per-wave partials; a lane reads whole 16-byte runs");
   const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   Segment sg = sg_own;                                   // what the workgroup streams; the whole row once a shared row's counts are merged
-
-#pragma unroll
-  for (int j = 0; j < WPL * REPL / 4; ++j) *(uint4*)(hist + 4 * (tid + j * NT)) = make_uint4(0u, 0u, 0u, 0u);
-  if (tid == 0) { hs.n_cells = 0; hs.n_el = 0; hs.out.s_tiny = 0.0; hs.out.n_tiny = 0; hs.out.n_masked = 0; hs.out.mag_max = 0u; }
-  if (tid < WAVE) hs.out.masked_by_lane[tid] = 0u;
-  __syncthreads();
 
   // ---------------- streaming loop: count values, record cell maxima ----------------
   uint32_t vo_after;
@@ -1246,6 +1277,10 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     uint4 q[DEPTH];
 #pragma unroll
     for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<STREAMED>(in.rs, in.vo, (uint32_t)k * (NT * 16u));
+    if (!cleared) {                                      // (uniform) while they are on their way
+      clear_counts<NT, REPL>(tid, hist, hs);
+      __syncthreads();
+    }
     // Streaming waves issue ahead of the waves of co-resident workgroups that are in their
     // (latency-bound) epilogue or tail: the memory pipeline stays fed.  Measured: 3 % per full layer.
     __builtin_amdgcn_s_setprio(3);
@@ -1578,20 +1613,36 @@ __device__ __forceinline__ void combine_hist(const HistShared<NT>& hs, int M, Ro
 // 6 = three workgroups per CU on 80 registers, which needs no spills.
 template <int NT, bool TOPM, int WPS, int REPL, bool COOP, bool STREAMED>
 __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
-    const void* __restrict__ logits, int64_t row_stride_elems, int V, int cps, const double* __restrict__ tab_e,
-    const float* __restrict__ cls, TreeState st, ScoreParams sp) {
+    C2T_START_PARAMETERS, const double* __restrict__ tab_e, const float* __restrict__ cls, TreeState st, ScoreParams sp) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
-  touch_kernel_arguments<40 + (int)sizeof(TreeState) + (int)sizeof(ScoreParams)>();
-  const int nsplit = (COOP && sp.coop > 1) ? sp.coop : sp.nsplit, K = sp.K;     // workgroups per row, either way
-  const int split = blockIdx.x % nsplit;
-  const RowOfWorkgroup rw = row_of_workgroup(st, sp, blockIdx.x / nsplit);
-  const int b = rw.b, f = rw.f, rl = b * sp.rows_per_seq + f, nf = rw.nf;
-  if (f >= nf) { if (nf == 0) end_of_sequence(st, sp, b, f, split); return; }   // uniform for the workgroup
-  const int64_t row = (int64_t)b * sp.F + f;
-  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_elems * 2);
-  const Segment sg = make_segment<8>(V, split, cps);
   __shared__ RowResult rr;
   __shared__ HistShared<NT> hs;
+  constexpr int REST = START_BYTES + 16;
+  const uint32_t rows_per_seq = shape & 0xffu, F = (shape >> 8) & 0xffu;
+  const QuotientRemainder wg = divide(blockIdx.x, Division{per_row, inv_per_row});     // per_row workgroups a row: splits of it, or those that share it
+  const int split = (int)wg.r;
+  const bool dealt = WPS == 8 && (shape & SHAPE_COMPACT) != 0u;                          // (uniform)
+  RowOfWorkgroup rw;
+  constexpr int ARGUMENT_BYTES = REST + (int)sizeof(TreeState) + (int)sizeof(ScoreParams);
+  if (dealt) {
+    if (threadIdx.x < WAVE) {
+      rw = dealt_row(nfs, (int)B, (int)wg.q);
+      if (threadIdx.x == 0) { hs.kth[0] = rw.b; hs.kth[1] = rw.f; hs.kth[2] = rw.nf; }
+    } else {
+      touch_kernel_arguments<ARGUMENT_BYTES>();
+      clear_counts<NT - WAVE, REPL>((int)threadIdx.x - WAVE, (uint32_t*)dyn_lds, hs);
+    }
+    __syncthreads();
+    rw.b = __builtin_amdgcn_readfirstlane(hs.kth[0]); rw.f = __builtin_amdgcn_readfirstlane(hs.kth[1]); rw.nf = __builtin_amdgcn_readfirstlane(hs.kth[2]);
+  } else {
+    rw = row_of_workgroup(nfs, st, sp.layer, B, inv_B, rows_per_seq, inv_rows, wg.q);
+    touch_kernel_arguments<ARGUMENT_BYTES>();
+  }
+  const int K = sp.K, b = rw.b, f = rw.f, rl = b * (int)rows_per_seq + f, nf = rw.nf;
+  if (f >= nf) { if (nf == 0) end_of_sequence(st, sp, b, f, split); return; }   // uniform for the workgroup
+  const int64_t row = (int64_t)b * F + f;
+  const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_bytes);
+  const Segment sg = make_segment<8>(V, split, cps);
   C2T_PT(PT_START);
   // The classifier's parameters (5h+1 <= 1281 floats) are copied to LDS for the scoring step: the
   // loads are issued now, four floats a thread, and stored behind the streaming loop.
@@ -1605,10 +1656,10 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     __syncthreads();
   } else {
     top = hist_segment<NT, TOPM, WPS, REPL, COOP, STREAMED>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, list,
-                                                  (uint16_t*)(dyn_lds + hist_lds_bytes<NT>(REPL)), sel, &rr, hs, cst, cls, st, sp, split, rl, row, tid);
+                                                  (uint16_t*)(dyn_lds + hist_lds_bytes<NT>(REPL)), sel, &rr, hs, cst, cls, st, sp, split, rl, row, dealt, tid);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
-  const TailArguments& ta = tail_arguments<40>();
+  const TailArguments& ta = tail_arguments<REST>();
   finish_layer<NT>(tid, ta.st, ta.sp, b, f, nf, split, rl, rr, top, list, sel, dyn_lds, cls, cst.dst,
                    [&] { if (top.n_el >= 0) combine_hist<NT, TOPM>(hs, sp.M, rr); },
                    [&](RowResult& r) { if (TOPM) top_m_of_whole_row<1, NT>(tid, rowp, V, sp.M, r, sel); });

@@ -244,11 +244,10 @@ struct __attribute__((aligned(32))) CoopAcc {
 
 struct ScoreParams {
   RowPartial* part; float* part_topv; int32_t* part_topi;    // [launched row][split] records and their top-K lists
-  int nsplit, rows_per_seq, B, F, K, N, h, layer, D;
+  int nsplit, F, K, N, h, layer, D;
   int M;                                                     // 0: entropy over the whole row; M > 0: over the M largest logits
   int lds_bytes;                                             // dynamic LDS of the launch
   int w_lds_off;                                             // byte offset of the classifier's copy in dynamic LDS
-  int compact;                                               // 1: workgroup w takes the w-th live row (see row_of_workgroup)
   uint32_t k_inverse;                                        // ceil(2^20 / K): (i * k_inverse) >> 20 is i / K for i < 2048, K <= 64
   int spread_min;                                            // hidden units from which on the whole workgroup evaluates the classifier
   float z_beta;
@@ -261,6 +260,23 @@ struct ScoreParams {
                                                              // them [launched row][coop][WAVE] uint32: the segments' columns
   CoopAcc* coop_acc;                                         // [launched row][coop]
 };
+
+// What a workgroup needs to find its row and to request its first logits: the layer kernels' first arguments, which the compiler has the dispatcher
+// put into scalar registers ahead of the wavefront's first instruction (kernel argument preload, at most fourteen registers; the build's
+// flags ask for it).  Loaded, they cost a first touch of the arguments, a dependent one and two divisions of some twenty instructions before the frontier size was even requested.
+struct Division { uint32_t n, inverse; };                    // inverse: ceil(2^32 / n), 0 for n = 1
+struct QuotientRemainder { uint32_t q, r; };
+__device__ __forceinline__ QuotientRemainder divide(uint32_t x, const Division& d) {
+  uint32_t q = d.inverse ? __umulhi(x, d.inverse) : x;       // at most one too many
+  uint32_t r = x - q * d.n;
+  if ((int32_t)r < 0) { q -= 1; r += d.n; }                  // (divisors and what is divided stay below 2^31)
+  return QuotientRemainder{q, r};
+}
+// shape: rows launched per sequence, F << 8, 1 << 16: workgroup w takes the w-th live row (see row_of_workgroup)
+constexpr uint32_t SHAPE_COMPACT = 1u << 16;
+#define C2T_START_PARAMETERS const void* __restrict__ logits, const int32_t* __restrict__ nfs, int64_t row_stride_bytes, int V, int cps, uint32_t B, uint32_t shape, \
+                             uint32_t per_row, uint32_t inv_per_row, uint32_t inv_rows, uint32_t inv_B
+constexpr int START_BYTES = 56, START_ARGUMENTS = 11;
 
 // The last two arguments of the layer kernels, at byte OFFSET of the argument segment, read again for the tail: the compiler loads what it
 // can reach early and keeps it in scalar registers through the streaming loop, or, there being too few, in lanes of vector registers.

@@ -338,6 +338,21 @@ def test_sequence_step_at_its_edges(F, K, h, N, dtype):
     assert total > 0
 
 
+# live rows dealt round the CUs (more workgroups than CUs, one round): a lane a slot to the largest frontier, sets of sequences in one to four ballots, frontiers
+# of any length between none and full (confidence = the path's probability, thresholds across what the layers hold); and the fixed orders beyond
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,F,K", [(5, 64, 8), (17, 60, 2), (63, 16, 4), (64, 16, 4), (65, 15, 4), (129, 7, 4), (255, 4, 4), (256, 4, 4), (300, 3, 4), (70, 33, 2)])
+def test_ragged_frontiers_dealt_to_workgroups(B, F, K, dtype):
+    lengths = set()
+    for beta in (0.02, 0.2):
+        cfg = _cfg(B=B, F=F, K=K, h=2, N=3 * F, D=5, V=520, dtype=dtype, beta=beta)
+        W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+        cls = (W1, np.zeros(2, np.float32), np.array([8, 0], np.float32), -4.0)          # C = sigmoid(8 P - 4)
+        go, oo, _ = run_both(cfg, cls, _layers(cfg), tag="B=%d F=%d beta %g" % (B, F, beta))
+        lengths |= set(go["n_nodes"].tolist())
+    assert len(lengths) > 2
+
+
 # more than 64 survivors in one candidate a thread, of which 1 to 16 are kept: the bound from sorted maxima, and the ballots beyond
 @pytest.mark.parametrize("F,K,N", [(2, 50, 12), (3, 64, 7), (15, 30, 50), (16, 31, 60), (17, 30, 60)])
 def test_sequence_step_where_the_bound_changes(F, K, N):
