@@ -965,18 +965,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_buffer(uint64_t base, 
   return __builtin_amdgcn_make_buffer_rsrc((void*)base_u, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
-// The loop of a row that masks part of its vocabulary.  Out of line, so that rows that mask nothing keep their registers.
-// A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 41 us when every chunk took hist_chunk_outside, 30.
+// The loop of a row that masks part of its vocabulary, from its first chunk on again: in line, with the eight chunks in flight of the usual loop the build has too few registers.
+// A layer of 256 rows of 128256 logits, alone on their CUs, with 30 % masked: 41 us when every chunk took hist_chunk_outside, 30; a phase of 16 sequences, 16 rows each,
+// 167.0 us with this loop out of line, where it fetched its uniform arguments from vector registers, 162.3 so.
 template <int NT, bool STREAMED>
-__device__ __noinline__ uint32_t hist_stream_masked(uint64_t base, int whole_chunks, int tail_valid, uint32_t vo, uint32_t hist, LdsHalves keys, OutsideAcc* acc) {
+__device__ __forceinline__ uint32_t hist_stream_masked(const StreamInput& in) {
   constexpr int DEPTH = 4;
-  const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
-  StreamInput in;
-  in.whole = uniform(whole_chunks); in.tail_valid = uniform(tail_valid); in.vo = vo; in.hist = hist; in.keys = keys; in.acc = acc;
-  in.rs = uniform_buffer(base, (in.whole + (in.tail_valid > 0 ? 1 : 0)) * 16);
   uint4 q[DEPTH];
 #pragma unroll
-  for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<STREAMED>(in.rs, vo, (uint32_t)k * (NT * 16u));
+  for (int k = 0; k < DEPTH; ++k) q[k] = load_stream_buffer<STREAMED>(in.rs, in.vo, (uint32_t)k * (NT * 16u));
   return hist_stream<NT, DEPTH, true, false, STREAMED>(in, q);
 }
 
@@ -1302,15 +1299,10 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       masks = __builtin_amdgcn_readfirstlane(2 * n >= DEPTH ? 1 : 0);      // (a scalar branch: as a lane mask both sides' registers would be live at once)
     }
     vo_after = in.vo;
-    if (masks != 0) {                                    // (nothing of this path is live across the call: what is would be spilled for every row)
-      M2 = hist_stream_masked<NT, STREAMED>(base, in.whole, in.tail_valid, in.vo, in.hist, in.keys, &hs.out);
-      C2T_PT(PT_STREAM_END);
-      store_classifier(tid, stage_classifier(tid, cls, sp.h, cst.dst));
-    } else {
-      M2 = hist_stream<NT, DEPTH, false, REPL == 1, STREAMED>(in, q);
-      C2T_PT(PT_STREAM_END);
-      store_classifier(tid, cst);                               // published by the barriers below
-    }
+    if (masks != 0) M2 = hist_stream_masked<NT, STREAMED>(in);
+    else M2 = hist_stream<NT, DEPTH, false, REPL == 1, STREAMED>(in, q);
+    C2T_PT(PT_STREAM_END);
+    store_classifier(tid, cst);                                 // published by the barriers below
   }
   // The thread index should not be kept in a register through the loop on top of the lane's
   // buffer offset: a spill that crosses the loop is reloaded behind all the logits in flight on the
