@@ -339,7 +339,7 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   int n_el = sh.n_list;
   if (__builtin_expect(n_el > 2 * WAVE || n_el < K, 0)) n_el = settle_list<NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, (DirectSharedLds<NT>)&sh);
   if (__builtin_expect(n_el == UNSETTLED, 0)) generic_segment<0, NT>((int)threadIdx.x, rowp, V, K, 0, sg, sel.list, sel, rr, 0u);   // (its cell map overlays the list)
-  return SegmentTop{n_el};
+  return SegmentTop{n_el, false};
 }
 // The segment's record from the wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.
 template <int NT>
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
   C2T_PT(PT_START);
   const ClassifierStage cst = stage_classifier((int)threadIdx.x, cls, sp.h, (float*)(dyn_lds + sp.w_lds_off));
   const SelectLds sel = make_select_lds<NT, T::EPC>(dyn_lds, sp.lds_bytes);
-  SegmentTop top{RANKED_IN_RR};
+  SegmentTop top{RANKED_IN_RR, false};
   bool have_record = true;                                 // (uniform) rr.part is complete
   if (sg.ncell == 0) {
     store_classifier((int)threadIdx.x, cst);

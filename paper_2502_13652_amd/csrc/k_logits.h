@@ -1007,6 +1007,7 @@ struct HistShared {
   uint32_t red_m[NW];               // their largest patterns
   int32_t total[NW], scan_p[NW], scan_n[NW];
   OutsideAcc out;
+  double e_minus_m;                 // e^-m (without TOPM)
   float m;                          // largest logit of the row
   int32_t n_cells, n_el, tot_p;
   int32_t kth[3];                   // KthOfCounts: rank, n_gt, n_ge
@@ -1108,6 +1109,36 @@ __device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp,
   const int n = hs.n_el, need = want - n;                      // (need > 0 only where it is strict)
   if (need > 0) tie_scan<1, NT>(tid, rowp, sg, V, tau, need, list, &hs.n_el, scan_tmp);
   return need > 0 ? want : n;
+}
+
+// The record of a row (or split) from its wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.  To rr, and in lane 0 returned.
+template <int NT, bool TOPM>
+__device__ __forceinline__ RowPartial combine_hist(const HistShared<NT>& hs, int M, RowResult& rr) {
+  constexpr int NW = NT / WAVE;
+  static_assert(NW <= 16, "one DPP row holds the per-wave sums");
+  const int lane = lane_id(), n_tiny = hs.out.n_tiny;
+  const double md = (double)hs.m;
+  const auto sum = [&](const double (&red)[2][NW], bool with_tiny, double& z, double& s) {
+    double tz = lane < NW ? red[0][lane] : 0.0, ts = lane < NW ? red[1][lane] : 0.0;
+    tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
+    tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
+    tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
+    if (NW > 8) { tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts); }
+    if (with_tiny && n_tiny) {                          // e^x = 1 + x, x e^x = x for |x| < 2^-25
+      const double zt = (double)n_tiny + hs.out.s_tiny;
+      tz += zt; ts += hs.out.s_tiny - md * zt;
+    }
+    z = tz; s = ts;
+  };
+  double Z, S, ZM = 0.0, SM = 0.0;
+  sum(hs.red_d, true, Z, S);
+  if (TOPM) sum(hs.red_m_d, hs.tot_p < M, ZM, SM);       // (where the tiny ones are among the M largest, all of them are)
+  RowPartial r; r.ref = md; r.a = 0.0; r.Z = Z; r.S = S; r.n_top = 0; r.flags = 0u;
+  if (lane == 0) {
+    rr.part = r;
+    if (TOPM) { rr.ZM = ZM; rr.SM = SM; }
+  }
+  return r;
 }
 
 // A row shared by sp.coop workgroups (launches that leave most of the chip idle: a single sequence,
@@ -1238,8 +1269,8 @@ template <int NT, bool TOPM, int WPS, int REPL, bool COOP, bool STREAMED>
 __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ rowp, int V, int K, int M, const Segment& sg_own,
                                              const double* __restrict__ tab_e, uint32_t* __restrict__ hist, const SelectLds& list, uint16_t* map,
                                              const SelectLds& sel, RowResult* rr, HistShared<NT>& hs,
-                                             const ClassifierStage cst, const float* __restrict__ cls, const TreeState& st, const ScoreParams& sp, int split,
-                                             int64_t row_launched, int64_t slot, bool cleared, int& tid) {
+                                             const ClassifierStage cst, const TreeState& st, const ScoreParams& sp, int split,
+                                             int64_t row_launched, int b, int64_t slot, bool cleared, int& tid) {
   constexpr int NW = NT / WAVE;
   constexpr int WPL = HP_WORDS / NT;                   // words per lane in the epilogue (8 at 512 threads)
   static_assert(NW <= 16 && WPL % 4 == 0, "one DPP row holds the per-wave partials; a lane reads whole 16-byte runs");
@@ -1351,11 +1382,12 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
 #pragma unroll
   for (int w = 0; w < NW; ++w) column = pk_max_f16_raw(column, columns[w * WAVE + lane]);
   if (shared_row) {
-    if (!share_row<NT>(tid, sp, split, row_launched, st.row_tickets + slot, sg, hist, w0, map, &hs.out, column, m2)) return SegmentTop{HANDED_OVER};
+    if (!share_row<NT>(tid, sp, split, row_launched, st.row_tickets + slot, sg, hist, w0, map, &hs.out, column, m2)) return SegmentTop{HANDED_OVER, false};
     sg = make_segment<8>(V, 0, (V + 7) / 8);             // the epilogue below is the whole row's
     ef = load_exp_factors(tab_e, tid);
     __syncthreads();                                     // the row's map
   }
+  if (!TOPM && wid == NW - 1 && sp.nsplit == 1) request_parent(st, b, slot, *rr);
   float tau;
   if (__builtin_expect(K > COLUMNS_MAX_K, 0)) {
     tau = bound_of_counts(kth_of_counts<NT>(tid, (LdsWords)hist, K, (HistSharedLds<NT>)&hs));
@@ -1470,6 +1502,11 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   }
   const int total = counts ? wave_sum_i(lane_pos + lane_neg) : 0;
   C2T_PT(PT_SUMS);
+  // e^-m for the entropy, which would have to wait for it: by a wavefront of magnitudes below 2^-17, which has hardly a count ever, while the cells are on their way
+  if (!TOPM && wid == 1) {
+    const double e = exp(-md);
+    if (lane == 0) hs.e_minus_m = e;
+  }
   // ---------------- their logits that reach the bound ----------------
   {
     if (WPS == 8) { wait_vector_memory(); cell_q = *(const uint4*)((unsigned char*)map + tid * 16); }
@@ -1501,6 +1538,14 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   __syncthreads();                                       // sums and list complete
   C2T_PT(PT_CELLS_READ);
 
+  // The last wavefront forms the entropy at once, ahead of the look at the row's rarer cases and while the others rank the list (a row that leaves
+  // this path has its record made again).  Its logarithm and division are 0.6 us, which the ranking hides then: phases of one sequence of 32000 86.4 -> 84.3 us,
+  // of 128256 111.5 -> 109.9, 32 of 32000 reranked 109.6 -> 107.8, 1024 chains 175.2 -> 174.2 (with the parent's values and e^-m requested or formed here it was 0.8 us and a
+  // round trip behind the ranking).
+  if (!TOPM && wid == NW - 1 && sp.nsplit == 1) {
+    const RowPartial r = combine_hist<NT, false>(hs, 0, *rr);
+    row_entropy(0, r.ref, hs.e_minus_m, r.Z, r.S, r.flags, *rr);
+  }
   int counted = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) counted += hs.total[w];
@@ -1565,38 +1610,9 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   if (__builtin_expect(leave, 0)) {
     __syncthreads();
     generic_segment<1, NT>(tid, rowp, V, K, M, sg, (unsigned char*)hist, sel, rr, 2u);
-    return SegmentTop{RANKED_IN_RR};
+    return SegmentTop{RANKED_IN_RR, false};
   }
-  return SegmentTop{n_el};
-}
-
-// The record of a row (or split) from its wavefronts' sums: lanes 0 .. NW-1 of one wavefront, fixed order.
-template <int NT, bool TOPM>
-__device__ __forceinline__ void combine_hist(const HistShared<NT>& hs, int M, RowResult& rr) {
-  constexpr int NW = NT / WAVE;
-  static_assert(NW <= 16, "one DPP row holds the per-wave sums");
-  const int lane = lane_id(), n_tiny = hs.out.n_tiny;
-  const double md = (double)hs.m;
-  const auto sum = [&](const double (&red)[2][NW], bool with_tiny, double& z, double& s) {
-    double tz = lane < NW ? red[0][lane] : 0.0, ts = lane < NW ? red[1][lane] : 0.0;
-    tz += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR1, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(tz); ts += dpp_f64<C2T_DPP_QUAD_XOR2, 0xf>(ts);
-    tz += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_HALF_MIRROR, 0xf>(ts);
-    if (NW > 8) { tz += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(tz); ts += dpp_f64<C2T_DPP_ROW_MIRROR, 0xf>(ts); }
-    if (with_tiny && n_tiny) {                          // e^x = 1 + x, x e^x = x for |x| < 2^-25
-      const double zt = (double)n_tiny + hs.out.s_tiny;
-      tz += zt; ts += hs.out.s_tiny - md * zt;
-    }
-    z = tz; s = ts;
-  };
-  double Z, S, ZM = 0.0, SM = 0.0;
-  sum(hs.red_d, true, Z, S);
-  if (TOPM) sum(hs.red_m_d, hs.tot_p < M, ZM, SM);       // (where the tiny ones are among the M largest, all of them are)
-  if (lane == 0) {
-    RowPartial r; r.ref = md; r.a = 0.0; r.Z = Z; r.S = S; r.n_top = 0; r.flags = 0u;
-    rr.part = r;
-    if (TOPM) { rr.ZM = ZM; rr.SM = SM; }
-  }
+  return SegmentTop{n_el, !TOPM && sp.nsplit == 1};
 }
 
 // grid: rows_launched * nsplit workgroups of NT threads.
@@ -1640,7 +1656,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
   // loads are issued now, four floats a thread, and stored behind the streaming loop.
   const ClassifierStage cst = stage_classifier(threadIdx.x, cls, sp.h, TOPM ? nullptr : (float*)(dyn_lds + sp.w_lds_off));
   const SelectLds sel = make_select_lds<NT, 8>(dyn_lds, sp.lds_bytes), list = hist_list(dyn_lds + HP_WORDS * 4 * REPL);
-  SegmentTop top{RANKED_IN_RR};
+  SegmentTop top{RANKED_IN_RR, false};
   int tid = threadIdx.x;
   if (sg.ncell == 0) {                                     // (loaded again here: the copy above must not stay in registers for this)
     store_classifier(tid, stage_classifier(tid, cls, sp.h, cst.dst));
@@ -1648,7 +1664,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
     __syncthreads();
   } else {
     top = hist_segment<NT, TOPM, WPS, REPL, COOP, STREAMED>(rowp, V, K, TOPM ? sp.M : 0, sg, tab_e, (uint32_t*)dyn_lds, list,
-                                                  (uint16_t*)(dyn_lds + hist_lds_bytes<NT>(REPL)), sel, &rr, hs, cst, cls, st, sp, split, rl, row, dealt, tid);
+                                                  (uint16_t*)(dyn_lds + hist_lds_bytes<NT>(REPL)), sel, &rr, hs, cst, st, sp, split, rl, b, row, dealt, tid);
     if (COOP && top.n_el == HANDED_OVER) { C2T_PT_FLUSH(); return; }   // a shared row's segment, handed over
   }
   const TailArguments& ta = tail_arguments<REST>();

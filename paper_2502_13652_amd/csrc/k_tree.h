@@ -298,8 +298,7 @@ struct RowResult {
   double Zr;          // sum of e^(x - R) over the row, R = part.ref
   float H;            // entropy of the row
   uint32_t bad;       // no candidate comes from this row
-  float parent_P, parent_s; int32_t parent_hidx, parent_node;   // of the row's frontier node
-  int32_t n_nodes;    // of the sequence's tree before this layer
+  struct { float P; int32_t node, n_nodes, hidx; float s; } parent;   // of the row's frontier node, and nodes of the sequence's tree before this layer; hidx, s: rerank contexts only
   float topv[64];
   int32_t topi[64];
 };
@@ -384,24 +383,44 @@ __device__ __forceinline__ void rank_list(int tid, int K, const SelectLds& sel, 
   }
 }
 
-// ---- row level: entropy (Eq. 2) from the row's sums, and what the row's frontier node hands down; by one wavefront.
+// What the row's frontier node hands down, from global memory to rr.
+// Straight to LDS, without registers meanwhile: requested by the last wavefront of an unsplit row on the histogram path ahead of the cells, and waited for behind the
+// entropy.  (Requested where the entropy is formed, its round trip was the row's critical path.)
+__device__ __forceinline__ void request_parent(const TreeState& s, int b, int64_t slot, RowResult& rr) {
+  const int lane = lane_id();
+  const void* from = s.fr_P + slot;
+  if (lane == 1) from = s.fr_node + slot;
+  if (lane == 2) from = s.n_nodes + b;
+  if (lane == 3) from = s.fr_hidx + slot;
+  if (lane == 4) from = s.fr_s + slot;
+  if (lane < (s.h_tok ? 5 : 3))
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from, (__attribute__((address_space(3))) void*)&rr.parent, 4, 0, 0);
+}
+// The same where nothing is there to hide it, beside the entropy.
+struct ParentStage { float P, s; int32_t hidx, node, n_nodes; };
+__device__ __forceinline__ ParentStage load_parent(const TreeState& s, int b, int64_t slot) {
+  ParentStage p{s.fr_P[slot], INFINITY, -1, s.fr_node[slot], s.n_nodes[b]};
+  if (s.h_tok) { p.hidx = s.fr_hidx[slot]; p.s = s.fr_s[slot]; }
+  return p;
+}
+__device__ __forceinline__ void store_parent(const ParentStage& p, RowResult& rr) {
+  if (lane_id() == 0) { rr.parent.P = p.P; rr.parent.s = p.s; rr.parent.hidx = p.hidx; rr.parent.node = p.node; rr.parent.n_nodes = p.n_nodes; }
+}
+
+// ---- row level: entropy (Eq. 2) from the row's sums; by one wavefront.
 // Re-references the sums from the offset a to the row maximum R: p_j = e^(x_j - R) / Zr, H = -sum p ln p = ln Zr - Sr / Zr.
-__device__ __forceinline__ void row_entropy(const TreeState& s, const ScoreParams& sp, int b, int64_t slot, double R, double a, double Z, double S,
-                                            uint32_t flags, RowResult& rr) {
-  const float pp = s.fr_P[slot];
-  const int node = s.fr_node[slot], nn = s.n_nodes[b];
-  int hidx = -1; float ps = INFINITY;
-  if (s.h_tok) { hidx = s.fr_hidx[slot]; ps = s.fr_s[slot]; }
+// M: 0, or the number of logits that the sums ZM, SM in rr are restricted to; sc: e^(a - R)
+__device__ __forceinline__ void row_entropy(int M, double R, double sc, double Z, double S, uint32_t flags, RowResult& rr) {
   const bool bad = (flags & 1u) != 0 || !(Z > 0.0) || !(R > -INFINITY) || !(R < INFINITY);
-  const double sc = a == R ? 1.0 : exp(a - R);
   const double Zr = Z * sc, Sr = S * sc;
   // Eq. 2, second line: -sum over the M most probable tokens of p ln p, p from the full softmax:
   // (ln Zr * ZMr - SMr) / Zr with the sums restricted to those tokens
-  const float H = bad ? 0.f : sp.M > 0 ? (float)((log(Zr) * (rr.ZM * sc) - rr.SM * sc) / Zr) : (float)(log(Zr) - Sr / Zr);
-  if (lane_id() == 0) {
-    rr.Zr = Zr; rr.H = H; rr.bad = bad ? 1u : 0u;
-    rr.parent_P = pp; rr.parent_s = ps; rr.parent_hidx = hidx; rr.parent_node = node; rr.n_nodes = nn;
-  }
+  const float H = bad ? 0.f : M > 0 ? (float)((log(Zr) * (rr.ZM * sc) - rr.SM * sc) / Zr) : (float)(log(Zr) - Sr / Zr);
+  if (lane_id() == 0) { rr.Zr = Zr; rr.H = H; rr.bad = bad ? 1u : 0u; }
+}
+
+__device__ __forceinline__ void row_entropy(int M, const RowPartial& r, RowResult& rr) {
+  row_entropy(M, r.ref, r.a == r.ref ? 1.0 : exp(r.a - r.ref), r.Z, r.S, r.flags, rr);
 }
 
 struct Candidate { float z, P, H; int32_t tok; uint32_t info; };   // candidate t of a lone row, in lane t of the first wavefront; info: the row's flags
@@ -424,7 +443,7 @@ __device__ __forceinline__ Candidate score_row(int tid, const TreeState& s, cons
   if (mine) {
     tok = rr.topi[cand];
     p32 = (float)(exp((double)rr.topv[cand] - rr.part.ref) / rr.Zr);
-    P32 = rr.parent_P * p32;
+    P32 = rr.parent.P * p32;
   }
   if (spread) {
     if (tid < K) rr.topv[tid] = P32;                         // each lane overwrites the logit it has just read
@@ -445,9 +464,9 @@ __device__ __forceinline__ Candidate score_row(int tid, const TreeState& s, cons
     if (tid == 0) st_dev(s.row_info + (int64_t)b * sp.F + f, info);
     if (s.h_tok) {                                           // keep the candidate for the reranking
       const int64_t h = ((int64_t)b * sp.D + sp.layer) * FK + (int64_t)f * K;
-      s.h_tok[h + cand] = tok; s.h_par[h + cand] = rr.parent_hidx;
+      s.h_tok[h + cand] = tok; s.h_par[h + cand] = rr.parent.hidx;
       s.h_P[h + cand] = P32; s.h_H[h + cand] = H; s.h_z[h + cand] = z;
-      s.h_s[h + cand] = fminf(rr.parent_s, z);
+      s.h_s[h + cand] = fminf(rr.parent.s, z);
     }
   }
   if (quads && lone) {                                       // (uniform) for the caller a lane a candidate again
@@ -889,7 +908,7 @@ __device__ __forceinline__ void prune_lone_row(int tid, const TreeState& s, cons
   const uint32_t zk = surv ? sortable_key(c.z) : 0u, tk = surv ? (uint32_t)~c.tok : 0u;
   const uint64_t key = ((uint64_t)zk << 32) | tk;
   const uint64_t survivors = __ballot(surv);
-  const int nn = rr.n_nodes, n_keep = max(0, min(min(F, sp.N - nn), __popcll(survivors)));
+  const int nn = rr.parent.n_nodes, n_keep = max(0, min(min(F, sp.N - nn), __popcll(survivors)));
   int rank = 0;
   if (n_keep > 0) {
     for (int j0 = 0; j0 < K; j0 += 4) {                      // K <= 64: lanes K .. 63 hold 0
@@ -903,10 +922,10 @@ __device__ __forceinline__ void prune_lone_row(int tid, const TreeState& s, cons
   const bool kept = surv && rank < n_keep;
   if (kept) {
     const int64_t tb = (int64_t)b * sp.N + nn;
-    s.t_tok[tb + rank] = c.tok; s.t_parent[tb + rank] = rr.parent_node; s.t_depth[tb + rank] = layer;
+    s.t_tok[tb + rank] = c.tok; s.t_parent[tb + rank] = rr.parent.node; s.t_depth[tb + rank] = layer;
     s.t_P[tb + rank] = c.P; s.t_H[tb + rank] = c.H; s.t_z[tb + rank] = c.z;
     s.fr_tok[fb + rank] = c.tok; s.fr_pslot[fb + rank] = 0; s.fr_node[fb + rank] = nn + rank; s.fr_P[fb + rank] = c.P;
-    if (s.h_tok) { s.fr_hidx[fb + rank] = layer * FK + tid; s.fr_s[fb + rank] = fminf(rr.parent_s, c.z); }
+    if (s.h_tok) { s.fr_hidx[fb + rank] = layer * FK + tid; s.fr_s[fb + rank] = fminf(rr.parent.s, c.z); }
   }
   if (tid < FK) s.c_kept[cb + tid] = kept ? 1 : 0;
   if (tid == 0) {
@@ -937,8 +956,8 @@ __device__ __forceinline__ bool last_arrival(int tid, int32_t* ticket, int expec
 }
 
 // How a workgroup leaves its segment's largest logits: n_el elements in its element list, not ranked yet, or (n_el < 0)
-// ranked in rr.topv, rr.topi with rr.part.n_top of them.
-struct SegmentTop { int n_el; };
+// ranked in rr.topv, rr.topi with rr.part.n_top of them.  recorded: the last wavefront has completed rr.part, and the entropy of an unsplit row
+struct SegmentTop { int n_el; bool recorded; };
 
 // Tail of the logits pass for the workgroup that owned (sequence b, frontier slot f, split).  The workgroup
 // that completes a row scores the row's candidates; the workgroup that completes a sequence's last row prunes
@@ -957,8 +976,16 @@ __device__ __forceinline__ void finish_layer(int tid, const TreeState& s, const 
   const bool last_wave = (tid >> 6) == NW - 1;
   const int64_t slot = (int64_t)b * sp.F + f;
   if (last_wave) {
-    record();
-    if (sp.nsplit == 1) row_entropy(s, sp, b, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
+    if (top.recorded) {
+      wait_vector_memory();                                  // request_parent
+    } else {
+      record();
+      if (sp.nsplit == 1) {
+        const ParentStage p = load_parent(s, b, slot);
+        row_entropy(sp.M, rr.part, rr);
+        store_parent(p, rr);
+      }
+    }
   }
   if (top.n_el >= 0) rank_list<NT>(tid, K, list, top.n_el, rr.topv, rr.topi);
   __syncthreads();                                           // rr is complete
@@ -982,13 +1009,15 @@ __device__ __forceinline__ void finish_layer(int tid, const TreeState& s, const 
         RowPartial r; r.ref = m.R; r.a = m.R; r.Z = m.Z; r.S = m.S; r.flags = m.flags; r.n_top = min(m.n_valid, K);
         rr.part = r;
       }
-      if (sp.M <= 0) row_entropy(s, sp, b, slot, m.R, m.R, m.Z, m.S, m.flags, rr);
+      const ParentStage p = load_parent(s, b, slot);
+      if (sp.M <= 0) row_entropy(0, m.R, 1.0, m.Z, m.S, m.flags, rr);
+      store_parent(p, rr);
     }
     if (staged) rank_list<NT>(tid, K, sel, per_row, rr.topv, rr.topi);
     __syncthreads();
     if (sp.M > 0) {
       after_merge(rr);
-      if (last_wave) row_entropy(s, sp, b, slot, rr.part.ref, rr.part.a, rr.part.Z, rr.part.S, rr.part.flags, rr);
+      if (last_wave) row_entropy(sp.M, rr.part, rr);
       __syncthreads();
     }
     n = rr.part.n_top;
