@@ -90,6 +90,9 @@ __device__ __forceinline__ void touch_kernel_arguments() {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+// a value that is the same in every lane, as the compiler cannot know of one that comes from LDS: what is decided by it is then branched on, not masked
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // monotone map float -> uint32 (total order of the reals; -0 and +0 map to the same key)
 __device__ __forceinline__ uint32_t sortable_key(float x) {
   uint32_t u = __float_as_uint(x + 0.0f);   // -0 + 0 = +0

@@ -206,7 +206,7 @@ typedef __attribute__((address_space(3))) unsigned char* LdsBytes;
 template <int NT>
 __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsBytes lds, int list_cap, DirectSharedLds<NT> shl) {
   typedef LogitTraits<0> T;
-  const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
+  // (arguments arrive in vector registers)
   const int K = uniform(top_k);
   const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -336,8 +336,8 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   if (s.bad || !(s.lane_max < INFINITY)) sh.bad = 1;
   __syncthreads();
   C2T_PT(PT_HIST_COMPLETE);
-  int n_el = sh.n_list;
-  if (__builtin_expect(n_el > 2 * WAVE || n_el < K, 0)) n_el = settle_list<NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, (DirectSharedLds<NT>)&sh);
+  int n_el = uniform(sh.n_list);
+  if (__builtin_expect(n_el > 2 * WAVE || n_el < K, 0)) n_el = uniform(settle_list<NT>(rowp, V, K, sg, (LdsBytes)sel.list, sel.list_cap, (DirectSharedLds<NT>)&sh));
   if (__builtin_expect(n_el == UNSETTLED, 0)) generic_segment<0, NT>((int)threadIdx.x, rowp, V, K, 0, sg, sel.list, sel, rr, 0u);   // (its cell map overlays the list)
   return SegmentTop{n_el, false};
 }

@@ -1084,7 +1084,7 @@ __device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp,
                                         LdsHalves cell_map, int cells_max, HistSharedLds<NT> shl) {
   typedef LogitTraits<1> T;
   __shared__ int32_t scan_tmp[1][NT / WAVE];
-  const auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };    // (arguments arrive in vector registers)
+  // (arguments arrive in vector registers)
   HistShared<NT>& hs = *(HistShared<NT>*)shl;
   const int K = uniform(top_k), cell_cap = uniform(cells_max);
   const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
@@ -1433,7 +1433,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   }
   __syncthreads();
   C2T_PT(PT_CELLS_LISTED);
-  const int n_cells = hs.n_cells;
+  const int n_cells = uniform(hs.n_cells);
   const bool listed = n_cells <= sel.cell_cap;           // (uniform) else settle_hist makes the list
   int my_chunk = -1;
   uint4 cell_q = make_uint4(0u, 0u, 0u, 0u);
@@ -1549,12 +1549,12 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   int counted = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) counted += hs.total[w];
-  const int n_tiny = hs.out.n_tiny, n_ninf = hs.out.n_masked;
+  const int n_tiny = uniform(hs.out.n_tiny), n_ninf = hs.out.n_masked;
   const int n_elems = (sg.tail_chunk >= 0 ? (sg.ncell - 1) * 8 + sg.tail_valid : sg.ncell * 8);
-  int n_el = listed ? hs.n_el : HIST_LIST + 1;
+  int n_el = listed ? uniform(hs.n_el) : HIST_LIST + 1;
   // Leave this path (uniformly) if a logit that is not masked lies above the window (|x| >= 2^7, +inf, NaN), or if a
   // 16-bit counter overflowed (the total is then off by a multiple of 65535 or 65536).
-  bool leave = hs.out.mag_max >= HP_MAG_LO + HP_MAG_SPAN || counted + n_tiny + n_ninf != n_elems;
+  bool leave = uniform(hs.out.mag_max >= HP_MAG_LO + HP_MAG_SPAN || counted + n_tiny + n_ninf != n_elems ? 1 : 0) != 0;
   int before_p = 0, before_n = 0, tot_p = 0;            // TOPM: counts in lower lanes / in the whole segment
   if (TOPM) {
 #pragma unroll
@@ -1562,6 +1562,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       if (w < wid) { before_p += hs.scan_p[w]; before_n += hs.scan_n[w]; }
       tot_p += hs.scan_p[w];
     }
+    tot_p = uniform(tot_p);
     // ... or if some but not all of the logits below the window are among the M largest (which ones cannot be told from the histogram)
     leave = leave || (n_tiny > 0 && tot_p < M && M < tot_p + n_tiny);
   }
@@ -1603,7 +1604,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   // (A bound among the window's positive values is reached by K logits, so that the K-th largest is one of them too: logits below the window change
   // nothing then.  Asked about each row with such a logit, settle_hist took a layer of three rows of 8279 from 11.8 us to 13.6, one of 128256 from 15.9 to 17.4.)
   if (__builtin_expect(!leave && ((n_tiny > 0 && !(tau >= hp_value_of_mag(0u, false))) || n_el > HIST_LIST || n_el < min(K, n_elems)), 0)) {
-    n_el = settle_hist<NT>(tid, rowp, V, K, sg, (LdsWords)hist, lds_address(list.list), (LdsHalves)map, sel.cell_cap, (HistSharedLds<NT>)&hs);
+    n_el = uniform(settle_hist<NT>(tid, rowp, V, K, sg, (LdsWords)hist, lds_address(list.list), (LdsHalves)map, sel.cell_cap, (HistSharedLds<NT>)&hs));
     leave = n_el == UNSETTLED;
     __syncthreads();                                     // the list is complete
   }

@@ -338,49 +338,58 @@ __device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int by
 // ---- ranking of the element list by (logit desc, id asc), exactly; the best K go to topv, topi.  By every wavefront but the last, which
 // forms the row's entropy meanwhile: T lanes per element (four at least), each compares it with four entries per LDS read, of every
 // T-th group of four; the partial ranks are summed over the T lanes.  Equal logits are told apart by id where a count shows them, four a read as
-// well (one at a time, a layer of four rows of 20011 whose list holds 160 equal logits took 21.8 us, 17.8 so).
+// well (one at a time, a layer of four rows of 20011 whose list holds 160 equal logits took 21.8 us, 17.8 so).  T is a constant in each of the three forms, and of the
+// usual list (28 entries at most) every loop is one step: with T from the length, told to the compiler as uniform or not, the phases of one sequence of 32000 took 68.3 us, 67.3 so, with the
+// same in the sequence step (32 listed at most); of 128256 114.3 / 112.7, 32 sequences reranked 108.4 / 106.3, 64 of 128256 258.1 / 256.2.
 template <int NT>
 __device__ __forceinline__ void rank_list(int tid, int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
   constexpr int nt = NT - WAVE;
   const float* el_v = sel.values(); const int32_t* el_i = sel.ids();
   if (tid >= nt) return;                                     // a whole wavefront
-  int tshift = 2;
-  while (tshift < 4 && (n_el << (tshift + 1)) <= nt) ++tshift;
-  const int T = 1 << tshift, sub = tid & (T - 1);
+  const auto rank = [&](auto shift) {
+    constexpr int tshift = decltype(shift)::value, T = 1 << tshift;
+    constexpr bool SHORT = tshift == 4;                        // the usual list: all loops are one step
+    const int sub = tid & (T - 1);
 #pragma unroll 1
-  for (int e0 = 0; e0 < n_el; e0 += nt >> tshift) {
-    const int e = e0 + (tid >> tshift);
-    const bool mine = e < n_el;
-    int rank = 0, id = 0; float v = 0.f;                     // rank: greater ones; equal ones (itself among them) in the upper half
-    if (mine) {
-      v = el_v[e]; id = el_i[e];
+    for (int e0 = 0; e0 < n_el; e0 += nt >> tshift) {
+      const int e = e0 + (tid >> tshift);
+      const bool mine = e < n_el;
+      int rank = 0, id = 0; float v = 0.f;                     // rank: greater ones; equal ones (itself among them) in the upper half
+      if (mine) {
+        v = el_v[e]; id = el_i[e];
 #pragma unroll 2
-      for (int o = sub * 4; o < n_el; o += T * 4) {          // (values past the last, three at most, are read and not counted)
-        const float4 q = *(const float4*)(el_v + o);
-        const int past = max(o + 4 - n_el, 0);               // of the group's four
-        const uint32_t gt = (q.x > v ? 1u : 0u) | (q.y > v ? 2u : 0u) | (q.z > v ? 4u : 0u) | (q.w > v ? 8u : 0u);
-        const uint32_t eq = (q.x == v ? 1u : 0u) | (q.y == v ? 2u : 0u) | (q.z == v ? 4u : 0u) | (q.w == v ? 8u : 0u), in = 15u >> past;
-        rank += __popc(gt & in) + (__popc(eq & in) << 16);
-      }
-    }
-    rank = sum_of_lanes(tshift, rank);
-    const bool tied = mine && (rank >> 16) > 1 && (rank & 0xffff) < K;   // (the same in the element's T lanes)
-    rank &= 0xffff;
-    if (__builtin_amdgcn_ballot_w64(tied) != 0ull) {         // (uniform)
-      int ahead = 0;
-      if (tied) {
-#pragma unroll 2
-        for (int o = sub * 4; o < n_el; o += T * 4) {
+        for (int o = sub * 4; o < n_el; o += T * 4) {          // (values past the last, three at most, are read and not counted)
           const float4 q = *(const float4*)(el_v + o);
-          const int4 i = *(const int4*)(el_i + o);
-          const uint32_t hit = (q.x == v && i.x < id ? 1u : 0u) | (q.y == v && i.y < id ? 2u : 0u) | (q.z == v && i.z < id ? 4u : 0u) | (q.w == v && i.w < id ? 8u : 0u);
-          ahead += __popc(hit & (15u >> max(o + 4 - n_el, 0)));
+          const int past = max(o + 4 - n_el, 0);               // of the group's four
+          const uint32_t gt = (q.x > v ? 1u : 0u) | (q.y > v ? 2u : 0u) | (q.z > v ? 4u : 0u) | (q.w > v ? 8u : 0u);
+          const uint32_t eq = (q.x == v ? 1u : 0u) | (q.y == v ? 2u : 0u) | (q.z == v ? 4u : 0u) | (q.w == v ? 8u : 0u), in = 15u >> past;
+          rank += __popc(gt & in) + (__popc(eq & in) << 16);
+          if (SHORT) break;
         }
       }
-      rank += sum_of_lanes(tshift, ahead);
+      rank = sum_of_lanes(tshift, rank);
+      const bool tied = mine && (rank >> 16) > 1 && (rank & 0xffff) < K;   // (the same in the element's T lanes)
+      rank &= 0xffff;
+      if (__builtin_amdgcn_ballot_w64(tied) != 0ull) {         // (uniform)
+        int ahead = 0;
+        if (tied) {
+#pragma unroll 2
+          for (int o = sub * 4; o < n_el; o += T * 4) {
+            const float4 q = *(const float4*)(el_v + o);
+            const int4 i = *(const int4*)(el_i + o);
+            const uint32_t hit = (q.x == v && i.x < id ? 1u : 0u) | (q.y == v && i.y < id ? 2u : 0u) | (q.z == v && i.z < id ? 4u : 0u) | (q.w == v && i.w < id ? 8u : 0u);
+            ahead += __popc(hit & (15u >> max(o + 4 - n_el, 0)));
+          }
+        }
+        rank += sum_of_lanes(tshift, ahead);
+      }
+      if (mine && sub == 0 && rank < K) { topv[rank] = v; topi[rank] = id; }
+      if (SHORT) break;
     }
-    if (mine && sub == 0 && rank < K) { topv[rank] = v; topi[rank] = id; }
-  }
+  };
+  if (n_el <= nt >> 4) rank(std::integral_constant<int, 4>());
+  else if (n_el <= nt >> 3) rank(std::integral_constant<int, 3>());
+  else rank(std::integral_constant<int, 2>());
 }
 
 // What the row's frontier node hands down, from global memory to rr.
@@ -451,7 +460,7 @@ __device__ __forceinline__ Candidate score_row(int tid, const TreeState& s, cons
     z = mlp_logit_spread<NT>(tid, (LdsFloats)w_lds, sp.h, rr.topv, H, (float)sp.layer, K, sp.k_inverse, (float*)lds, sp.lds_bytes);
     if (!mine) z = -INFINITY;
   }
-  const uint32_t info = (rr.bad ? 1u : 0u) | (rr.part.flags & 2u);
+  const uint32_t info = (uniform((int)rr.bad) ? 1u : 0u) | (rr.part.flags & 2u);
   if (tid >= (quads ? WAVE : K)) return Candidate{-INFINITY, 0.f, 0.f, -1, 0u};
   if (mine && !spread) {
     z = quads ? mlp_logit_quads((LdsFloats)w_lds, sp.h, P32, H, (float)sp.layer)
@@ -697,7 +706,8 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
   int n_surv = 0;
 #pragma unroll
   for (int v = 0; v < NW; ++v) n_surv += ps.surv_w[v];
-  const int n_keep = max(0, min(min(F, N - nn), n_surv));
+  n_surv = uniform(n_surv);
+  const int n_keep = max(0, min(min(F, N - uniform(nn)), n_surv));
   uint32_t bound = 1u;                                       // every survivor
   const bool to_digits = BY_DIGITS && n_surv > PRUNE_DIRECT_MAX;
   if (!BY_DIGITS && n_keep > 0 && n_surv > PRUNE_DIRECT_MAX) {
@@ -824,54 +834,66 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
   }
   C2T_PT(PT_PRUNE_PRESELECTED);
   if (n_keep > 0) {
-    int tshift = 0;
-    while (tshift < 4 && (ns << (tshift + 1)) <= NT) ++tshift;
-    const int T = 1 << tshift, sub = tid & (T - 1), ustride = NT >> tshift;
+    // tshift: see rank_list
+    const auto rank_listed = [&](auto shift) {
+      constexpr bool SHORT = !std::is_same<decltype(shift), int>::value;
+      const int tshift = shift, T = 1 << tshift, sub = tid & (T - 1), ustride = NT >> tshift;
 #pragma unroll 1
-    for (int u0 = 0; u0 < ns; u0 += ustride) {               // uniform trip count: every lane meets in the DPP sums
-      const int u = u0 + (tid >> tshift);
-      const bool mine = u < ns;
-      const uint64_t key = mine ? skey[u] : 0ull;
-      const int i = mine ? sidx[u] : 0;
-      const float z = key_to_float((uint32_t)(key >> 32));
-      const int tok = (int)~(uint32_t)key;
-      float P = 0.f, H = 0.f;
-      if (mine && sub == 0) {
-        if (listed_order) { P = list_P[u]; H = list_H[u]; }
-        else { P = ld_dev(s.c_P + cb + i); H = ld_dev(s.c_H + cb + i); }
-      }
-      // rank = survivors with a greater key, and those with the same key (the same token under two parents, with
-      // the same z: looked for only where a count shows them) and a lower candidate index; the survivor's T
-      // lanes take two keys a step each.  (Ties by one lane alone: 7.5 us for 100 survivors of equal z whose rows share tokens.)
-      int rank = 0;                                          // lower half: greater keys, upper half: equal ones (itself among them)
-      if (mine) {
+      for (int u0 = 0; u0 < ns; u0 += ustride) {               // uniform trip count: every lane meets in the DPP sums
+        const int u = u0 + (tid >> tshift);
+        const bool mine = u < ns;
+        const uint64_t key = mine ? skey[u] : 0ull;
+        const int i = mine ? sidx[u] : 0;
+        const float z = key_to_float((uint32_t)(key >> 32));
+        const int tok = (int)~(uint32_t)key;
+        float P = 0.f, H = 0.f;
+        if (mine && sub == 0) {
+          if (listed_order) { P = list_P[u]; H = list_H[u]; }
+          else { P = ld_dev(s.c_P + cb + i); H = ld_dev(s.c_H + cb + i); }
+        }
+        // rank = survivors with a greater key, and those with the same key (the same token under two parents, with
+        // the same z: looked for only where a count shows them) and a lower candidate index; the survivor's T
+        // lanes take two keys a step each.  (Ties by one lane alone: 7.5 us for 100 survivors of equal z whose rows share tokens.)
+        int rank = 0;                                          // lower half: greater keys, upper half: equal ones (itself among them)
+        if (mine) {
 #pragma unroll 2
-        for (int v = sub * 2; v < ns; v += T * 2) {
-          const uint4 q = *(const uint4*)(skey + v);
-          const uint64_t k0 = ((uint64_t)q.y << 32) | q.x, k1 = v + 1 < ns ? ((uint64_t)q.w << 32) | q.z : 0ull;
-          rank += (k0 > key ? 1 : 0) + (k1 > key ? 1 : 0) + (k0 == key ? 0x10000 : 0) + (k1 == key ? 0x10000 : 0);
+          for (int v = sub * 2; v < ns; v += T * 2) {
+            const uint4 q = *(const uint4*)(skey + v);
+            const uint64_t k0 = ((uint64_t)q.y << 32) | q.x, k1 = v + 1 < ns ? ((uint64_t)q.w << 32) | q.z : 0ull;
+            rank += (k0 > key ? 1 : 0) + (k1 > key ? 1 : 0) + (k0 == key ? 0x10000 : 0) + (k1 == key ? 0x10000 : 0);
+            if (SHORT) break;                                  // (T lanes of two keys are all there are)
+          }
         }
-      }
-      rank = sum_of_lanes(tshift, rank);
-      const bool tied = mine && (rank >> 16) > 1;            // (the same in the entry's T lanes)
-      rank &= 0xffff;
-      if (__builtin_amdgcn_ballot_w64(tied) != 0ull) {       // (uniform)
-        int ahead = 0;
-        if (tied) {
+        rank = sum_of_lanes(tshift, rank);
+        const bool tied = mine && (rank >> 16) > 1;            // (the same in the entry's T lanes)
+        rank &= 0xffff;
+        if (__builtin_amdgcn_ballot_w64(tied) != 0ull) {       // (uniform)
+          int ahead = 0;
+          if (tied) {
 #pragma unroll 4
-          for (int v = sub; v < ns; v += T) ahead += (int)(skey[v] == key && sidx[v] < i);
+            for (int v = sub; v < ns; v += T) ahead += (int)(skey[v] == key && sidx[v] < i);
+          }
+          rank += sum_of_lanes(tshift, ahead);
         }
-        rank += sum_of_lanes(tshift, ahead);
+        if (mine && sub == 0 && rank < n_keep) {
+          const int f = (int)(((uint32_t)i * sp.k_inverse) >> 20);         // i / K
+          const int64_t tb = (int64_t)b * N + nn;
+          atomicOr(&ps.kept[i >> 5], 1u << (i & 31));
+          s.t_tok[tb + rank] = tok; s.t_parent[tb + rank] = ps.old_node[f]; s.t_depth[tb + rank] = layer;
+          s.t_P[tb + rank] = P; s.t_H[tb + rank] = H; s.t_z[tb + rank] = z;
+          s.fr_tok[fb + rank] = tok; s.fr_pslot[fb + rank] = f; s.fr_node[fb + rank] = nn + rank; s.fr_P[fb + rank] = P;
+          if (s.h_tok) { s.fr_hidx[fb + rank] = layer * FK + i; s.fr_s[fb + rank] = fminf(ps.old_s[f], z); }
+        }
+        if (SHORT) break;
       }
-      if (mine && sub == 0 && rank < n_keep) {
-        const int f = (int)(((uint32_t)i * sp.k_inverse) >> 20);         // i / K
-        const int64_t tb = (int64_t)b * N + nn;
-        atomicOr(&ps.kept[i >> 5], 1u << (i & 31));
-        s.t_tok[tb + rank] = tok; s.t_parent[tb + rank] = ps.old_node[f]; s.t_depth[tb + rank] = layer;
-        s.t_P[tb + rank] = P; s.t_H[tb + rank] = H; s.t_z[tb + rank] = z;
-        s.fr_tok[fb + rank] = tok; s.fr_pslot[fb + rank] = f; s.fr_node[fb + rank] = nn + rank; s.fr_P[fb + rank] = P;
-        if (s.h_tok) { s.fr_hidx[fb + rank] = layer * FK + i; s.fr_s[fb + rank] = fminf(ps.old_s[f], z); }
-      }
+    };
+    static_assert((NT >> 4) <= 2 << 4, "a short list is one step of two keys a lane");
+    if (ns <= NT >> 4) {
+      rank_listed(std::integral_constant<int, 4>());
+    } else {
+      int tshift = 0;
+      while (tshift < 3 && (ns << (tshift + 1)) <= NT) ++tshift;
+      rank_listed(tshift);
     }
   }
   __syncthreads();                                           // ps.kept is complete
@@ -908,7 +930,7 @@ __device__ __forceinline__ void prune_lone_row(int tid, const TreeState& s, cons
   const uint32_t zk = surv ? sortable_key(c.z) : 0u, tk = surv ? (uint32_t)~c.tok : 0u;
   const uint64_t key = ((uint64_t)zk << 32) | tk;
   const uint64_t survivors = __ballot(surv);
-  const int nn = rr.parent.n_nodes, n_keep = max(0, min(min(F, sp.N - nn), __popcll(survivors)));
+  const int nn = uniform(rr.parent.n_nodes), n_keep = max(0, min(min(F, sp.N - nn), __popcll(survivors)));
   int rank = 0;
   if (n_keep > 0) {
     for (int j0 = 0; j0 < K; j0 += 4) {                      // K <= 64: lanes K .. 63 hold 0
@@ -952,7 +974,7 @@ __device__ __forceinline__ bool last_arrival(int tid, int32_t* ticket, int expec
     }
   }
   __syncthreads();
-  return sh_last != 0;
+  return uniform(sh_last) != 0;
 }
 
 // How a workgroup leaves its segment's largest logits: n_el elements in its element list, not ranked yet, or (n_el < 0)
@@ -989,7 +1011,7 @@ __device__ __forceinline__ void finish_layer(int tid, const TreeState& s, const 
   }
   if (top.n_el >= 0) rank_list<NT>(tid, K, list, top.n_el, rr.topv, rr.topi);
   __syncthreads();                                           // rr is complete
-  int n = top.n_el >= 0 ? min(top.n_el, K) : rr.part.n_top;
+  int n = top.n_el >= 0 ? min(top.n_el, K) : uniform(rr.part.n_top);
   C2T_PT(PT_RANKED);
   if (sp.nsplit > 1) {
     const int nsplit = sp.nsplit, per_row = nsplit * K;
