@@ -59,6 +59,32 @@ __device__ __forceinline__ double exp_nonpositive(double t, const double* tab) {
   return __builtin_bit_cast(double, w) * p;
 }
 
+// The same for the logits of a tile, from v = (a - x) / 512 in [0, 1]: one fused multiply-add forms v and its clamp modifier cuts it off (e^-512 is nothing beside the
+// largest term, which is 1), where a subtraction and a maximum were two instructions of sixteen.  The scale being a power of two, v and the
+// reduced argument are those of t = x - a, rounded alike.
+constexpr double TILE_SCALE = 512.0;
+__device__ __forceinline__ double scaled_distance(float x, double a_scaled) {      // a_scaled = a / 512
+  double v;
+  asm("v_fma_f64 %0, %1, %2, %3 clamp" : "=v"(v) : "v"((double)x), "s"(-1.0 / TILE_SCALE), "v"(a_scaled));
+  return v;
+}
+__device__ __forceinline__ double exp_of_distance(double v, const double* tab) {
+  constexpr double SHIFT = 6755399441055744.0;
+  const double kf = __builtin_fma(v, -0x1.71547652b82fep+8 * TILE_SCALE, SHIFT);
+  const int k = __double2loint(kf);
+  const double r = __builtin_fma(kf - SHIFT, -0x1.62e42fefa39efp-9 / TILE_SCALE, -v);      // a 512th of the reduced argument
+  const double e = tab[k & (EXP_TAB - 1)];
+  constexpr double S1 = TILE_SCALE, S2 = S1 * S1, S3 = S2 * S1, S4 = S3 * S1;
+  double p = __builtin_fma(0x1.5555565bb9890p-5 * S4, r, 0x1.555556deeba30p-3 * S3);
+  p = __builtin_fma(p, r, 0.5 * S2);
+  p = __builtin_fma(p, r, S1);
+  p = __builtin_fma(p, r, 1.0);
+  typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
+  uint2v w = __builtin_bit_cast(uint2v, e);
+  w.y += (uint32_t)k << (20 - EXP_TAB_BITS);
+  return __builtin_bit_cast(double, w) * p;
+}
+
 template <int NT>
 struct DirectShared {
   static constexpr int NW = NT / WAVE;
@@ -99,7 +125,7 @@ __device__ __forceinline__ float column_bound(const DirectShared<NT>& sh, int K)
 template <int NT>
 struct DirectState {                            // of one wavefront
   float a, lane_max, tau;                       // a: reference of the sums, the wave's largest logit so far (uniform)
-  double Z, S;
+  double Z, S;                                  // S: sum of v e^(x - a), v = (a - x) / 512
   bool bad;
 };
 
@@ -147,11 +173,12 @@ __device__ __forceinline__ void direct_tile(uint4 (&q)[DIRECT_CHUNKS], int t, co
   if (wm > s.a) {                                            // uniform
     if (s.a > -INFINITY) {
       const double d = fmax((double)s.a - (double)wm, -700.0), f = exp_nonpositive(d, sh.exp_tab);
-      s.S = (s.S + d * s.Z) * f; s.Z *= f;
+      s.S = (s.S - d / TILE_SCALE * s.Z) * f; s.Z *= f;
     }
     s.a = wm;
   }
-  const double ad = (double)s.a;
+  const double ad = (double)s.a / TILE_SCALE;
+  const bool masked = !(s.a > -INFINITY);                    // (uniform) no logit yet that adds anything
 #pragma unroll
   for (int c = 0; c < DIRECT_CHUNKS; ++c) {
     asm volatile("" : "+v"(q[c].x), "+v"(q[c].y), "+v"(q[c].z), "+v"(q[c].w));     // (conversions of later chunks are not hoisted: they would spill; of a copy: a move a logit)
@@ -160,12 +187,13 @@ __device__ __forceinline__ void direct_tile(uint4 (&q)[DIRECT_CHUNKS], int t, co
 #pragma unroll
     for (int j = 0; j < T::EPC; ++j) {
       if (j & 1) s.bad |= __builtin_isunordered(x[j - 1], x[j]);           // (+inf shows in the maximum)
-      const double d = fmax((double)x[j] - ad, -700.0);
-      const double e = exp_nonpositive(d, sh.exp_tab);
-      s.Z += e; s.S = __builtin_fma(d, e, s.S);
+      const double v = scaled_distance(x[j], ad);
+      const double e = exp_of_distance(v, sh.exp_tab);
+      s.Z += e; s.S = __builtin_fma(v, e, s.S);
       if (j % 4 == 3) asm volatile("" : "+v"(s.Z), "+v"(s.S));   // four exponentials at a time cover their latency; more would spill
     }
   }
+  if (masked) s.Z = s.S = 0.0;                               // (what has been added is not a number's)
   if (t == 0) __syncthreads();                               // the first tile's maxima are complete
   if ((t & (t - 1)) == 0 && t != 1) s.tau = fmaxf(s.tau, column_bound<NT>(sh, K));
   float* el_v = sel.values();
@@ -331,7 +359,7 @@ __device__ __forceinline__ SegmentTop direct_segment(const uint4* __restrict__ r
   }
   C2T_PT(PT_STREAM_END);
   store_classifier((int)threadIdx.x, cst);                                     // published by the barriers below
-  s.Z = wave_sum(s.Z); s.S = wave_sum(s.S);
+  s.Z = wave_sum(s.Z); s.S = -TILE_SCALE * wave_sum(s.S);    // the sum of (x - a) e^(x - a)
   if (lane == 0) { sh.wave_z[wid] = s.Z; sh.wave_s[wid] = s.S; sh.wave_a[wid] = s.a; }
   if (s.bad || !(s.lane_max < INFINITY)) sh.bad = 1;
   __syncthreads();
