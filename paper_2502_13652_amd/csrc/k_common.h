@@ -246,6 +246,19 @@ __device__ __forceinline__ int append_places(int n, int32_t* counter) {
   return __builtin_amdgcn_readlane(base, WAVE - 1) + incl - n;
 }
 
+// The place of one entry of each lane that is here, in a list that others append to as well.  Few lanes add for themselves; many at once, which the LDS would serve
+// one after the other, by one addition and their count (320 rows of 32000 equal fp32 logits: 76 us a layer with 64 additions each, 42 so).
+constexpr int APPEND_FEW = 4;
+__device__ __forceinline__ int append_place(int32_t* counter) {
+  const uint64_t here = __builtin_amdgcn_ballot_w64(true);
+  const int n = __builtin_popcountll(here);
+  if (n <= APPEND_FEW) return atomicAdd(counter, 1);         // (uniform)
+  const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(here >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)here, 0u));
+  int base = 0;
+  if (before == 0) base = atomicAdd(counter, n);
+  return __builtin_amdgcn_readfirstlane(base) + before;
+}
+
 // K-th largest (k >= 1) of the keys held by one wave, NV keys per lane (invalid keys = 0,
 // the smallest key).  Radix select from the most significant bit with wave ballots; the
 // result is wave-uniform.  If fewer than k keys are valid the result is 0.

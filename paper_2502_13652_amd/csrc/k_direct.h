@@ -1,9 +1,9 @@
 // Logits pass without a histogram: every logit's exponential is evaluated in fp64 as it is read, in one
 // pass over the segment.  The path of fp32 rows (whose values are too many to be counted).
 //
-// What bounds it: instruction issue.  About seventeen vector instructions a logit, thirteen of them fp64: 2048 rows of 65536
-// take 121 us, 4.4 TB/s, two thirds of what HBM delivers (with a table of 32, one more fp64 instruction, a move of the logit and its own test
-// for NaN 127 us; 320 rows of 32000 25.6 -> 24.3).  The two-pass form that it replaces read
+// What bounds it: instruction issue.  About fifteen vector instructions a logit, twelve of them fp64: 2048 rows of 65536
+// take 129 us, 4.2 TB/s, two thirds of what HBM delivers (134 with the distance from the maximum and its cut-off by two instructions, see scaled_distance;
+// without the table, by a polynomial of degree 11, four instructions more, 156).  The two-pass form that it replaces read
 // the segment twice (the maximum first) and spent about fifty instructions in the library's exp.
 //
 // Sums.  Each wavefront keeps Z = sum e^(x-a) and S = sum (x-a) e^(x-a) against its own largest logit so far, a
@@ -208,7 +208,7 @@ __device__ __forceinline__ void direct_tile(uint4 (&q)[DIRECT_CHUNKS], int t, co
     for (int j = 0; j < T::EPC; ++j) {
       const int id = (sg.c0 + g) * T::EPC + j;
       if (x[j] >= s.tau && g < sg.ncell && id < V) {
-        const int slot = atomicAdd(&sh.n_list, 1);
+        const int slot = append_place(&sh.n_list);
         if (slot < sel.list_cap) { el_v[slot] = x[j]; el_i[slot] = id; }
       }
     }
@@ -269,7 +269,7 @@ __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, i
 #pragma unroll
         for (int k = 0; k < KEEP; ++k) {
           if (id[k] >= 0 && (strict ? v[k] > bound : v[k] >= bound)) {
-            const int slot = atomicAdd(&sh.n_list, 1);
+            const int slot = append_place(&sh.n_list);
             el_v[slot] = v[k]; el_i[slot] = id[k];
           }
         }
@@ -298,7 +298,7 @@ __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, i
           for (int j = 0; j < T::EPC; ++j) {
             const int id = (sg.c0 + g) * T::EPC + j;
             if (x[j] > bound && g < sg.ncell && id < V) {
-              const int slot = atomicAdd(&sh.n_list, 1);
+              const int slot = append_place(&sh.n_list);
               if (slot < sel.list_cap) { el_v[slot] = x[j]; el_i[slot] = id; }
             }
           }

@@ -140,7 +140,7 @@ __device__ __forceinline__ int list_cells(int tid, const typename LogitTraits<DT
   for (int c = tid; c < ncells; c += NT) {
     const float kv = T::from_key(map[c]);
     if (strict ? kv > tau : kv >= tau) {
-      const int slot = atomicAdd(sh_n, 1);
+      const int slot = append_place(sh_n);
       if (slot < cell_cap) cell_list[slot] = c;
     }
   }
@@ -214,7 +214,7 @@ __device__ __forceinline__ void tie_scan(int tid, const uint4* __restrict__ rowp
     for (int w = 0; w < NW; ++w) { if (w < wid) before += scan_tmp[0][w]; total += scan_tmp[0][w]; }
     while (hit && before < need) {
       const int j = __ffs(hit) - 1; hit &= hit - 1;
-      const int slot = atomicAdd(sh_cnt, 1);
+      const int slot = append_place(sh_cnt);
       if (slot < sel.list_cap) { el_v[slot] = tau; el_i[slot] = g * T::EPC + j; }
       ++before;
     }
@@ -1404,7 +1404,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       for (int j = 0; j < 8; ++j) {
         const float kv = (j & 1) ? bf16_hi(kw[j >> 1]) : bf16_lo(kw[j >> 1]);
         if (c8 + j < ncells && kv >= tau) {
-          const int at = atomicAdd(&hs.n_cells, 1);
+          const int at = append_place(&hs.n_cells);
           if (at < sel.cell_cap) hs.cells[at] = c8 + j;
         }
       }
@@ -1527,7 +1527,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
       while (hit) {
         const int j = __ffs(hit) - 1; hit &= hit - 1;
         const uint32_t w = (j & 4) ? ((j & 2) ? cell_q.w : cell_q.z) : (j & 2) ? cell_q.y : cell_q.x;
-        if (WPS == 8) at = atomicAdd(&hs.n_el, 1);
+        if (WPS == 8) at = append_place(&hs.n_el);
         if (at < HIST_LIST) { el_v[at] = (j & 1) ? bf16_hi(w) : bf16_lo(w); el_i[at] = my_chunk * 8 + j; }
         ++at;
       }

@@ -809,7 +809,7 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
         if (ri[k] >= 0 && (rk[k] >> shift) >= cut) {
-          const int u = atomicAdd(&ps.n_red, 1);
+          const int u = append_place(&ps.n_red);
           skey[u] = rk[k]; sidx[u] = ri[k];
         }
       }
