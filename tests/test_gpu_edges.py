@@ -18,6 +18,40 @@ def test_fp32_rows_at_tile_edges(V, K):
     rows_against_oracle("f32", V, K, 1)
 
 
+# fp32: tiles without a finite logit ahead of others (they add nothing, a NaN among them still shows), and logits around the distance of 512 from the largest
+# at which the exponential is cut off (e^-512 is nothing beside 1, whatever the sums hold: the tolerance is that of all rows)
+@pytest.mark.parametrize("V,splits", [(16384, 1), (20001, 1), (40963, 3)])
+def test_fp32_masked_tiles_and_far_logits(V, splits):
+    from oracle import ref_row
+    from paper_2502_13652_amd import C2TContext
+    g = torch.Generator().manual_seed(V)
+    x = torch.randn((7, V), generator=g)
+    x[0, :8192] = x[1, :8192] = x[5, :8192] = -float("inf")
+    x[1, 8192:-3] = -float("inf")                              # three finite logits in all
+    x[2] = x[2].mul(100).sub(511)
+    x[2, V - 1] = 0.0
+    x[3] = torch.linspace(-513, -511, V)
+    x[3, V // 2] = 0.0
+    x[4] = x[4] * 1000                                         # the maximum is raised often, by more than 512
+    x[5, 77] = float("nan")
+    x[6] = -3e38
+    x[6, [5, V - 2]] = torch.tensor([3e38, 3e38])
+    per = torch.full((7, 1, (V + 3) // 4 * 4), float("inf")); per[:, 0, :V] = x
+    ctx = C2TContext(7, V, 1, 5, 1, 1, 2, 0, 0.0)
+    W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+    ctx.set_classifier(W1, np.zeros(2, np.float32), np.array([1, 0], np.float32), 0.0)
+    ctx.set_row_splits(splits, splits)
+    ctx.reset()
+    ctx.expand_layer(per.cuda())
+    c, out = to_np(ctx.candidates()), to_np(ctx.finalize_tree())
+    np.testing.assert_array_equal(out["status"] & 1, [0, 0, 0, 0, 0, 1, 0])
+    for b in (0, 1, 2, 3, 4, 6):
+        r = ref_row(x[b].numpy(), 5)
+        np.testing.assert_array_equal(c["token"][b, :5], r["ids"], err_msg=str(b))
+        assert close(c["p"][b, :5], r["p"].astype(np.float32), atol=1e-37).all(), b
+        assert close(c["H"][b, 0], np.float32(r["H"]), atol=V * 2.0 ** -53).all(), b
+
+
 # bf16 lists of K to 2K-1 elements, ranked by four lanes or more to an element up to 128 of them
 @pytest.mark.parametrize("K", [16, 17, 32, 33, 63, 64])
 def test_bf16_lists_at_the_ranking_s_edges(K):
