@@ -387,6 +387,24 @@ def test_ragged_frontiers_dealt_to_workgroups(B, F, K, dtype):
     assert len(lengths) > 2
 
 
+# the same with several workgroups a row: the row and its split from one index, splits that are empty (68 logits in seven: two are in bf16, one in fp32) or hold fewer
+# than K logits, the records of a row merged by whichever split is done last, the entropy over the M largest of the merged row, ended sequences noted by their first split alone
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,F,K,V,splits,M", [(17, 20, 8, 520, 2, 0), (5, 64, 4, 520, 3, 0), (63, 5, 4, 520, 3, 37), (9, 16, 8, 68, 7, 0), (65, 2, 4, 68, 7, 0), (256, 2, 2, 520, 2, 0)])
+def test_ragged_frontiers_of_split_rows(B, F, K, V, splits, M, dtype):
+    assert 256 < B * F * splits <= 1024 and B <= 256          # one round of workgroups, more of them than CUs
+    chunks = -(-V // (8 if dtype == "bf16" else 4))
+    assert splits < 7 or -(-chunks // splits) * (splits - 1) >= chunks          # the last split is empty
+    lengths = set()
+    for beta in (0.02, 0.2):
+        cfg = _cfg(B=B, F=F, K=K, h=2, N=3 * F, D=5, V=V, dtype=dtype, beta=beta, entropy_top_m=M)
+        W1 = np.zeros((2, 3), np.float32); W1[0, 0] = 1
+        cls = (W1, np.zeros(2, np.float32), np.array([8, 0], np.float32), -4.0)
+        go, oo, _ = run_both(cfg, cls, _layers(cfg), splits=(splits, splits), tag="B=%d F=%d splits %d beta %g" % (B, F, splits, beta))
+        lengths |= set(go["n_nodes"].tolist())
+    assert len(lengths) > 2
+
+
 # more than 64 survivors in one candidate a thread, of which 1 to 16 are kept: the bound from sorted maxima, and the ballots beyond
 @pytest.mark.parametrize("F,K,N", [(2, 50, 12), (3, 64, 7), (15, 30, 50), (16, 31, 60), (17, 30, 60)])
 def test_sequence_step_where_the_bound_changes(F, K, N):
