@@ -16,9 +16,10 @@ _lib = None
 F32, BF16 = 0, 1
 _ERR = {-1: "invalid argument", -2: "unsupported", -3: "workspace", -4: "state", -5: "hip", -6: "out of host memory"}
 
+_PRELOADED = 11                            # the layer kernels' first arguments, which arrive in registers (compared with their list in k_tree.h as it is compiled)
 HIPCC_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-               "-mllvm", "-amdgpu-kernarg-preload-count=11",      # the layer kernels' first arguments arrive in registers
+               "-mllvm", "-amdgpu-kernarg-preload-count=%d" % _PRELOADED, "-DC2T_KERNARG_PRELOAD=%d" % _PRELOADED,
                # Additions of one lane or a few to a counter as they are written: combined over the wavefront by the compiler, each became a
                # ballot, a count, the addition by one lane and a wait for its answer, on paths that everything waits for (phases up to 1.4 % longer).
                # Where many lanes may add at once, append_place combines them.

@@ -184,7 +184,7 @@ static_assert(4 * hist_lds_of_workgroup(229376 / 16, C2T_MAX_HIDDEN) <= 160 * 10
               "four workgroups a CU");
 // Builds of the histogram kernel, see launch_logits
 enum HistBuild { HB_FOUR_PER_CU, HB_SHARED, HB_SHORT, HB_LONG, HB_LONG_STREAMED, HB_COUNT };
-typedef void (*HistKernel)(const void*, const int32_t*, int64_t, int, int, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, const double*, const float*, TreeState, ScoreParams);
+typedef void (*HistKernel)(C2T_START_LIST(C2T_AS_TYPE) const double*, const float*, TreeState, ScoreParams);
 template <bool TOPM>
 HistKernel hist_kernel(int build) {
   switch (build) {

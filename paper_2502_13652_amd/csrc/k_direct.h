@@ -398,7 +398,7 @@ __device__ __forceinline__ void combine_waves(const DirectShared<NT>& sh, RowRes
 // Dynamic LDS (sp.lds_bytes): the list of the selection, over the cell map of generic_segment (cps keys); reused by the tail.
 template <int NT>
 __global__ __launch_bounds__(NT, 4) void k_logits_direct(
-    C2T_START_PARAMETERS, const float* __restrict__ cls, TreeState st, ScoreParams sp) {
+    C2T_START_LIST(C2T_AS_PARAMETER) const float* __restrict__ cls, TreeState st, ScoreParams sp) {
   typedef LogitTraits<0> T;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ RowResult rr;

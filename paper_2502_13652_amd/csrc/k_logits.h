@@ -1622,7 +1622,7 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
 // 6 = three workgroups per CU on 80 registers, which needs no spills.
 template <int NT, bool TOPM, int WPS, int REPL, bool COOP, bool STREAMED>
 __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
-    C2T_START_PARAMETERS, const double* __restrict__ tab_e, const float* __restrict__ cls, TreeState st, ScoreParams sp) {
+    C2T_START_LIST(C2T_AS_PARAMETER) const double* __restrict__ tab_e, const float* __restrict__ cls, TreeState st, ScoreParams sp) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ RowResult rr;
   __shared__ HistShared<NT> hs;

@@ -262,8 +262,7 @@ struct ScoreParams {
 };
 
 // What a workgroup needs to find its row and to request its first logits: the layer kernels' first arguments, which the compiler has the dispatcher
-// put into scalar registers ahead of the wavefront's first instruction (kernel argument preload, at most fourteen registers; the build's
-// flags ask for it).  Loaded, they cost a first touch of the arguments, a dependent one and two divisions of some twenty instructions before the frontier size was even requested.
+// put into scalar registers ahead of the wavefront's first instruction (kernel argument preload; the build's flags say how many of them).  Loaded, they cost a first touch of the arguments, a dependent one and two divisions of some twenty instructions before the frontier size was even requested.
 struct Division { uint32_t n, inverse; };                    // inverse: ceil(2^32 / n), 0 for n = 1
 struct QuotientRemainder { uint32_t q, r; };
 __device__ __forceinline__ QuotientRemainder divide(uint32_t x, const Division& d) {
@@ -272,11 +271,21 @@ __device__ __forceinline__ QuotientRemainder divide(uint32_t x, const Division& 
   if ((int32_t)r < 0) { q -= 1; r += d.n; }                  // (divisors and what is divided stay below 2^31)
   return QuotientRemainder{q, r};
 }
-// shape: rows launched per sequence, F << 8, 1 << 16: workgroup w takes the w-th live row (see row_of_workgroup)
+// shape: rows launched per sequence, F << 8, 1 << 16: workgroup w takes the w-th live row (see dealt_row)
 constexpr uint32_t SHAPE_COMPACT = 1u << 16;
-#define C2T_START_PARAMETERS const void* __restrict__ logits, const int32_t* __restrict__ nfs, int64_t row_stride_bytes, int V, int cps, uint32_t B, uint32_t shape, \
-                             uint32_t per_row, uint32_t inv_per_row, uint32_t inv_rows, uint32_t inv_B
-constexpr int START_BYTES = 56, START_ARGUMENTS = 11;
+#define C2T_START_LIST(X) X(const void* __restrict__, logits) X(const int32_t* __restrict__, nfs) X(int64_t, row_stride_bytes) X(int, V) X(int, cps) X(uint32_t, B) \
+                          X(uint32_t, shape) X(uint32_t, per_row) X(uint32_t, inv_per_row) X(uint32_t, inv_rows) X(uint32_t, inv_B)
+#define C2T_AS_PARAMETER(type, name) type name,
+#define C2T_AS_TYPE(type, name) type,
+#define C2T_AS_MEMBER(type, name) type name;
+#define C2T_AS_ONE(type, name) + 1
+struct StartArguments { C2T_START_LIST(C2T_AS_MEMBER) };
+constexpr int START_BYTES = sizeof(StartArguments), START_ARGUMENTS = 0 C2T_START_LIST(C2T_AS_ONE);
+static_assert(START_BYTES <= 14 * 4, "fourteen registers take preloaded arguments");
+static_assert(START_BYTES % 8 == 0, "the pointers that follow lie right behind them");
+#ifdef C2T_KERNARG_PRELOAD
+static_assert(C2T_KERNARG_PRELOAD == START_ARGUMENTS, "the build's flags preload as many arguments as there are");
+#endif
 
 // The last two arguments of the layer kernels, at byte OFFSET of the argument segment, read again for the tail: the compiler loads what it
 // can reach early and keeps it in scalar registers through the streaming loop, or, there being too few, in lanes of vector registers.
