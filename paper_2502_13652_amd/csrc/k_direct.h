@@ -42,15 +42,17 @@ __device__ __forceinline__ float max3_raw(float a, float b, float c) {     // wi
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
   return d;
 }
+constexpr double EXP_SHIFT = 6755399441055744.0;             // 1.5 * 2^52: the sum's low word is the rounded integer
+constexpr double EXP_PER_STEP = 0x1.71547652b82fep+8, EXP_STEP = 0x1.62e42fefa39efp-9;      // 256 / ln 2, ln 2 / 256
+constexpr double EXP_C4 = 0x1.5555565bb9890p-5, EXP_C3 = 0x1.555556deeba30p-3, EXP_C2 = 0.5;    // of e^r = 1 + r + C2 r^2 + C3 r^3 + C4 r^4
 // e^t for t <= 0 (clamped at -700: 1e-304, nothing beside the largest term, which is 1)
 __device__ __forceinline__ double exp_nonpositive(double t, const double* tab) {
-  constexpr double SHIFT = 6755399441055744.0;               // 1.5 * 2^52: the sum's low word is the rounded integer
-  const double kf = __builtin_fma(t, 0x1.71547652b82fep+8, SHIFT);
+  const double kf = __builtin_fma(t, EXP_PER_STEP, EXP_SHIFT);
   const int k = __double2loint(kf);
-  const double r = __builtin_fma(kf - SHIFT, -0x1.62e42fefa39efp-9, t);
+  const double r = __builtin_fma(kf - EXP_SHIFT, -EXP_STEP, t);
   const double e = tab[k & (EXP_TAB - 1)];
-  double p = __builtin_fma(0x1.5555565bb9890p-5, r, 0x1.555556deeba30p-3);
-  p = __builtin_fma(p, r, 0.5);
+  double p = __builtin_fma(EXP_C4, r, EXP_C3);
+  p = __builtin_fma(p, r, EXP_C2);
   p = __builtin_fma(p, r, 1.0);
   p = __builtin_fma(p, r, 1.0);
   typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
@@ -69,14 +71,13 @@ __device__ __forceinline__ double scaled_distance(float x, double a_scaled) {   
   return v;
 }
 __device__ __forceinline__ double exp_of_distance(double v, const double* tab) {
-  constexpr double SHIFT = 6755399441055744.0;
-  const double kf = __builtin_fma(v, -0x1.71547652b82fep+8 * TILE_SCALE, SHIFT);
+  const double kf = __builtin_fma(v, -EXP_PER_STEP * TILE_SCALE, EXP_SHIFT);
   const int k = __double2loint(kf);
-  const double r = __builtin_fma(kf - SHIFT, -0x1.62e42fefa39efp-9 / TILE_SCALE, -v);      // a 512th of the reduced argument
+  const double r = __builtin_fma(kf - EXP_SHIFT, -EXP_STEP / TILE_SCALE, -v);      // a 512th of the reduced argument
   const double e = tab[k & (EXP_TAB - 1)];
   constexpr double S1 = TILE_SCALE, S2 = S1 * S1, S3 = S2 * S1, S4 = S3 * S1;
-  double p = __builtin_fma(0x1.5555565bb9890p-5 * S4, r, 0x1.555556deeba30p-3 * S3);
-  p = __builtin_fma(p, r, 0.5 * S2);
+  double p = __builtin_fma(EXP_C4 * S4, r, EXP_C3 * S3);
+  p = __builtin_fma(p, r, EXP_C2 * S2);
   p = __builtin_fma(p, r, S1);
   p = __builtin_fma(p, r, 1.0);
   typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
