@@ -8,16 +8,19 @@ namespace c2t {
 constexpr int WAVE = 64;
 
 // Optional build (-DC2T_PHASE_TIMES): thread 0 of every workgroup of the layer kernel notes the time
-// (100 MHz wall clock) at which it passes each phase boundary; c2t_phase_times_read copies the notes
+// (100 MHz wall clock) at which it passes each phase boundary, PT_START ahead of everything, PT_ROW when it knows its row; c2t_phase_times_read copies the notes
 // out.  In the normal build the marks expand to nothing.
 constexpr int PT_WORKGROUPS = 8192, PT_SLOTS = 16;
-enum PhaseMark { PT_START = 0, PT_STREAM_END, PT_HIST_COMPLETE, PT_SUMS, PT_TAU, PT_CELLS_LISTED, PT_CELLS_READ, PT_RANKED,
+enum PhaseMark { PT_START = 0, PT_STREAM_END, PT_HIST_COMPLETE, PT_SUMS, PT_ROW, PT_CELLS_LISTED, PT_CELLS_READ, PT_RANKED,
                  PT_PUBLISHED, PT_TICKET, PT_PRUNED, PT_PRUNE_LOADED, PT_PRUNE_FIRST, PT_PRUNE_PRESELECTED, PT_PRUNE_RANKED, PT_MERGED };
 #ifdef C2T_PHASE_TIMES
 __device__ unsigned long long c2t_phase_times[PT_WORKGROUPS * PT_SLOTS];
 // The marks go to LDS (a store to memory would be waited for at the next hand-over) and out at the workgroup's end.
 __device__ __forceinline__ unsigned long long* phase_marks() { __shared__ unsigned long long t[PT_SLOTS]; return t; }
-__device__ __forceinline__ void phase_start() { for (int i = 0; i < PT_SLOTS; ++i) phase_marks()[i] = 0ull; phase_marks()[0] = wall_clock64(); }
+__device__ __forceinline__ void phase_start() {
+  const unsigned long long now = wall_clock64();
+  for (int i = 0; i < PT_SLOTS; ++i) phase_marks()[i] = i == 0 ? now : 0ull;
+}
 __device__ __forceinline__ void phase_flush() {
   if (threadIdx.x == 0 && blockIdx.x < PT_WORKGROUPS) for (int i = 0; i < PT_SLOTS; ++i) c2t_phase_times[blockIdx.x * PT_SLOTS + i] = phase_marks()[i];
 }

@@ -235,7 +235,7 @@ typedef __attribute__((address_space(3))) unsigned char* LdsBytes;
 template <int NT>
 __device__ __noinline__ int settle_list(const uint4* __restrict__ rowp, int V, int top_k, const Segment segment, LdsBytes lds, int list_cap, DirectSharedLds<NT> shl) {
   typedef LogitTraits<0> T;
-  // (arguments arrive in vector registers)
+  // (told to be uniform: the arguments of a call arrive in vector registers)
   const int K = uniform(top_k);
   const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
   const int tid = threadIdx.x, lane = tid & (WAVE - 1);
@@ -404,6 +404,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ RowResult rr;
   __shared__ DirectShared<NT> sh;
+  C2T_PT(PT_START);
   constexpr int REST = START_BYTES + 8, ARGUMENT_BYTES = REST + (int)sizeof(TreeState) + (int)sizeof(ScoreParams);
   const uint32_t rows_per_seq = shape & 0xffu, F = (shape >> 8) & 0xffu;
   const QuotientRemainder wg = divide(blockIdx.x, Division{per_row, inv_per_row});
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(NT, 4) void k_logits_direct(
   const int64_t row = (int64_t)b * F + f;
   const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_bytes);
   const Segment sg = make_segment<T::EPC>(V, split, cps);
-  C2T_PT(PT_START);
+  C2T_PT(PT_ROW);
   const ClassifierStage cst = stage_classifier((int)threadIdx.x, cls, sp.h, (float*)(dyn_lds + sp.w_lds_off));
   const SelectLds sel = make_select_lds<NT, T::EPC>(dyn_lds, sp.lds_bytes);
   SegmentTop top{RANKED_IN_RR, false};

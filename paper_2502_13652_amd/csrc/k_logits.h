@@ -436,7 +436,6 @@ __device__ __noinline__ void generic_segment(int tid, const uint4* __restrict__ 
     if (lane == 0) sh_tau = t;
   }
   __syncthreads();
-  C2T_PT(PT_TAU);
   uint32_t tau_key = sh_tau;
   float tau = tau_key ? key_to_float(tau_key) : -INFINITY;
   bool ties = false;
@@ -511,7 +510,6 @@ __device__ __forceinline__ int nth_set_bit(uint64_t m, int n) {
   const uint64_t hit = __builtin_amdgcn_ballot_w64(((m >> lane) & 1ull) != 0ull && below == n);
   return (int)__builtin_ctzll(hit);
 }
-//
 // Dealt by the first wavefront for its workgroup, while the others clear its counts: lane f forms the set of sequences that have a row in slot f, from
 // ballots over the bits of the frontier sizes; the slot follows from a prefix sum of their numbers.  About a hundred instructions whatever the
 // shape.  (Every wavefront for itself, a scalar loop over the slots with a search in each: the last of 1024 workgroups started 4.8 us after the first,
@@ -1084,7 +1082,7 @@ __device__ __noinline__ int settle_hist(int tid, const uint4* __restrict__ rowp,
                                         LdsHalves cell_map, int cells_max, HistSharedLds<NT> shl) {
   typedef LogitTraits<1> T;
   __shared__ int32_t scan_tmp[1][NT / WAVE];
-  // (arguments arrive in vector registers)
+  // (told to be uniform: the arguments of a call arrive in vector registers)
   HistShared<NT>& hs = *(HistShared<NT>*)shl;
   const int K = uniform(top_k), cell_cap = uniform(cells_max);
   const Segment sg{uniform(segment.c0), uniform(segment.c1), uniform(segment.ncell), uniform(segment.tail_chunk), uniform(segment.tail_valid)};
@@ -1395,8 +1393,10 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
     tau = bound_of_patterns(column, K);
   }
   const int ncells = quad_cells_in_segment<NT>(sg.ncell);
-  if (WPS == 8) {                                        // four workgroups a CU: an addition per cell (by wavefront 0.6 % slower), one for all of a wavefront's
-#pragma unroll 1                                         // where a workgroup alone on its CU would wait out every round trip (1.3 % of a phase)
+  // Four workgroups a CU: a place for each of a lane's cells as it is found (append_place; all of a wavefront's at once was 0.6 % slower than an addition each).
+  // A workgroup alone on its CU, which would wait out every round trip, takes the places of a wavefront's cells by one addition (1.3 % of a phase).
+  if (WPS == 8) {
+#pragma unroll 1
     for (int c8 = tid * 8; c8 < ncells; c8 += NT * 8) {  // eight keys per read (the map is padded to 16 bytes)
       const uint4 kq = *(const uint4*)(map + c8);
       const uint32_t kw[4] = {kq.x, kq.y, kq.z, kq.w};
@@ -1626,6 +1626,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ RowResult rr;
   __shared__ HistShared<NT> hs;
+  C2T_PT(PT_START);
   constexpr int REST = START_BYTES + 16;
   const uint32_t rows_per_seq = shape & 0xffu, F = (shape >> 8) & 0xffu;
   const QuotientRemainder wg = divide(blockIdx.x, Division{per_row, inv_per_row});     // per_row workgroups a row: splits of it, or those that share it
@@ -1652,7 +1653,7 @@ __global__ __launch_bounds__(NT, WPS) void k_logits_hist(
   const int64_t row = (int64_t)b * F + f;
   const uint4* rowp = (const uint4*)((const char*)logits + row * row_stride_bytes);
   const Segment sg = make_segment<8>(V, split, cps);
-  C2T_PT(PT_START);
+  C2T_PT(PT_ROW);
   // The classifier's parameters (5h+1 <= 1281 floats) are copied to LDS for the scoring step: the
   // loads are issued now, four floats a thread, and stored behind the streaming loop.
   const ClassifierStage cst = stage_classifier(threadIdx.x, cls, sp.h, TOPM ? nullptr : (float*)(dyn_lds + sp.w_lds_off));

@@ -17,12 +17,12 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
 sys.path.insert(0, _ROOT)
 
-# in the order of the marks' slots; the rows of the histogram path pass those of ROW in that order (the bound's own mark is the two-pass path's)
-MARKS = ["start", "own stream ends", "histogram complete", "sums", "K-th largest known", "cells listed", "cells re-read",
+# in the order of the marks' slots; the rows of the histogram path pass those of ROW in that order
+MARKS = ["start", "own stream ends", "histogram complete", "sums", "row known", "cells listed", "cells re-read",
          "top K ranked", "row scored, handed over", "sequence ticket", "sequence pruned",
          "  candidates loaded", "  first pruning done", "  preselected", "  ranked and appended",
          "  (split rows) row merged"]
-ROW = [0, 1, 2, 5, 3, 6, 7, 8]
+ROW = [0, 4, 1, 2, 5, 3, 6, 7, 8]
 
 
 def build():
@@ -85,7 +85,7 @@ def main():
     if per_row > 1:
         print("(the workgroups that hand a segment's counts over end after 'histogram complete'; 'cells listed' includes the hand-over)")
     print("%-26s %8s %8s %8s %6s" % ("boundary", "mean us", "min", "max", "n"))
-    for i in ROW + [4] + list(range(9, len(MARKS))):
+    for i in ROW + list(range(9, len(MARKS))):
         c, nm = us[:, i], MARKS[i]
         if np.all(np.isnan(c)):
             continue
