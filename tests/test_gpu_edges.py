@@ -537,6 +537,32 @@ def test_fp32_lists_that_are_long_or_short(V, splits, K):
     _rows_equal_oracle(names, np.stack(rows), K, splits)
 
 
+# fp32: how many lanes of a wavefront reach the bound in a chunk (one adds to the list's length for itself, several at once): one, two and all of them, with one
+# to four logits each, in the first wavefront's chunk, a later one's and the row's last, which may be partial or narrower than a wavefront
+@pytest.mark.parametrize("V", [255, 4097, 20003, 40962])
+@pytest.mark.parametrize("K", [1, 10, 64])
+def test_fp32_lanes_that_reach_the_bound(V, K):
+    rng = np.random.default_rng(V + K)
+    names, rows = [], []
+    for at in sorted({0, 37 * 256 % max(V // 1024 * 1024, 256), (V - 1) // 256 * 256}):
+        for lanes in ([0], [63], [0, 1], [5, 62], [1, 2, 3, 40], range(64)):
+            for each in ([0], [3], [0, 1, 2, 3]):
+                ids = np.array([at + 4 * i + j for i in lanes for j in each])
+                ids = ids[ids < V]
+                r = rng.standard_normal(V); r[ids] = 8 + np.round(rng.standard_normal(len(ids)))
+                names.append("%d lanes, %d each, at %d" % (len(lanes), len(each), at)); rows.append(r.astype(np.float32))
+    _rows_equal_oracle(names, np.stack(rows), K, 1)
+
+
+# 256 rows of 128256 equal logits took 2.26 times as long as rows of which few reach the bound where every logit took its place by itself (88.9 us, 39.3), 2.00 times so
+def test_fp32_layer_time_of_equal_logits():
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = 3 * torch.randn((256, 128256), generator=g, device="cuda")
+    equal, usual = _row_layer_us(torch.ones_like(x), 16), _row_layer_us(x, 16)
+    print("equal %.1f us, usual %.1f us" % (equal, usual), flush=True)
+    assert equal < 2.13 * usual
+
+
 # Such rows take little longer than others: 320 rows of 32000 take 24 us, 23 to 51 us if they are tied, masked or sorted.  The bound is
 # what the second read of an overflowed segment and the search for ties can cost: before there were rows of 2300 us (3000 tied) and
 # of 70 (three finite logits); ten rows of 4000 took 3400 us where 11 are usual (18 now).
