@@ -815,12 +815,14 @@ __device__ __forceinline__ void prune_sequence(int tid, const TreeState& s, cons
         if (u < ns) { rk[k] = skey[u]; ri[k] = sidx[u]; }
       }
       __syncthreads();
+      // one addition a wavefront (a place a survivor by append_place: phases of four sequences, 2048 candidates of equal confidence a layer, 176.6 us, 173.7 so)
+      int n_mine = 0;
+#pragma unroll
+      for (int k = 0; k < PER; ++k) n_mine += ri[k] >= 0 && (rk[k] >> shift) >= cut ? 1 : 0;
+      int to = append_places(n_mine, &ps.n_red);
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
-        if (ri[k] >= 0 && (rk[k] >> shift) >= cut) {
-          const int u = append_place(&ps.n_red);
-          skey[u] = rk[k]; sidx[u] = ri[k];
-        }
+        if (ri[k] >= 0 && (rk[k] >> shift) >= cut) { skey[to] = rk[k]; sidx[to] = ri[k]; ++to; }
       }
       for (int i = tid; i < PRUNE_HIST_WORDS; i += NT) hist[i] = 0u;   // for the next level, if there is one
       __syncthreads();
