@@ -52,7 +52,7 @@ constexpr int MLP_SPREAD_MIN = 48;             // hidden units from which on a w
 constexpr int PARTIAL_SLOTS_MIN = 16384;       // (row, split) records the workspace always has room for
 // Row splits.  A split adds an epilogue, a device-scope ticket and a merge (a few microseconds of
 // dependent round trips), which costs more than it saves on the histogram path even for a single
-// sequence; the fp32 path issues fifteen instructions a logit and gains from a few while CUs are idle: at most one
+// sequence; the fp32 path issues 23 instructions a logit, tails included, and gains from a few while CUs are idle: at most one
 // workgroup a CU, four a row, eight for rows that leave each a tile and a third (2700 chunks).  Layers in us, by splits:
 // 10 rows of 32000: 17.6 with 4, 24 with 16; 40 rows of 65541: 22.3 / 18.8 / 17.8 / 20.3 with 2 / 4 / 6 / 10; 16 rows of
 // 128256: 28.6 / 24.7 / 29.6 with 3 / 8 / 16.  More than four only while the merged lists stay within 256 entries: 40 rows of 128256

@@ -1,9 +1,11 @@
 // Logits pass without a histogram: every logit's exponential is evaluated in fp64 as it is read, in one
 // pass over the segment.  The path of fp32 rows (whose values are too many to be counted).
 //
-// What bounds it: instruction issue.  About fifteen vector instructions a logit, twelve of them fp64: 2048 rows of 65536
-// take 129 us, 4.2 TB/s, two thirds of what HBM delivers (134 with the distance from the maximum and its cut-off by two instructions, see scaled_distance;
-// without the table, by a polynomial of degree 11, four instructions more, 156).  The two-pass form that it replaces read
+// What bounds it where the CUs have several rows each: instruction issue.  Fourteen vector instructions a logit for the exponential and the sums, twelve of them
+// fp64, 23 in all by the counter (maxima, tests for NaN, the bound, the rows' tails).  2048 rows of 65536 take 130 to 137 us, 4.0 TB/s; their 48.0 k instructions a SIMD
+// are, at four cycles each, 74 % of its busy cycles.  (The distance from the maximum and its cut-off by two instructions, see scaled_distance: 0.9 % longer; no
+// table but a polynomial of degree 11, four instructions more: 21 % longer.)  Fewer rows wait for the start and the tail, and for CUs that have one row more than others:
+// layers of 250, 320 and 510 rows of 32000 on 256 CUs take 18.0, 22.6 and 24.3 us.  The two-pass form that it replaces read
 // the segment twice (the maximum first) and spent about fifty instructions in the library's exp.
 //
 // Sums.  Each wavefront keeps Z = sum e^(x-a) and S = sum (x-a) e^(x-a) against its own largest logit so far, a

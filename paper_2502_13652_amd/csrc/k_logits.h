@@ -567,9 +567,10 @@ __device__ __forceinline__ RowOfWorkgroup dealt_row(const int32_t* __restrict__ 
   return r;
 }
 // Rows in a fixed order.  What bounds the start of a layer is a chain of round trips ahead of the first logit: with the start's arguments in registers, the frontier size
-// requested at once and the first logits before the counts are cleared, phases of one sequence took 96.0 -> 89.2 us (32000, bf16, eight layers), 120.8 -> 113.1
-// (128256), 83.8 -> 80.2 (32000, fp32), 1024 chains 181.2 -> 177.1, 256 sequences of 152064 1782 -> 1762; with the rows dealt by one wavefront 64 sequences
-// of 128256 260.8 -> 259.2, 32 with 1000 top logits 178.8 -> 176.0.
+// requested at once and the first logits before the counts are cleared, phases of one sequence are 1.05 to 1.08 times as fast.  Each part by itself, phases of the build without it over
+// those of the build with it: the arguments in registers 1.041 (one sequence of 32000, bf16), 1.016 (fp32), 1.025 (128256), others 1.003 to 1.008; divisions by multiplication
+// 1.000 to 1.011; the first logits ahead of the clearing 1.016 (16 masked sequences), others 1.001 to 1.006, but 0.995 (256 of 152064, whose builds differ by as much in the place of their code);
+// the dealing by one wavefront 1.009 (64 of 128256), 1.003 to 1.006 (32).
 __device__ __forceinline__ RowOfWorkgroup row_of_workgroup(const int32_t* __restrict__ nfs, const TreeState& st, int layer, uint32_t B, uint32_t inv_B, uint32_t rows_per_seq,
                                                            uint32_t inv_rows, uint32_t w) {
   const QuotientRemainder by_seq = divide(w, Division{rows_per_seq, inv_rows});
@@ -1539,9 +1540,9 @@ __device__ __forceinline__ SegmentTop hist_segment(const uint4* __restrict__ row
   C2T_PT(PT_CELLS_READ);
 
   // The last wavefront forms the entropy at once, ahead of the look at the row's rarer cases and while the others rank the list (a row that leaves
-  // this path has its record made again).  Its logarithm and division are 0.6 us, which the ranking hides then: phases of one sequence of 32000 86.4 -> 84.3 us,
-  // of 128256 111.5 -> 109.9, 32 of 32000 reranked 109.6 -> 107.8, 1024 chains 175.2 -> 174.2 (with the parent's values and e^-m requested or formed here it was 0.8 us and a
-  // round trip behind the ranking).
+  // this path has its record made again).  Its logarithm and division are 0.6 us, which the ranking hides then.  With the parent's values and e^-m requested and formed here it was 0.8 us and a
+  // round trip behind the ranking.  Phases without each over those with it: the values requested ahead (request_parent) 1.025 (one sequence of 32000), 1.020 (128256), 1.017 (1024
+  // chains), 1.016 (32 reranked), 1.003 (64 of 128256); e^-m by another wavefront 1.003 to 1.007; the entropy ahead of the rarer cases 1.007 (one of 32000), 0.999 to 1.003 (others).
   if (!TOPM && wid == NW - 1 && sp.nsplit == 1) {
     const RowPartial r = combine_hist<NT, false>(hs, 0, *rr);
     row_entropy(0, r.ref, hs.e_minus_m, r.Z, r.S, r.flags, *rr);

@@ -348,8 +348,8 @@ __device__ __forceinline__ SelectLds make_select_lds(unsigned char* base, int by
 // forms the row's entropy meanwhile: T lanes per element (four at least), each compares it with four entries per LDS read, of every
 // T-th group of four; the partial ranks are summed over the T lanes.  Equal logits are told apart by id where a count shows them, four a read as
 // well (one at a time, a layer of four rows of 20011 whose list holds 160 equal logits took 21.8 us, 17.8 so).  T is a constant in each of the three forms, and of the
-// usual list (28 entries at most) every loop is one step: with T from the length, told to the compiler as uniform or not, the phases of one sequence of 32000 took 68.3 us, 67.3 so, with the
-// same in the sequence step (32 listed at most); of 128256 114.3 / 112.7, 32 sequences reranked 108.4 / 106.3, 64 of 128256 258.1 / 256.2.
+// usual list (28 entries at most) every loop is one step: with T from the length, here and in the sequence step (32 listed at most there), phases of one sequence of 32000 took 1.015 times
+// as long, of 128256 1.014, of 32 sequences reranked 1.020, of 64 of 128256 1.007.
 template <int NT>
 __device__ __forceinline__ void rank_list(int tid, int K, const SelectLds& sel, int n_el, float* topv, int32_t* topi) {
   constexpr int nt = NT - WAVE;
